@@ -1,6 +1,6 @@
 // Expert FFN kernels: grouped gate/up GEMM with fused SwiGLU, grouped down GEMM (paper Sec. 2: E_i(x), the part
-// that holds nearly all parameters and FLOPs).  bf16 operands on MFMA with fp32 accumulation; a plain fp32 kernel
-// covers fp32 layers.
+// that holds nearly all parameters and FLOPs).  bf16 operands on MFMA with fp32 accumulation.  (fp32 layers take
+// the weight-streaming schedule's kernel at every size.)
 //
 // Orientation: the weight block is the MFMA "A" operand (its 16 rows are features), the token block is the "B"
 // operand (its 16 columns are tokens).  In the 16x16 accumulator a lane then owns ONE token (column lane%16) and
@@ -223,34 +223,6 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
     }
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// fp32 layers: one thread per output element, fp32 fused multiply-add chain over K.  Plumbing-scale only.
-// ---------------------------------------------------------------------------------------------------------
-template <bool GATEUP>
-__global__ void __launch_bounds__(256)
-ffn_f32_kernel(const float* __restrict__ in, const int32_t* __restrict__ row_token, const float* __restrict__ w0,
-               const float* __restrict__ w1, int K, int features, int M, int tile_tokens,
-               const int32_t* __restrict__ sched, const int32_t* __restrict__ sched_count, float* __restrict__ out) {
-    TileInfo ti;
-    if (!fetch_tile(sched, sched_count, blockIdx.y, M, tile_tokens, ti)) return;
-    const int f = blockIdx.x * 256 + threadIdx.x;
-    if (f >= features) return;
-    const float* wr0 = w0 + (size_t)ti.expert * features * K;
-    const float* wr1 = GATEUP ? w1 + (size_t)ti.expert * features * K : nullptr;
-    for (int r = 0; r < ti.rows; ++r) {
-        const int src_row = row_token ? row_token[ti.row0 + r] : ti.row0 + r;
-        const float* xr = in + (size_t)src_row * K;
-        float a0 = 0.0f, a1 = 0.0f;
-        for (int j = 0; j < K; ++j) {
-            const float xv = xr[j];
-            const size_t wi = packed_index(f, j, K);
-            a0 = __builtin_fmaf(xv, wr0[wi], a0);
-            if (GATEUP) a1 = __builtin_fmaf(xv, wr1[wi], a1);
-        }
-        out[(size_t)(ti.row0 + r) * features + f] = GATEUP ? silu(a0) * a1 : a0;
-    }
-}
-
 // pack_kernel: row-major [n_mat][R][K] -> packed layout, one 16-byte (bf16) or 32-byte (fp32) run per thread.
 template <typename VEC>
 __global__ void __launch_bounds__(256)
@@ -285,24 +257,17 @@ static hipError_t launch_ffn(const FfnArgs& a, hipStream_t s) {
     if (a.max_tiles <= 0) return hipSuccess;
     if ((a.ksplit > 1 || a.scatter != nullptr) && !(a.is_bf16 && !a.streaming && !GATEUP))
         return hipErrorInvalidValue;   // split reduction and scattered rows exist on the bf16 tile schedule's DOWN only
-    if (a.is_bf16 && a.streaming) return GATEUP ? launch_gateup_stream(a, s) : launch_down_stream(a, s);
-    if (a.is_bf16) {
-        // the tile kernel addresses its input rows with 32-bit byte offsets
-        const size_t in_rows = a.row_token ? (size_t)a.in_rows : (size_t)a.M;
-        if (in_rows * (size_t)a.K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
-        const int ncb = (a.features + (GATEUP ? 127 : 255)) / (GATEUP ? 128 : 256);
-        const int ksplit = GATEUP ? 1 : (a.ksplit > 1 ? a.ksplit : 1);
-        if (ksplit > 1 && ((a.K / BK) % ksplit != 0 || a.scatter != nullptr)) return hipErrorInvalidValue;
-        const dim3 grid(xcd_grid(ncb, a.max_tiles, ksplit));
-        hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP>), grid, dim3(256), 0, s, (const bf16_t*)a.in, a.row_token,
-                           (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_tokens, a.sched,
-                           a.sched_count, a.out, ksplit, a.plane_stride, GATEUP ? nullptr : a.scatter, a.out_bf16 ? 1 : 0);
-    } else {
-        const dim3 grid((a.features + 255) / 256, a.max_tiles);
-        hipLaunchKernelGGL((ffn_f32_kernel<GATEUP>), grid, dim3(256), 0, s, (const float*)a.in, a.row_token,
-                           (const float*)a.w0, (const float*)a.w1, a.K, a.features, a.M, a.tile_tokens, a.sched,
-                           a.sched_count, (float*)a.out);
-    }
+    if (a.streaming || !a.is_bf16) return GATEUP ? launch_gateup_stream(a, s) : launch_down_stream(a, s);
+    // the tile kernel addresses its input rows with 32-bit byte offsets
+    const size_t in_rows = a.row_token ? (size_t)a.in_rows : (size_t)a.M;
+    if (in_rows * (size_t)a.K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+    const int ncb = (a.features + (GATEUP ? 127 : 255)) / (GATEUP ? 128 : 256);
+    const int ksplit = GATEUP ? 1 : (a.ksplit > 1 ? a.ksplit : 1);
+    if (ksplit > 1 && ((a.K / BK) % ksplit != 0 || a.scatter != nullptr)) return hipErrorInvalidValue;
+    const dim3 grid(xcd_grid(ncb, a.max_tiles, ksplit));
+    hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP>), grid, dim3(256), 0, s, (const bf16_t*)a.in, a.row_token,
+                       (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_tokens, a.sched,
+                       a.sched_count, a.out, ksplit, a.plane_stride, GATEUP ? nullptr : a.scatter, a.out_bf16 ? 1 : 0);
     return hipGetLastError();
 }
 

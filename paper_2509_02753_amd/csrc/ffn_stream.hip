@@ -6,18 +6,48 @@
 // 16 x 32 weight blocks -- 1 KB fully coalesced loads, many in flight -- and multiplies each against the tile's
 // token blocks (16 tokens x 32 K, read straight from the token rows, which stay cache-resident) with
 // v_mfma_f32_16x16x32_bf16.  The four partial accumulators are added in wave order through LDS (fixed order: same
-// bits every run), then the epilogue of the tile schedule's kernel applies: silu(gate)*up -> bf16, or fp32 rows.
+// bits every run), then the epilogue of the tile schedule's kernel applies: silu(gate)*up -> layer dtype, or fp32 rows.
+//
+// fp32 layers always take this schedule, whatever their size: a packed block is then 2 KB, a lane's run 8 floats, and
+// block x block is eight v_mfma_f32_16x16x4_f32 (full fp32 products and sums), the j-th of them taking element j of
+// every run: which four K positions meet in one instruction does not matter as long as both operands agree.  fp32 is
+// used at test scale (d 128, F 256, 64 tokens, two experts each), where a launch is bound by latency: one output
+// element per thread walking K alone took 636 + 664 us for that layer's two GEMMs, a unit per workgroup with K over
+// the waves 4.8 + 4.6 us (of which about 4 are the launch itself).
 #include "ffn_common.hpp"
 
 namespace lexi {
 
 template <int N> struct IntTag { static constexpr int value = N; };
 
-template <bool GATEUP>
+// One lane's 8 consecutive K elements of an operand block, and the product of two blocks on the matrix cores.
+template <bool BF16> struct Frag;
+template <> struct Frag<true> {
+    typedef bf16_t elem_t;
+    bf16x8_t v;
+    __device__ __forceinline__ void load(const bf16_t* p) { v = *(const bf16x8_t*)p; }
+    __device__ __forceinline__ static f32x4_t mul(const Frag& a, const Frag& b, const f32x4_t& c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
+    }
+};
+template <> struct Frag<false> {
+    typedef float elem_t;
+    f32x4_t v[2];
+    __device__ __forceinline__ void load(const float* p) { v[0] = *(const f32x4_t*)p; v[1] = *(const f32x4_t*)(p + 4); }
+    __device__ __forceinline__ static f32x4_t mul(const Frag& a, const Frag& b, f32x4_t c) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j >> 2][j & 3], b.v[j >> 2][j & 3], c, 0, 0, 0);
+        return c;
+    }
+};
+
+template <bool GATEUP, bool BF16>
 __global__ void __launch_bounds__(256)
-ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
-                  const bf16_t* __restrict__ w1, int K, int features, int M, int tile_tokens,
+ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_token, const void* __restrict__ w0_,
+                  const void* __restrict__ w1_, int K, int features, int M, int tile_tokens,
                   const int32_t* __restrict__ sched, const int32_t* __restrict__ sched_count, void* __restrict__ out) {
+    typedef typename Frag<BF16>::elem_t elem_t;
+    const elem_t *in = (const elem_t*)in_, *w0 = (const elem_t*)w0_, *w1 = (const elem_t*)w1_;
     __shared__ __attribute__((aligned(16))) f32x4_t red[4][2][64];
 
     TileInfo ti;
@@ -30,12 +60,12 @@ ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row
     const int nkb = K >> 5;
     const int kb0 = wave * nkb / 4, kb1 = (wave + 1) * nkb / 4;
     const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
-    const bf16_t* a0 = w0 + wbase;
-    const bf16_t* a1 = GATEUP ? w1 + wbase : nullptr;
+    const elem_t* a0 = w0 + wbase;
+    const elem_t* a1 = GATEUP ? w1 + wbase : nullptr;
 
     auto body = [&](auto ntb_tag) {
         constexpr int NTB = decltype(ntb_tag)::value;
-        const bf16_t* xp[NTB];
+        const elem_t* xp[NTB];
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
             const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
@@ -49,17 +79,17 @@ ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row
             accu[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
         auto k_step = [&](int kb) {
-            const bf16x8_t ag = *(const bf16x8_t*)(a0 + (size_t)kb * 512);
-            bf16x8_t au;
-            if (GATEUP) au = *(const bf16x8_t*)(a1 + (size_t)kb * 512);
+            Frag<BF16> ag, au, b;
+            ag.load(a0 + (size_t)kb * 512);
+            if (GATEUP) au.load(a1 + (size_t)kb * 512);
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb) {
-                const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
-                accg[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, b, accg[tb], 0, 0, 0);
-                if (GATEUP) accu[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, b, accu[tb], 0, 0, 0);
+                b.load(xp[tb] + kb * 32);
+                accg[tb] = Frag<BF16>::mul(ag, b, accg[tb]);
+                if (GATEUP) accu[tb] = Frag<BF16>::mul(au, b, accu[tb]);
             }
         };
-        constexpr int UNROLL = NTB <= 2 ? 8 : 4;  // K blocks whose loads are in flight together
+        constexpr int UNROLL = (NTB <= 2 ? 8 : 4) / (BF16 ? 1 : 2);  // K blocks whose loads are in flight together
         int kb = kb0;
         for (; kb + UNROLL <= kb1; kb += UNROLL) {
 #pragma unroll
@@ -85,9 +115,13 @@ ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row
                 if (r < ti.rows) {
                     const size_t row = (size_t)(ti.row0 + r);
                     if (GATEUP) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) g[i] = silu(g[i]) * u[i];
+                    }
+                    if (GATEUP && BF16) {
                         u32x2_t pk;
-                        pk[0] = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
-                        pk[1] = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
+                        pk[0] = pack_bf16x2(g[0], g[1]);
+                        pk[1] = pack_bf16x2(g[2], g[3]);
                         *(u32x2_t*)((bf16_t*)out + row * features + unit * 16 + kq * 4) = pk;
                     } else {
                         *(f32x4_t*)((float*)out + row * features + unit * 16 + kq * 4) = g;
@@ -108,9 +142,12 @@ template <bool GATEUP>
 static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
     if (a.max_tiles <= 0) return hipSuccess;
     const dim3 grid(a.features / 16, a.max_tiles);
-    hipLaunchKernelGGL((ffn_stream_kernel<GATEUP>), grid, dim3(256), 0, s, (const bf16_t*)a.in, a.row_token,
-                       (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_tokens, a.sched,
-                       a.sched_count, a.out);
+    if (a.is_bf16)
+        hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, true>), grid, dim3(256), 0, s, a.in, a.row_token, a.w0, a.w1, a.K,
+                           a.features, a.M, a.tile_tokens, a.sched, a.sched_count, a.out);
+    else
+        hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, false>), grid, dim3(256), 0, s, a.in, a.row_token, a.w0, a.w1, a.K,
+                           a.features, a.M, a.tile_tokens, a.sched, a.sched_count, a.out);
     return hipGetLastError();
 }
 
