@@ -20,3 +20,27 @@ pytestmark = pytest.mark.gpu
 def test_fp32_layers_at_tile_edges(T, k, d, F, shared):
     cfg = replace(S.mini(S.C1, L=1, d=d, F=F, F_shared=0), F_shared=192 if shared else 0, shared_kind=shared)
     run_and_check_layer(cfg, 0, T, k)
+
+
+@pytest.mark.parametrize("k_base,n_k,T", [(1, 1, 3), (3, 7, 40), (5, 8, 40), (6, 9, 40), (9, 17, 33), (64, 64, 17)])
+def test_profile_list_lengths_around_a_group(k_base, n_k, T):
+    """Listed k are taken eight at a time, slots four at a time: lists and baselines around multiples of both, the same
+    k in several groups, against single-k calls (bit for bit: an entry does not depend on its neighbours) and the
+    oracle's deltas (relative 5e-3, the bound derived in test_profile_gpu.py)."""
+    import numpy as np
+    import torch
+    import oracle as O
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = S.mini(S.C2, L=1, d=256, F=128)
+    dl, hl = device_and_host_layer(cfg, 0)
+    x, xh = S.device_x(cfg, 0, T), S.host_x(cfg, 0, T)
+    ks = [1 + (5 * i) % k_base for i in range(n_k)]
+    got = P.lexi_moe_profile_layer(dl, x, k_base, ks)
+    for i in {0, n_k // 2, n_k - 1}:
+        assert torch.equal(got[i:i + 1], P.lexi_moe_profile_layer(dl, x, k_base, ks[i:i + 1]))
+    ref = O.profile_layer(hl, xh, k_base, ks, round_act=True)
+    scale = float(np.sqrt(np.sum(O.moe_layer(hl, xh, k_base, round_act=True).out ** 2)))
+    for i, k in enumerate(ks):
+        assert abs(float(got[i]) - ref[i]) <= 5e-3 * ref[i] + 1e-6 * scale
+        assert k != k_base or float(got[i]) == 0.0
