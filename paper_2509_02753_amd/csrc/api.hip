@@ -116,17 +116,16 @@ Workspace carve(const lexi_layer_t& ly, int T, int k, void* base) {
     Carver c(base);
     const size_t A = (size_t)T * k;
     const size_t es = ly.dtype == LEXI_BF16 ? 2 : 4;
-    const size_t nblk = ((size_t)T + 7) / 8;  // router blocks never hold fewer than 8 tokens
     // every expert with rows has one ragged tile at most, the rest are full
     w.max_tiles = (int)(A / kTileTokens) + (int)(A < (size_t)ly.E ? A : (size_t)ly.E);
     // chained stack: the normalised MoE input.  First, so that its place does not depend on the layer or on k: a
     // block's combine writes the next block's input there.
     w.u = c.take<char>((size_t)T * ly.d * es);
-    w.partial = c.take<float>((size_t)(ly.d / 128) * T * 64);
+    w.partial = c.take<float>((size_t)(ly.d / 128) * router_partial_tokens(T) * 64);
     w.topk_idx = c.take<int32_t>(A);
     w.gates = c.take<float>(A);
     w.local_rank = c.take<int32_t>(A);
-    w.blk_hist = c.take<int32_t>(nblk * 64);
+    w.blk_hist = c.take<int32_t>(router_hist_rows(T) * 64);
     w.counts = c.take<int32_t>(64);
     w.offsets = c.take<int32_t>(68);
     w.perm = c.take<int32_t>(A);

@@ -10,328 +10,360 @@ namespace lexi {
 // The fp32 logit of (token t, expert e) has ONE defined evaluation order: d is cut into segments of 128; inside a
 // segment the partial starts at +0 and takes one fused multiply-add per element, ascending; the partials are added
 // in ascending segment order; the bias is added last.  The segment partials are independent chains, which is where
-// the parallelism comes from: partial[seg][t][e] is produced by the two kernels below (a register-tiled one for
-// prefill-sized T, a latency-oriented one for decode-sized T) and summed in order by topk_kernel.
+// the parallelism comes from: one wave computes one segment.
 // ---------------------------------------------------------------------------------------------------------
 
-// router_partial_kernel: workgroup = 256 tokens x 64 experts x one segment, 8 waves.  A wave owns 64 tokens and one
-// half of the experts; a lane owns an 8 (tokens) x 4 (experts) block of accumulators, so per j it reads 8 x-values and
-// 4 w-values from LDS for 32 fused multiply-adds.  (Blocks of 8 x 8 with four waves leave one wave per SIMD, which
-// measured 45 % of the plain-FMA rate; two waves per SIMD fill each other's issue gaps.)  x is staged through LDS
-// transposed ([j][token], fp32) by the thread that owns the token row, W[j][e] row-major by the other four waves;
-// the next 32-j stage is prefetched into registers while the current one is consumed.
+// router_partial_small_kernel (T <= kSmallRouterMaxT): one wave = one segment of one token, lane = expert.  The segment's
+// 128 router weights of the lane's expert sit in registers (128 coalesced loads in flight at once), the token's x values
+// are wave-uniform (scalar loads): one 128-long chain of fused multiply-adds, partials to partial[seg][t][e].  A few
+// tokens are bound by latency: d/128 * T workgroups each pull 32 KB of W, where one workgroup per token block would pull
+// all of it through one CU.
 template <bool IS_BF16>
-__global__ void __launch_bounds__(512)
-router_partial_kernel(const void* __restrict__ x, const float* __restrict__ w_router, int T, int d, int E,
-                      float* __restrict__ partial) {
-    constexpr int SJ = 32;                      // j per LDS stage
-    constexpr int NSTAGE = kRouterSegment / SJ;
-    __shared__ __attribute__((aligned(16))) float xs[4][SJ][64];
-    __shared__ __attribute__((aligned(16))) float wsm[SJ][64];
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int tw = wave & 3, eh = wave >> 2;    // token quarter, expert half
-    const int eg = lane & 7, tg = lane >> 3;
-    const int seg = blockIdx.y;
-    const int tok_base = blockIdx.x * 256;
-    const bool x_loader = tid < 256;            // waves 0..3 stage x (one token row per thread), waves 4..7 stage W
-    const int my_row = min(tok_base + (tid & 255), T - 1);  // rows past T re-read the last row; never stored
-    const int j_seg = seg * kRouterSegment;
-
-    u32x4_t xr[IS_BF16 ? 4 : 8];
-    float wr[8];
-    auto load_stage = [&](int st) {
-        const int j0 = j_seg + st * SJ;
-        if (x_loader) {
-            if (IS_BF16) {
-                const u32x4_t* p = (const u32x4_t*)((const bf16_t*)x + (size_t)my_row * d + j0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) xr[i] = p[i];
-            } else {
-                const u32x4_t* p = (const u32x4_t*)((const float*)x + (size_t)my_row * d + j0);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) xr[i] = p[i];
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int i = (tid - 256) + 256 * r, jj = i >> 6, e = i & 63;
-                wr[r] = (e < E) ? w_router[(size_t)(j0 + jj) * E + e] : 0.0f;
-            }
-        }
-    };
-    auto store_stage = [&]() {
-        if (x_loader) {
-            if (IS_BF16) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        xs[wave][8 * i + 2 * c][lane] = __uint_as_float(xr[i][c] << 16);
-                        xs[wave][8 * i + 2 * c + 1][lane] = __uint_as_float(xr[i][c] & 0xFFFF0000u);
-                    }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) xs[wave][4 * i + c][lane] = __uint_as_float(xr[i][c]);
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int i = (tid - 256) + 256 * r;
-                wsm[i >> 6][i & 63] = wr[r];
-            }
-        }
-    };
-
-    float acc[8][4];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = 0.0f;
-
-    load_stage(0);
-    for (int st = 0; st < NSTAGE; ++st) {
-        __syncthreads();
-        store_stage();
-        __syncthreads();
-        if (st + 1 < NSTAGE) load_stage(st + 1);
-#pragma unroll 4
-        for (int jj = 0; jj < SJ; ++jj) {
-            const f32x4_t x0 = *(const f32x4_t*)&xs[tw][jj][8 * tg];
-            const f32x4_t x1 = *(const f32x4_t*)&xs[tw][jj][8 * tg + 4];
-            const f32x4_t w0 = *(const f32x4_t*)&wsm[jj][32 * eh + 4 * eg];
-#pragma unroll
-            for (int a = 0; a < 8; ++a) {
-                const float xv = a < 4 ? x0[a & 3] : x1[a & 3];
-#pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_fmaf(xv, w0[b], acc[a][b]);
-            }
-        }
-    }
-
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-        const int t = tok_base + tw * 64 + 8 * tg + a;
-        if (t < T) {
-            float* o = partial + ((size_t)seg * T + t) * 64 + 32 * eh + 4 * eg;
-            f32x4_t v0 = {acc[a][0], acc[a][1], acc[a][2], acc[a][3]};
-            *(f32x4_t*)o = v0;
-        }
-    }
-}
-
-// router_partial_small_kernel: one wave = one segment x TW tokens, lane = expert.  The segment's 128 router weights
-// of the lane's expert sit in registers (128 coalesced loads in flight at once); the token's x values are
-// wave-uniform (scalar loads), so each token costs one 128-long chain of fused multiply-adds.
-template <bool IS_BF16, int TW>
 __global__ void __launch_bounds__(64)
 router_partial_small_kernel(const void* __restrict__ x, const float* __restrict__ w_router, int T, int d, int E,
                             float* __restrict__ partial) {
     const int lane = threadIdx.x;
     const int seg = blockIdx.x;
-    const int t0 = blockIdx.y * TW;
+    const int t = blockIdx.y;
     const int j_seg = seg * kRouterSegment;
     float w[kRouterSegment];
     const float* wp = w_router + (size_t)j_seg * E + min(lane, E - 1);   // lanes >= E read a valid column; never used
 #pragma unroll
     for (int jj = 0; jj < kRouterSegment; ++jj) w[jj] = wp[(size_t)jj * E];
-    for (int m = 0; m < TW; ++m) {
-        const int t = t0 + m;
-        if (t >= T) break;
-        float acc = 0.0f;
-        if (IS_BF16) {
-            const uint32_t* xp = (const uint32_t*)((const bf16_t*)x + (size_t)t * d + j_seg);
+    float acc = 0.0f;
+    if (IS_BF16) {
+        const uint32_t* xp = (const uint32_t*)((const bf16_t*)x + (size_t)t * d + j_seg);
 #pragma unroll
-            for (int i = 0; i < kRouterSegment / 2; ++i) {
-                const uint32_t p = xp[i];
-                acc = __builtin_fmaf(__uint_as_float(p << 16), w[2 * i], acc);
-                acc = __builtin_fmaf(__uint_as_float(p & 0xFFFF0000u), w[2 * i + 1], acc);
-            }
-        } else {
-            const float* xp = (const float*)x + (size_t)t * d + j_seg;
-#pragma unroll
-            for (int i = 0; i < kRouterSegment; ++i) acc = __builtin_fmaf(xp[i], w[i], acc);
+        for (int i = 0; i < kRouterSegment / 2; ++i) {
+            const uint32_t p = xp[i];
+            acc = __builtin_fmaf(__uint_as_float(p << 16), w[2 * i], acc);
+            acc = __builtin_fmaf(__uint_as_float(p & 0xFFFF0000u), w[2 * i + 1], acc);
         }
-        partial[((size_t)seg * T + t) * 64 + lane] = acc;
+    } else {
+        const float* xp = (const float*)x + (size_t)t * d + j_seg;
+#pragma unroll
+        for (int i = 0; i < kRouterSegment; ++i) acc = __builtin_fmaf(xp[i], w[i], acc);
     }
+    partial[((size_t)seg * T + t) * 64 + lane] = acc;
 }
 
-// router_partial_narrow_kernel (prefill-sized T, exactly EW = 8 or 16 experts): with so few experts the 64-wide
-// register tile above would spend most of its multiply-adds on padding.  Here a lane owns one token and all EW
-// experts, a wave 64 tokens x one segment (the four waves of a workgroup take four neighbouring segments of the
-// same tokens, 1 KB of each row together): the lane's 128 activations of the segment sit in registers (one
-// contiguous 256-byte run of its row), the segment's weights are wave-uniform and come through scalar loads, so
-// every instruction of the inner loop is a useful fused multiply-add.  Row stride of the partials: EW floats (no
-// padding to 64 lanes).  (One segment per workgroup and 256 tokens instead measured 10 % slower.)
-template <bool IS_BF16, int EW>
-__global__ void __launch_bounds__(256)
-router_partial_narrow_kernel(const void* __restrict__ x, const float* __restrict__ w_router, int T, int d,
-                             float* __restrict__ partial) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int seg = blockIdx.y * 4 + wave;
-    if (seg >= d / kRouterSegment) return;                 // (no barrier in this kernel)
-    const int tok = blockIdx.x * 64 + lane;
-    const int t = min(tok, T - 1);                         // rows past T re-read the last row; never stored
-    const int j0 = seg * kRouterSegment;
-    constexpr int NV = IS_BF16 ? kRouterSegment / 8 : kRouterSegment / 4;   // 16-byte pieces of the row segment
-    u32x4_t xr[NV];
-    const u32x4_t* xp = (const u32x4_t*)((const char*)x + ((size_t)t * d + j0) * (IS_BF16 ? 2 : 4));
+// The logits before the bias of tokens t[]: ordered sums of the segment partials; the loads of 8 segments are issued
+// together (the adds stay in order).  A row of partials holds `pstride` floats; lanes past it hold no expert.
+template <int TM>
+__device__ __forceinline__ void sum_partials(const float* __restrict__ partial, int pstride, const int (&t)[TM], int T, int nseg,
+                                             int lane, float (&total)[TM]) {
+    const int col = min(lane, pstride - 1);
 #pragma unroll
-    for (int i = 0; i < NV; ++i) xr[i] = xp[i];
-    const float* __restrict__ wseg = w_router + (size_t)j0 * EW;   // [128][EW], wave-uniform
-    float acc[EW];
+    for (int m = 0; m < TM; ++m) total[m] = partial[(size_t)t[m] * pstride + col];
+    for (int sg0 = 1; sg0 < nseg; sg0 += 8) {
+        float tmp[8][TM];
 #pragma unroll
-    for (int e = 0; e < EW; ++e) acc[e] = 0.0f;
+        for (int c = 0; c < 8; ++c)
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
+            for (int m = 0; m < TM; ++m)
+                tmp[c][m] = partial[((size_t)min(sg0 + c, nseg - 1) * T + t[m]) * pstride + col];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (IS_BF16) {
-                const float lo = __uint_as_float(xr[i][c] << 16), hi = __uint_as_float(xr[i][c] & 0xFFFF0000u);
-                const int j = 8 * i + 2 * c;
-#pragma unroll
-                for (int e = 0; e < EW; ++e) acc[e] = __builtin_fmaf(lo, wseg[j * EW + e], acc[e]);
-#pragma unroll
-                for (int e = 0; e < EW; ++e) acc[e] = __builtin_fmaf(hi, wseg[(j + 1) * EW + e], acc[e]);
-            } else {
-                const float v = __uint_as_float(xr[i][c]);
-                const int j = 4 * i + c;
-#pragma unroll
-                for (int e = 0; e < EW; ++e) acc[e] = __builtin_fmaf(v, wseg[j * EW + e], acc[e]);
-            }
-        }
-    }
-    if (tok < T) {
-        float* o = partial + ((size_t)seg * T + tok) * EW;
-#pragma unroll
-        for (int e = 0; e < EW; e += 4) *(f32x4_t*)(o + e) = f32x4_t{acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
-    }
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// topk_kernel: one lane per expert (E <= 64), TM tokens per wave, WAVES waves per workgroup.
-//   logit = ordered sum of the segment partials, then the bias.
-//   top-k: k rounds of {wave maximum by DPP, ballot of the lanes that hold it, lowest set bit} -- the lowest
-//   index among equal logits wins; comparisons are on floats, so +0 == -0.
-//   gates: softmax over the k selected logits.
-//   Each selected (token, slot) also gets its rank among the workgroup's earlier assignments to the same expert
-//   (tokens ascending), which is what makes the later scatter a stable counting sort without atomics.
-// ---------------------------------------------------------------------------------------------------------
-template <int TM, int WAVES>
-__global__ void __launch_bounds__(WAVES * 64)
-topk_kernel(const float* __restrict__ partial, int pstride, const float* __restrict__ bias, int T, int nseg, int E, int k,
-            int32_t* __restrict__ topk_idx, float* __restrict__ gates, int32_t* __restrict__ local_rank,
-            int32_t* __restrict__ blk_hist) {
-    constexpr int TB = TM * WAVES;
-    __shared__ int32_t wave_cnt[WAVES][64];
-
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int tok0 = blockIdx.x * TB + wave * TM;
-    const int tok_end = T;
-
-    // a row of partials holds `pstride` floats (64, or the expert count of the narrow partial kernel); lanes past it
-    // hold no expert and load nothing
-    const bool has_col = lane < pstride;
-    float total[TM];
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-        const int t = min(tok0 + m, T - 1);
-        total[m] = has_col ? partial[(size_t)t * pstride + lane] : 0.0f;
-    }
-    // ordered sum of the remaining partials; the loads of CH segments are issued together (the adds stay in order)
-    constexpr int CH = 8;
-    for (int sg0 = 1; sg0 < nseg; sg0 += CH) {
-        float tmp[CH][TM];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int sg = min(sg0 + c, nseg - 1);
-#pragma unroll
-            for (int m = 0; m < TM; ++m) {
-                const int t = min(tok0 + m, T - 1);
-                tmp[c][m] = has_col ? partial[((size_t)sg * T + t) * pstride + lane] : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
+        for (int c = 0; c < 8; ++c)
             if (sg0 + c < nseg) {
 #pragma unroll
                 for (int m = 0; m < TM; ++m) total[m] = total[m] + tmp[c][m];
             }
-        }
     }
-    const bool lane_valid = lane < E;
-    if (bias != nullptr) {
-        const float b = lane_valid ? bias[lane] : 0.0f;
-#pragma unroll
-        for (int m = 0; m < TM; ++m) total[m] = total[m] + b;
-    }
-    // Inputs are finite by contract.  A NaN logit (one NaN or Inf activation is enough) compares unequal to every
-    // maximum, which would leave the ballot below empty and the expert index undefined; it ranks as -inf instead, so
-    // every round selects a valid expert (all-NaN row: experts 0..k-1) and the token's gates and output come out NaN.
-#pragma unroll
-    for (int m = 0; m < TM; ++m) total[m] = (total[m] == total[m]) ? total[m] : -INFINITY;
+}
 
-    // ---- top-k: slot-major, token-minor, so the TM independent reduction chains of one round overlap ----
-    uint32_t taken = 0;        // lane e: bit m set once token m has selected expert e
-    int32_t sel[TM];           // lane s (< k): expert in slot s of token m
-    float val[TM];             // lane s (< k): its logit
+// Selection for the TOK tokens of a workgroup of NW waves, one lane per expert (E <= 64); this wave's are m0 .. m0 + TM - 1
+// with the logits (before the bias) `logit`.
+//   top-k: k rounds of {wave maximum by DPP, ballot of the lanes that hold it, lowest set bit} -- the lowest index among
+//   equal logits wins; comparisons are on floats, so +0 == -0.
+//   gates: softmax over the k selected logits.
+//   Each selected (token, slot) also gets its rank among the workgroup's earlier assignments to the same expert (tokens
+//   ascending), which is what makes the later scatter a stable counting sort without atomics.
+template <int TOK, int TM, int NW>
+__device__ __forceinline__ void select_experts(const float (&logit)[TM], const float* __restrict__ bias, int m0, int tok0,
+                                               int T, int E, int k, int32_t (*hit)[64], int32_t* __restrict__ topk_idx,
+                                               float* __restrict__ gates, int32_t* __restrict__ local_rank,
+                                               int32_t* __restrict__ blk_hist) {
+    const int lane = threadIdx.x & 63;
+    const bool owner = m0 < TOK;
+    const bool lane_valid = lane < E;
+    float total[TM];
+    int32_t sel[TM];            // lane s (< k): expert in slot s
+    float val[TM];              // lane s (< k): its logit
+    bool taken[TM];             // lane e: the token selected expert e
+    const float b = (bias != nullptr && lane_valid) ? bias[lane] : 0.0f;
 #pragma unroll
-    for (int m = 0; m < TM; ++m) { sel[m] = 0; val[m] = -INFINITY; }
-    for (int s = 0; s < k; ++s) {
+    for (int m = 0; m < TM; ++m) {
+        total[m] = bias != nullptr ? logit[m] + b : logit[m];
+        // Inputs are finite by contract.  A NaN logit (one NaN or Inf activation is enough) compares unequal to every
+        // maximum, which would leave the ballot below empty and the expert index undefined; it ranks as -inf instead, so
+        // every round selects a valid expert (all-NaN row: experts 0..k-1) and the token's gates and output come out NaN.
+        total[m] = (total[m] == total[m]) ? total[m] : -INFINITY;
+        sel[m] = 0; val[m] = -INFINITY; taken[m] = false;
+    }
+    if (owner) {
+        for (int s = 0; s < k; ++s) {
 #pragma unroll
-        for (int m = 0; m < TM; ++m) {
-            if (tok0 + m < tok_end) {  // wave-uniform: rows past the wave's range are skipped
-                const bool open = lane_valid && !((taken >> m) & 1u);
+            for (int m = 0; m < TM; ++m) {   // (rows past T hold the last row's logits; they are dropped below)
+                const bool open = lane_valid && !taken[m];
                 const float mx = wave_max(open ? total[m] : -INFINITY);
                 const uint64_t holders = __ballot(open && total[m] == mx);
-                const int e_star = __builtin_ctzll(holders);  // lowest index among equal logits
-                if (lane == e_star) taken |= 1u << m;
+                const int e_star = __builtin_ctzll(holders);
+                if (lane == e_star) taken[m] = true;
                 if (lane == s) { sel[m] = e_star; val[m] = mx; }
             }
         }
-    }
-    // ---- gates: softmax over the selected logits; slot 0 holds the largest ----
-    float gte[TM];
 #pragma unroll
-    for (int m = 0; m < TM; ++m) {
-        const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val[m]), 0));
-        const float ex = (lane < k) ? __expf(val[m] - v0) : 0.0f;
-        gte[m] = ex / wave_sum(ex);
+        for (int m = 0; m < TM; ++m) hit[m0 + m][lane] = (taken[m] && tok0 + m0 + m < T) ? 1 : 0;   // (hit is [TOK][64])
     }
-    // ---- rank of each assignment among this wave's earlier assignments to the same expert (tokens ascending):
-    //      lane e counts its own expert's hits in token order, the slot lanes fetch theirs with one permute ----
-    int32_t cnt = 0;
-    int32_t rnk[TM];
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-        rnk[m] = __builtin_amdgcn_ds_bpermute(sel[m] << 2, cnt);
-        cnt += (int32_t)((taken >> m) & 1u);
-    }
-
-    wave_cnt[wave][lane] = cnt;
     __syncthreads();
-    if (wave == 0) {
+    if ((int)(threadIdx.x >> 6) == NW - 1) {
         int32_t h = 0;
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w) h += wave_cnt[w][lane];
+        for (int m = 0; m < TOK; ++m) h += hit[m][lane];
         blk_hist[(size_t)blockIdx.x * 64 + lane] = h;
     }
+    if (!owner) return;
 #pragma unroll
     for (int m = 0; m < TM; ++m) {
-        const int t = tok0 + m;
-        if (t < T && lane < k) {
+        const int t = tok0 + m0 + m;
+        if (t >= T) break;
+        const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val[m]), 0));   // slot 0 holds the largest
+        const float ex = (lane < k) ? __expf(val[m] - v0) : 0.0f;
+        const float g = ex / wave_sum(ex);
+        if (lane < k) {
+            // rank among the block's earlier assignments to the same expert (tokens ascending), which is what makes the
+            // later scatter a stable counting sort without atomics
             int32_t before = 0;
-            for (int w = 0; w < wave; ++w) before += wave_cnt[w][sel[m]];
+#pragma unroll
+            for (int q = 0; q < TOK; ++q) before += q < m0 + m ? hit[q][sel[m]] : 0;
             const size_t a = (size_t)t * k + lane;
             topk_idx[a] = sel[m];
-            gates[a] = gte[m];
-            local_rank[a] = before + rnk[m];
+            gates[a] = g;
+            local_rank[a] = before;
         }
     }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// The segment chains of router_partial_mfma_kernel and router_topk_kernel run on the matrix cores: the fp32 MFMAs with a
+// reduction length of ONE give every accumulator exactly one fused multiply-add per instruction (same bits as fmaf,
+// denormals, infinities and NaN included), so the order above is kept at twice the rate of v_fma_f32.  Their blocks are
+// used as a broadcast: one operand (CBSZ) is taken by all blocks from the lanes ABID names.
+// ---------------------------------------------------------------------------------------------------------
+template <int N> struct IntC { static constexpr int value = N; };
+
+// Eight consecutive elements of a row of x as loaded, and widened exactly.
+template <bool IS_BF16> struct Octet;
+template <> struct Octet<true> {
+    u32x4_t p;
+    __device__ __forceinline__ void load(const void* x, size_t i) { p = *(const u32x4_t*)((const bf16_t*)x + i); }
+    __device__ __forceinline__ float get(int e) const {
+        return __uint_as_float((e & 1) ? (p[e >> 1] & 0xFFFF0000u) : (p[e >> 1] << 16));
+    }
+};
+template <> struct Octet<false> {
+    f32x4_t p[2];
+    __device__ __forceinline__ void load(const void* x, size_t i) {
+        p[0] = *(const f32x4_t*)((const float*)x + i);
+        p[1] = *(const f32x4_t*)((const float*)x + i + 4);
+    }
+    __device__ __forceinline__ float get(int e) const { return p[e >> 2][e & 3]; }
+};
+
+// router_topk_kernel (kSmallRouterMaxT < T <= kFineRouterMaxT): logits, top-k and gates of 4 tokens per workgroup of 16
+// waves, one segment per wave and pass.  v_mfma_f32_4x4x1_16b_f32: the 16 blocks are 16 groups of 4 experts (lane =
+// expert), W is read one 256-byte row per element of the reduction, and the 4 tokens are broadcast: a lane's 16 bytes of x
+// are octet lane / 4 of token lane % 4.  The partials meet in LDS and are added in segment order by the wave that owns the
+// token, which then selects its experts.  Bound by the 256 * d bytes of W that every workgroup pulls through its CU
+// (31 B/clk: about 7 us at d = 2048), so it only pays while the workgroups are few.
+// Measured against partials through memory and a top-k launch: 10.5 us against 11.1 + 14.3 us at T = 256, d = 2048, 64
+// experts; 9.1 against 11.3 + 16.4 us at T = 777, d = 1280.  For T <= 64 the two launches are as fast (8.6 + 6.5 us at
+// T = 64: more CUs share the reading of W), above 1024 workgroups of 4 tokens no longer fit the chip at once.
+template <bool IS_BF16>
+__device__ __forceinline__ void router_segment(const void* __restrict__ x, const float* __restrict__ w_router, int tok0, int T,
+                                               int d, int E, int j0, int lane, float (*out)[64]) {
+    typedef const __attribute__((address_space(1))) char* global_ptr;
+    Octet<IS_BF16> xo;                           // rows past T re-read the last row; never used
+    xo.load(x, (size_t)min(tok0 + (lane & 3), T - 1) * d + j0 + 8 * (lane >> 2));
+    float w[2][32];                              // two chunks of 32 rows of W: one in use, one on its way
+    const uint32_t off = (uint32_t)min(lane, E - 1) * 4u;                // lanes >= E read a valid column
+    global_ptr row = (global_ptr)(w_router + (size_t)j0 * E);
+    const size_t step = (size_t)E * 4;
+    auto fetch_w = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) {
+            // the origin stays in scalar registers and is advanced: as 128 hoisted 64-bit products it spills
+            asm volatile("" : "+s"(row));
+            w[buf][i] = *(const __attribute__((address_space(1))) float*)(row + off);
+            row += step;
+        }
+    };
+    fetch_w(0);
+    fetch_w(1);
+    f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    float xf[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) xf[e] = xo.get(e);
+    auto octet = [&](auto b) {                   // elements 8b .. 8b + 7 of the segment
+        constexpr int B = decltype(b)::value;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            acc = __builtin_amdgcn_mfma_f32_4x4x1f32(xf[e], w[(B / 4) & 1][8 * (B % 4) + e], acc, 4, B, 0);
+    };
+    auto chunk = [&](auto c) {
+        constexpr int C = decltype(c)::value;
+        octet(IntC<4 * C>{}); octet(IntC<4 * C + 1>{}); octet(IntC<4 * C + 2>{}); octet(IntC<4 * C + 3>{});
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (C < 2) fetch_w(C);         // the chunk after the next, into the registers just used
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    chunk(IntC<0>{}); chunk(IntC<1>{}); chunk(IntC<2>{}); chunk(IntC<3>{});
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i][lane] = acc[i];
+}
+
+template <bool IS_BF16>
+__global__ void __launch_bounds__(1024)
+router_topk_kernel(const void* __restrict__ x, const float* __restrict__ w_router, const float* __restrict__ bias, int T,
+                   int d, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
+                   int32_t* __restrict__ local_rank, int32_t* __restrict__ blk_hist) {
+    constexpr int NW = 16, TOK = 4;
+    __shared__ float part[NW][TOK][64];
+    __shared__ int32_t hit[TOK][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tok0 = blockIdx.x * TOK;
+    const int nseg = d / kRouterSegment;
+    float total[1] = {0.0f};
+    for (int s0 = 0; s0 < nseg; s0 += NW) {
+        const int seg = s0 + wave;
+        if (seg < nseg) router_segment<IS_BF16>(x, w_router, tok0, T, d, E, seg * kRouterSegment, lane, part[wave]);
+        __syncthreads();
+        if (wave < TOK) {                        // the segments in order; the first partial is taken as is
+            const int n = min(NW, nseg - s0);
+            float p[NW];
+#pragma unroll
+            for (int s = 0; s < NW; ++s) p[s] = part[s][wave][lane];   // (rows past the last segment are not used)
+            total[0] = s0 == 0 ? p[0] : total[0] + p[0];
+#pragma unroll
+            for (int s = 1; s < NW; ++s)
+                if (s < n) total[0] = total[0] + p[s];
+        }
+        __syncthreads();
+    }
+    select_experts<TOK, 1, NW>(total, bias, wave, tok0, T, E, k, hit, topk_idx, gates, local_rank, blk_hist);
+}
+
+// router_partial_mfma_kernel (T > kFineRouterMaxT): segment partials of 8 waves' tokens; a workgroup takes one segment,
+// whose W (512 * E bytes) it keeps in LDS for all its tokens.
+//   NARROW = false: v_mfma_f32_16x16x1_4b_f32 as four groups of 16 experts x 16 tokens; the tokens (rows) are broadcast: a
+//                   lane holds octets 4o + lane / 16 of token lane % 16.  16 tokens per wave; partial rows of 64 floats.
+//   NARROW = true (E <= 16): four groups of 16 tokens x 16 experts; the experts (rows) are broadcast: a lane holds
+//                   W[4j + lane / 16][lane % 16], and all of its own token's segment.  64 tokens per wave, rows of 16.
+// Bound by the multiply-adds (2*T*d*64 flop at 157 TFLOP/s: 6.9 us at T = 4096, d = 2048; with E <= 16 by reading x).  One
+// workgroup per token block with all segments, partials in LDS (no memory round trip, one launch less) is bound by pulling
+// all of W through every CU at 31 B/clk instead: 27 us with the selection.
+// Measured against register-tiled v_fma_f32 kernels: 19.0 us against 27.4 at T = 4096, d = 2048, 64 experts (32.7 against
+// 41.9 at T = 8192, 9.9 against 21.7 at T = 2048); NARROW 16.5 us against 20.4 at T = 4096, d = 4096, 8 experts.  W is
+// read from LDS eight registers ahead (one read per multiply-add, waited for at once, took 22.7 us).
+template <bool IS_BF16, bool NARROW>
+__global__ void __launch_bounds__(512)
+router_partial_mfma_kernel(const void* __restrict__ x, const float* __restrict__ w_router, int T, int d, int E,
+                           float* __restrict__ partial) {
+    constexpr int TW = NARROW ? 64 : 16;         // tokens per wave
+    typedef __attribute__((ext_vector_type(16))) float f32x16;
+    __shared__ __attribute__((aligned(16))) float ws[kRouterSegment * (NARROW ? 16 : 64)];   // [128][16 or 64]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int seg = blockIdx.y, j0 = seg * kRouterSegment;
+    const int t0 = (blockIdx.x * 8 + wave) * TW;
+    const int l16 = lane & 15, q = lane >> 4;
+
+    constexpr int NO = NARROW ? 16 : 4;
+    Octet<IS_BF16> xo[NO];                       // rows past T re-read the last row; never stored
+    const size_t xrow = (size_t)min(t0 + (NARROW ? lane : l16), T - 1) * d + j0;
+#pragma unroll
+    for (int o = 0; o < NO; ++o) xo[o].load(x, xrow + 8 * (NARROW ? o : 4 * o + q));
+    constexpr int EW = NARROW ? 16 : 64, NL = kRouterSegment * EW / 512;
+    float wst[NL];
+#pragma unroll
+    for (int p = 0; p < NL; ++p) {               // columns past E repeat the last one; never used
+        const int i = tid + 512 * p;
+        wst[p] = w_router[(size_t)(j0 + i / EW) * E + min(i % EW, E - 1)];
+    }
+#pragma unroll
+    for (int p = 0; p < NL; ++p) ws[tid + 512 * p] = wst[p];
+    __syncthreads();
+
+    // W in groups of NG registers, the next group read from LDS while the current one is multiplied.  A register holds
+    // element k of column `lane`, or (NARROW) elements 4j + 0..3 of the 16 columns.
+    constexpr int NR = kRouterSegment * EW / 64, NG = 8;
+    f32x16 acc = {};
+    float w[2][NG];
+    auto read_w = [&](int g) {
+#pragma unroll
+        for (int i = 0; i < NG; ++i) w[g & 1][i] = ws[(g * NG + i) * 64 + lane];
+    };
+    read_w(0);
+#pragma unroll
+    for (int g = 0; g < NR / NG; ++g) {
+        if (g + 1 < NR / NG) read_w(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (NARROW) {
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {       // elements 4j .. 4j + 3 of the segment, j = NG * g + i
+                const Octet<IS_BF16>& o = xo[(NG * g + i) >> 1];
+                acc = __builtin_amdgcn_mfma_f32_16x16x1f32(w[g & 1][i], o.get(4 * (i & 1)), acc, 2, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x1f32(w[g & 1][i], o.get(4 * (i & 1) + 1), acc, 2, 1, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x1f32(w[g & 1][i], o.get(4 * (i & 1) + 2), acc, 2, 2, 0);
+                acc = __builtin_amdgcn_mfma_f32_16x16x1f32(w[g & 1][i], o.get(4 * (i & 1) + 3), acc, 2, 3, 0);
+            }
+        } else {
+            const Octet<IS_BF16>& o = xo[g >> 2];   // octet g: lanes 16 * (g % 4) .. of register g / 4
+#pragma unroll
+            for (int e = 0; e < NG; ++e) {
+                if ((g & 3) == 0) acc = __builtin_amdgcn_mfma_f32_16x16x1f32(o.get(e), w[g & 1][e], acc, 2, 0, 0);
+                if ((g & 3) == 1) acc = __builtin_amdgcn_mfma_f32_16x16x1f32(o.get(e), w[g & 1][e], acc, 2, 1, 0);
+                if ((g & 3) == 2) acc = __builtin_amdgcn_mfma_f32_16x16x1f32(o.get(e), w[g & 1][e], acc, 2, 2, 0);
+                if ((g & 3) == 3) acc = __builtin_amdgcn_mfma_f32_16x16x1f32(o.get(e), w[g & 1][e], acc, 2, 3, 0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // accumulator element 4b + i of a lane: row 4 * (lane / 16) + i, column lane % 16 of block b
+    float* out = partial + ((size_t)seg * T) * (NARROW ? 16 : 64);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        if constexpr (NARROW) {                  // rows are experts, columns tokens
+            const int t = t0 + 16 * b + l16;
+            if (t < T) *(f32x4_t*)(out + (size_t)t * 16 + 4 * q) = f32x4_t{acc[4 * b], acc[4 * b + 1], acc[4 * b + 2], acc[4 * b + 3]};
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int t = t0 + 4 * q + i;
+                if (t < T) out[(size_t)t * 64 + 16 * b + l16] = acc[4 * b + i];
+            }
+        }
+    }
+}
+
+// topk_kernel: ordered sum of the segment partials (rows of `pstride` floats) and the selection, TOK tokens per workgroup
+// of NW waves.
+template <int TOK, int NW>
+__global__ void __launch_bounds__(NW * 64)
+topk_kernel(const float* __restrict__ partial, int pstride, const float* __restrict__ bias, int T, int nseg, int E, int k,
+            int32_t* __restrict__ topk_idx, float* __restrict__ gates, int32_t* __restrict__ local_rank,
+            int32_t* __restrict__ blk_hist) {
+    constexpr int TM = TOK / NW;
+    __shared__ int32_t hit[TOK][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tok0 = blockIdx.x * TOK;
+    int t[TM];
+    float total[TM];
+#pragma unroll
+    for (int m = 0; m < TM; ++m) t[m] = min(tok0 + wave * TM + m, T - 1);
+    sum_partials<TM>(partial, pstride, t, T, nseg, lane, total);
+    select_experts<TOK, TM, NW>(total, bias, wave * TM, tok0, T, E, k, hit, topk_idx, gates, local_rank, blk_hist);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -437,7 +469,6 @@ scan_kernel(int32_t* __restrict__ blk_hist, int nblk, int E, int tile_tokens, in
 // counting sort needs no block histograms in memory: an assignment's position is offsets[e] + (assignments to e by
 // earlier tokens), kept in LDS.  Saves two dependent launches on the latency-bound path.
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kFusedTailMaxT = 16;
 constexpr int kFusedTailMaxA = kFusedTailMaxT * 64;   // assignments (k <= E <= 64)
 
 __global__ void __launch_bounds__(1024)
@@ -464,18 +495,12 @@ topk_scan_kernel(const float* __restrict__ partial, const float* __restrict__ bi
         int32_t sel = 0;
         bool hit = false;
         if (live) {
-            // logit = ordered sum of the segment partials, then the bias (same order as topk_kernel)
-            float total = partial[(size_t)t * 64 + lane];
-            for (int sg0 = 1; sg0 < nseg; sg0 += 8) {
-                float tmp[8];
-#pragma unroll
-                for (int c = 0; c < 8; ++c) tmp[c] = partial[((size_t)min(sg0 + c, nseg - 1) * T + t) * 64 + lane];
-#pragma unroll
-                for (int c = 0; c < 8; ++c)
-                    if (sg0 + c < nseg) total = total + tmp[c];
-            }
+            float sum[1];
+            const int tt[1] = {t};
+            sum_partials<1>(partial, 64, tt, T, nseg, lane, sum);
+            float total = sum[0];
             if (bias != nullptr) total = total + b;
-            total = (total == total) ? total : -INFINITY;   // a NaN logit ranks last (see topk_kernel)
+            total = (total == total) ? total : -INFINITY;   // a NaN logit ranks last (see select_experts)
             float val = -INFINITY;
             for (int s = 0; s < k; ++s) {
                 const bool open = lane_valid && !hit;
@@ -565,67 +590,59 @@ permute_kernel(const int32_t* __restrict__ topk_idx, const int32_t* __restrict__
 // ---------------------------------------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kTinyRouterMaxT = 128;    // at or below: one token per wave in the partial and top-k kernels
-constexpr int kSmallRouterMaxT = 1024;  // at or below this many tokens the latency-oriented partial kernel runs
+constexpr int kFusedPermuteMaxT = 1024;  // at or below this many tokens the scan's workgroup scatters the assignments itself
+constexpr int kNarrowRouterMaxE = 16;
 
-int router_tokens_per_block(int T) { return T >= 2048 ? 16 : 8; }
-
-// Row stride of the segment partials: the narrow kernel (prefill-sized T, exactly 8 or 16 experts) packs them.
-static int partial_stride(const RoutingArgs& a) {
-    return (a.T > kSmallRouterMaxT && (a.E == 8 || a.E == 16)) ? a.E : 64;
-}
+static int router_tokens_per_block(int T) { return T <= kSmallRouterMaxT ? 8 : T <= kFineRouterMaxT ? 4 : 16; }
 
 template <bool IS_BF16>
 static hipError_t launch_partials(const RoutingArgs& a, hipStream_t s) {
     const int nseg = a.d / kRouterSegment;
-    if (partial_stride(a) != 64) {
-        const dim3 grid((a.T + 63) / 64, (nseg + 3) / 4);
-        if (a.E == 8)
-            hipLaunchKernelGGL((router_partial_narrow_kernel<IS_BF16, 8>), grid, dim3(256), 0, s, a.x, a.w_router, a.T, a.d, a.partial);
-        else
-            hipLaunchKernelGGL((router_partial_narrow_kernel<IS_BF16, 16>), grid, dim3(256), 0, s, a.x, a.w_router, a.T, a.d, a.partial);
-        return hipGetLastError();
-    }
-    if (a.T <= kTinyRouterMaxT) {
-        // a handful of tokens: one token per wave, so the chains of different tokens run on different CUs
-        hipLaunchKernelGGL((router_partial_small_kernel<IS_BF16, 1>), dim3(nseg, a.T), dim3(64), 0, s, a.x, a.w_router,
-                           a.T, a.d, a.E, a.partial);
-    } else if (a.T <= kSmallRouterMaxT) {
-        constexpr int TW = 4;
-        hipLaunchKernelGGL((router_partial_small_kernel<IS_BF16, TW>), dim3(nseg, (a.T + TW - 1) / TW), dim3(64), 0, s,
-                           a.x, a.w_router, a.T, a.d, a.E, a.partial);
-    } else {
-        hipLaunchKernelGGL((router_partial_kernel<IS_BF16>), dim3((a.T + 255) / 256, nseg), dim3(512), 0, s, a.x,
+    if (a.T <= kSmallRouterMaxT)
+        hipLaunchKernelGGL(router_partial_small_kernel<IS_BF16>, dim3(nseg, a.T), dim3(64), 0, s, a.x, a.w_router, a.T, a.d,
+                           a.E, a.partial);
+    else if (a.E <= kNarrowRouterMaxE)
+        hipLaunchKernelGGL((router_partial_mfma_kernel<IS_BF16, true>), dim3((a.T + 511) / 512, nseg), dim3(512), 0, s, a.x,
                            a.w_router, a.T, a.d, a.E, a.partial);
-    }
+    else
+        hipLaunchKernelGGL((router_partial_mfma_kernel<IS_BF16, false>), dim3((a.T + 127) / 128, nseg), dim3(512), 0, s, a.x,
+                           a.w_router, a.T, a.d, a.E, a.partial);
     return hipGetLastError();
 }
 
 hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
-    hipError_t err = a.is_bf16 ? launch_partials<true>(a, s) : launch_partials<false>(a, s);
-    if (err != hipSuccess) return err;
     const int nseg = a.d / kRouterSegment;
-    if (a.T <= kFusedTailMaxT) {
-        hipLaunchKernelGGL(topk_scan_kernel, dim3(1), dim3(1024), 0, s, a.partial, a.bias, a.T, nseg, a.E, a.k,
-                           a.tile_tokens, a.topk_idx, a.gates, a.counts, a.offsets, a.sched, a.sched_count, a.perm,
-                           a.inv_perm, a.row_token);
-        return hipGetLastError();
-    }
     const int tb = router_tokens_per_block(a.T);
     const int nblk = (a.T + tb - 1) / tb;
-    const int ps = partial_stride(a);
-    if (tb == 16)
-        hipLaunchKernelGGL((topk_kernel<4, 4>), dim3(nblk), dim3(256), 0, s, a.partial, ps, a.bias, a.T, nseg, a.E, a.k,
-                           a.topk_idx, a.gates, a.local_rank, a.blk_hist);
-    else if (a.T <= kTinyRouterMaxT)
-        hipLaunchKernelGGL((topk_kernel<1, 8>), dim3(nblk), dim3(512), 0, s, a.partial, ps, a.bias, a.T, nseg, a.E, a.k,
-                           a.topk_idx, a.gates, a.local_rank, a.blk_hist);
-    else
-        hipLaunchKernelGGL((topk_kernel<8, 1>), dim3(nblk), dim3(64), 0, s, a.partial, ps, a.bias, a.T, nseg, a.E, a.k,
-                           a.topk_idx, a.gates, a.local_rank, a.blk_hist);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
+    hipError_t err;
+    if (a.T > kSmallRouterMaxT && a.T <= kFineRouterMaxT) {
+        if (a.is_bf16)
+            hipLaunchKernelGGL(router_topk_kernel<true>, dim3(nblk), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E,
+                               a.k, a.topk_idx, a.gates, a.local_rank, a.blk_hist);
+        else
+            hipLaunchKernelGGL(router_topk_kernel<false>, dim3(nblk), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E,
+                               a.k, a.topk_idx, a.gates, a.local_rank, a.blk_hist);
+        err = hipGetLastError();
+    } else {
+        err = a.is_bf16 ? launch_partials<true>(a, s) : launch_partials<false>(a, s);
+        if (err != hipSuccess) return err;
+        if (a.T <= kFusedTailMaxT) {
+            hipLaunchKernelGGL(topk_scan_kernel, dim3(1), dim3(1024), 0, s, a.partial, a.bias, a.T, nseg, a.E, a.k,
+                               a.tile_tokens, a.topk_idx, a.gates, a.counts, a.offsets, a.sched, a.sched_count, a.perm,
+                               a.inv_perm, a.row_token);
+            return hipGetLastError();
+        }
+        if (tb == 8)
+            hipLaunchKernelGGL((topk_kernel<8, 8>), dim3(nblk), dim3(512), 0, s, a.partial, 64, a.bias, a.T, nseg, a.E, a.k,
+                               a.topk_idx, a.gates, a.local_rank, a.blk_hist);
+        else
+            hipLaunchKernelGGL((topk_kernel<16, 8>), dim3(nblk), dim3(512), 0, s, a.partial, a.E <= kNarrowRouterMaxE ? 16 : 64,
+                               a.bias, a.T, nseg, a.E, a.k, a.topk_idx, a.gates, a.local_rank, a.blk_hist);
+        err = hipGetLastError();
+    }
+    if (err != hipSuccess) return err;
     const int A = a.T * a.k;
-    if (a.T <= kSmallRouterMaxT) {   // decode-sized: the scan's workgroup scatters the assignments itself
+    if (a.T <= kFusedPermuteMaxT) {   // decode-sized: the scan's workgroup scatters the assignments itself
         hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(1024), 0, s, a.blk_hist, nblk, a.E, a.tile_tokens, a.counts,
                            a.offsets, a.sched, a.sched_count, a.topk_idx, a.local_rank, A, a.k, tb, a.perm, a.inv_perm,
                            a.row_token);

@@ -44,3 +44,13 @@ def test_profile_list_lengths_around_a_group(k_base, n_k, T):
     for i, k in enumerate(ks):
         assert abs(float(got[i]) - ref[i]) <= 5e-3 * ref[i] + 1e-6 * scale
         assert k != k_base or float(got[i]) == 0.0
+
+
+@pytest.mark.parametrize("T", [16, 17, 64, 65, 67, 1024, 1025, 1169])
+@pytest.mark.parametrize("E,d,k,kind", [(1, 128, 1, "c1"), (8, 2176, 8, "c2"), (16, 256, 3, "c2"), (17, 1280, 5, "c2"),
+                                        (60, 2048, 4, "c1"), (64, 384, 64, "c2")])
+def test_router_at_block_and_segment_edges(T, E, d, k, kind):
+    """Every router route at the ends of its range of T, one expert to 64 (the narrow form's last 16, and 17), segment
+    counts around a pass of 16; bf16 (c2) and fp32 (c1) layers.  The routing is compared bit for bit."""
+    cfg = replace(S.mini(S.C1 if kind == "c1" else S.C2, L=1, d=d, F=64, F_shared=0), E=E)
+    run_and_check_layer(cfg, 0, T, k)
