@@ -2,37 +2,103 @@
 // Nothing here allocates, synchronises or copies to the host; every launch goes to the caller's stream.
 #include "../../include/lexi_moe.h"
 #include "kernels.hpp"
+#include <algorithm>
+#include <math.h>
 #include <mutex>
 
 namespace {
 
 using namespace lexi;
 
-constexpr int kTileTokens = 128;  // token-tile height of the grouped GEMM kernels
 constexpr int kStreamRowsPerExpert = 2;   // mean rows per expert at or below which the routed FFN streams weights
-constexpr int kStreamDownMaxItems = 256;   // (token tiles x column blocks) at or below which the routed down GEMM streams
+// The down projection has few column blocks (d / 256): where the tile schedule would have no more than
+// kStreamDownMaxItems work items, it streams up to kStreamDownRowsPerExpert mean rows per expert.  (A unit of the streaming
+// schedule reads all of its tile's rows for 16 output features: at 16 rows per expert, d 4096, F 14336 it takes 228 us
+// against 161 us on the tile schedule with the reduction cut in two, at 128 rows 1222 against 212 us.)
+constexpr int kStreamDownMaxItems = 256;
+constexpr int kStreamDownRowsPerExpert = 8;
 constexpr int kStreamDenseRows = 64;      // token count at or below which the shared expert streams weights
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-// Split of the down GEMM's reduction dimension on the tile schedule.  A launch runs (token tiles x column blocks of
-// 256 features) work items on 512 workgroup slots (two per CU).  When a launch with a long reduction cannot fill
-// those slots even once, cutting the reduction in two gives twice as many items of half the length; the halves land
-// in two planes of the output that the consumer adds.  Eligible: at least 32 K-steps of 64, an even number of them.
-// Taken when the expected number of items (full tiles plus half a ragged tile per expert; the real number is only
-// known on the device) is at most half the slots and the time saved outweighs writing and re-reading the second
-// plane.  (For launches of several rounds, e.g. 1100 items of 14336, the split measured no gain in the down GEMM and
-// cost the combine a second plane, so it is not taken there.)
-constexpr int kWorkgroupSlots = 512;
+// Launch plan of one GEMM on the tile schedule.  A launch runs (token tiles x column blocks) work items on the chip's
+// workgroup slots: 512 of four waves (two per CU, 256 weight rows each) or 256 of eight (one per CU, 512 weight rows: a
+// token row is fetched for twice as many weight rows, which is what the loop is bound by, but a partly filled last round
+// costs nearly a whole one).  The number of rows an expert gets is only known on the device; here they are taken as spread
+// around rows / groups as a balanced router leaves them.
+struct TilePlan {
+    bool wide;        // eight waves
+    int tile_rows;    // tile height
+    int ksplit;       // parts of the reduction
+};
+
+// Relative duration of a launch on the tile schedule: rounds of the chip times an item's duration (in 16-row blocks x
+// K-steps of a four-wave workgroup), the tallest item once.  An item pays about 2 blocks' worth per K-step whatever its height
+// (the weight stream) and `store` K-steps' worth per block for storing its rows.
+double gemm_cost(int64_t rows, int groups, int K, int features, int store, const TilePlan& p, int col_width) {
+    const double mean = (double)rows / groups, sd = groups > 1 ? sqrt(mean * (1.0 - 1.0 / groups)) : 0.0;
+    const double in_use = groups > 1 && mean < 4.0 ? groups * (1.0 - exp(-mean)) : groups;
+    double tiles = 0.0, blocks = 0.0, tallest = 0.0;
+    for (double z : {-1.28, -0.52, 0.0, 0.52, 1.28}) {     // fifths of a normal distribution
+        const double r = fmax(mean + z * sd, 1.0);
+        const double n = ceil(r / p.tile_rows), nb = ceil(r / 16.0);
+        tiles += n / 5.0;
+        blocks += nb / 5.0;
+        tallest = fmax(tallest, ceil(nb / n));
+    }
+    const double height = blocks / tiles;
+    const double rounds = tiles * in_use * ((features + col_width - 1) / col_width) * p.ksplit / (p.wide ? 256.0 : 512.0);
+    const double full = floor(rounds), part = rounds - full;
+    const double base = p.wide ? 0.7 : 0.25;                // what the emptiest last round costs
+    const double steps = (double)(K / 64) / p.ksplit, scale = p.wide ? 0.86 : 1.0;
+    const double item = ((height + (p.wide ? 2.0 : 1.7)) * steps + store * height) * scale;
+    return (full + (part > 0.02 ? base + (1.0 - base) * part : 0.0)) * item + (tallest - height) * (steps + store) * scale;
+}
+
+// The best height for four-wave workgroups.  With few rows per expert, where the heights are nearly equal for a balanced
+// router, a taller tile has to be clearly better: a lower one spreads the rows of a skewed router over more, shorter items
+// (batch-256 decode with Zipf-distributed experts: 1305 us at 64 rows, 1399 at 160).
+TilePlan plan_narrow_tiles(int64_t rows, int groups, int K, int features, int store, int ksplit, int col_width) {
+    TilePlan best{false, 64, ksplit};
+    double cost = gemm_cost(rows, groups, K, features, store, best, col_width);
+    for (int h : {96, 128, 160}) {
+        const TilePlan p{false, h, ksplit};
+        const double c = gemm_cost(rows, groups, K, features, store, p, col_width);
+        if (c < (rows < (int64_t)96 * groups ? 0.98 : 1.0) * cost) { best = p; cost = c; }
+    }
+    return best;
+}
+TilePlan plan_gateup_tiles(int64_t rows, int groups, int K, int features) {
+    return plan_narrow_tiles(rows, groups, K, features, 4, 1, 128);
+}
+
+// The reduction is cut in two where a launch with a long one cannot fill half the slots: twice as many items of half the
+// length, whose results land in two planes of the output that the consumer adds.  Eligible: at least 32 K-steps of 64, an
+// even number of them.  Taken when the time saved outweighs writing and re-reading the second plane.  (For launches of
+// several rounds, e.g. 1100 items of 14336, the split measured no gain in the down GEMM and cost the combine a second
+// plane; four parts measured 0 to 10 % slower than two on launches of 72 to 192 items.)
 inline bool ksplit_eligible(int K) { return K / 64 >= 32 && (K / 64) % 2 == 0; }
-int choose_ksplit(int64_t rows, int groups, int K, int features, bool is_bf16) {
-    if (!is_bf16 || !ksplit_eligible(K) || rows <= 0) return 1;
-    const double ragged = groups > 1 ? 0.5 * (double)(groups < rows ? groups : rows) : (rows % kTileTokens ? 0.5 : 0.0);
-    const double items = ((double)(rows / kTileTokens) + ragged) * ((features + 255) / 256);
-    if (items > kWorkgroupSlots / 2) return 1;
-    const double t_item = (2.0 * kTileTokens * 256.0 * K) / 3.9e12;           // one item at what one CU sustains
-    const double t_plane = 2.0 * (double)rows * features * 4.0 / 5.0e12;      // second plane: written once, read once
-    return 0.5 * t_item > 1.5 * t_plane ? 2 : 1;
+TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool allow_split, bool direct) {
+    constexpr int kPlanRows = 128;
+    const double ragged = groups > 1 ? 0.5 * (double)(groups < rows ? groups : rows) : (rows % kPlanRows ? 0.5 : 0.0);
+    const double items = ((double)(rows / kPlanRows) + ragged) * ((features + 255) / 256);
+    if (allow_split && ksplit_eligible(K) && items <= 256) {
+        const double t_item = (2.0 * kPlanRows * 256.0 * K) / 3.9e12;           // one item at what one CU sustains
+        const double t_plane = 2.0 * (double)rows * features * 4.0 / 5.0e12;    // second plane: written once, read once
+        // (rows stored straight into the layer's output need no combine launch at all while the reduction is whole)
+        if (0.5 * t_item > 1.5 * t_plane + (direct ? 20e-6 : 0.0))
+            return plan_narrow_tiles(rows, groups, K, features, 7, 2, 256);
+    }
+    TilePlan best = plan_narrow_tiles(rows, groups, K, features, 7, 1, 256);
+    // a few rows per expert: a launch streams weights, for which more and smaller workgroups are as good or better
+    if (rows < (int64_t)64 * groups) return best;
+    double cost = gemm_cost(rows, groups, K, features, 7, best, 256);
+    for (int h : {kTileRows, 128}) {
+        const TilePlan p{true, h, 1};
+        const double c = gemm_cost(rows, groups, K, features, 7, p, 512);
+        if (c < cost) { best = p; cost = c; }
+    }
+    return best;
 }
 
 // The shared expert depends on x only, not on the routing, so for decode-sized batches (where its kernels are short
@@ -41,6 +107,9 @@ int choose_ksplit(int64_t rows, int groups, int K, int features, bool is_bf16) {
 // until the process ends; the caller sees plain stream semantics (and a capture of the caller's stream picks the
 // side stream up through the events).
 constexpr int kSideStreamMaxT = 1024;
+// Tile height of its GEMMs there: they share the chip with the routing and the routed GEMMs, so neither their own duration
+// nor the slots they take may grow (64 to 160 rows measured between -5 and +5 % of the call, 128 never the slower side).
+constexpr int kSideTileRows = 128;
 struct SideStream {
     hipStream_t stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
@@ -101,10 +170,9 @@ struct Carver {
 };
 
 struct Workspace {
-    int32_t *topk_idx, *local_rank, *blk_hist, *counts, *offsets, *perm, *inv_perm, *row_token, *sched, *sched_count;
+    int32_t *topk_idx, *local_rank, *blk_hist, *counts, *offsets, *perm, *inv_perm, *row_token, *sched;
     float *gates, *partial, *y_slot, *y_shared;
     void *act, *act_shared, *u;
-    int max_tiles;
     int slot_planes = 1, shared_planes = 1;   // planes of y_slot / y_shared the last launches wrote
     bool direct = false;                      // the routed down GEMM wrote the layer's output itself
     bool fused = false;                       // the caller launches down + combine as one kernel (run_routed stopped after gate/up)
@@ -116,8 +184,6 @@ Workspace carve(const lexi_layer_t& ly, int T, int k, void* base) {
     Carver c(base);
     const size_t A = (size_t)T * k;
     const size_t es = ly.dtype == LEXI_BF16 ? 2 : 4;
-    // every expert with rows has one ragged tile at most, the rest are full
-    w.max_tiles = (int)(A / kTileTokens) + (int)(A < (size_t)ly.E ? A : (size_t)ly.E);
     // chained stack: the normalised MoE input.  First, so that its place does not depend on the layer or on k: a
     // block's combine writes the next block's input there.
     w.u = c.take<char>((size_t)T * ly.d * es);
@@ -131,8 +197,7 @@ Workspace carve(const lexi_layer_t& ly, int T, int k, void* base) {
     w.perm = c.take<int32_t>(A);
     w.inv_perm = c.take<int32_t>(A);
     w.row_token = c.take<int32_t>(A);
-    w.sched = c.take<int32_t>((size_t)w.max_tiles * 8);
-    w.sched_count = c.take<int32_t>(4);
+    w.sched = c.take<int32_t>(kSchedInts);
     w.act = c.take<char>(A * ly.F * es);
     // two planes wherever the down GEMM may split its reduction (independent of T and k, so that the size asked for
     // at (T_max, k_max) covers every smaller call)
@@ -201,33 +266,43 @@ lexi_status check_call(const lexi_layer_t* ly, const void* x, const void* y, int
 // Routing and the routed expert GEMMs of one layer at top-k = k: fills the routing arrays, act and y_slot of `w`.
 // `allow_split`: the down GEMM may write two planes of y_slot (w.slot_planes tells).  `direct_y` != null (k == 1, nothing
 // else to add): the down GEMM stores the output rows straight into the layer's output (w.direct tells whether it did).
-// Launch plan of the down GEMMs of one call (also what lexi_moe_down_plan reports).
-struct DownPlan {
-    bool routed_streams, shared_streams;   // weight-streaming schedule instead of the tile schedule
-    int routed_ksplit, shared_ksplit;      // parts of the reduction on the tile schedule (1 or 2)
+// Launch plan of the GEMMs of one call (the down part is also what lexi_moe_down_plan reports).
+struct LayerPlan {
+    bool gateup_streams;                   // weight-streaming schedule instead of the tile schedule
+    bool routed_streams, shared_streams;   // same, for the down GEMMs
+    TilePlan gateup;                       // routed gate/up GEMM on the tile schedule
+    TilePlan routed, shared;               // down GEMMs on the tile schedule
     bool routed_direct;                    // with k == 1 and nothing to add: rows stored straight into y
     bool routed_fused;                     // a handful of tokens: down projection and combine in one launch
 };
-DownPlan plan_down(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_split, bool allow_direct) {
-    DownPlan p{};
+LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_split, bool allow_direct) {
+    LayerPlan p{};
     const bool bf = ly.dtype == LEXI_BF16;
     const int64_t A = (int64_t)T * k;
-    const int max_tiles = (int)(A / kTileTokens) + (int)(A < ly.E ? A : ly.E);
-    const bool stream_routed = A <= (int64_t)kStreamRowsPerExpert * ly.E;
-    // the down projection has few column blocks (d / 256): with few token tiles as well the tile schedule would leave
-    // most CUs idle, so it streams too (16-feature units, K split over the waves)
-    p.routed_streams = stream_routed || (int64_t)max_tiles * ((ly.d + 255) / 256) <= kStreamDownMaxItems;
-    p.shared_streams = T <= kStreamDenseRows;
-    p.routed_ksplit = p.shared_ksplit = 1;
-    const bool tile_routed = bf && !p.routed_streams;
-    p.routed_direct = tile_routed && allow_direct && k == 1 && ly.F_shared == 0;
+    const int64_t few_items = (A / 128 + (A < ly.E ? A : ly.E)) * ((ly.d + 255) / 256);
+    p.gateup_streams = !bf || A <= (int64_t)kStreamRowsPerExpert * ly.E;
+    p.routed_streams = p.gateup_streams || (A <= (int64_t)kStreamDownRowsPerExpert * ly.E && few_items <= kStreamDownMaxItems);
+    p.shared_streams = !bf || T <= kStreamDenseRows;
+    p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
+    if (!p.gateup_streams) p.gateup = plan_gateup_tiles(A, ly.E, ly.d, ly.F);
     // (allow_direct: the caller wants nothing but y -- no slot rows, no residual, no normalised copy)
-    p.routed_fused = bf && p.routed_streams && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&
-                     ly.shared_kind != LEXI_SHARED_SIGMOID;
-    if (tile_routed && allow_split && !p.routed_direct) p.routed_ksplit = choose_ksplit(A, ly.E, ly.F, ly.d, bf);
-    if (ly.F_shared > 0 && bf && !p.shared_streams) p.shared_ksplit = choose_ksplit(T, 1, ly.F_shared, ly.d, bf);
+    p.routed_fused = bf && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&
+                     (p.gateup_streams || few_items <= kStreamDownMaxItems) && ly.shared_kind != LEXI_SHARED_SIGMOID;
+    if (p.routed_fused) p.routed_streams = true;
+    if (!p.routed_streams) {
+        const bool direct = allow_direct && k == 1 && ly.F_shared == 0;
+        p.routed = plan_down_tiles(A, ly.E, ly.F, ly.d, allow_split, direct);
+        p.routed_direct = direct && p.routed.ksplit == 1;
+    }
+    if (ly.F_shared > 0 && !p.shared_streams) {
+        p.shared = plan_down_tiles(T, 1, ly.F_shared, ly.d, true, false);
+        if (T <= kSideStreamMaxT) p.shared = TilePlan{false, kSideTileRows, p.shared.ksplit};
+    }
     return p;
 }
+
+// Items of a launch at most, whatever the routing: an expert with n rows has ceil(n / tile_rows) tiles.
+inline int64_t max_tiles(int64_t rows, int groups, int tile_rows) { return rows / tile_rows + (rows < groups ? rows : groups); }
 
 lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t k, Workspace& w, hipStream_t s,
                        const lexi_stage_events_t* events, bool allow_split = true, void* direct_y = nullptr,
@@ -238,31 +313,33 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
     const bool bf = ly.dtype == LEXI_BF16;
     RoutingArgs r{};
     r.x = x; r.is_bf16 = bf; r.w_router = ly.w_router; r.bias = ly.router_bias;
-    r.T = T; r.d = ly.d; r.E = ly.E; r.k = k; r.tile_tokens = kTileTokens;
+    r.T = T; r.d = ly.d; r.E = ly.E; r.k = k;
     r.partial = w.partial; r.topk_idx = w.topk_idx; r.gates = w.gates; r.local_rank = w.local_rank; r.blk_hist = w.blk_hist;
     r.counts = w.counts; r.offsets = w.offsets; r.perm = w.perm; r.inv_perm = w.inv_perm; r.row_token = w.row_token;
-    r.sched = w.sched; r.sched_count = w.sched_count;
+    r.sched = w.sched;
+    const int64_t A = (int64_t)T * k;
+    const LayerPlan plan = plan_layer(ly, T, k, allow_split, direct_y != nullptr);
+    r.plan.tile_rows[0] = plan.gateup.tile_rows;
+    r.plan.tile_rows[1] = plan.routed.tile_rows;
     if (launch_routing(r, s) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(1);
 
-    // few rows per expert (decode): the weight-streaming schedule; otherwise the MFMA tile schedule
-    const bool stream_routed = (int64_t)T * k <= (int64_t)kStreamRowsPerExpert * ly.E;
     FfnArgs g{};
-    g.streaming = stream_routed;
+    g.streaming = plan.gateup_streams;
     g.is_bf16 = bf; g.in = x; g.row_token = w.row_token; g.in_rows = T; g.w0 = ly.w_gate; g.w1 = ly.w_up; g.K = ly.d;
-    g.features = ly.F; g.M = T * k; g.max_tiles = w.max_tiles; g.tile_tokens = kTileTokens; g.sched = w.sched;
-    g.sched_count = w.sched_count; g.out = w.act;
+    g.features = ly.F; g.M = (int)A; g.tile_rows = r.plan.tile_rows[0];
+    g.max_tiles = (int)max_tiles(A, ly.E, g.tile_rows); g.sched = w.sched; g.out = w.act;
     if (launch_gateup(g, s) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(2);
 
     FfnArgs dn{};
     dn.is_bf16 = bf; dn.in = w.act; dn.row_token = nullptr; dn.w0 = ly.w_down; dn.w1 = nullptr; dn.K = ly.F;
-    dn.features = ly.d; dn.M = T * k; dn.max_tiles = w.max_tiles; dn.tile_tokens = kTileTokens; dn.sched = w.sched;
-    dn.sched_count = w.sched_count; dn.out = w.y_slot;
-    const DownPlan plan = plan_down(ly, T, k, allow_split, direct_y != nullptr);
+    dn.features = ly.d; dn.M = (int)A; dn.tile_rows = r.plan.tile_rows[1];
+    dn.max_tiles = (int)max_tiles(A, ly.E, dn.tile_rows); dn.sched = w.sched; dn.out = w.y_slot;
     dn.streaming = plan.routed_streams;
-    dn.ksplit = w.slot_planes = plan.routed_ksplit;
-    dn.plane_stride = (size_t)T * k * ly.d;
+    dn.wide = plan.routed.wide;
+    dn.ksplit = w.slot_planes = plan.routed.ksplit;
+    dn.plane_stride = (size_t)A * ly.d;
     w.direct = plan.routed_direct;
     w.fused = plan.routed_fused;
     if (plan.routed_fused) return LEXI_OK;   // run_layer launches down + combine once the shared expert's rows are there
@@ -305,21 +382,21 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
     }
 
     auto run_shared = [&](hipStream_t st) -> bool {
-        const int dense_tiles = (T + kTileTokens - 1) / kTileTokens;
-        const bool stream_shared = T <= kStreamDenseRows;
+        const LayerPlan plan = plan_layer(ly, T, k, true, false);
+        auto dense = [&](FfnArgs& a, int tile_rows) {   // one group of T rows
+            a.is_bf16 = bf; a.M = T; a.streaming = plan.shared_streams; a.tile_rows = tile_rows;
+            a.max_tiles = (T + tile_rows - 1) / tile_rows;
+        };
         FfnArgs sg{};
-        sg.streaming = stream_shared;
-        sg.is_bf16 = bf; sg.in = x; sg.row_token = nullptr; sg.w0 = ly.ws_gate; sg.w1 = ly.ws_up; sg.K = ly.d;
-        sg.features = ly.F_shared; sg.M = T; sg.max_tiles = dense_tiles; sg.tile_tokens = kTileTokens;
-        sg.sched = nullptr; sg.sched_count = nullptr; sg.out = w.act_shared;
+        sg.in = x; sg.w0 = ly.ws_gate; sg.w1 = ly.ws_up; sg.K = ly.d; sg.features = ly.F_shared; sg.out = w.act_shared;
+        dense(sg, T <= kSideStreamMaxT ? kSideTileRows : kTileRows);
         if (launch_gateup(sg, st) != hipSuccess) return false;
         FfnArgs sd{};
-        sd.streaming = stream_shared;
-        sd.is_bf16 = bf; sd.in = w.act_shared; sd.row_token = nullptr; sd.w0 = ly.ws_down; sd.w1 = nullptr;
-        sd.K = ly.F_shared; sd.features = ly.d; sd.M = T; sd.max_tiles = dense_tiles; sd.tile_tokens = kTileTokens;
-        sd.sched = nullptr; sd.sched_count = nullptr; sd.out = w.y_shared;
-        sd.ksplit = w.shared_planes = plan_down(ly, T, k, true, false).shared_ksplit;
+        sd.in = w.act_shared; sd.w0 = ly.ws_down; sd.K = ly.F_shared; sd.features = ly.d; sd.out = w.y_shared;
+        sd.wide = plan.shared.wide;
+        sd.ksplit = w.shared_planes = plan.shared.ksplit;
         sd.plane_stride = (size_t)T * ly.d;
+        dense(sd, plan.shared.tile_rows);
         return launch_down(sd, st) == hipSuccess;
     };
     SideStream* side = (allow_side_stream && ly.F_shared > 0 && T <= kSideStreamMaxT) ? side_stream() : nullptr;
@@ -355,7 +432,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         }
         DownCombineArgs f{};
         f.act = w.act; f.w_down = ly.w_down; f.F = ly.F; f.d = ly.d; f.T = T; f.k = k; f.sched = w.sched;
-        f.sched_count = w.sched_count; f.inv_perm = w.inv_perm; f.gates = w.gates;
+        f.inv_perm = w.inv_perm; f.gates = w.gates;
         f.y_shared = ly.F_shared > 0 ? w.y_shared : nullptr; f.y = y; f.y_bf16 = y_dtype == LEXI_BF16;
         if (launch_down_combine(f, s) != hipSuccess) return LEXI_ERR_LAUNCH;
         mark(3);
@@ -558,10 +635,10 @@ lexi_status lexi_moe_profile_layer(const lexi_layer_t* layer, const void* x, int
 
 int32_t lexi_moe_down_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int32_t which) {
     if (check_layer(layer) != LEXI_OK || T < 1 || k < 1 || k > layer->E) return -1;
-    const DownPlan p = plan_down(*layer, T, k, true, true);
+    const LayerPlan p = plan_layer(*layer, T, k, true, true);
     switch (which) {
-        case 0: return p.routed_fused ? 4 : (p.routed_streams ? 0 : (p.routed_direct ? 3 : p.routed_ksplit));
-        case 1: return layer->F_shared == 0 ? -1 : (p.shared_streams ? 0 : p.shared_ksplit);
+        case 0: return p.routed_fused ? 4 : (p.routed_streams ? 0 : (p.routed_direct ? 3 : p.routed.ksplit));
+        case 1: return layer->F_shared == 0 ? -1 : (p.shared_streams ? 0 : p.shared.ksplit);
         default: return -1;
     }
 }

@@ -53,8 +53,8 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
         f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
         for (int s = 0; s < k; ++s) {  // slot order = rank order
             f32x4_t v = *(const f32x4_t*)(y_slot + (size_t)ip[s] * d + j);
-            if (slot_planes > 1) {   // the down GEMM's reduction was cut in two: the halves are added first
-                const f32x4_t v1 = *(const f32x4_t*)(y_slot + slot_plane_stride + (size_t)ip[s] * d + j);
+            for (int p = 1; p < slot_planes; ++p) {   // the down GEMM's reduction was cut: the parts are added first
+                const f32x4_t v1 = *(const f32x4_t*)(y_slot + p * slot_plane_stride + (size_t)ip[s] * d + j);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = v[i] + v1[i];
             }
@@ -64,8 +64,8 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
         }
         if (y_shared != nullptr) {
             f32x4_t v = *(const f32x4_t*)(y_shared + (size_t)t * d + j);
-            if (shared_planes > 1) {
-                const f32x4_t v1 = *(const f32x4_t*)(y_shared + shared_plane_stride + (size_t)t * d + j);
+            for (int p = 1; p < shared_planes; ++p) {
+                const f32x4_t v1 = *(const f32x4_t*)(y_shared + p * shared_plane_stride + (size_t)t * d + j);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[i] = v[i] + v1[i];
             }

@@ -11,15 +11,21 @@
 namespace lexi {
 
 // ---------------------------------------------------------------------------------------------------------
-// ffn_mfma_kernel<GATEUP>
-//   Workgroup = 4 waves; token tile = 128 rows shared by all waves through double-buffered LDS; each wave owns its
-//   own 64 weight rows (4 feature blocks of 16) against all 128 tokens (8 token blocks): 32 accumulator blocks of
-//   16 x 16 (v_mfma_f32_16x16x32_bf16), i.e. a 256 x 128 workgroup tile in at most 256 registers per lane, so two
-//   workgroups share a CU and one's prologue/epilogue overlaps the other's MFMA loop.  Weight rows are not shared between waves
-//   and are stored in the packed layout, so their MFMA operand fragments go straight from global memory to
-//   registers as fully coalesced 1 KB wave loads; only the token tile passes through LDS (8 fragment reads per 32 MFMAs).
+// ffn_mfma_kernel<GATEUP, NW>
+//   Workgroup = NW waves; a token tile of up to 160 rows is shared by all waves through double-buffered LDS; each wave owns
+//   its own 64 weight rows (4 feature blocks of 16) against all rows of the tile (up to 10 token blocks): up to 40
+//   accumulator blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16) in at most 256 registers per lane, two waves per SIMD.  Weight
+//   rows are not shared between waves and are stored in the packed layout, so their MFMA operand fragments go straight from
+//   global memory to registers as fully coalesced 1 KB wave loads; only the token tile passes through LDS.
+//   The loop is bound by the bytes a CU pulls through its vector-memory path (it delivers 31 B/clk, against the 47 B/clk
+//   that 256 rows x 128 tokens would need at full matrix rate), so the tile is as tall as the registers allow: 160 tokens
+//   instead of 128 take 8 to 14 % off the gate/up launches (64 experts, d 2048, F 1024, 2048 tokens, k = 8: 154 -> 137 us).
+//   NW = 4: two workgroups share a CU and one's prologue/epilogue overlaps the other's MFMA loop.
+//   NW = 8 (DOWN): one workgroup per CU, a token row is fetched for 512 weight rows instead of 256.  8 experts, d 4096,
+//   F 14336, 4096 tokens: 950 -> 780 us (k = 2), 506 -> 400 us (k = 1); 64 experts, F 1024, 2048 tokens, k = 8: 102 -> 88 us.
+//   Gate/up launches, whose items are shorter, gained nothing from it (between -6 and +15 %).
 //   GATEUP: a wave's blocks 0,1 are gate rows g0..g0+31 and blocks 2,3 the matching up rows, so the epilogue is
-//   silu(gate)*up -> bf16 act[row][f]; the workgroup covers 128 hidden features.
+//   silu(gate)*up -> bf16 act[row][f]; a workgroup of four waves covers 128 hidden features.
 //   DOWN:   a wave's blocks are 64 consecutive output features; the epilogue stores fp32 out[row][j].  Options: the
 //           reduction cut in two halves handled by two workgroups that write two planes of `out` (more, shorter work
 //           items when a launch would otherwise leave most CUs idle in its last round; the consumer adds the planes);
@@ -29,28 +35,38 @@ namespace lexi {
 // ---------------------------------------------------------------------------------------------------------
 template <int S> struct StageTag { static constexpr int value = S; };
 
-template <bool GATEUP>
-__global__ void __launch_bounds__(256, 2)
+template <bool GATEUP, int NW>
+__global__ void __launch_bounds__(NW * 64, 2)
 ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
-                const bf16_t* __restrict__ w1, int K, int features, int M, int tile_tokens,
-                const int32_t* __restrict__ sched, const int32_t* __restrict__ sched_count, void* __restrict__ out,
-                int ksplit, size_t plane_stride, const int32_t* __restrict__ scatter, int out_bf16) {
-    constexpr int TT = 128, TB = TT / 16, WB = 4, KS = BK / 32;
-    __shared__ __attribute__((aligned(16))) bf16_t lds_x[2][TT * LDS_LD];
+                const bf16_t* __restrict__ w1, int K, int features, int M, int tile_rows,
+                const int32_t* __restrict__ sched, void* __restrict__ out, int ksplit, size_t plane_stride,
+                const int32_t* __restrict__ scatter, int out_bf16) {
+    constexpr int TT = kTileRows, TB = TT / 16, WB = 4, KS = BK / 32;
+    constexpr int CB = NW * (GATEUP ? 32 : 64);      // output features of a workgroup
+    constexpr int ELD = CB + 8;                      // GATEUP: bf16 elements per row of the staged output tile
+    constexpr int LDS_ELEMS = (GATEUP && TT * ELD > 2 * TT * LDS_LD) ? TT * ELD : 2 * TT * LDS_LD;
+    __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS];
+    auto lds_x = [&](int buf) { return lds + buf * (TT * LDS_LD); };
 
     TileInfo ti;
-    int cb, part = 0;
-    if (!fetch_item(sched, sched_count, (features + (GATEUP ? 127 : 255)) / (GATEUP ? 128 : 256), M, tile_tokens, ti, cb,
-                    GATEUP ? 1 : ksplit, &part))
-        return;
-    // DOWN with a split reduction: this workgroup covers K-steps [part * nk, (part + 1) * nk) and writes plane `part`
-    const int nk = GATEUP ? K / BK : K / BK / ksplit;
-    const uint32_t kstep0 = GATEUP ? 0u : (uint32_t)(part * nk);
+    int cb, part;
+    if (!fetch_item<GATEUP ? 0 : 1>(sched, (features + CB - 1) / CB, M, tile_rows, GATEUP ? 1 : ksplit, ti, cb, part)) return;
+    // (wave-uniform, but their divisions run on the vector unit: back to scalar registers, the loop has no vector ones to spare)
+    ti.row0 = __builtin_amdgcn_readfirstlane(ti.row0);
+    ti.rows = __builtin_amdgcn_readfirstlane(ti.rows);
+    ti.expert = __builtin_amdgcn_readfirstlane(ti.expert);
+    cb = __builtin_amdgcn_readfirstlane(cb);
+    part = __builtin_amdgcn_readfirstlane(part);
+    // DOWN with a split reduction: this workgroup covers K-steps [part * steps / ksplit, (part + 1) * steps / ksplit)
+    // and writes plane `part`
+    const int steps = K / BK;
+    const int kstep0 = GATEUP ? 0 : part * steps / ksplit;
+    const int nk = GATEUP ? steps : (part + 1) * steps / ksplit - kstep0;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave_f0 = cb * (GATEUP ? 128 : 256) + wave * (GATEUP ? 32 : 64);  // first output feature
+    const int wave_f0 = cb * CB + wave * (GATEUP ? 32 : 64);  // first output feature
     const bool active = wave_f0 < features;
     const int l16 = lane & 15, kq = lane >> 4;
     const int koff = kq * 8;
@@ -76,26 +92,22 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
     }
     const uint32_t alane = lane * 16;
 
-    // ---- token tile staging: thread owns 16-byte chunk (tid % 8) of rows tid/8 + 32p ----
-    const int chunk = tid & 7;
-    uint32_t xoff[4];   // byte offsets from `in` (the launcher rejects inputs of 4 GiB or more)
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int r = (tid >> 3) + 32 * p;
+    // ---- token tile staging: thread owns 16-byte chunk (tid % 8) of rows tid/8 + SR*p; where the last pass has rows for
+    //      half of the threads only, everyone takes 8-byte chunk (tid % 16) of row SR*XP + tid/16 instead (a branch there
+    //      would make the wait for the weights at its join a wait for all loads) ----
+    constexpr int SR = NW * 8;                       // token rows staged per pass of the workgroup
+    constexpr int XP = TT / SR;
+    constexpr bool HALF = TT % SR != 0;
+    static_assert(!HALF || TT % SR == SR / 2, "the last pass stages a whole or a half set of rows");
+    auto x_row = [&](int r) {   // byte offset of tile row r from `in` (the launcher rejects inputs of 4 GiB or more)
         const int rr = min(r, ti.rows - 1);  // rows past the group end re-read its last row; never stored
         const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
-        xoff[p] = (uint32_t)(((size_t)src_row * K + (size_t)kstep0 * BK + chunk * 8) * 2);
-    }
-    u32x4_t xreg[4];
-    auto load_x = [&](int kt) {
-#pragma unroll
-        for (int p = 0; p < 4; ++p) xreg[p] = *(const u32x4_t*)((const char*)in + (xoff[p] + (uint32_t)kt * (BK * 2)));
+        return (uint32_t)(((size_t)src_row * K + (size_t)kstep0 * BK) * 2);
     };
-    auto store_x = [&](int buf) {
+    uint32_t xoff[XP], xoff_half = 0;
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
-            *(u32x4_t*)(&lds_x[buf][((tid >> 3) + 32 * p) * LDS_LD + chunk * 8]) = xreg[p];
-    };
+    for (int p = 0; p < XP; ++p) xoff[p] = x_row((tid >> 3) + SR * p) + (tid & 7) * 16;
+    if (HALF) xoff_half = x_row((tid >> 4) + SR * XP) + (tid & 15) * 8;
 
     f32x4_t acc[WB][TB];
 #pragma unroll
@@ -106,40 +118,80 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0f;
 
     bf16x8_t areg[WB][KS];
-    load_x(0);
 #pragma unroll
     for (int fb = 0; fb < WB; ++fb)
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)ks * 1024u));
-    store_x(0);
-    __syncthreads();
 
-    // The K loop, specialised on the number of 16-token blocks the tile really holds: the last tile of an expert's
-    // group (and every tile of a decode-sized batch) skips the MFMAs of token blocks that would only hold padding.
+    // The K loop, specialised on the number of 16-token blocks the tile really holds: nothing is staged, read or multiplied
+    // for blocks that would only hold padding.
+    // Up to 8 blocks: the tile of the next K-step is fetched at the top of a step and stored at its end, the token
+    // fragments of a half step are read together.  9 and 10 blocks leave too few of the 256 registers for that: fragments
+    // are read two blocks at a time, the next pair while the current one is multiplied, and (four waves) the tile is
+    // fetched and stored in two halves, one per half step.
     auto k_loop = [&](auto ntb_tag) {
         constexpr int NTB = decltype(ntb_tag)::value;
+        constexpr bool TALL = NTB > 8;
+        constexpr int NP = (NTB * 16 + SR - 1) / SR < XP ? (NTB * 16 + SR - 1) / SR : XP;   // 16-byte passes of this tile
+        constexpr bool LAST_HALF = HALF && NTB * 16 > SR * XP;
+        constexpr int PARTS = TALL && !HALF ? 2 : 1;     // the passes are fetched in this many parts per K-step
+        constexpr int PP = (NP + PARTS - 1) / PARTS;
+        constexpr int GB = TALL ? 2 : NTB;               // token blocks whose fragments are read together
+        constexpr int NG = (NTB + GB - 1) / GB;
+        static_assert(KS == 2, "a K-step has two halves");
+        u32x4_t xreg[PP];
+        u32x2_t xreg_half;
+        auto load_x = [&](int kt, int h) {
+#pragma unroll
+            for (int p = 0; p < PP; ++p)
+                if (h * PP + p < NP) xreg[p] = *(const u32x4_t*)((const char*)in + (xoff[h * PP + p] + (uint32_t)kt * (BK * 2)));
+            if (LAST_HALF) xreg_half = *(const u32x2_t*)((const char*)in + (xoff_half + (uint32_t)kt * (BK * 2)));
+        };
+        auto store_x = [&](int buf, int h) {
+#pragma unroll
+            for (int p = 0; p < PP; ++p)
+                if (h * PP + p < NP)
+                    *(u32x4_t*)(lds_x(buf) + ((tid >> 3) + SR * (h * PP + p)) * LDS_LD + (tid & 7) * 8) = xreg[p];
+            if (LAST_HALF) *(u32x2_t*)(lds_x(buf) + ((tid >> 4) + SR * XP) * LDS_LD + (tid & 15) * 4) = xreg_half;
+        };
+#pragma unroll
+        for (int h = 0; h < PARTS; ++h) {
+            load_x(0, h);
+            store_x(0, h);
+        }
+        __syncthreads();
         for (int kt = 0; kt < nk; ++kt) {
             const int buf = kt & 1;
             const int kn = min(kt + 1, nk - 1);  // the last stage re-fetches itself: branch-free, in bounds, unused
-            load_x(kn);
-            __builtin_amdgcn_sched_barrier(0);  // keep the token-tile loads at the top: they are consumed after the MFMAs
             // (waves of a ragged last column run the same loop on weight row 0 instead of branching around it)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                bf16x8_t b[NTB];
+                if (ks < PARTS) load_x(kn, ks);
+                __builtin_amdgcn_sched_barrier(0);  // keep the token-tile loads in front: they are consumed after the MFMAs
+                bf16x8_t b[2][GB];
+                auto read_group = [&](int g) {
 #pragma unroll
-                for (int tb = 0; tb < NTB; ++tb)
-                    b[tb] = *(const bf16x8_t*)(&lds_x[buf][(tb * 16 + l16) * LDS_LD + ks * 32 + koff]);
+                    for (int u = 0; u < GB; ++u)
+                        if (GB * g + u < NTB)
+                            b[g & 1][u] = *(const bf16x8_t*)(lds_x(buf) + ((GB * g + u) * 16 + l16) * LDS_LD + ks * 32 + koff);
+                };
+                read_group(0);
 #pragma unroll
-                for (int fb = 0; fb < WB; ++fb)
+                for (int g = 0; g < NG; ++g) {
+                    if (g + 1 < NG) read_group(g + 1);
+                    if (TALL) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                    for (int tb = 0; tb < NTB; ++tb)
-                        acc[fb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg[fb][ks], b[tb], acc[fb][tb], 0, 0, 0);
+                    for (int fb = 0; fb < WB; ++fb)
+#pragma unroll
+                        for (int u = 0; u < GB; ++u)
+                            if (GB * g + u < NTB)
+                                acc[fb][GB * g + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg[fb][ks], b[g & 1][u], acc[fb][GB * g + u], 0, 0, 0);
+                }
 #pragma unroll
                 for (int fb = 0; fb < WB; ++fb) areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)(kn * KS + ks) * 1024u));
                 __builtin_amdgcn_sched_barrier(0);  // refill each fragment right after its last use, one k-step at a time
+                if (PARTS == 2 || ks == KS - 1) store_x(buf ^ 1, PARTS == 2 ? ks : 0);
             }
-            store_x(buf ^ 1);
             __syncthreads();
         }
     };
@@ -151,16 +203,16 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
         case 5: k_loop(StageTag<5>{}); break;
         case 6: k_loop(StageTag<6>{}); break;
         case 7: k_loop(StageTag<7>{}); break;
-        default: k_loop(StageTag<8>{}); break;
+        case 8: k_loop(StageTag<8>{}); break;
+        case 9: k_loop(StageTag<9>{}); break;
+        default: k_loop(StageTag<10>{}); break;
     }
     // ---- epilogue: in a 16 x 16 accumulator block a lane owns token (lane % 16) and features 4*(lane/16) + 0..3
     if (GATEUP) {
-        // The workgroup's 128 tokens x 128 features of silu(gate)*up are transposed through LDS (the token-tile
+        // The workgroup's tokens x 128 features of silu(gate)*up are transposed through LDS (the token-tile
         // buffers are free now), so that the global stores are whole 256-byte rows instead of 8-byte pieces.
         // Row stride 272 B: the 8-byte writes of a half-wave (16 tokens x 2 lane groups) then fall on 64 distinct banks.
-        constexpr int ELD = 136;   // bf16 elements per staged row
-        static_assert(TT * ELD <= 2 * TT * LDS_LD, "the staged output tile must fit the token-tile buffers");
-        bf16_t* stage = &lds_x[0][0];
+        bf16_t* stage = lds;
         __syncthreads();           // every wave is done reading the token tile
 #pragma unroll
         for (int tb = 0; tb < TB; ++tb) {
@@ -177,14 +229,15 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
             }
         }
         __syncthreads();
-        const int c16 = tid & 15;                       // 16-byte chunk of the 256-byte row
-        const int f = cb * 128 + c16 * 8;               // first of its 8 features
+        constexpr int CH = CB / 8, RP = NW * 64 / CH;    // 16-byte chunks of a row, rows per pass of the workgroup
+        const int ch = tid % CH;
+        const int f = cb * CB + ch * 8;                 // first of the chunk's 8 features
         if (f < features) {                             // (ragged last column block: features is a multiple of 64)
 #pragma unroll
-            for (int p = 0; p < TT / 16; ++p) {
-                const int r = (tid >> 4) + 16 * p;
+            for (int p = 0; p < TT / RP; ++p) {
+                const int r = tid / CH + RP * p;
                 if (r < ti.rows)
-                    *(u32x4_t*)((bf16_t*)out + (size_t)(ti.row0 + r) * features + f) = *(const u32x4_t*)(&stage[r * ELD + c16 * 8]);
+                    *(u32x4_t*)((bf16_t*)out + (size_t)(ti.row0 + r) * features + f) = *(const u32x4_t*)(&stage[r * ELD + ch * 8]);
             }
         }
     } else {
@@ -257,17 +310,23 @@ static hipError_t launch_ffn(const FfnArgs& a, hipStream_t s) {
     if (a.max_tiles <= 0) return hipSuccess;
     if ((a.ksplit > 1 || a.scatter != nullptr) && !(a.is_bf16 && !a.streaming && !GATEUP))
         return hipErrorInvalidValue;   // split reduction and scattered rows exist on the bf16 tile schedule's DOWN only
-    if (a.streaming || !a.is_bf16) return GATEUP ? launch_gateup_stream(a, s) : launch_down_stream(a, s);
+    if (a.streaming) return GATEUP ? launch_gateup_stream(a, s) : launch_down_stream(a, s);
     // the tile kernel addresses its input rows with 32-bit byte offsets
     const size_t in_rows = a.row_token ? (size_t)a.in_rows : (size_t)a.M;
     if (in_rows * (size_t)a.K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
-    const int ncb = (a.features + (GATEUP ? 127 : 255)) / (GATEUP ? 128 : 256);
     const int ksplit = GATEUP ? 1 : (a.ksplit > 1 ? a.ksplit : 1);
-    if (ksplit > 1 && ((a.K / BK) % ksplit != 0 || a.scatter != nullptr)) return hipErrorInvalidValue;
-    const dim3 grid(xcd_grid(ncb, a.max_tiles, ksplit));
-    hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP>), grid, dim3(256), 0, s, (const bf16_t*)a.in, a.row_token,
-                       (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_tokens, a.sched,
-                       a.sched_count, a.out, ksplit, a.plane_stride, GATEUP ? nullptr : a.scatter, a.out_bf16 ? 1 : 0);
+    if (ksplit > 1 && (a.K / BK < ksplit || a.scatter != nullptr)) return hipErrorInvalidValue;
+    auto launch = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value, CB = NW * (GATEUP ? 32 : 64);
+        const long long pieces = (long long)((a.features + CB - 1) / CB) * a.max_tiles * ksplit;
+        const dim3 grid((unsigned)((pieces + kXcds - 1) / kXcds * kXcds));
+        hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP, NW>), grid, dim3(NW * 64), 0, s, (const bf16_t*)a.in,
+                           a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
+                           a.out, ksplit, a.plane_stride, GATEUP ? nullptr : a.scatter, a.out_bf16 ? 1 : 0);
+    };
+    if constexpr (GATEUP) launch(StageTag<4>{});
+    else if (a.wide) launch(StageTag<8>{});
+    else launch(StageTag<4>{});
     return hipGetLastError();
 }
 

@@ -21,77 +21,85 @@ struct TileInfo {
     int expert, row0, rows;
 };
 
-// Tile schedule written by the scan kernel: one entry of kSchedStride ints per token tile,
-//   (expert, first permuted row of the expert, rows of the expert, index of the tile inside its expert, tiles of the
-//   expert, 0, 0, 0),
-// tiles sorted by expert; sched_count[0] = number of tiles.  Every entry carries its expert's whole extent, so any tile
-// of the expert can be derived from any of its entries with one load.  sched == null: one dense group of M rows.
-constexpr int kSchedStride = 8;
+// Tile t of the n = ceil(rows / tile height) tiles of a group: the group's 16-row blocks are dealt out evenly (heights
+// differ by one block at most), so no tile is a short remainder that streams a whole weight slab for a few rows.
+__device__ __forceinline__ void even_tile(int group_row0, int group_rows, int t, int n, TileInfo& ti) {
+    const int nb = (group_rows + 15) >> 4;
+    const int per = nb / n, extra = nb - per * n;
+    const int b0 = t * per + min(t, extra);
+    const int blocks = per + (t < extra ? 1 : 0);
+    ti.row0 = group_row0 + b0 * 16;
+    ti.rows = min(blocks * 16, group_rows - b0 * 16);
+}
 
-__device__ __forceinline__ bool fetch_tile(const int32_t* sched, const int32_t* sched_count, int tile, int M,
-                                           int tile_tokens, TileInfo& ti) {
-    if (sched != nullptr) {
-        if (tile >= sched_count[0]) return false;
-        const int32_t* s = sched + (size_t)tile * kSchedStride;
-        ti.expert = s[0];
-        ti.row0 = s[1] + s[3] * tile_tokens;
-        ti.rows = min(tile_tokens, s[2] - s[3] * tile_tokens);
-        return true;
+// The group token tile `tile` of GEMM G belongs to: its rows, its tiles [first, first + n).  One lane per expert looks, all
+// lanes of the wave call it with the same tile.  sched == null: one dense group of M rows.
+struct TileGroup {
+    int expert, row0, rows, first, n;
+};
+template <int G>
+__device__ __forceinline__ bool fetch_group(const int32_t* sched, int tile, int M, int tile_rows, TileGroup& g) {
+    if (sched == nullptr) {
+        g = TileGroup{0, 0, M, 0, (M + tile_rows - 1) / tile_rows};
+        return tile < g.n;
     }
-    ti.expert = 0;
-    ti.row0 = tile * tile_tokens;
-    ti.rows = min(tile_tokens, M - ti.row0);
-    return ti.rows > 0;
+    const int lane = threadIdx.x & 63;
+    const int off = sched[kSchedOff + lane], cnt = sched[kSchedCount + lane];
+    const int end = sched[kSchedTiles + 64 * G + lane];     // tiles of experts 0 .. lane
+    g.expert = __popcll(__ballot(end <= tile));
+    if (g.expert >= 64) return false;
+    const int e = __builtin_amdgcn_readfirstlane(g.expert);
+    g.row0 = __builtin_amdgcn_readlane(off, e);
+    g.rows = __builtin_amdgcn_readlane(cnt, e);
+    g.first = e > 0 ? __builtin_amdgcn_readlane(end, e - 1) : 0;
+    g.n = __builtin_amdgcn_readlane(end, e) - g.first;
+    return true;
+}
+
+template <int G>
+__device__ __forceinline__ bool fetch_tile(const int32_t* sched, int tile, int M, int tile_rows, TileInfo& ti) {
+    TileGroup g;
+    if (!fetch_group<G>(sched, tile, M, tile_rows, g)) return false;
+    ti.expert = g.expert;
+    even_tile(g.row0, g.rows, tile - g.first, g.n, ti);
+    return true;
 }
 
 // XCD-aware work order for the tile kernels.  Workgroup ids are handed to the 8 XCDs round-robin (id % 8), each XCD
-// with its own L2, and a CU holds two workgroups, so 64 consecutive work items of an XCD are resident together.
-// Work items are (token tile, column block).  They are ordered expert by expert; inside an expert by groups of
+// with its own L2, and a CU holds two workgroups of four waves, so 64 consecutive work items of an XCD are resident
+// together.  Work items are (token tile, column block).  They are ordered expert by expert; inside an expert by groups of
 // kCbGroup column blocks; inside a group tile-major.  A window of 64 items then holds few distinct weight slabs,
 // each read by ALL token tiles of its expert at the same time, whatever the number of column blocks is (sharing the
 // weight stream is what pays: groups of 1 or 2 column blocks measured 10 to 40 % faster than groups of 8 or more,
-// which favour sharing the much smaller token tile).  The item list is cut into 8 contiguous parts, XCD x takes
-// the x-th.
-// The grid is 1-D: 8 * ceil(ncb * max_tiles / 8) workgroups.
-constexpr int kXcds = 8;
+// which favour sharing the much smaller token tile).  The item list is cut into 8 contiguous parts of equal length, XCD x
+// takes the x-th.  (Parts of equal estimated cost measured up to 60 % slower: a part only slightly longer than the average
+// needs a whole further round of its XCD's workgroup slots.)
+// The grid is 1-D: 8 * ceil(ncb * max_tiles / 8) workgroups, times ksplit.
 constexpr int kCbGroup = 2;
-inline unsigned xcd_grid(int ncb, int max_tiles, int ksplit = 1) {
-    const long long total = (long long)ncb * max_tiles * ksplit;
-    return (unsigned)(((total + kXcds - 1) / kXcds) * kXcds);
-}
 
 // With ksplit > 1 every item appears ksplit times in a row, once per part of the reduction dimension.
-__device__ __forceinline__ bool fetch_item(const int32_t* sched, const int32_t* sched_count, int ncb, int M,
-                                           int tile_tokens, TileInfo& ti, int& cb, int ksplit = 1, int* part = nullptr) {
-    const int ntiles = sched != nullptr ? sched_count[0] : (M + tile_tokens - 1) / tile_tokens;
-    const int total = ntiles * ncb;
-    const int pieces = total * ksplit;
-    const int per = (pieces + kXcds - 1) / kXcds;
+template <int G>
+__device__ __forceinline__ bool fetch_item(const int32_t* sched, int ncb, int M, int tile_rows, int ksplit, TileInfo& ti, int& cb,
+                                           int& part) {
     const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+    const int ntiles = sched != nullptr ? sched[kSchedTiles + 64 * G + 63] : (M + tile_rows - 1) / tile_rows;
+    const int total = ntiles * ncb * ksplit;
+    const int per = (total + kXcds - 1) / kXcds;
     const int piece = xcd * per + slot;
-    if (slot >= per || piece >= pieces) return false;
+    if (slot >= per || piece >= total) return false;
     const int item = piece / ksplit;
-    if (part != nullptr) *part = piece - item * ksplit;
+    part = piece - item * ksplit;
     // an expert with n tiles owns n * ncb consecutive items, so tile (item / ncb) belongs to the item's expert
-    int first = 0, n = ntiles, erow0 = 0, erows = M;
-    ti.expert = 0;
-    if (sched != nullptr) {
-        const int tq = item / ncb;
-        const int32_t* s = sched + (size_t)tq * kSchedStride;
-        ti.expert = s[0];
-        erow0 = s[1];
-        erows = s[2];
-        first = tq - s[3];
-        n = s[4];
-    }
-    const int j = item - first * ncb;
-    const int gsz = n * kCbGroup;
-    const int g = j / gsz, r = j - g * gsz;
-    const int gw = min(kCbGroup, ncb - g * kCbGroup);   // the last group of an expert may be narrower
+    TileGroup g;
+    if (!fetch_group<G>(sched, item / ncb, M, tile_rows, g)) return false;
+    const int j = item - g.first * ncb;
+    const int gsz = g.n * kCbGroup;
+    const int q = j / gsz, r = j - q * gsz;
+    const int gw = min(kCbGroup, ncb - q * kCbGroup);   // the last group of an expert may be narrower
     const int t = r / gw;
-    cb = g * kCbGroup + (r - t * gw);
-    ti.row0 = erow0 + t * tile_tokens;
-    ti.rows = min(tile_tokens, erows - t * tile_tokens);
+    cb = q * kCbGroup + (r - t * gw);
+    ti.expert = g.expert;
+    even_tile(g.row0, g.rows, t, g.n, ti);
     return true;
 }
 

@@ -44,14 +44,14 @@ template <> struct Frag<false> {
 template <bool GATEUP, bool BF16>
 __global__ void __launch_bounds__(256)
 ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_token, const void* __restrict__ w0_,
-                  const void* __restrict__ w1_, int K, int features, int M, int tile_tokens,
-                  const int32_t* __restrict__ sched, const int32_t* __restrict__ sched_count, void* __restrict__ out) {
+                  const void* __restrict__ w1_, int K, int features, int M, int tile_rows,
+                  const int32_t* __restrict__ sched, void* __restrict__ out) {
     typedef typename Frag<BF16>::elem_t elem_t;
     const elem_t *in = (const elem_t*)in_, *w0 = (const elem_t*)w0_, *w1 = (const elem_t*)w1_;
     __shared__ __attribute__((aligned(16))) f32x4_t red[4][2][64];
 
     TileInfo ti;
-    if (!fetch_tile(sched, sched_count, blockIdx.y, M, tile_tokens, ti)) return;
+    if (!fetch_tile<GATEUP ? 0 : 1>(sched, blockIdx.y, M, tile_rows, ti)) return;
 
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -131,11 +131,16 @@ ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_
             __syncthreads();
         }
     };
-    const int ntb = (ti.rows + 15) >> 4;
-    if (ntb <= 1) body(IntTag<1>{});
-    else if (ntb <= 2) body(IntTag<2>{});
-    else if (ntb <= 4) body(IntTag<4>{});
-    else body(IntTag<8>{});
+    // 128 rows at a time (a tile may be taller; the second pass over the weights is then served by the cache)
+    const int row_end = ti.row0 + ti.rows;
+    for (; ti.row0 < row_end; ti.row0 += 128) {
+        ti.rows = min(128, row_end - ti.row0);
+        const int ntb = (ti.rows + 15) >> 4;
+        if (ntb <= 1) body(IntTag<1>{});
+        else if (ntb <= 2) body(IntTag<2>{});
+        else if (ntb <= 4) body(IntTag<4>{});
+        else body(IntTag<8>{});
+    }
 }
 
 template <bool GATEUP>
@@ -144,10 +149,10 @@ static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
     const dim3 grid(a.features / 16, a.max_tiles);
     if (a.is_bf16)
         hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, true>), grid, dim3(256), 0, s, a.in, a.row_token, a.w0, a.w1, a.K,
-                           a.features, a.M, a.tile_tokens, a.sched, a.sched_count, a.out);
+                           a.features, a.M, a.tile_rows, a.sched, a.out);
     else
         hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, false>), grid, dim3(256), 0, s, a.in, a.row_token, a.w0, a.w1, a.K,
-                           a.features, a.M, a.tile_tokens, a.sched, a.sched_count, a.out);
+                           a.features, a.M, a.tile_rows, a.sched, a.out);
     return hipGetLastError();
 }
 
@@ -163,9 +168,8 @@ static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
 template <bool Y_BF16>
 __global__ void __launch_bounds__(1024)
 down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w_down, int K, int d,
-                    const int32_t* __restrict__ sched, const int32_t* __restrict__ sched_count,
-                    const int32_t* __restrict__ inv_perm, const float* __restrict__ gates,
-                    const float* __restrict__ y_shared, int T, int k, void* __restrict__ y) {
+                    const int32_t* __restrict__ sched, const int32_t* __restrict__ inv_perm,
+                    const float* __restrict__ gates, const float* __restrict__ y_shared, int T, int k, void* __restrict__ y) {
     __shared__ __attribute__((aligned(16))) f32x4_t red[16][64];
     __shared__ __attribute__((aligned(16))) f32x4_t ys[kFusedDownMaxRows][4];   // row -> the unit's 16 features
 
@@ -175,7 +179,10 @@ down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w
     const int l16 = lane & 15, kq = lane >> 4;
     const int unit = blockIdx.x;   // output features 16*unit .. 16*unit+15
     const int nkb = K >> 5;
-    const int ntiles = sched_count[0];
+    // an expert with rows has one tile
+    const int e_off = sched[kSchedOff + lane], e_cnt = sched[kSchedCount + lane];
+    const int e_end = sched[kSchedTiles + 64 + lane];
+    const int ntiles = __builtin_amdgcn_readlane(e_end, 63);
     // combine: thread (t, q) owns features 16*unit + 4*q + 0..3 of token t; what it adds at the end that does not
     // depend on the projection is fetched now, under the weight stream
     const bool combiner = tid < T * 4;
@@ -203,10 +210,9 @@ down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w
         int row0 = 0, rows = 0;
         f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
         if (live) {
-            const int32_t* sp = sched + (size_t)tile * kSchedStride;
-            const int expert = sp[0];
-            row0 = sp[1];
-            rows = min(sp[2], 16);
+            const int expert = __builtin_amdgcn_readfirstlane(__popcll(__ballot(e_end <= tile)));
+            row0 = __builtin_amdgcn_readlane(e_off, expert);
+            rows = min(__builtin_amdgcn_readlane(e_cnt, expert), 16);
             const int kb0 = kpart * nkb / wpt, kb1 = (kpart + 1) * nkb / wpt;
             const bf16_t* a0 = w_down + ((size_t)expert * (d >> 4) + unit) * ((size_t)K * 16) + lane * 8;
             // rows past the expert's end re-read its last row; their results are never used
@@ -276,10 +282,10 @@ hipError_t launch_down_combine(const DownCombineArgs& a, hipStream_t s) {
     const dim3 grid(a.d / 16);
     if (a.y_bf16)
         hipLaunchKernelGGL(down_combine_kernel<true>, grid, dim3(1024), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
-                           a.F, a.d, a.sched, a.sched_count, a.inv_perm, a.gates, a.y_shared, a.T, a.k, a.y);
+                           a.F, a.d, a.sched, a.inv_perm, a.gates, a.y_shared, a.T, a.k, a.y);
     else
         hipLaunchKernelGGL(down_combine_kernel<false>, grid, dim3(1024), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
-                           a.F, a.d, a.sched, a.sched_count, a.inv_perm, a.gates, a.y_shared, a.T, a.k, a.y);
+                           a.F, a.d, a.sched, a.inv_perm, a.gates, a.y_shared, a.T, a.k, a.y);
     return hipGetLastError();
 }
 

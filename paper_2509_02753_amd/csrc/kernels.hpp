@@ -4,13 +4,25 @@
 
 namespace lexi {
 
+// Height of the token tiles of the grouped GEMMs (rows a tile holds at most), and the XCDs their work is dealt out to.
+constexpr int kTileRows = 160;
+constexpr int kXcds = 8;
+
+// Tiles of the two grouped GEMMs of a layer (0: gate/up, 1: down), written by the routing kernels: an expert with n rows
+// has ceil(n / tile_rows) of them.  In memory: 64 expert offsets, 64 counts, and per GEMM the 64 inclusive sums of the
+// experts' tiles.
+struct WorkPlan {
+    int tile_rows[2];         // tile height, a multiple of 16, at most kTileRows
+};
+constexpr int kSchedOff = 0, kSchedCount = 64, kSchedTiles = 128, kSchedInts = 256;
+
 struct RoutingArgs {
     const void* x;            // [T][d]
     bool is_bf16;
     const float* w_router;    // [d][E]
     const float* bias;        // [E] or null
     int T, d, E, k;
-    int tile_tokens;          // token-tile height the grouped GEMM schedule is built for
+    WorkPlan plan;
     float* partial;           // [d/128][T][64] segment partials of the logits, where they go through memory (router_partial_tokens)
     int32_t* topk_idx;        // [T*k]
     float* gates;             // [T*k]
@@ -21,8 +33,7 @@ struct RoutingArgs {
     int32_t* perm;            // [T*k]
     int32_t* inv_perm;        // [T*k]
     int32_t* row_token;       // [T*k]  permuted row -> token
-    int32_t* sched;           // [max_tiles][8]  (expert, its first row, its rows, tile index in it, its tiles, 0, 0, 0)
-    int32_t* sched_count;     // [1]
+    int32_t* sched;           // [kSchedInts]
 };
 
 constexpr int kFusedTailMaxT = 16;     // T at or below which one workgroup does everything after the segment partials
@@ -42,8 +53,8 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s);
 // One grouped (or dense) GEMM of the expert FFN.
 //   GATE/UP:  act[r][f] = silu(in[tok(r)] . Wg[e][f]) * (in[tok(r)] . Wu[e][f])      K = d, features = F
 //   DOWN:     out[r][j] = act[r] . Wd[e][j]                                           K = F, features = d
-// rows r are the permuted assignment rows (grouped: tile schedule from the scan) or plain token rows (dense, sched
-// == null: one group of M rows, expert 0).
+// rows r are the permuted assignment rows (grouped: work list from the scan) or plain token rows (dense, sched == null:
+// one group of M rows, expert 0).
 struct FfnArgs {
     bool is_bf16;
     bool streaming;            // few rows per expert: use the weight-streaming (HBM-bound) schedule
@@ -54,14 +65,14 @@ struct FfnArgs {
     const void* w1;            // up weights or null
     int K;                     // reduction length
     int features;              // F (gate/up) or d (down)
-    int M;                     // total rows (dense mode bound / grid sizing)
+    int M;                     // total rows
+    int tile_rows;             // as in the work list (WorkPlan)
     int max_tiles;             // upper bound on the number of token tiles
-    int tile_tokens;           // must equal the value the schedule was built with
     const int32_t* sched;      // null = dense
-    const int32_t* sched_count;
     void* out;                 // GATE/UP: act [rows][F] (layer dtype);  DOWN: [rows][d] fp32
     // DOWN on the tile schedule only:
-    int ksplit;                // 1, or 2: the reduction is cut in two halves, half h writes plane h of `out`
+    bool wide;                 // workgroups of eight waves (512 output features) instead of four (256)
+    int ksplit;                // the reduction is cut in ksplit parts, part p writes plane p of `out`
     size_t plane_stride;       // elements between the planes of `out`
     const int32_t* scatter;    // null, or row -> output row: rows are stored at out[scatter[row]] (ksplit must be 1)
     bool out_bf16;             // with scatter: `out` is bf16 (nearest-even rounding of the fp32 result) instead of fp32
@@ -103,8 +114,7 @@ struct DownCombineArgs {
     const void* act;           // [T*k][F] bf16, permuted rows
     const void* w_down;        // [E] packed matrices of [d][F]
     int F, d, T, k;
-    const int32_t* sched;      // tile schedule (one tile per expert with rows)
-    const int32_t* sched_count;
+    const int32_t* sched;      // work list (one tile per expert with rows)
     const int32_t* inv_perm;   // [T*k]
     const float* gates;        // [T*k]
     const float* y_shared;     // [T][d] fp32 or null (added with coefficient 1)

@@ -367,23 +367,40 @@ topk_kernel(const float* __restrict__ partial, int pstride, const float* __restr
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// write_work_list: the expert table and the tiles of the two grouped GEMMs, by one wave (lane = expert, `total` = its
+// rows); returns the expert's first permuted row.
+// ---------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ int32_t write_work_list(int32_t total, int E, const WorkPlan& plan, int32_t* __restrict__ counts,
+                                                   int32_t* __restrict__ offsets, int32_t* __restrict__ sched) {
+    const int lane = threadIdx.x & 63;
+    const int32_t off = wave_inclusive_sum(total) - total;
+    if (lane < E) {
+        counts[lane] = total;
+        offsets[lane] = off;
+    }
+    if (lane == 63) offsets[E] = off + total;       // lanes >= E hold no rows
+    sched[kSchedOff + lane] = off;
+    sched[kSchedCount + lane] = total;
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+        sched[kSchedTiles + 64 * g + lane] = wave_inclusive_sum((total + plan.tile_rows[g] - 1) / plan.tile_rows[g]);
+    return off;
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // scan_kernel (one workgroup of 16 waves): per expert, exclusive prefix of the block histograms (in place),
-// counts, offsets, and the token-tile schedule of the grouped GEMMs: 8 ints per tile (expert, the expert's first
-// row and row count, index of the tile inside the expert, tiles of the expert).
+// counts, offsets, and the work list of the grouped GEMMs.
 // Wave w scans its contiguous chunk of blocks, the chunk totals are combined through LDS.
 // ---------------------------------------------------------------------------------------------------------
 // With FUSE_PERMUTE (decode-sized batches) the same workgroup then scatters the assignments (the body of
 // permute_kernel), which saves a launch on the latency-bound path.
 template <bool FUSE_PERMUTE>
 __global__ void __launch_bounds__(1024)
-scan_kernel(int32_t* __restrict__ blk_hist, int nblk, int E, int tile_tokens, int32_t* __restrict__ counts,
-            int32_t* __restrict__ offsets, int32_t* __restrict__ sched, int32_t* __restrict__ sched_count,
-            const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_rank, int A, int k,
+scan_kernel(int32_t* __restrict__ blk_hist, int nblk, int E, WorkPlan plan, int32_t* __restrict__ counts,
+            int32_t* __restrict__ offsets, int32_t* __restrict__ sched, const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_rank, int A, int k,
             int tokens_per_block, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
             int32_t* __restrict__ row_token) {
     __shared__ int32_t chunk_tot[16][64];
-    __shared__ int32_t s_cnt[64];
-    __shared__ int32_t s_tiles[64];
     __shared__ int32_t s_off[64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int chunk = (nblk + 15) / 16;
@@ -421,34 +438,7 @@ scan_kernel(int32_t* __restrict__ blk_hist, int nblk, int E, int tile_tokens, in
                 if (b + u < b1) blk_hist[(size_t)(b + u) * 64 + lane] = h[u] + base;
         }
     }
-    const int32_t ntile = (total + tile_tokens - 1) / tile_tokens;
-    if (wave == 0) {
-        s_cnt[lane] = total;
-        s_tiles[lane] = ntile;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        int32_t off = 0, tile_base = 0;
-        for (int e = 0; e < lane; ++e) { off += s_cnt[e]; tile_base += s_tiles[e]; }
-        s_off[lane] = off;
-        if (lane < E) {
-            counts[lane] = total;
-            offsets[lane] = off;
-            for (int i = 0; i < ntile; ++i) {
-                int32_t* s = sched + (size_t)(tile_base + i) * 8;
-                s[0] = lane;      // expert
-                s[1] = off;       // first permuted row of the expert
-                s[2] = total;     // rows of the expert
-                s[3] = i;         // index of the tile inside its expert
-                s[4] = ntile;     // tiles of the expert
-            }
-        }
-        if (lane == 63) {
-            // lanes >= E carry zero counts, so lane 63's exclusive sums plus its own are the totals
-            offsets[E] = off + total;
-            sched_count[0] = tile_base + ntile;
-        }
-    }
+    if (wave == 0) s_off[lane] = write_work_list(total, E, plan, counts, offsets, sched);
     if (!FUSE_PERMUTE) return;
     __syncthreads();   // s_off, and this workgroup's own writes to blk_hist, are visible to all its waves from here
     for (int a = threadIdx.x; a < A; a += 1024) {
@@ -473,13 +463,12 @@ constexpr int kFusedTailMaxA = kFusedTailMaxT * 64;   // assignments (k <= E <= 
 
 __global__ void __launch_bounds__(1024)
 topk_scan_kernel(const float* __restrict__ partial, const float* __restrict__ bias, int T, int nseg, int E, int k,
-                 int tile_tokens, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
+                 WorkPlan plan, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
                  int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
-                 int32_t* __restrict__ sched_count, int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
+                 int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
                  int32_t* __restrict__ row_token) {
     __shared__ int32_t wave_hit[16][64];        // this pass: 1 if the wave's token selected expert e
     __shared__ int32_t s_seen[64];              // assignments to expert e by the tokens of earlier passes
-    __shared__ int32_t s_tiles[64];
     __shared__ int32_t s_off[64];
     __shared__ uint8_t s_e[kFusedTailMaxA];     // expert of assignment a
     __shared__ int16_t s_rank[kFusedTailMaxA];  // assignments to that expert by earlier tokens
@@ -536,28 +525,7 @@ topk_scan_kernel(const float* __restrict__ partial, const float* __restrict__ bi
         }
         __syncthreads();
     }
-    if (wave == 0) {
-        const int32_t total = s_seen[lane];
-        const int32_t ntile = (total + tile_tokens - 1) / tile_tokens;
-        s_tiles[lane] = ntile;
-        __builtin_amdgcn_s_waitcnt(0);          // wave 0 reads what its own lanes wrote: order the LDS accesses
-        __builtin_amdgcn_wave_barrier();
-        int32_t off = 0, tile_base = 0;
-        for (int e = 0; e < lane; ++e) { off += s_seen[e]; tile_base += s_tiles[e]; }
-        s_off[lane] = off;
-        if (lane < E) {
-            counts[lane] = total;
-            offsets[lane] = off;
-            for (int i = 0; i < ntile; ++i) {
-                int32_t* sp = sched + (size_t)(tile_base + i) * 8;
-                sp[0] = lane; sp[1] = off; sp[2] = total; sp[3] = i; sp[4] = ntile;
-            }
-        }
-        if (lane == 63) {
-            offsets[E] = off + total;
-            sched_count[0] = tile_base + ntile;
-        }
-    }
+    if (wave == 0) s_off[lane] = write_work_list(s_seen[lane], E, plan, counts, offsets, sched);
     __syncthreads();
     const int A = T * k;
     for (int a = threadIdx.x; a < A; a += 1024) {
@@ -628,8 +596,7 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
         if (err != hipSuccess) return err;
         if (a.T <= kFusedTailMaxT) {
             hipLaunchKernelGGL(topk_scan_kernel, dim3(1), dim3(1024), 0, s, a.partial, a.bias, a.T, nseg, a.E, a.k,
-                               a.tile_tokens, a.topk_idx, a.gates, a.counts, a.offsets, a.sched, a.sched_count, a.perm,
-                               a.inv_perm, a.row_token);
+                               a.plan, a.topk_idx, a.gates, a.counts, a.offsets, a.sched, a.perm, a.inv_perm, a.row_token);
             return hipGetLastError();
         }
         if (tb == 8)
@@ -643,13 +610,13 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
     if (err != hipSuccess) return err;
     const int A = a.T * a.k;
     if (a.T <= kFusedPermuteMaxT) {   // decode-sized: the scan's workgroup scatters the assignments itself
-        hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(1024), 0, s, a.blk_hist, nblk, a.E, a.tile_tokens, a.counts,
-                           a.offsets, a.sched, a.sched_count, a.topk_idx, a.local_rank, A, a.k, tb, a.perm, a.inv_perm,
+        hipLaunchKernelGGL(scan_kernel<true>, dim3(1), dim3(1024), 0, s, a.blk_hist, nblk, a.E, a.plan, a.counts,
+                           a.offsets, a.sched, a.topk_idx, a.local_rank, A, a.k, tb, a.perm, a.inv_perm,
                            a.row_token);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(scan_kernel<false>, dim3(1), dim3(1024), 0, s, a.blk_hist, nblk, a.E, a.tile_tokens, a.counts,
-                       a.offsets, a.sched, a.sched_count, a.topk_idx, a.local_rank, A, a.k, tb, a.perm, a.inv_perm,
+    hipLaunchKernelGGL(scan_kernel<false>, dim3(1), dim3(1024), 0, s, a.blk_hist, nblk, a.E, a.plan, a.counts,
+                       a.offsets, a.sched, a.topk_idx, a.local_rank, A, a.k, tb, a.perm, a.inv_perm,
                        a.row_token);
     if ((err = hipGetLastError()) != hipSuccess) return err;
     hipLaunchKernelGGL(permute_kernel, dim3((A + 255) / 256), dim3(256), 0, s, a.topk_idx, a.local_rank, a.blk_hist,

@@ -54,3 +54,22 @@ def test_router_at_block_and_segment_edges(T, E, d, k, kind):
     counts around a pass of 16; bf16 (c2) and fp32 (c1) layers.  The routing is compared bit for bit."""
     cfg = replace(S.mini(S.C1 if kind == "c1" else S.C2, L=1, d=d, F=64, F_shared=0), E=E)
     run_and_check_layer(cfg, 0, T, k)
+
+
+@pytest.mark.parametrize("T,k,E,d,F,zipf", [
+    (161, 1, 1, 128, 64, 0.0), (160, 1, 1, 640, 192, 0.0),      # one tile of 160 rows; a second one of 16-row blocks
+    (320, 2, 2, 512, 128, 0.0), (321, 2, 2, 1152, 128, 0.0),    # every expert: whole tiles; one row more
+    (1100, 2, 8, 1152, 320, 0.0),     # column blocks of 512 whose last holds 128 features; gate/up blocks half empty
+    (1100, 3, 16, 256, 1024, 1.5),    # skewed: tall tiles for few experts, cuts of the item list by cost
+    (700, 4, 64, 384, 2048, 2.0),     # most experts with a handful of rows, a few with many; reduction cut in two
+    (130, 2, 3, 256, 4096, 0.0),      # 87 rows per expert, few items: cut in two where it streamed
+    (40, 2, 8, 256, 448, 0.0),        # 10 rows per expert, reduction too short to cut: whole, on tiles
+    (1030, 1, 8, 512, 128, 1.0),      # output rows stored directly from the wide form
+])
+def test_grouped_gemm_tiles(T, k, E, d, F, zipf):
+    """Token tiles of up to 160 rows dealt out evenly, the eight-wave down GEMM, the cuts of the work list, and the sizes
+    around the streaming schedule's limits, against the oracle (routing bit for bit, TOL_BF16 of RMS)."""
+    cfg = replace(S.mini(S.C5 if zipf else S.C2, L=1, d=d, F=F, F_shared=0), E=E, F_shared=0, shared_kind=S.SHARED_NONE)
+    if zipf:
+        cfg = replace(cfg, zipf_s=zipf)
+    run_and_check_layer(cfg, 0, T, k)
