@@ -6,48 +6,18 @@
 // 16 x 32 weight blocks -- 1 KB fully coalesced loads, many in flight -- and multiplies each against the tile's
 // token blocks (16 tokens x 32 K, read straight from the token rows, which stay cache-resident) with
 // v_mfma_f32_16x16x32_bf16.  The four partial accumulators are added in wave order through LDS (fixed order: same
-// bits every run), then the epilogue of the tile schedule's kernel applies: silu(gate)*up -> layer dtype, or fp32 rows.
-//
-// fp32 layers always take this schedule, whatever their size: a packed block is then 2 KB, a lane's run 8 floats, and
-// block x block is eight v_mfma_f32_16x16x4_f32 (full fp32 products and sums), the j-th of them taking element j of
-// every run: which four K positions meet in one instruction does not matter as long as both operands agree.  fp32 is
-// used at test scale (d 128, F 256, 64 tokens, two experts each), where a launch is bound by latency: one output
-// element per thread walking K alone took 636 + 664 us for that layer's two GEMMs, a unit per workgroup with K over
-// the waves 4.8 + 4.6 us (of which about 4 are the launch itself).
+// bits every run), then the epilogue of the tile schedule's kernel applies: silu(gate)*up -> bf16, or fp32 rows.
 #include "ffn_common.hpp"
 
 namespace lexi {
 
 template <int N> struct IntTag { static constexpr int value = N; };
 
-// One lane's 8 consecutive K elements of an operand block, and the product of two blocks on the matrix cores.
-template <bool BF16> struct Frag;
-template <> struct Frag<true> {
-    typedef bf16_t elem_t;
-    bf16x8_t v;
-    __device__ __forceinline__ void load(const bf16_t* p) { v = *(const bf16x8_t*)p; }
-    __device__ __forceinline__ static f32x4_t mul(const Frag& a, const Frag& b, const f32x4_t& c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
-    }
-};
-template <> struct Frag<false> {
-    typedef float elem_t;
-    f32x4_t v[2];
-    __device__ __forceinline__ void load(const float* p) { v[0] = *(const f32x4_t*)p; v[1] = *(const f32x4_t*)(p + 4); }
-    __device__ __forceinline__ static f32x4_t mul(const Frag& a, const Frag& b, f32x4_t c) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[j >> 2][j & 3], b.v[j >> 2][j & 3], c, 0, 0, 0);
-        return c;
-    }
-};
-
-template <bool GATEUP, bool BF16>
+template <bool GATEUP>
 __global__ void __launch_bounds__(256)
-ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_token, const void* __restrict__ w0_,
-                  const void* __restrict__ w1_, int K, int features, int M, int tile_rows,
+ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
+                  const bf16_t* __restrict__ w1, int K, int features, int M, int tile_rows,
                   const int32_t* __restrict__ sched, void* __restrict__ out) {
-    typedef typename Frag<BF16>::elem_t elem_t;
-    const elem_t *in = (const elem_t*)in_, *w0 = (const elem_t*)w0_, *w1 = (const elem_t*)w1_;
     __shared__ __attribute__((aligned(16))) f32x4_t red[4][2][64];
 
     TileInfo ti;
@@ -60,12 +30,12 @@ ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_
     const int nkb = K >> 5;
     const int kb0 = wave * nkb / 4, kb1 = (wave + 1) * nkb / 4;
     const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
-    const elem_t* a0 = w0 + wbase;
-    const elem_t* a1 = GATEUP ? w1 + wbase : nullptr;
+    const bf16_t* a0 = w0 + wbase;
+    const bf16_t* a1 = GATEUP ? w1 + wbase : nullptr;
 
     auto body = [&](auto ntb_tag) {
         constexpr int NTB = decltype(ntb_tag)::value;
-        const elem_t* xp[NTB];
+        const bf16_t* xp[NTB];
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
             const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
@@ -79,17 +49,17 @@ ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_
             accu[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
         }
         auto k_step = [&](int kb) {
-            Frag<BF16> ag, au, b;
-            ag.load(a0 + (size_t)kb * 512);
-            if (GATEUP) au.load(a1 + (size_t)kb * 512);
+            const bf16x8_t ag = *(const bf16x8_t*)(a0 + (size_t)kb * 512);
+            bf16x8_t au;
+            if (GATEUP) au = *(const bf16x8_t*)(a1 + (size_t)kb * 512);
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb) {
-                b.load(xp[tb] + kb * 32);
-                accg[tb] = Frag<BF16>::mul(ag, b, accg[tb]);
-                if (GATEUP) accu[tb] = Frag<BF16>::mul(au, b, accu[tb]);
+                const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
+                accg[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, b, accg[tb], 0, 0, 0);
+                if (GATEUP) accu[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, b, accu[tb], 0, 0, 0);
             }
         };
-        constexpr int UNROLL = (NTB <= 2 ? 8 : 4) / (BF16 ? 1 : 2);  // K blocks whose loads are in flight together
+        constexpr int UNROLL = NTB <= 2 ? 8 : 4;  // K blocks whose loads are in flight together
         int kb = kb0;
         for (; kb + UNROLL <= kb1; kb += UNROLL) {
 #pragma unroll
@@ -115,13 +85,9 @@ ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_
                 if (r < ti.rows) {
                     const size_t row = (size_t)(ti.row0 + r);
                     if (GATEUP) {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) g[i] = silu(g[i]) * u[i];
-                    }
-                    if (GATEUP && BF16) {
                         u32x2_t pk;
-                        pk[0] = pack_bf16x2(g[0], g[1]);
-                        pk[1] = pack_bf16x2(g[2], g[3]);
+                        pk[0] = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
+                        pk[1] = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
                         *(u32x2_t*)((bf16_t*)out + row * features + unit * 16 + kq * 4) = pk;
                     } else {
                         *(f32x4_t*)((float*)out + row * features + unit * 16 + kq * 4) = g;
@@ -143,16 +109,85 @@ ffn_stream_kernel(const void* __restrict__ in_, const int32_t* __restrict__ row_
     }
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// fp32 layers: every output is ONE chain of fp32 fused multiply-adds over K, ascending, starting at +0 -- kept as such, so
+// that the rounding of a chained stack of fp32 layers (where a router may turn a last bit into another expert) does not
+// depend on how the work is dealt out.  v_mfma_f32_4x4x1_16b_f32 takes one element of the reduction per instruction, for
+// four token rows (broadcast) and 64 features (lane = feature): a wave owns 4 rows x 64 features, a workgroup 16 rows of a
+// tile at a time.  fp32 is used at test scale (d 128, F 256, 64 tokens, two experts each), where a launch is bound by the
+// latency of the chain (4.7 ns an instruction): 7.4 + 8.3 us for that layer's two GEMMs, where one output element per thread
+// walking K alone took 636 + 664 us (same bits).  Cutting K over the waves is faster still (4.8 + 4.6 us) but not the same sum.
+// ---------------------------------------------------------------------------------------------------------
+template <bool GATEUP>
+__global__ void __launch_bounds__(256)
+ffn_f32_kernel(const float* __restrict__ in, const int32_t* __restrict__ row_token, const float* __restrict__ w0,
+               const float* __restrict__ w1, int K, int features, int M, int tile_rows, const int32_t* __restrict__ sched,
+               float* __restrict__ out) {
+    TileInfo ti;
+    if (!fetch_tile<GATEUP ? 0 : 1>(sched, blockIdx.y, M, tile_rows, ti)) return;
+    constexpr int NM = GATEUP ? 2 : 1;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // packed weights: a lane's feature is row lane % 16 of 16-row slab lane / 16; its 32 elements of a K block are four runs
+    // of 8, 128 floats apart
+    const size_t slab = (size_t)ti.expert * (features >> 4) + blockIdx.x * 4 + (lane >> 4);
+    const float* wp[2] = {w0 + slab * ((size_t)K * 16) + (lane & 15) * 8, GATEUP ? w1 + slab * ((size_t)K * 16) + (lane & 15) * 8 : nullptr};
+    struct Block { f32x4_t v[NM][4][2]; };
+    auto fetch_w = [&](Block& b, int kb) {
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) b.v[m][q][h] = *(const f32x4_t*)(wp[m] + (size_t)kb * 512 + q * 128 + 4 * h);
+    };
+    for (int r0 = wave * 4; r0 < ti.rows; r0 += 16) {   // (no barrier in this kernel)
+        const int rr = min(r0 + (lane & 3), ti.rows - 1);   // rows past the tile's end re-read its last row; never stored
+        const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
+        const float* xp = in + (size_t)src_row * K + ((lane >> 2) & 7) * 8;   // octet (lane / 4) % 8 of 64 elements
+        f32x4_t acc[NM];
+#pragma unroll
+        for (int m = 0; m < NM; ++m) acc[m] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        Block w[2];
+        fetch_w(w[0], 0);
+        for (int k0 = 0; k0 < K; k0 += 64) {            // (K is a multiple of 64)
+            const f32x4_t x0 = *(const f32x4_t*)(xp + k0), x1 = *(const f32x4_t*)(xp + k0 + 4);
+            auto octet = [&](const Block& b, auto o) {  // elements k0 + 8 * O .. + 7, octet O % 4 of K block O / 4
+                constexpr int O = decltype(o)::value;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int m = 0; m < NM; ++m)
+                        acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(e < 4 ? x0[e & 3] : x1[e & 3], b.v[m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
+            };
+            fetch_w(w[1], (k0 >> 5) + 1);
+            __builtin_amdgcn_sched_barrier(0);   // the next block's loads in front of this one's chain
+            octet(w[0], IntTag<0>{}); octet(w[0], IntTag<1>{}); octet(w[0], IntTag<2>{}); octet(w[0], IntTag<3>{});
+            fetch_w(w[0], min((k0 >> 5) + 2, (K >> 5) - 1));   // (the last one is not used)
+            __builtin_amdgcn_sched_barrier(0);
+            octet(w[1], IntTag<4>{}); octet(w[1], IntTag<5>{}); octet(w[1], IntTag<6>{}); octet(w[1], IntTag<7>{});
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (r0 + i < ti.rows) {
+                float v = acc[0][i];
+                if (GATEUP) v = silu(v) * acc[NM - 1][i];
+                out[(size_t)(ti.row0 + r0 + i) * features + blockIdx.x * 64 + lane] = v;
+            }
+        }
+    }
+}
+
 template <bool GATEUP>
 static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
     if (a.max_tiles <= 0) return hipSuccess;
-    const dim3 grid(a.features / 16, a.max_tiles);
     if (a.is_bf16)
-        hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, true>), grid, dim3(256), 0, s, a.in, a.row_token, a.w0, a.w1, a.K,
-                           a.features, a.M, a.tile_rows, a.sched, a.out);
+        hipLaunchKernelGGL(ffn_stream_kernel<GATEUP>, dim3(a.features / 16, a.max_tiles), dim3(256), 0, s, (const bf16_t*)a.in,
+                           a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
+                           a.out);
     else
-        hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, false>), grid, dim3(256), 0, s, a.in, a.row_token, a.w0, a.w1, a.K,
-                           a.features, a.M, a.tile_rows, a.sched, a.out);
+        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3(a.features / 64, a.max_tiles), dim3(256), 0, s, (const float*)a.in,
+                           a.row_token, (const float*)a.w0, (const float*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
+                           (float*)a.out);
     return hipGetLastError();
 }
 
