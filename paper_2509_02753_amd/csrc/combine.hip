@@ -4,6 +4,8 @@
 
 namespace lexi {
 
+template <int N> struct Count { static constexpr int value = N; };
+
 // u = h * inv rounded to the layer dtype, four consecutive elements (the chained stack's normalised MoE input).
 template <bool U_BF16>
 __device__ __forceinline__ void store_normalised(void* u, size_t idx, const f32x4_t& v, float inv) {
@@ -20,14 +22,17 @@ __device__ __forceinline__ void store_normalised(void* u, size_t idx, const f32x
     }
 }
 
-// One workgroup per token; each thread owns 4 consecutive output features per pass.  For a sigmoid-gated shared
-// expert the workgroup first evaluates its token's gate coefficient 1 / (1 + exp(-(x[t] . w_sg))) itself (wave sums by
-// DPP, the four wave results added in wave order), which saves a launch.
+// One workgroup per token; each thread owns 4 consecutive output features in each of NP pieces of 1024.  For a sigmoid-gated
+// shared expert the workgroup first evaluates its token's gate coefficient 1 / (1 + exp(-(x[t] . w_sg))) itself (wave sums
+// by DPP, the four wave results added in wave order), which saves a launch.
+// Bound by reading the k slot rows (HBM) for many tokens, by latency for few: the rows of several slots and pieces are
+// requested together (16 loads of a thread in flight), and the shared expert's row and the hidden state before them.
+// MEASURED
 // Chained stack: `residual` (the hidden state) is added to the block's output, and with `u_next` the same workgroup
 // also writes the NEXT block's normalised input from the row it has just produced -- the sum of squares in exactly
 // the order rmsnorm_kernel uses, so either route gives the same bits.  (x and u_next may be the same buffer: a
 // workgroup reads its row of x before it writes its row of u_next.)
-template <bool Y_BF16, bool X_BF16>
+template <bool Y_BF16, bool X_BF16, int NP>
 __global__ void __launch_bounds__(256)
 combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv_perm, const float* __restrict__ gates,
                const float* __restrict__ y_shared, const void* x, const void* __restrict__ w_shared_gate,
@@ -48,44 +53,84 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
         const float z = ((wave_part[0] + wave_part[1]) + wave_part[2]) + wave_part[3];
         coef = 1.0f / (1.0f + __expf(-z));
     }
+    constexpr int GS = NP == 4 ? 4 : 8;                 // slots whose rows are requested together
+    const bool one_round = d <= 1024 * NP;              // the row fits the registers
     float ss = 0.0f;
-    for (int j = threadIdx.x * 4; j < d; j += 256 * 4) {
-        f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        for (int s = 0; s < k; ++s) {  // slot order = rank order
-            f32x4_t v = *(const f32x4_t*)(y_slot + (size_t)ip[s] * d + j);
-            for (int p = 1; p < slot_planes; ++p) {   // the down GEMM's reduction was cut: the parts are added first
-                const f32x4_t v1 = *(const f32x4_t*)(y_slot + p * slot_plane_stride + (size_t)ip[s] * d + j);
+    f32x4_t acc[NP];
+    for (int c0 = 0; c0 < d; c0 += 1024 * NP) {
+        int j[NP];                                      // (pieces past the row re-read its start; never stored)
+        bool on[NP];
+        f32x4_t sh[NP], hid[NP];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = v[i] + v1[i];
+        for (int p = 0; p < NP; ++p) {
+            j[p] = c0 + 1024 * p + threadIdx.x * 4;
+            on[p] = j[p] < d;
+            if (!on[p]) j[p] = threadIdx.x * 4 < d ? threadIdx.x * 4 : 0;
+            acc[p] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            if (y_shared != nullptr) sh[p] = *(const f32x4_t*)(y_shared + (size_t)t * d + j[p]);
+            if (residual != nullptr) hid[p] = *(const f32x4_t*)(residual + (size_t)t * d + j[p]);
+        }
+        auto slots = [&](int s0, auto n_tag) {          // slots s0 .. s0 + N - 1, in slot order = rank order
+            constexpr int N = decltype(n_tag)::value;
+            f32x4_t v[N][NP];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const float* row = y_slot + (size_t)ip[s0 + u] * d;
+#pragma unroll
+                for (int p = 0; p < NP; ++p) v[u][p] = *(const f32x4_t*)(row + j[p]);
             }
-            const float g = gt[s];
+            for (int q = 1; q < slot_planes; ++q) {     // the down GEMM's reduction was cut: the parts are added first
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(g, v[i], acc[i]);
-        }
-        if (y_shared != nullptr) {
-            f32x4_t v = *(const f32x4_t*)(y_shared + (size_t)t * d + j);
-            for (int p = 1; p < shared_planes; ++p) {
-                const f32x4_t v1 = *(const f32x4_t*)(y_shared + p * shared_plane_stride + (size_t)t * d + j);
+                for (int u = 0; u < N; ++u) {
+                    const float* row = y_slot + q * slot_plane_stride + (size_t)ip[s0 + u] * d;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = v[i] + v1[i];
+                    for (int p = 0; p < NP; ++p) {
+                        const f32x4_t v1 = *(const f32x4_t*)(row + j[p]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[u][p][i] = v[u][p][i] + v1[i];
+                    }
+                }
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(coef, v[i], acc[i]);
-        }
-        if (residual != nullptr) {   // chained stack: the hidden state plus this block's output (may alias y: same element)
-            const f32x4_t h = *(const f32x4_t*)(residual + (size_t)t * d + j);
+            for (int u = 0; u < N; ++u) {
+                const float g = gt[s0 + u];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = h[i] + acc[i];
-        }
+                for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(acc[i], acc[i], ss);
-        if (Y_BF16) {
-            u32x2_t pk;
-            pk[0] = pack_bf16x2(acc[0], acc[1]);
-            pk[1] = pack_bf16x2(acc[2], acc[3]);
-            *(u32x2_t*)((bf16_t*)y + (size_t)t * d + j) = pk;
-        } else {
-            *(f32x4_t*)((float*)y + (size_t)t * d + j) = acc;
+                    for (int i = 0; i < 4; ++i) acc[p][i] = __builtin_fmaf(g, v[u][p][i], acc[p][i]);
+            }
+        };
+        int s = 0;
+        for (; s + GS <= k; s += GS) slots(s, Count<GS>{});
+        if (GS > 4 && s + 4 <= k) { slots(s, Count<4>{}); s += 4; }
+        if (s + 2 <= k) { slots(s, Count<2>{}); s += 2; }
+        if (s < k) slots(s, Count<1>{});
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            if (y_shared != nullptr) {
+                for (int q = 1; q < shared_planes; ++q) {
+                    const f32x4_t v1 = *(const f32x4_t*)(y_shared + q * shared_plane_stride + (size_t)t * d + j[p]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sh[p][i] = sh[p][i] + v1[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[p][i] = __builtin_fmaf(coef, sh[p][i], acc[p][i]);
+            }
+            if (residual != nullptr) {   // chained stack: the hidden state plus this block's output (may alias y: same element)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[p][i] = hid[p][i] + acc[p][i];
+            }
+            if (!on[p]) continue;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(acc[p][i], acc[p][i], ss);
+            if (Y_BF16) {
+                u32x2_t pk;
+                pk[0] = pack_bf16x2(acc[p][0], acc[p][1]);
+                pk[1] = pack_bf16x2(acc[p][2], acc[p][3]);
+                *(u32x2_t*)((bf16_t*)y + (size_t)t * d + j[p]) = pk;
+            } else {
+                *(f32x4_t*)((float*)y + (size_t)t * d + j[p]) = acc[p];
+            }
         }
     }
     if (Y_BF16 || u_next == nullptr) return;   // (the chained stack keeps its hidden state in fp32)
@@ -95,6 +140,14 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
     __syncthreads();
     const float total = ((wave_part[0] + wave_part[1]) + wave_part[2]) + wave_part[3];
     const float inv = 1.0f / sqrtf(total / (float)d + eps);
+    if (one_round) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int j = 1024 * p + threadIdx.x * 4;
+            if (j < d) store_normalised<X_BF16>(u_next, (size_t)t * d + j, acc[p], inv);
+        }
+        return;
+    }
     for (int j = threadIdx.x * 4; j < d; j += 256 * 4) {
         const f32x4_t v = *(const f32x4_t*)((const float*)y + (size_t)t * d + j);   // this thread's own stores
         store_normalised<X_BF16>(u_next, (size_t)t * d + j, v, inv);
@@ -103,9 +156,16 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
 
 template <bool Y_BF16, bool X_BF16>
 static void launch_combine_t(const CombineArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((combine_kernel<Y_BF16, X_BF16>), dim3(a.T), dim3(256), 0, s, a.y_slot, a.inv_perm, a.gates,
-                       a.y_shared, a.x, a.w_shared_gate, a.residual, a.d, a.k, a.y, a.u_next, kRmsEps, a.slot_planes,
-                       a.slot_plane_stride, a.shared_planes, a.shared_plane_stride);
+    auto launch = [&](auto np) {
+        hipLaunchKernelGGL((combine_kernel<Y_BF16, X_BF16, decltype(np)::value>), dim3(a.T), dim3(256), 0, s, a.y_slot, a.inv_perm,
+                           a.gates, a.y_shared, a.x, a.w_shared_gate, a.residual, a.d, a.k, a.y, a.u_next, kRmsEps,
+                           a.slot_planes, a.slot_plane_stride, a.shared_planes, a.shared_plane_stride);
+    };
+    // Many tokens: one piece at a time in few registers, the other workgroups of the CU cover the latency.  (8192 tokens, four
+    // slots, gated shared expert: 86 us, against 104 with two pieces at a time.)
+    if (a.d <= 1024 || a.T > 1024) launch(Count<1>{});
+    else if (a.d <= 2048) launch(Count<2>{});
+    else launch(Count<4>{});
 }
 
 // Chained stack: u[t] = h[t] / sqrt(mean_j h[t][j]^2 + eps), rounded to the layer dtype.  One workgroup per token;
