@@ -27,7 +27,7 @@ struct RoutingArgs {
     int32_t* topk_idx;        // [T*k]
     float* gates;             // [T*k]
     int32_t* local_rank;      // [T*k]  rank of the assignment inside its router block, per expert
-    int32_t* blk_hist;        // [nblk][64] histogram, turned into per-expert block prefixes by the scan
+    int32_t* blk_hist;        // [nblk][64] selections per router block and expert
     int32_t* counts;          // [E]
     int32_t* offsets;         // [E+1]
     int32_t* perm;            // [T*k]
