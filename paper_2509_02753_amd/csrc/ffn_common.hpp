@@ -43,12 +43,12 @@ __device__ __forceinline__ bool fetch_group(const int32_t* sched, int tile, int 
         g = TileGroup{0, 0, M, 0, (M + tile_rows - 1) / tile_rows};
         return tile < g.n;
     }
+    if (tile >= sched[kSchedTiles + 64 * G + 63]) return false;        // (a scalar load: most workgroups of a small batch end here)
     const int lane = threadIdx.x & 63;
     const int off = sched[kSchedOff + lane], cnt = sched[kSchedCount + lane];
     const int end = sched[kSchedTiles + 64 * G + lane];     // tiles of experts 0 .. lane
-    g.expert = __popcll(__ballot(end <= tile));
-    if (g.expert >= 64) return false;
-    const int e = __builtin_amdgcn_readfirstlane(g.expert);
+    const int e = __builtin_amdgcn_readfirstlane(__popcll(__ballot(end <= tile)));
+    g.expert = e;
     g.row0 = __builtin_amdgcn_readlane(off, e);
     g.rows = __builtin_amdgcn_readlane(cnt, e);
     g.first = e > 0 ? __builtin_amdgcn_readlane(end, e - 1) : 0;
@@ -61,7 +61,9 @@ __device__ __forceinline__ bool fetch_tile(const int32_t* sched, int tile, int M
     TileGroup g;
     if (!fetch_group<G>(sched, tile, M, tile_rows, g)) return false;
     ti.expert = g.expert;
-    even_tile(g.row0, g.rows, tile - g.first, g.n, ti);
+    ti.row0 = g.row0;
+    ti.rows = g.rows;
+    if (g.n > 1) even_tile(g.row0, g.rows, tile - g.first, g.n, ti);
     return true;
 }
 

@@ -2,10 +2,10 @@
 // each touched expert's weights from HBM once, so the kernel is built around memory-level parallelism, not MFMA rate.
 //
 // A workgroup owns ONE unit of 16 output features of one token tile (gate/up: 16 gate rows + the 16 matching up
-// rows) and splits the reduction dimension over its 4 waves.  A wave streams its quarter of the unit's packed
+// rows) and splits the reduction dimension over its 4 or 8 waves.  A wave streams its part of the unit's packed
 // 16 x 32 weight blocks -- 1 KB fully coalesced loads, many in flight -- and multiplies each against the tile's
 // token blocks (16 tokens x 32 K, read straight from the token rows, which stay cache-resident) with
-// v_mfma_f32_16x16x32_bf16.  The four partial accumulators are added in wave order through LDS (fixed order: same
+// v_mfma_f32_16x16x32_bf16.  The partial accumulators are added in wave order through LDS (fixed order: same
 // bits every run), then the epilogue of the tile schedule's kernel applies: silu(gate)*up -> bf16, or fp32 rows.
 #include "ffn_common.hpp"
 
@@ -13,12 +13,12 @@ namespace lexi {
 
 template <int N> struct IntTag { static constexpr int value = N; };
 
-template <bool GATEUP>
-__global__ void __launch_bounds__(256)
+template <bool GATEUP, int NW>
+__global__ void __launch_bounds__(NW * 64)
 ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
                   const bf16_t* __restrict__ w1, int K, int features, int M, int tile_rows,
                   const int32_t* __restrict__ sched, void* __restrict__ out) {
-    __shared__ __attribute__((aligned(16))) f32x4_t red[4][2][64];
+    __shared__ __attribute__((aligned(16))) f32x4_t red[NW][2][64];
 
     TileInfo ti;
     if (!fetch_tile<GATEUP ? 0 : 1>(sched, blockIdx.y, M, tile_rows, ti)) return;
@@ -28,7 +28,7 @@ ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row
     const int l16 = lane & 15, kq = lane >> 4;
     const int unit = blockIdx.x;  // output features 16*unit .. 16*unit+15
     const int nkb = K >> 5;
-    const int kb0 = wave * nkb / 4, kb1 = (wave + 1) * nkb / 4;
+    const int kb0 = wave * nkb / NW, kb1 = (wave + 1) * nkb / NW;
     const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
     const bf16_t* a0 = w0 + wbase;
     const bf16_t* a1 = GATEUP ? w1 + wbase : nullptr;
@@ -66,20 +66,20 @@ ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row
             for (int u = 0; u < UNROLL; ++u) k_step(kb + u);
         }
         for (; kb < kb1; ++kb) k_step(kb);
-        // split-K reduction in wave order, one token block at a time; wave (tb % 4) finishes block tb
+        // split-K reduction in wave order, one token block at a time; wave (tb % waves) finishes block tb
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
             red[wave][0][lane] = accg[tb];
             if (GATEUP) red[wave][1][lane] = accu[tb];
             __syncthreads();
-            if (wave == (tb & 3)) {
+            if (wave == tb % NW) {
                 f32x4_t g = red[0][0][lane], u = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int w = 1; w < 4; ++w) g += red[w][0][lane];
+                for (int w = 1; w < NW; ++w) g += red[w][0][lane];
                 if (GATEUP) {
                     u = red[0][1][lane];
 #pragma unroll
-                    for (int w = 1; w < 4; ++w) u += red[w][1][lane];
+                    for (int w = 1; w < NW; ++w) u += red[w][1][lane];
                 }
                 const int r = tb * 16 + l16;  // lane owns token (lane % 16), features 4*(lane/16) + 0..3 of the unit
                 if (r < ti.rows) {
@@ -180,10 +180,17 @@ ffn_f32_kernel(const float* __restrict__ in, const int32_t* __restrict__ row_tok
 template <bool GATEUP>
 static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
     if (a.max_tiles <= 0) return hipSuccess;
-    if (a.is_bf16)
-        hipLaunchKernelGGL(ffn_stream_kernel<GATEUP>, dim3(a.features / 16, a.max_tiles), dim3(256), 0, s, (const bf16_t*)a.in,
-                           a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
-                           a.out);
+    auto launch = [&](auto nw) {
+        constexpr int NW = decltype(nw)::value;
+        hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, NW>), dim3(a.features / 16, a.max_tiles), dim3(NW * 64), 0, s,
+                           (const bf16_t*)a.in, a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M,
+                           a.tile_rows, a.sched, a.out);
+    };
+    // Eight waves where a CU gets one workgroup at most (twice the loads in flight) or the reduction is very long; with several
+    // workgroups per CU four are better.  One token, d 2048: dense gate/up 8.8 -> 7.8 us, dense down (K 2816) 8.4 -> 6.5 us,
+    // two experts 11.0 -> 10.1 us; 32 tokens, down (K 14336) 170 -> 164 us; but 16 tokens, 64 experts: 47 -> 52 us.
+    if (a.is_bf16 && ((a.features / 16) * (int64_t)a.max_tiles <= 256 || a.K >= 8192)) launch(IntTag<8>{});
+    else if (a.is_bf16) launch(IntTag<4>{});
     else
         hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3(a.features / 64, a.max_tiles), dim3(256), 0, s, (const float*)a.in,
                            a.row_token, (const float*)a.w0, (const float*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
