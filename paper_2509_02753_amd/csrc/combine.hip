@@ -25,14 +25,14 @@ __device__ __forceinline__ void store_normalised(void* u, size_t idx, const f32x
 // One workgroup per token; each thread owns 4 consecutive output features in each of NP pieces of 1024.  For a sigmoid-gated
 // shared expert the workgroup first evaluates its token's gate coefficient 1 / (1 + exp(-(x[t] . w_sg))) itself (wave sums
 // by DPP, the four wave results added in wave order), which saves a launch.
-// Bound by reading the k slot rows (HBM) for many tokens, by latency for few: the rows of several slots and pieces are
-// requested together (16 loads of a thread in flight), and the shared expert's row and the hidden state before them.
-// MEASURED
+// Bound by reading the k slot rows (HBM) for many tokens, by latency for few: the rows of GS slots in NP pieces are
+// requested together, and the shared expert's row and the hidden state before them (16 tokens, chained: 6.8 -> 4.0 us; 256
+// tokens: 6.5 -> 5.0 us).
 // Chained stack: `residual` (the hidden state) is added to the block's output, and with `u_next` the same workgroup
 // also writes the NEXT block's normalised input from the row it has just produced -- the sum of squares in exactly
 // the order rmsnorm_kernel uses, so either route gives the same bits.  (x and u_next may be the same buffer: a
 // workgroup reads its row of x before it writes its row of u_next.)
-template <bool Y_BF16, bool X_BF16, int NP>
+template <bool Y_BF16, bool X_BF16, int NP, int GS>
 __global__ void __launch_bounds__(256)
 combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv_perm, const float* __restrict__ gates,
                const float* __restrict__ y_shared, const void* x, const void* __restrict__ w_shared_gate,
@@ -53,7 +53,6 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
         const float z = ((wave_part[0] + wave_part[1]) + wave_part[2]) + wave_part[3];
         coef = 1.0f / (1.0f + __expf(-z));
     }
-    constexpr int GS = NP == 4 ? 4 : 8;                 // slots whose rows are requested together
     const bool one_round = d <= 1024 * NP;              // the row fits the registers
     float ss = 0.0f;
     f32x4_t acc[NP];
@@ -156,16 +155,17 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
 
 template <bool Y_BF16, bool X_BF16>
 static void launch_combine_t(const CombineArgs& a, hipStream_t s) {
-    auto launch = [&](auto np) {
-        hipLaunchKernelGGL((combine_kernel<Y_BF16, X_BF16, decltype(np)::value>), dim3(a.T), dim3(256), 0, s, a.y_slot, a.inv_perm,
-                           a.gates, a.y_shared, a.x, a.w_shared_gate, a.residual, a.d, a.k, a.y, a.u_next, kRmsEps,
-                           a.slot_planes, a.slot_plane_stride, a.shared_planes, a.shared_plane_stride);
+    auto launch = [&](auto np, auto gs) {
+        hipLaunchKernelGGL((combine_kernel<Y_BF16, X_BF16, decltype(np)::value, decltype(gs)::value>), dim3(a.T), dim3(256), 0, s,
+                           a.y_slot, a.inv_perm, a.gates, a.y_shared, a.x, a.w_shared_gate, a.residual, a.d, a.k, a.y, a.u_next,
+                           kRmsEps, a.slot_planes, a.slot_plane_stride, a.shared_planes, a.shared_plane_stride);
     };
-    // Many tokens: one piece at a time in few registers, the other workgroups of the CU cover the latency.  (8192 tokens, four
-    // slots, gated shared expert: 86 us, against 104 with two pieces at a time.)
-    if (a.d <= 1024 || a.T > 1024) launch(Count<1>{});
-    else if (a.d <= 2048) launch(Count<2>{});
-    else launch(Count<4>{});
+    // Many tokens: few loads per thread in few registers, the other workgroups of the CU cover the latency.  (8192 tokens, two
+    // or four slots, gated shared expert: 83 us, against 92 with eight slots and 104 with two pieces of them.)
+    if (a.T > 1024) launch(Count<1>{}, Count<4>{});
+    else if (a.d <= 1024) launch(Count<1>{}, Count<8>{});
+    else if (a.d <= 2048) launch(Count<2>{}, Count<8>{});
+    else launch(Count<4>{}, Count<4>{});
 }
 
 // Chained stack: u[t] = h[t] / sqrt(mean_j h[t][j]^2 + eps), rounded to the layer dtype.  One workgroup per token;
