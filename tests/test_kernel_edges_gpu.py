@@ -76,3 +76,15 @@ def test_grouped_gemm_tiles(T, k, E, d, F, zipf):
     if zipf:
         cfg = replace(cfg, zipf_s=zipf)
     run_and_check_layer(cfg, 0, T, k)
+
+
+@pytest.mark.parametrize("T,k,E,d,F", [
+    (4, 4, 64, 2048, 1408), (6, 1, 64, 2048, 1408),     # 14 and 6 experts expected in use: 156 items of gate/up (tiles), 63 (streams)
+    (16, 4, 64, 256, 1408), (20, 4, 64, 2048, 128),     # gate/up on tiles with a streaming down GEMM, and the reverse
+    (2, 6, 64, 1024, 2816), (16, 1, 8, 2304, 8192),     # 240 items: streams; 443: tiles
+    (33, 2, 64, 2048, 1408),                            # both on tiles
+])
+def test_decode_schedules_around_their_limits(T, k, E, d, F):
+    """Decode-sized calls on either side of the line between weight streaming and tiles, against the oracle."""
+    cfg = replace(S.mini(S.C2, L=1, d=d, F=F, F_shared=0), E=E)
+    run_and_check_layer(cfg, 0, T, k)
