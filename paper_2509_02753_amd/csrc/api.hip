@@ -200,17 +200,24 @@ Workspace carve(const lexi_layer_t& ly, int T, int k, void* base) {
     // chained stack: the normalised MoE input.  First, so that its place does not depend on the layer or on k: a
     // block's combine writes the next block's input there.
     w.u = c.take<char>((size_t)T * ly.d * es);
-    w.partial = c.take<float>((size_t)(ly.d / 128) * router_partial_tokens(T) * 64);
+    const size_t partial = (size_t)(ly.d / 128) * T * 64;
+    w.partial = c.take<float>(partial);
     w.topk_idx = c.take<int32_t>(A);
     w.gates = c.take<float>(A);
     w.local_rank = c.take<int32_t>(A);
-    w.blk_hist = c.take<int32_t>(router_hist_rows(T) * 64);
+    w.blk_hist = c.take<int32_t>(((size_t)T + 7) / 8 * 64);
+    // (blocks of 4 tokens: more histograms, but the partials then stay in LDS and leave their place)
+    const bool fine = T > kSmallRouterMaxT && T <= kFineRouterMaxT;
+    if (fine) w.blk_hist = (int32_t*)w.partial;
+    const size_t hist_in_partial = fine ? align_up(((size_t)T + 3) / 4 * 64, 64) : 0;
     w.counts = c.take<int32_t>(64);
     w.offsets = c.take<int32_t>(68);
     w.perm = c.take<int32_t>(A);
     w.inv_perm = c.take<int32_t>(A);
     w.row_token = c.take<int32_t>(A);
-    w.sched = c.take<int32_t>(kSchedInts);
+    // the expert table: the partials have been read when it is written
+    if (base != nullptr && partial >= hist_in_partial + kSchedInts) w.sched = (int32_t*)w.partial + hist_in_partial;
+    if (partial < hist_in_partial + kSchedInts) w.sched = c.take<int32_t>(kSchedInts);
     w.act = c.take<char>(A * ly.F * es);
     // two planes wherever the down GEMM may split its reduction (independent of T and k, so that the size asked for
     // at (T_max, k_max) covers every smaller call)

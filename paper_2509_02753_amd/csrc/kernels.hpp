@@ -23,7 +23,8 @@ struct RoutingArgs {
     const float* bias;        // [E] or null
     int T, d, E, k;
     WorkPlan plan;
-    float* partial;           // [d/128][T][64] segment partials of the logits, where they go through memory (router_partial_tokens)
+    float* partial;           // [d/128][T][64] segment partials of the logits, where they go through memory (T <= kSmallRouterMaxT or
+                              // T > kFineRouterMaxT; between them it may share memory with blk_hist)
     int32_t* topk_idx;        // [T*k]
     float* gates;             // [T*k]
     int32_t* local_rank;      // [T*k]  rank of the assignment inside its router block, per expert
@@ -39,15 +40,6 @@ struct RoutingArgs {
 constexpr int kFusedTailMaxT = 16;     // T at or below which one workgroup does everything after the segment partials
 constexpr int kSmallRouterMaxT = 64;   // T at or below which a wave takes one segment of one token
 constexpr int kFineRouterMaxT = 1024;  // T at or below which (down to the line above) router and top-k are one launch
-// Of RoutingArgs: tokens `partial` must hold, and rows of `blk_hist` (both grow with T, so that the workspace of the
-// largest T covers every smaller one).
-inline size_t router_partial_tokens(int T) {
-    return T > kFineRouterMaxT ? T : T < kSmallRouterMaxT ? T : kSmallRouterMaxT;
-}
-inline size_t router_hist_rows(int T) {   // blocks of 4 tokens or more up to 1024 tokens, of 16 above
-    const size_t fine = ((size_t)T + 3) / 4, coarse = ((size_t)T + 15) / 16;
-    return fine < 256 ? fine : coarse > 256 ? coarse : 256;
-}
 hipError_t launch_routing(const RoutingArgs& a, hipStream_t s);
 
 // One grouped (or dense) GEMM of the expert FFN.

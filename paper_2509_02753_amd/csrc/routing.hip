@@ -460,14 +460,15 @@ permute_kernel(const int32_t* __restrict__ blk_hist, int nblk, int E, WorkPlan p
 // segment partials -- the top-k and gates of every token (one token per wave per pass, tokens ascending), the
 // per-expert counts, offsets and tile schedule, and the scatter.  With all tokens in one workgroup the stable
 // counting sort needs no block histograms in memory: an assignment's position is offsets[e] + (assignments to e by
-// earlier tokens), kept in LDS.  Saves two dependent launches on the latency-bound path.
+// earlier tokens), kept in LDS.  Saves two dependent launches on the latency-bound path.  (`sched` may lie in the memory of
+// `partial`: it is written after the last barrier behind the reads.)
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kFusedTailMaxA = kFusedTailMaxT * 64;   // assignments (k <= E <= 64)
 
 __global__ void __launch_bounds__(1024)
-topk_scan_kernel(const float* __restrict__ partial, const float* __restrict__ bias, int T, int nseg, int E, int k,
+topk_scan_kernel(const float* partial, const float* __restrict__ bias, int T, int nseg, int E, int k,
                  WorkPlan plan, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
-                 int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
+                 int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* sched,
                  int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
                  int32_t* __restrict__ row_token) {
     __shared__ int32_t wave_hit[16][64];        // this pass: 1 if the wave's token selected expert e
