@@ -25,6 +25,20 @@ lexi_status lexi_probe_hbm_read(const void* src, size_t bytes, void* sink, void*
  *   launch; -1 = invalid arguments or no shared expert. */
 int32_t lexi_moe_down_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int32_t which);
 
+/* How one GEMM of a call is launched (a diagnostic like the above; reads the layer's sizes only).
+ *   chained != 0: as a block of the chained stack.  which: 0 = routed gate/up, 1 = routed down, 2 = shared gate/up,
+ *   3 = shared down.  Returns LEXI_ERR_SHAPE where there is no such GEMM. */
+typedef struct {
+    int32_t streams;    /* 1 = weight-streaming schedule (decode-sized batches, every fp32 layer), 0 = tile schedule */
+    int32_t waves;      /* per workgroup */
+    int32_t tile_rows;  /* rows a token tile holds at most */
+    int32_t ksplit;     /* parts of the reduction (tile schedule) */
+    int32_t direct;     /* 1 = the down GEMM stores the layer's output rows itself */
+    int32_t fused;      /* 1 = down projection and combine are one launch */
+} lexi_gemm_plan_t;
+lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int32_t chained, int32_t which,
+                               lexi_gemm_plan_t* out);
+
 #ifdef __cplusplus
 }
 #endif

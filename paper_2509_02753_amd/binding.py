@@ -21,8 +21,8 @@ SHARED_NONE, SHARED_UNGATED, SHARED_SIGMOID = 0, 1, 2
 EXPORTS = ("lexi_pack_weights", "lexi_moe_workspace_bytes", "lexi_moe_layer_forward", "lexi_moe_layer_forward_static",
            "lexi_moe_stack_forward",
            "lexi_moe_stack_forward_profiled", "lexi_moe_profile_workspace_bytes", "lexi_moe_profile_layer",
-           "lexi_allocate_topk", "lexi_probe_mfma_bf16", "lexi_probe_hbm_read", "lexi_moe_down_plan", "lexi_strerror",
-           "lexi_moe_version")
+           "lexi_allocate_topk", "lexi_probe_mfma_bf16", "lexi_probe_hbm_read", "lexi_moe_down_plan", "lexi_moe_gemm_plan",
+           "lexi_strerror", "lexi_moe_version")
 N_STAGE_EVENTS = 6
 STAGE_NAMES = ("routing", "gate_up", "down", "shared", "combine")
 
@@ -50,6 +50,10 @@ class lexi_routing_out_t(ctypes.Structure):
 
 class lexi_stage_events_t(ctypes.Structure):
     _fields_ = [("ev", ctypes.c_void_p * N_STAGE_EVENTS)]
+
+
+class lexi_gemm_plan_t(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("streams", "waves", "tile_rows", "ksplit", "direct", "fused")]
 
 
 def _load() -> ctypes.CDLL:
@@ -86,6 +90,8 @@ def _load() -> ctypes.CDLL:
     lib.lexi_probe_hbm_read.argtypes = [vp, sz, vp, vp]
     lib.lexi_moe_down_plan.restype = i32
     lib.lexi_moe_down_plan.argtypes = [ctypes.POINTER(lexi_layer_t), i32, i32, i32]
+    lib.lexi_moe_gemm_plan.restype = i32
+    lib.lexi_moe_gemm_plan.argtypes = [ctypes.POINTER(lexi_layer_t), i32, i32, i32, i32, ctypes.POINTER(lexi_gemm_plan_t)]
     lib.lexi_strerror.restype = ctypes.c_char_p
     lib.lexi_strerror.argtypes = [i32]
     lib.lexi_moe_version.restype = ctypes.c_char_p
@@ -318,6 +324,17 @@ def lexi_moe_down_plan(layer: Layer, T: int, k: int, shared: bool = False) -> in
     two, 3 tiles storing the output rows directly, 4 streaming with the combine in the same launch; -1 if there is no
     such GEMM."""
     return int(_lib.lexi_moe_down_plan(ctypes.byref(layer.c), int(T), int(k), 1 if shared else 0))
+
+
+def lexi_moe_gemm_plan(layer: Layer, T: int, k: int, gemm: str = "down", shared: bool = False, chained: bool = False) -> Dict[str, int]:
+    """How a GEMM ("gate_up" or "down", routed or shared) of a call is launched: streams, waves, tile_rows, ksplit, direct,
+    fused (include/lexi_probe.h)."""
+    p = lexi_gemm_plan_t()
+    st = _lib.lexi_moe_gemm_plan(ctypes.byref(layer.c), int(T), int(k), int(chained),
+                                 {"gate_up": 0, "down": 1}[gemm] + 2 * int(shared), ctypes.byref(p))
+    if st != LEXI_OK:
+        raise LexiError(st, "lexi_moe_gemm_plan")
+    return {n: int(getattr(p, n)) for n, _ in p._fields_}
 
 
 def lexi_probe_mfma_bf16(operands: torch.Tensor, sink: torch.Tensor, iters: int, workgroups: int,

@@ -1,6 +1,6 @@
 // C ABI of the library: argument validation, workspace slicing and the per-layer launch sequence.
 // Nothing here allocates, synchronises or copies to the host; every launch goes to the caller's stream.
-#include "../../include/lexi_moe.h"
+#include "../../include/lexi_probe.h"
 #include "kernels.hpp"
 #include <algorithm>
 #include <math.h>
@@ -286,11 +286,11 @@ lexi_status check_call(const lexi_layer_t* ly, const void* x, const void* y, int
 // Routing and the routed expert GEMMs of one layer at top-k = k: fills the routing arrays, act and y_slot of `w`.
 // `allow_split`: the down GEMM may write two planes of y_slot (w.slot_planes tells).  `direct_y` != null (k == 1, nothing
 // else to add): the down GEMM stores the output rows straight into the layer's output (w.direct tells whether it did).
-// Launch plan of the GEMMs of one call (the down part is also what lexi_moe_down_plan reports).
+// Launch plan of the GEMMs of one call (what lexi_moe_gemm_plan and, its down part, lexi_moe_down_plan report).
 struct LayerPlan {
     bool gateup_streams;                   // weight-streaming schedule instead of the tile schedule
     bool routed_streams, shared_streams;   // same, for the down GEMMs
-    TilePlan gateup;                       // routed gate/up GEMM on the tile schedule
+    TilePlan gateup, shared_gateup;        // gate/up GEMMs on the tile schedule
     TilePlan routed, shared;               // down GEMMs on the tile schedule
     bool routed_direct;                    // with k == 1 and nothing to add: rows stored straight into y
     bool routed_fused;                     // a handful of tokens: down projection and combine in one launch
@@ -308,6 +308,7 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
                        (A <= (int64_t)kStreamDownRowsPerExpert * ly.E && few_items <= kStreamDownMaxItems);
     p.shared_streams = !bf || T <= kStreamDenseRows;
     p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
+    p.shared_gateup = TilePlan{false, T <= kSideStreamMaxT ? kSideTileRows : kTileRows, 1};
     if (!p.gateup_streams) p.gateup = plan_gateup_tiles(A, ly.E, ly.d, ly.F);
     // (allow_direct: the caller wants nothing but y -- no slot rows, no residual, no normalised copy)
     p.routed_fused = bf && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&
@@ -413,7 +414,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         };
         FfnArgs sg{};
         sg.in = x; sg.w0 = ly.ws_gate; sg.w1 = ly.ws_up; sg.K = ly.d; sg.features = ly.F_shared; sg.out = w.act_shared;
-        dense(sg, T <= kSideStreamMaxT ? kSideTileRows : kTileRows);
+        dense(sg, plan.shared_gateup.tile_rows);
         if (launch_gateup(sg, st) != hipSuccess) return false;
         FfnArgs sd{};
         sd.in = w.act_shared; sd.w0 = ly.ws_down; sd.K = ly.F_shared; sd.features = ly.d; sd.out = w.y_shared;
@@ -665,6 +666,30 @@ int32_t lexi_moe_down_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int3
         case 1: return layer->F_shared == 0 ? -1 : (p.shared_streams ? 0 : p.shared.ksplit);
         default: return -1;
     }
+}
+
+lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int32_t chained, int32_t which,
+                               lexi_gemm_plan_t* out) {
+    if (out == nullptr) return LEXI_ERR_NULL;
+    lexi_status st = check_layer(layer);
+    if (st == LEXI_OK) st = check_sizes(layer, T, k);
+    if (st != LEXI_OK) return st;
+    if (T < 1 || which < 0 || which > 3 || (which >= 2 && layer->F_shared == 0)) return LEXI_ERR_SHAPE;
+    const LayerPlan p = plan_layer(*layer, T, k, true, !chained);
+    const bool shared = which >= 2, down = which & 1;
+    const TilePlan& t = shared ? (down ? p.shared : p.shared_gateup) : (down ? p.routed : p.gateup);
+    const int F = shared ? layer->F_shared : layer->F, K = down ? F : layer->d, features = down ? layer->d : F;
+    const int64_t tiles = shared ? (T + t.tile_rows - 1) / t.tile_rows : max_tiles((int64_t)T * k, layer->E, t.tile_rows);
+    *out = lexi_gemm_plan_t{};
+    out->streams = shared ? p.shared_streams : down ? p.routed_streams : p.gateup_streams;
+    out->tile_rows = t.tile_rows;
+    out->ksplit = t.ksplit;
+    out->direct = down && !shared && p.routed_direct;
+    out->fused = down && !shared && p.routed_fused;
+    if (out->fused) out->waves = 16;
+    else if (out->streams) out->waves = layer->dtype == LEXI_BF16 ? stream_waves(K, features, tiles) : 4;
+    else out->waves = t.wide ? 8 : 4;
+    return LEXI_OK;
 }
 
 const char* lexi_strerror(int32_t status) {

@@ -186,10 +186,7 @@ static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
                            (const bf16_t*)a.in, a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M,
                            a.tile_rows, a.sched, a.out);
     };
-    // Eight waves where a CU gets one workgroup at most (twice the loads in flight) or the reduction is very long; with several
-    // workgroups per CU four are better.  One token, d 2048: dense gate/up 8.8 -> 7.8 us, dense down (K 2816) 8.4 -> 6.5 us,
-    // two experts 11.0 -> 10.1 us; 32 tokens, down (K 14336) 170 -> 164 us; but 16 tokens, 64 experts: 47 -> 52 us.
-    if (a.is_bf16 && ((a.features / 16) * (int64_t)a.max_tiles <= 256 || a.K >= 8192)) launch(IntTag<8>{});
+    if (a.is_bf16 && stream_waves(a.K, a.features, a.max_tiles) == 8) launch(IntTag<8>{});
     else if (a.is_bf16) launch(IntTag<4>{});
     else
         hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3(a.features / 64, a.max_tiles), dim3(256), 0, s, (const float*)a.in,

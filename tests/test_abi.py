@@ -138,6 +138,36 @@ def test_down_gemm_plan_is_host_logic():
     assert plan(16, 9, d=1024, E=8, F=2048) == -1
 
 
+def gemm_plan(P, ly, T, k, which, chained=0):
+    from paper_2509_02753_amd.binding import _lib, lexi_gemm_plan_t
+    p = lexi_gemm_plan_t()
+    st = _lib.lexi_moe_gemm_plan(ctypes.byref(ly), T, k, chained, which, ctypes.byref(p))
+    return {n: getattr(p, n) for n, _ in p._fields_} if st == 0 else st
+
+
+def test_gemm_plan_agrees_with_the_down_plan():
+    import itertools
+
+    import paper_2509_02753_amd as P
+    from paper_2509_02753_amd.binding import _lib
+    shared = dict(F_shared=2048, shared_kind=1, ws_gate=0x80000, ws_up=0x90000, ws_down=0xA0000)
+    for T, k, E, F, sh in itertools.product((1, 8, 16, 64, 65, 300, 1025, 5000), (1, 2, 6), (1, 8, 60), (1024, 4096), ({}, shared)):
+        ly = fake_layer(P, dtype=1, d=2048, E=E, F=F, **sh)
+        if k > E:
+            assert gemm_plan(P, ly, T, k, 1) == -3
+            continue
+        p, old = gemm_plan(P, ly, T, k, 1), _lib.lexi_moe_down_plan(ctypes.byref(ly), T, k, 0)
+        assert old == (4 if p["fused"] else 0 if p["streams"] else 3 if p["direct"] else p["ksplit"])
+        assert p["tile_rows"] % 16 == 0 and 16 <= p["tile_rows"] <= 160 and p["waves"] in (4, 8, 16)
+        assert not (gemm_plan(P, ly, T, k, 1, chained=1)["fused"] or gemm_plan(P, ly, T, k, 1, chained=1)["direct"])
+        if sh:
+            p = gemm_plan(P, ly, T, k, 3)
+            assert _lib.lexi_moe_down_plan(ctypes.byref(ly), T, k, 1) == (0 if p["streams"] else p["ksplit"])
+        else:
+            assert gemm_plan(P, ly, T, k, 3) == -2
+    assert gemm_plan(P, fake_layer(P), 0, 1, 0) == -2 and gemm_plan(P, fake_layer(P), 1, 1, 4) == -2
+
+
 def test_workspace_query_is_monotone_and_checked():
     import paper_2509_02753_amd as P
     from paper_2509_02753_amd.binding import _lib, lexi_layer_t
