@@ -10,16 +10,7 @@ namespace {
 
 using namespace lexi;
 
-// At or below 2 mean rows per expert the routed FFN streams weights in units of 16 features, unless the experts expected to
-// have rows give the tile schedule's workgroups (which stream as well, few and long-lived instead of thousands of short ones)
-// a number that spreads evenly: clearly less than one per CU, or between 1.3 and 2.4.  4-layer stacks, d 2048: 135 items 264 ->
-// 238 us (12 tokens, k = 2, 32 experts of F 1024), 156 items 287 -> 269 (4 tokens, k = 4, 64 of F 1408), 440 items 617 -> 578
-// (16 tokens); but 243 items 396 -> 405, 263 items 641 -> 701 (one CU or the other gets two), 640 items 637 -> 645.
-constexpr int kStreamRowsPerExpert = 2;
-inline bool spreads_evenly(double experts, int col_blocks) {
-    const double items = experts * col_blocks;
-    return (items >= 128 && items <= 190) || (items >= 340 && items <= 614);
-}
+constexpr int kStreamRowsPerExpert = 2;   // mean rows per expert at or below which the routed FFN streams weights
 // The down projection has few column blocks (d / 256): where the tile schedule would have no more than
 // kStreamDownMaxItems work items, it streams up to kStreamDownRowsPerExpert mean rows per expert.  (A unit of the streaming
 // schedule reads all of its tile's rows for 16 output features: at 16 rows per expert, d 4096, F 14336 it takes 228 us
@@ -300,19 +291,15 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     const bool bf = ly.dtype == LEXI_BF16;
     const int64_t A = (int64_t)T * k;
     const int64_t few_items = (A / 128 + (A < ly.E ? A : ly.E)) * ((ly.d + 255) / 256);
-    const bool few_rows = A <= (int64_t)kStreamRowsPerExpert * ly.E;
-    const double in_use = ly.E * (1.0 - exp(-(double)A / ly.E));
-    p.gateup_streams = !bf || (few_rows && !spreads_evenly(in_use, (ly.F + 127) / 128));
-    // (the down projection's items are half as many: it keeps streaming up to 1.2 rows per expert)
-    p.routed_streams = !bf || (few_rows && !(5 * A > 6 * (int64_t)ly.E && spreads_evenly(in_use, (ly.d + 255) / 256))) ||
-                       (A <= (int64_t)kStreamDownRowsPerExpert * ly.E && few_items <= kStreamDownMaxItems);
+    p.gateup_streams = !bf || A <= (int64_t)kStreamRowsPerExpert * ly.E;
+    p.routed_streams = p.gateup_streams || (A <= (int64_t)kStreamDownRowsPerExpert * ly.E && few_items <= kStreamDownMaxItems);
     p.shared_streams = !bf || T <= kStreamDenseRows;
     p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
     p.shared_gateup = TilePlan{false, T <= kSideStreamMaxT ? kSideTileRows : kTileRows, 1};
     if (!p.gateup_streams) p.gateup = plan_gateup_tiles(A, ly.E, ly.d, ly.F);
     // (allow_direct: the caller wants nothing but y -- no slot rows, no residual, no normalised copy)
     p.routed_fused = bf && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&
-                     (few_rows || few_items <= kStreamDownMaxItems) && ly.shared_kind != LEXI_SHARED_SIGMOID;
+                     (p.gateup_streams || few_items <= kStreamDownMaxItems) && ly.shared_kind != LEXI_SHARED_SIGMOID;
     if (p.routed_fused) p.routed_streams = true;
     if (!p.routed_streams) {
         const bool direct = allow_direct && k == 1 && ly.F_shared == 0;

@@ -168,6 +168,22 @@ def test_gemm_plan_agrees_with_the_down_plan():
     assert gemm_plan(P, fake_layer(P), 0, 1, 0) == -2 and gemm_plan(P, fake_layer(P), 1, 1, 4) == -2
 
 
+def test_decode_sized_calls_stream_whatever_the_router():
+    """Up to two rows per expert both routed GEMMs take the weight-streaming schedule: how many experts really get rows is
+    only known on the device (behind a biased router a third of what a uniform one would use), so no schedule -- and with
+    it no summation order -- may depend on a guess of it."""
+    import itertools
+
+    import paper_2509_02753_amd as P
+    for T, k, E, d, F, bias in itertools.product((1, 4, 12, 16, 20, 33, 64), (1, 2, 4, 6), (8, 32, 60, 64), (1024, 2048, 4096),
+                                                 (896, 1408, 2496, 8192), (None, 0xC0000)):
+        if k > E or T * k > 2 * E:
+            continue
+        ly = fake_layer(P, dtype=1, d=d, E=E, F=F, router_bias=bias)
+        for which in (0, 1):
+            assert gemm_plan(P, ly, T, k, which)["streams"] == 1, (T, k, E, d, F, which)
+
+
 def test_workspace_query_is_monotone_and_checked():
     import paper_2509_02753_amd as P
     from paper_2509_02753_amd.binding import _lib, lexi_layer_t
