@@ -318,7 +318,7 @@ inline int64_t max_tiles(int64_t rows, int groups, int tile_rows) { return rows 
 
 lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t k, Workspace& w, hipStream_t s,
                        const lexi_stage_events_t* events, bool allow_split = true, void* direct_y = nullptr,
-                       bool direct_bf16 = false) {
+                       bool direct_bf16 = false, bool chained = false) {
     auto mark = [&](int i) {
         if (events && events->ev[i]) (void)hipEventRecord((hipEvent_t)events->ev[i], s);
     };
@@ -338,6 +338,7 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
 
     FfnArgs g{};
     g.streaming = plan.gateup_streams;
+    g.chained = chained;
     g.is_bf16 = bf; g.in = x; g.row_token = w.row_token; g.in_rows = T; g.w0 = ly.w_gate; g.w1 = ly.w_up; g.K = ly.d;
     g.features = ly.F; g.M = (int)A; g.tile_rows = r.plan.tile_rows[0];
     g.max_tiles = (int)max_tiles(A, ly.E, g.tile_rows); g.sched = w.sched; g.out = w.act;
@@ -349,6 +350,7 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
     dn.features = ly.d; dn.M = (int)A; dn.tile_rows = r.plan.tile_rows[1];
     dn.max_tiles = (int)max_tiles(A, ly.E, dn.tile_rows); dn.sched = w.sched; dn.out = w.y_slot;
     dn.streaming = plan.routed_streams;
+    dn.chained = chained;
     dn.wide = plan.routed.wide;
     dn.ksplit = w.slot_planes = plan.routed.ksplit;
     dn.plane_stride = (size_t)A * ly.d;
@@ -396,7 +398,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
     auto run_shared = [&](hipStream_t st) -> bool {
         const LayerPlan plan = plan_layer(ly, T, k, true, false);
         auto dense = [&](FfnArgs& a, int tile_rows) {   // one group of T rows
-            a.is_bf16 = bf; a.M = T; a.streaming = plan.shared_streams; a.tile_rows = tile_rows;
+            a.is_bf16 = bf; a.M = T; a.streaming = plan.shared_streams; a.chained = hidden != nullptr; a.tile_rows = tile_rows;
             a.max_tiles = (T + tile_rows - 1) / tile_rows;
         };
         FfnArgs sg{};
@@ -427,7 +429,8 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
     // (plan_down decides).
     const bool direct = hidden == nullptr && u_out == nullptr;
     {
-        const lexi_status st = run_routed(ly, x, T, k, w, s, events, true, direct ? y : nullptr, y_dtype == LEXI_BF16);
+        const lexi_status st = run_routed(ly, x, T, k, w, s, events, true, direct ? y : nullptr, y_dtype == LEXI_BF16,
+                                         hidden != nullptr);
         if (st != LEXI_OK) return st;
     }
     const bool fused = w.fused;
@@ -674,7 +677,7 @@ lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, 
     out->direct = down && !shared && p.routed_direct;
     out->fused = down && !shared && p.routed_fused;
     if (out->fused) out->waves = 16;
-    else if (out->streams) out->waves = layer->dtype == LEXI_BF16 ? stream_waves(K, features, tiles) : 4;
+    else if (out->streams) out->waves = layer->dtype == LEXI_BF16 ? stream_waves(K, features, tiles, chained != 0) : 4;
     else out->waves = t.wide ? 8 : 4;
     return LEXI_OK;
 }

@@ -186,7 +186,7 @@ static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
                            (const bf16_t*)a.in, a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M,
                            a.tile_rows, a.sched, a.out);
     };
-    if (a.is_bf16 && stream_waves(a.K, a.features, a.max_tiles) == 8) launch(IntTag<8>{});
+    if (a.is_bf16 && stream_waves(a.K, a.features, a.max_tiles, a.chained) == 8) launch(IntTag<8>{});
     else if (a.is_bf16) launch(IntTag<4>{});
     else
         hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3(a.features / 64, a.max_tiles), dim3(256), 0, s, (const float*)a.in,

@@ -50,6 +50,7 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s);
 struct FfnArgs {
     bool is_bf16;
     bool streaming;            // few rows per expert: use the weight-streaming (HBM-bound) schedule
+    bool chained;              // a block of the chained stack: the streaming schedule sums the reduction in four parts
     const void* in;            // row-major [*][K]
     const int32_t* row_token;  // gather map row -> input row, or null (identity)
     int in_rows;               // rows of `in` when row_token is given (bound of the gather)
@@ -70,12 +71,14 @@ struct FfnArgs {
     bool out_bf16;             // with scatter: `out` is bf16 (nearest-even rounding of the fp32 result) instead of fp32
 };
 
-// Waves per unit of the weight-streaming schedule (bf16): eight where a CU gets one workgroup at most (twice the loads in
-// flight) or the reduction is very long; with several workgroups per CU four are better.  One token, d 2048: dense gate/up
-// 8.8 -> 7.8 us, dense down (K 2816) 8.4 -> 6.5 us, two experts 11.0 -> 10.1 us; 32 tokens, down (K 14336) 170 -> 164 us; but
-// 16 tokens, 64 experts: 47 -> 52 us.
-inline int stream_waves(int K, int features, int64_t max_tiles) {
-    return (features / 16) * max_tiles <= 256 || K >= 8192 ? 8 : 4;
+// Waves per unit of the weight-streaming schedule (bf16), which is also the number of parts its reduction is summed in: eight
+// where a CU gets one workgroup at most (twice the loads in flight) or the reduction is very long; with several workgroups
+// per CU four are better.  One token, d 2048: dense gate/up 8.8 -> 7.8 us, dense down (K 2816) 8.4 -> 6.5 us, two experts
+// 11.0 -> 10.1 us; 32 tokens, down (K 14336) 170 -> 164 us; but 16 tokens, 64 experts: 47 -> 52 us.
+// In the chained stack always four: which side of a bf16 rounding a block's input falls on may send a token to another
+// expert further down, so the order of a sum there must not depend on the batch the token is in.
+inline int stream_waves(int K, int features, int64_t max_tiles, bool chained) {
+    return !chained && ((features / 16) * max_tiles <= 256 || K >= 8192) ? 8 : 4;
 }
 
 hipError_t launch_gateup(const FfnArgs& a, hipStream_t s);

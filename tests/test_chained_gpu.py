@@ -123,6 +123,28 @@ def test_in_place_chain_and_reported_inputs():
     assert torch.equal(r.moe_input, x)
 
 
+@pytest.mark.parametrize("base,sizes", [("C5", (21, 16, 8, 5, 1)), ("C3", (30, 7, 1)), ("C4", (8, 3, 1))])
+def test_decode_sized_chain_does_not_depend_on_the_batch(base, sizes):
+    """Up to two rows per expert every sum of a block has one order, whatever else is in the batch: a token's hidden state
+    after every block has the same bits alone and among others.  (Another order flips bf16 roundings of the normalised
+    inputs, and those a near-tied expert of a later block: 1e-2 of an 8-block stack's output.)"""
+    import torch
+    import paper_2509_02753_amd as P
+    cfg = S.mini(getattr(S, base), L=4, d=256, F=384)
+    kv = cfg.k_lexi()
+    assert sizes[0] * int(kv.max()) <= 2 * cfg.E
+    dls = [device_and_host_layer(cfg, l)[0] for l in range(cfg.L)]
+    x = S.device_x(cfg, 0, sizes[0])
+    ys = []
+    for T in sizes:
+        y = torch.empty((cfg.L, T, cfg.d), dtype=torch.float32, device="cuda:0")
+        P.lexi_moe_stack_forward(dls, kv, x[:T].contiguous(), y, P.alloc_workspace(dls, T, int(kv.max())), chained=True)
+        ys.append(y)
+    torch.cuda.synchronize()
+    for T, y in zip(sizes, ys):
+        assert torch.equal(y, ys[0][:, :T]), f"{T} of {sizes[0]} tokens"
+
+
 def test_chained_mode_rejects_what_it_cannot_run():
     import torch
     import paper_2509_02753_amd as P
