@@ -2,7 +2,6 @@
 // Nothing here allocates, synchronises or copies to the host; every launch goes to the caller's stream.
 #include "../../include/lexi_probe.h"
 #include "kernels.hpp"
-#include <algorithm>
 #include <math.h>
 #include <mutex>
 
@@ -78,7 +77,7 @@ TilePlan plan_gateup_tiles(int64_t rows, int groups, int K, int features) {
 // several rounds, e.g. 1100 items of 14336, the split measured no gain in the down GEMM and cost the combine a second
 // plane; four parts measured 0 to 10 % slower than two on launches of 72 to 192 items.)
 inline bool ksplit_eligible(int K) { return K / 64 >= 32 && (K / 64) % 2 == 0; }
-TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool allow_split, bool direct, bool skewed) {
+TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool allow_split, bool direct) {
     constexpr int kPlanRows = 128;
     const double ragged = groups > 1 ? 0.5 * (double)(groups < rows ? groups : rows) : (rows % kPlanRows ? 0.5 : 0.0);
     const double items = ((double)(rows / kPlanRows) + ragged) * ((features + 255) / 256);
@@ -92,10 +91,6 @@ TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool all
     TilePlan best = plan_narrow_tiles(rows, groups, K, features, 7, 1, 256);
     // a few rows per expert: a launch streams weights, for which more and smaller workgroups are as good or better
     if (rows < (int64_t)64 * groups) return best;
-    // a router with a bias: some experts get several times the mean, their tall tiles end up in one XCD's part of the work
-    // list, and the fewer and larger the items, the longer its last round (60 experts, d 1792, F 2624, 3108 tokens, k = 8, bias
-    // -1.1 ln(rank): 389 us wide, 327 at 160 rows, 313 at 128)
-    if (skewed) return {false, std::min(best.tile_rows, 128), 1};
     double cost = gemm_cost(rows, groups, K, features, 7, best, 256);
     for (int h : {kTileRows, 128}) {
         const TilePlan p{true, h, 1};
@@ -303,11 +298,11 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     if (p.routed_fused) p.routed_streams = true;
     if (!p.routed_streams) {
         const bool direct = allow_direct && k == 1 && ly.F_shared == 0;
-        p.routed = plan_down_tiles(A, ly.E, ly.F, ly.d, allow_split, direct, ly.router_bias != nullptr);
+        p.routed = plan_down_tiles(A, ly.E, ly.F, ly.d, allow_split, direct);
         p.routed_direct = direct && p.routed.ksplit == 1;
     }
     if (ly.F_shared > 0 && !p.shared_streams) {
-        p.shared = plan_down_tiles(T, 1, ly.F_shared, ly.d, true, false, false);
+        p.shared = plan_down_tiles(T, 1, ly.F_shared, ly.d, true, false);
         if (T <= kSideStreamMaxT) p.shared = TilePlan{false, kSideTileRows, p.shared.ksplit};
     }
     return p;

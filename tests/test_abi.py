@@ -184,6 +184,19 @@ def test_decode_sized_calls_stream_whatever_the_router():
             assert gemm_plan(P, ly, T, k, which)["streams"] == 1, (T, k, E, d, F, which)
 
 
+def test_plan_does_not_depend_on_the_presence_of_a_router_bias():
+    """A bias may balance the load, skew it or be zero; its pointer says nothing about the rows an expert gets."""
+    import itertools
+
+    import paper_2509_02753_amd as P
+    for T, k, (d, E, F), which, chained in itertools.product(
+            (1, 16, 64, 256, 1500, 4096, 8192), (1, 2, 4, 8),
+            ((2048, 64, 1024), (2048, 60, 1408), (4096, 8, 14336), (4096, 8, 7168), (1024, 32, 2048)), (0, 1), (0, 1)):
+        shape = dict(dtype=1, d=d, E=E, F=F)
+        assert gemm_plan(P, fake_layer(P, router_bias=0xC0000, **shape), T, k, which, chained) == \
+            gemm_plan(P, fake_layer(P, **shape), T, k, which, chained)
+
+
 def test_workspace_query_is_monotone_and_checked():
     import paper_2509_02753_amd as P
     from paper_2509_02753_amd.binding import _lib, lexi_layer_t
