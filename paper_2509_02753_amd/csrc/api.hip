@@ -14,8 +14,15 @@ constexpr int kStreamRowsPerExpert = 2;   // mean rows per expert at or below wh
 // kStreamDownMaxItems work items, it streams up to kStreamDownRowsPerExpert mean rows per expert.  (A unit of the streaming
 // schedule reads all of its tile's rows for 16 output features: at 16 rows per expert, d 4096, F 14336 it takes 228 us
 // against 161 us on the tile schedule with the reduction cut in two, at 128 rows 1222 against 212 us.)
+// With more rows it still streams while its units are few: the tile schedule then is one chain of K-steps on a few CUs (0.4
+// us a step), the units read little beside the weights.  Whole call, streaming against tiles: 24 against 36 us (13 rows, 3
+// experts, d 640, F 2624), 27 / 32 (48 rows, 3 experts, d 512, F 1408), 60 / 66 (14 rows, 24 experts, d 640, F 2624: 960 units
+// of 16 rows), but 58 / 50 (22 rows, 8 experts, d 2560, F 1408: 2560) and 60 / 51 (39 rows, 6 experts, d 1024, F 4096: 3072).  From 64 rows on a wave's chain of
+// loads is as long (28 / 28 at 126 rows, 1 expert, d 512, F 896), except where the reduction is short (25 / 31 at 73 rows, F 192).
 constexpr int kStreamDownMaxItems = 256;
 constexpr int kStreamDownRowsPerExpert = 8;
+constexpr int kStreamShortK = 512;
+constexpr int kStreamDownUnits = 1024;    // units x their 16-row blocks (x parts the tile schedule would cut the reduction in)
 constexpr int kStreamDenseRows = 64;      // token count at or below which the shared expert streams weights
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -77,6 +84,12 @@ TilePlan plan_gateup_tiles(int64_t rows, int groups, int K, int features) {
 // several rounds, e.g. 1100 items of 14336, the split measured no gain in the down GEMM and cost the combine a second
 // plane; four parts measured 0 to 10 % slower than two on launches of 72 to 192 items.)
 inline bool ksplit_eligible(int K) { return K / 64 >= 32 && (K / 64) % 2 == 0; }
+inline bool down_streams(int64_t rows, int groups, int K, int features) {
+    if (rows <= (int64_t)kStreamDownRowsPerExpert * groups) return true;
+    if (rows > (int64_t)(K <= kStreamShortK ? 128 : 64) * groups) return false;
+    const int blocks = rows <= (int64_t)16 * groups ? 1 : rows <= (int64_t)32 * groups ? 2 : rows <= (int64_t)64 * groups ? 4 : 8;
+    return (int64_t)(features / 16) * groups * blocks * (ksplit_eligible(K) ? 2 : 1) <= kStreamDownUnits;
+}
 TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool allow_split, bool direct) {
     constexpr int kPlanRows = 128;
     const double ragged = groups > 1 ? 0.5 * (double)(groups < rows ? groups : rows) : (rows % kPlanRows ? 0.5 : 0.0);
@@ -287,7 +300,7 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     const int64_t A = (int64_t)T * k;
     const int64_t few_items = (A / 128 + (A < ly.E ? A : ly.E)) * ((ly.d + 255) / 256);
     p.gateup_streams = !bf || A <= (int64_t)kStreamRowsPerExpert * ly.E;
-    p.routed_streams = p.gateup_streams || (A <= (int64_t)kStreamDownRowsPerExpert * ly.E && few_items <= kStreamDownMaxItems);
+    p.routed_streams = p.gateup_streams || (few_items <= kStreamDownMaxItems && down_streams(A, ly.E, ly.F, ly.d));
     p.shared_streams = !bf || T <= kStreamDenseRows;
     p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
     p.shared_gateup = TilePlan{false, T <= kSideStreamMaxT ? kSideTileRows : kTileRows, 1};

@@ -197,6 +197,19 @@ def test_plan_does_not_depend_on_the_presence_of_a_router_bias():
             gemm_plan(P, fake_layer(P, **shape), T, k, which, chained)
 
 
+@pytest.mark.parametrize("T,k,E,d,F,streams", [
+    (13, 3, 3, 640, 2624, 1), (20, 2, 2, 640, 1984, 1), (15, 4, 6, 640, 4096, 1), (28, 1, 1, 512, 1408, 1),   # few units
+    (35, 1, 4, 128, 896, 1), (86, 4, 24, 640, 2624, 1), (48, 3, 3, 512, 1408, 1), (64, 1, 1, 2048, 1408, 1),
+    (65, 1, 1, 2048, 1408, 0), (45, 4, 8, 2560, 1408, 0), (58, 4, 6, 1024, 4096, 0),    # 65 rows; 2560 and 3072 units
+    (64, 2, 8, 4096, 14336, 0), (512, 2, 8, 4096, 14336, 0),
+    (89, 3, 4, 512, 192, 1), (128, 1, 1, 640, 384, 1), (129, 1, 1, 640, 384, 0), (100, 1, 1, 640, 576, 0),   # short reductions
+])
+def test_down_gemm_of_few_units_streams(T, k, E, d, F, streams):
+    """More than eight rows per expert in a launch of few units: one long chain of steps on a few CUs on tiles."""
+    import paper_2509_02753_amd as P
+    assert gemm_plan(P, fake_layer(P, dtype=1, d=d, E=E, F=F), T, k, 1)["streams"] == streams
+
+
 def test_workspace_query_is_monotone_and_checked():
     import paper_2509_02753_amd as P
     from paper_2509_02753_amd.binding import _lib, lexi_layer_t
