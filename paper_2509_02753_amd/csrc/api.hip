@@ -39,8 +39,13 @@ struct TilePlan {
 };
 
 // Relative duration of a launch on the tile schedule: rounds of the chip times an item's duration (in 16-row blocks x
-// K-steps of a four-wave workgroup), the tallest item once.  An item pays about 2 blocks' worth per K-step whatever its height
-// (the weight stream) and `store` K-steps' worth per block for storing its rows.
+// K-steps of a four-wave workgroup), the tallest item once.  An item pays about 5 blocks' worth per K-step whatever its height
+// (the weight stream) and `store` K-steps' worth per block for storing its rows.  Launches of at most one four-wave item per
+// CU are priced apart, at 0.4 of a round: alone on its CU an item is faster than beside another (gate/up, 3315 tokens, k = 1, 8
+// experts of d 2560, F 896: 224 items of 128 rows 44 us, 392 of 64 rows 57).  A column block counts as a whole one where only
+// part of it holds features.  Fitted on 168 routed launches (60 to 3500 tokens, with and without a router bias, each timed at
+// every height in both forms): against 128 rows everywhere the choice takes gate/up launches from +1.3 % (constants without the
+// round of single items) to -0.7 %, down launches from -0.2 to -3.6 %, and the worst gate/up launch from 1.36 to 1.16 times.
 double gemm_cost(int64_t rows, int groups, int K, int features, int store, const TilePlan& p, int col_width) {
     const double mean = (double)rows / groups, sd = groups > 1 ? sqrt(mean * (1.0 - 1.0 / groups)) : 0.0;
     const double in_use = groups > 1 && mean < 4.0 ? groups * (1.0 - exp(-mean)) : groups;
@@ -55,27 +60,39 @@ double gemm_cost(int64_t rows, int groups, int K, int features, int store, const
     const double height = blocks / tiles;
     const double rounds = tiles * in_use * ((features + col_width - 1) / col_width) * p.ksplit / (p.wide ? 256.0 : 512.0);
     const double full = floor(rounds), part = rounds - full;
-    const double base = p.wide ? 0.7 : 0.25;                // what the emptiest last round costs
+    double last = 0.0;                                      // the partly filled last round
+    if (p.wide) last = 0.7 + 0.3 * part;
+    else if (full == 0.0) last = part <= 0.5 ? 0.4 : 1.0;
+    else last = 0.25 + 0.75 * part;
+    if (full > 0.0 && part <= 0.02) last = 0.0;
     const double steps = (double)(K / 64) / p.ksplit, scale = p.wide ? 0.86 : 1.0;
-    const double item = ((height + (p.wide ? 2.0 : 1.7)) * steps + store * height) * scale;
-    return (full + (part > 0.02 ? base + (1.0 - base) * part : 0.0)) * item + (tallest - height) * (steps + store) * scale;
+    const double item = ((height + (p.wide ? 5.3 : 5.0)) * steps + store * height) * scale;
+    return (full + last) * item + (tallest - height) * (steps + store) * scale;
 }
+
+// Token tiles of a launch at most, whatever the routing: an expert with n rows has ceil(n / tile_rows) tiles.
+inline int64_t max_tiles(int64_t rows, int groups, int tile_rows) { return rows / tile_rows + (rows < groups ? rows : groups); }
 
 // The best height for four-wave workgroups.  With few rows per expert, where the heights are nearly equal for a balanced
 // router, a taller tile has to be clearly better: a lower one spreads the rows of a skewed router over more, shorter items
 // (batch-256 decode with Zipf-distributed experts: 1305 us at 64 rows, 1399 at 160).
-TilePlan plan_narrow_tiles(int64_t rows, int groups, int K, int features, int store, int ksplit, int col_width) {
-    TilePlan best{false, 64, ksplit};
-    double cost = gemm_cost(rows, groups, K, features, store, best, col_width);
-    for (int h : {96, 128, 160}) {
+// `gateup`: above 48 rows per expert lower tiles only stream the weights again behind a skewed router, unless a launch has at
+// most one of them per CU however the rows fall (1296 tokens, k = 1, 16 experts of d 3328, F 1408: 93 us at 64 rows, 96 at 96,
+// 71 at 128; but 190 tokens, k = 4, 6 experts of d 2048, F 896: the whole call 49 us at 64 rows, 61 at 160).
+TilePlan plan_narrow_tiles(int64_t rows, int groups, int K, int features, int store, int ksplit, int col_width, bool gateup) {
+    TilePlan best{false, 0, ksplit};
+    double cost = 0.0;
+    for (int h : {64, 96, 128, 160}) {
+        const int64_t items = max_tiles(rows, groups, h) * ((features + col_width - 1) / col_width);
+        if (gateup && h < 128 && rows > (int64_t)48 * groups && items > 256) continue;
         const TilePlan p{false, h, ksplit};
         const double c = gemm_cost(rows, groups, K, features, store, p, col_width);
-        if (c < (rows < (int64_t)96 * groups ? 0.98 : 1.0) * cost) { best = p; cost = c; }
+        if (best.tile_rows == 0 || c < (rows < (int64_t)48 * groups ? 0.98 : 1.0) * cost) { best = p; cost = c; }
     }
     return best;
 }
 TilePlan plan_gateup_tiles(int64_t rows, int groups, int K, int features) {
-    return plan_narrow_tiles(rows, groups, K, features, 4, 1, 128);
+    return plan_narrow_tiles(rows, groups, K, features, 4, 1, 128, true);
 }
 
 // The reduction is cut in two where a launch with a long one cannot fill half the slots: twice as many items of half the
@@ -84,8 +101,9 @@ TilePlan plan_gateup_tiles(int64_t rows, int groups, int K, int features) {
 // several rounds, e.g. 1100 items of 14336, the split measured no gain in the down GEMM and cost the combine a second
 // plane; four parts measured 0 to 10 % slower than two on launches of 72 to 192 items.)
 inline bool ksplit_eligible(int K) { return K / 64 >= 32 && (K / 64) % 2 == 0; }
-inline bool down_streams(int64_t rows, int groups, int K, int features) {
+inline bool down_streams(int64_t rows, int groups, int K, int features, bool direct) {
     if (rows <= (int64_t)kStreamDownRowsPerExpert * groups) return true;
+    if (direct && K <= kStreamShortK) return false;   // tiles store the layer's output rows: no combine launch
     if (rows > (int64_t)(K <= kStreamShortK ? 128 : 64) * groups) return false;
     const int blocks = rows <= (int64_t)16 * groups ? 1 : rows <= (int64_t)32 * groups ? 2 : rows <= (int64_t)64 * groups ? 4 : 8;
     return (int64_t)(features / 16) * groups * blocks * (ksplit_eligible(K) ? 2 : 1) <= kStreamDownUnits;
@@ -99,11 +117,13 @@ TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool all
         const double t_plane = 2.0 * (double)rows * features * 4.0 / 5.0e12;    // second plane: written once, read once
         // (rows stored straight into the layer's output need no combine launch at all while the reduction is whole)
         if (0.5 * t_item > 1.5 * t_plane + (direct ? 20e-6 : 0.0))
-            return plan_narrow_tiles(rows, groups, K, features, 7, 2, 256);
+            return plan_narrow_tiles(rows, groups, K, features, 7, 2, 256, false);
     }
-    TilePlan best = plan_narrow_tiles(rows, groups, K, features, 7, 1, 256);
-    // a few rows per expert: a launch streams weights, for which more and smaller workgroups are as good or better
-    if (rows < (int64_t)64 * groups) return best;
+    TilePlan best = plan_narrow_tiles(rows, groups, K, features, 7, 1, 256, false);
+    // The eight-wave form needs a few hundred rows per expert: with fewer a launch streams weights, and a skewed router leaves
+    // its few large items unevenly spread (1464 tokens, k = 5, 60 experts, d 1792, F 2240: 148 us behind a biased router
+    // against 124 at 128 rows, 123 on both sides behind an unbiased one).
+    if (rows < (int64_t)250 * groups) return best;
     double cost = gemm_cost(rows, groups, K, features, 7, best, 256);
     for (int h : {kTileRows, 128}) {
         const TilePlan p{true, h, 1};
@@ -300,7 +320,8 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     const int64_t A = (int64_t)T * k;
     const int64_t few_items = (A / 128 + (A < ly.E ? A : ly.E)) * ((ly.d + 255) / 256);
     p.gateup_streams = !bf || A <= (int64_t)kStreamRowsPerExpert * ly.E;
-    p.routed_streams = p.gateup_streams || (few_items <= kStreamDownMaxItems && down_streams(A, ly.E, ly.F, ly.d));
+    const bool direct = allow_direct && k == 1 && ly.F_shared == 0;
+    p.routed_streams = p.gateup_streams || (few_items <= kStreamDownMaxItems && down_streams(A, ly.E, ly.F, ly.d, direct));
     p.shared_streams = !bf || T <= kStreamDenseRows;
     p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
     p.shared_gateup = TilePlan{false, T <= kSideStreamMaxT ? kSideTileRows : kTileRows, 1};
@@ -310,7 +331,6 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
                      (p.gateup_streams || few_items <= kStreamDownMaxItems) && ly.shared_kind != LEXI_SHARED_SIGMOID;
     if (p.routed_fused) p.routed_streams = true;
     if (!p.routed_streams) {
-        const bool direct = allow_direct && k == 1 && ly.F_shared == 0;
         p.routed = plan_down_tiles(A, ly.E, ly.F, ly.d, allow_split, direct);
         p.routed_direct = direct && p.routed.ksplit == 1;
     }
@@ -320,9 +340,6 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     }
     return p;
 }
-
-// Items of a launch at most, whatever the routing: an expert with n rows has ceil(n / tile_rows) tiles.
-inline int64_t max_tiles(int64_t rows, int groups, int tile_rows) { return rows / tile_rows + (rows < groups ? rows : groups); }
 
 lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t k, Workspace& w, hipStream_t s,
                        const lexi_stage_events_t* events, bool allow_split = true, void* direct_y = nullptr,

@@ -202,12 +202,31 @@ def test_plan_does_not_depend_on_the_presence_of_a_router_bias():
     (35, 1, 4, 128, 896, 1), (86, 4, 24, 640, 2624, 1), (48, 3, 3, 512, 1408, 1), (64, 1, 1, 2048, 1408, 1),
     (65, 1, 1, 2048, 1408, 0), (45, 4, 8, 2560, 1408, 0), (58, 4, 6, 1024, 4096, 0),    # 65 rows; 2560 and 3072 units
     (64, 2, 8, 4096, 14336, 0), (512, 2, 8, 4096, 14336, 0),
-    (89, 3, 4, 512, 192, 1), (128, 1, 1, 640, 384, 1), (129, 1, 1, 640, 384, 0), (100, 1, 1, 640, 576, 0),   # short reductions
+    (89, 3, 4, 512, 192, 1), (128, 2, 2, 512, 384, 1), (129, 2, 2, 512, 384, 0), (100, 2, 2, 512, 576, 0),   # short reductions
+    (128, 1, 1, 640, 384, 0),     # the tile schedule stores the output rows of a layer with one active expert itself
 ])
 def test_down_gemm_of_few_units_streams(T, k, E, d, F, streams):
     """More than eight rows per expert in a launch of few units: one long chain of steps on a few CUs on tiles."""
     import paper_2509_02753_amd as P
     assert gemm_plan(P, fake_layer(P, dtype=1, d=d, E=E, F=F), T, k, 1)["streams"] == streams
+
+
+@pytest.mark.parametrize("T,k,E,d,F,gate_up,down", [
+    # launches of at most one item per CU: the height whose items fill more of them, never eight waves for 128 features
+    (190, 4, 6, 2048, 896, (64, 4), (64, 4)), (300, 5, 5, 128, 64, (64, 4), (64, 4)), (1300, 1, 5, 128, 64, (64, 4), (64, 4)),
+    # one item per CU at 128 rows, two on some at 64
+    (3315, 1, 8, 2560, 896, (128, 4), None), (198, 4, 8, 3328, 2624, (128, 4), None), (1296, 1, 16, 3328, 1408, (128, 4), None),
+    # eight waves from 250 rows per expert on
+    (1464, 5, 60, 1792, 2240, None, (None, 4)), (2999, 5, 60, 1792, 2240, None, (None, 4)),
+    (4096, 2, 8, 4096, 14336, (160, 4), (160, 8)), (4096, 8, 64, 2048, 1024, (160, 4), (160, 8)),
+])
+def test_tile_plans(T, k, E, d, F, gate_up, down):
+    import paper_2509_02753_amd as P
+    for which, want in ((0, gate_up), (1, down)):
+        p = gemm_plan(P, fake_layer(P, dtype=1, d=d, E=E, F=F), T, k, which)
+        assert p["streams"] == 0
+        if want is not None:
+            assert want[0] in (None, p["tile_rows"]) and p["waves"] == want[1], (which, p)
 
 
 def test_workspace_query_is_monotone_and_checked():
