@@ -202,7 +202,7 @@ struct Carver {
 };
 
 struct Workspace {
-    int32_t *topk_idx, *local_rank, *blk_hist, *counts, *offsets, *perm, *inv_perm, *row_token, *sched;
+    int32_t *topk_idx, *local_rank, *blk_hist, *hist_sums, *counts, *offsets, *perm, *inv_perm, *row_token, *sched;
     float *gates, *partial, *y_slot, *y_shared;
     void *act, *act_shared, *u;
     int slot_planes = 1, shared_planes = 1;   // planes of y_slot / y_shared the last launches wrote
@@ -234,7 +234,9 @@ Workspace carve(const lexi_layer_t& ly, int T, int k, void* base) {
     w.perm = c.take<int32_t>(A);
     w.inv_perm = c.take<int32_t>(A);
     w.row_token = c.take<int32_t>(A);
-    // the expert table: the partials have been read when it is written
+    // the sums of the histograms of many tokens and the expert table: the partials have been read when they are written
+    w.hist_sums = w.blk_hist;   // (unused up to kPermuteDirectBlocks blocks)
+    if (T > 16 * kPermuteDirectBlocks) w.hist_sums = (int32_t*)w.partial + kSchedInts;
     if (base != nullptr && partial >= hist_in_partial + kSchedInts) w.sched = (int32_t*)w.partial + hist_in_partial;
     if (partial < hist_in_partial + kSchedInts) w.sched = c.take<int32_t>(kSchedInts);
     w.act = c.take<char>(A * ly.F * es);
@@ -352,6 +354,7 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
     r.x = x; r.is_bf16 = bf; r.w_router = ly.w_router; r.bias = ly.router_bias;
     r.T = T; r.d = ly.d; r.E = ly.E; r.k = k;
     r.partial = w.partial; r.topk_idx = w.topk_idx; r.gates = w.gates; r.local_rank = w.local_rank; r.blk_hist = w.blk_hist;
+    r.hist_sums = w.hist_sums;
     r.counts = w.counts; r.offsets = w.offsets; r.perm = w.perm; r.inv_perm = w.inv_perm; r.row_token = w.row_token;
     r.sched = w.sched;
     const int64_t A = (int64_t)T * k;

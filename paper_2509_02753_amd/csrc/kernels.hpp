@@ -29,6 +29,7 @@ struct RoutingArgs {
     float* gates;             // [T*k]
     int32_t* local_rank;      // [T*k]  rank of the assignment inside its router block, per expert
     int32_t* blk_hist;        // [nblk][64] selections per router block and expert
+    int32_t* hist_sums;       // [kHistSums][64] the same per workgroup of the permutation, above kPermuteDirectBlocks blocks
     int32_t* counts;          // [E]
     int32_t* offsets;         // [E+1]
     int32_t* perm;            // [T*k]
@@ -40,6 +41,10 @@ struct RoutingArgs {
 constexpr int kFusedTailMaxT = 16;     // T at or below which one workgroup does everything after the segment partials
 constexpr int kSmallRouterMaxT = 64;   // T at or below which a wave takes one segment of one token
 constexpr int kFineRouterMaxT = 1024;  // T at or below which (down to the line above) router and top-k are one launch
+// Router blocks (of 16 tokens) up to which every workgroup of the permutation reads all their histograms, and the workgroups it
+// has at most above that.
+constexpr int kPermuteDirectBlocks = 512;
+constexpr int kHistSums = 512;
 hipError_t launch_routing(const RoutingArgs& a, hipStream_t s);
 
 // One grouped (or dense) GEMM of the expert FFN.

@@ -389,69 +389,97 @@ __device__ __forceinline__ int32_t write_work_list(int32_t total, int E, const W
 
 // ---------------------------------------------------------------------------------------------------------
 // permute_kernel (T > kFusedTailMaxT): the stable counting sort from the block histograms of the selection.  A workgroup of
-// 16 waves scatters the assignments of kPermuteBlocks router blocks: position of an assignment = offset of its expert +
-// assignments to it in earlier blocks + its rank in the block.  Every workgroup sums all histograms itself (256 bytes per
-// block, from the cache): one launch where a one-workgroup scan had to come first.  The first one also writes the counts,
+// 16 waves scatters the assignments of its router blocks, kPermuteBlocks at a time: position of an assignment = offset of its
+// expert + assignments to it in earlier blocks + its rank in the block.  Every workgroup sums all histograms itself (256 bytes
+// per block, from the cache): one launch where a one-workgroup scan had to come first.  The first one also writes the counts,
 // the offsets and the tiles of the grouped GEMMs.  Bound by latency: 5.6 us at 4096 tokens and 6.6 at 8192 against 5.9 + 5.7
 // and 10.2 + 5.8 us for scan and scatter, 6.5 us against 8.8 (scan and scatter in one workgroup) at 777.
+// What all workgroups read together grows with the square of the blocks.  Above kPermuteDirectBlocks of them hist_sum_kernel
+// first adds each workgroup's blocks up, and `sums` holds one row per workgroup instead of one per block: a launch more, and
+// linear.  The whole routing stage with either (d 128, 8 experts, k = 1, us): 8192 tokens 22 / 22, 16384 27 / 24, 65536 67 / 40,
+// 131072 177 / 51 (scan and scatter 169), 1048576 8545 / 287 (1225).
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kPermuteBlocks = 8;
 
 __global__ void __launch_bounds__(1024)
-permute_kernel(const int32_t* __restrict__ blk_hist, int nblk, int E, WorkPlan plan, int32_t* __restrict__ counts,
-               int32_t* __restrict__ offsets, int32_t* __restrict__ sched, const int32_t* __restrict__ topk_idx,
-               const int32_t* __restrict__ local_rank, int T, int k, int tokens_per_block, int32_t* __restrict__ perm,
-               int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token) {
-    __shared__ int32_t s_total[16][64], s_before[16][64];
-    __shared__ int32_t s_base[kPermuteBlocks][64];      // first position of expert e's assignments in block b0 + i
+hist_sum_kernel(const int32_t* __restrict__ blk_hist, int nblk, int blocks, int32_t* __restrict__ sums) {
+    __shared__ int32_t s_part[16][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b0 = blockIdx.x * kPermuteBlocks;
-    int32_t total = 0, before = 0;                      // of the blocks this wave sums; of those among them before b0
-    for (int b = wave; b < nblk; b += 16 * 8) {
+    const int b0 = blockIdx.x * blocks, b1 = min(b0 + blocks, nblk);
+    int32_t total = 0;
+    for (int b = b0 + wave; b < b1; b += 16) total += blk_hist[(size_t)b * 64 + lane];
+    s_part[wave][lane] = total;
+    __syncthreads();
+    if (wave != 0) return;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) total += s_part[w][lane];
+    sums[(size_t)blockIdx.x * 64 + lane] = total;
+}
+
+// `sums`: nsums rows of 64, one per router block (a workgroup owns kPermuteBlocks of them) or one per workgroup.
+__global__ void __launch_bounds__(1024)
+permute_kernel(const int32_t* __restrict__ blk_hist, int nblk, const int32_t* __restrict__ sums, int nsums, int blocks, int E,
+               WorkPlan plan, int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
+               const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ local_rank, int T, int k, int tokens_per_block,
+               int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token) {
+    __shared__ int32_t s_total[16][64], s_before[16][64];
+    __shared__ int32_t s_base[kPermuteBlocks][64];      // first position of expert e's assignments in block b + i
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b0 = blockIdx.x * blocks, b1 = min(b0 + blocks, nblk);
+    const int first = nsums == nblk ? b0 : blockIdx.x;  // the first row of `sums` that is this workgroup's
+    int32_t total = 0, before = 0;                      // of the rows this wave sums; of those among them before `first`
+    for (int b = wave; b < nsums; b += 16 * 8) {
         int32_t h[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) h[u] = blk_hist[(size_t)min(b + 16 * u, nblk - 1) * 64 + lane];
+        for (int u = 0; u < 8; ++u) h[u] = sums[(size_t)min(b + 16 * u, nsums - 1) * 64 + lane];
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const int32_t v = b + 16 * u < nblk ? h[u] : 0;
+            const int32_t v = b + 16 * u < nsums ? h[u] : 0;
             total += v;
-            before += b + 16 * u < b0 ? v : 0;
+            before += b + 16 * u < first ? v : 0;
         }
     }
     s_total[wave][lane] = total;
     s_before[wave][lane] = before;
     __syncthreads();
+    int32_t pos = 0;                                    // wave 0: the next position of expert `lane`
     if (wave == 0) {
-        int32_t own[kPermuteBlocks];
-#pragma unroll
-        for (int i = 0; i < kPermuteBlocks; ++i) own[i] = blk_hist[(size_t)min(b0 + i, nblk - 1) * 64 + lane];
         total = before = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) {
             total += s_total[w][lane];
             before += s_before[w][lane];
         }
-        int32_t pos = wave_inclusive_sum(total) - total + before;
-#pragma unroll
-        for (int i = 0; i < kPermuteBlocks; ++i) {
-            s_base[i][lane] = pos;
-            pos += own[i];
-        }
+        pos = wave_inclusive_sum(total) - total + before;
     } else if (wave == 1 && blockIdx.x == 0) {
         total = 0;
 #pragma unroll
         for (int w = 0; w < 16; ++w) total += s_total[w][lane];
         write_work_list(total, E, plan, counts, offsets, sched);
     }
-    __syncthreads();
-    const int a0 = b0 * tokens_per_block * k, a1 = min(b0 + kPermuteBlocks, nblk) * tokens_per_block * k;
-    for (int a = a0 + threadIdx.x; a < min(a1, T * k); a += 1024) {
-        const int e = topk_idx[a];
-        const int t = a / k;
-        const int pos = s_base[t / tokens_per_block - b0][e] + local_rank[a];
-        perm[pos] = a;
-        inv_perm[a] = pos;
-        row_token[pos] = t;
+    for (int b = b0; b < b1; b += kPermuteBlocks) {
+        if (wave == 0) {
+            int32_t own[kPermuteBlocks];
+#pragma unroll
+            for (int i = 0; i < kPermuteBlocks; ++i) own[i] = blk_hist[(size_t)min(b + i, nblk - 1) * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < kPermuteBlocks; ++i) {
+                s_base[i][lane] = pos;
+                pos += own[i];
+            }
+        }
+        __syncthreads();
+        const int a0 = b * tokens_per_block * k, a1 = min(min(b + kPermuteBlocks, b1) * tokens_per_block, T) * k;
+        for (int a = a0 + threadIdx.x; a < a1; a += 1024) {
+            const int e = topk_idx[a];
+            const int t = a / k;
+            const int at = s_base[t / tokens_per_block - b][e] + local_rank[a];
+            perm[at] = a;
+            inv_perm[a] = at;
+            row_token[at] = t;
+        }
+        __syncthreads();                                // s_base has been read
     }
 }
 
@@ -592,7 +620,17 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
         err = hipGetLastError();
     }
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(permute_kernel, dim3((nblk + kPermuteBlocks - 1) / kPermuteBlocks), dim3(1024), 0, s, a.blk_hist, nblk,
+    const int32_t* sums = a.blk_hist;
+    int nsums = nblk, blocks = kPermuteBlocks;
+    if (nblk > kPermuteDirectBlocks) {
+        blocks = (nblk + kHistSums * kPermuteBlocks - 1) / (kHistSums * kPermuteBlocks) * kPermuteBlocks;
+        nsums = (nblk + blocks - 1) / blocks;
+        sums = a.hist_sums;
+        hipLaunchKernelGGL(hist_sum_kernel, dim3(nsums), dim3(1024), 0, s, a.blk_hist, nblk, blocks, a.hist_sums);
+        err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    hipLaunchKernelGGL(permute_kernel, dim3((nblk + blocks - 1) / blocks), dim3(1024), 0, s, a.blk_hist, nblk, sums, nsums, blocks,
                        a.E, a.plan, a.counts, a.offsets, a.sched, a.topk_idx, a.local_rank, a.T, a.k, tb, a.perm, a.inv_perm,
                        a.row_token);
     return hipGetLastError();

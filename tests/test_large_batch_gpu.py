@@ -1,0 +1,41 @@
+"""Routing of batches of ten thousand tokens and more (narrow layers: the permutation is what grows)."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import lexi_synth as S
+from helpers import run_and_check_layer
+
+pytestmark = pytest.mark.gpu
+
+
+# 512 router blocks of 16 tokens are the most whose histograms every workgroup of the permutation reads itself; from 65536
+# tokens on a workgroup owns more than eight blocks
+@pytest.mark.parametrize("T,E,k", [(8192, 8, 2), (8193, 8, 1), (8192 + 16 * 5 + 3, 60, 4), (65536, 17, 2), (65537, 5, 1), (140001, 5, 1)])
+def test_permutation_of_many_tokens(T, E, k):
+    cfg = replace(S.mini(S.C2, L=1, d=128, F=64, F_shared=0), E=E)
+    tokens = np.unique(np.concatenate([[0, T - 1], np.random.default_rng(T).integers(0, T, 62)])).astype(np.int32)
+    run_and_check_layer(cfg, 0, T, k, tokens=tokens)
+
+
+def test_permutation_does_not_grow_faster_than_the_batch():
+    """Eight times the tokens: eight times the routing time in the limit, 64 times where every workgroup reads every
+    histogram.  Medians of the routing stage; the bound of 12 leaves room for either end's fixed costs."""
+    import torch
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(S.C2, L=1, d=128, F=64, F_shared=0), E=8)
+    dl, _ = device_and_host_layer(cfg, 0)
+    ms = []
+    for T in (131072, 1048576):
+        x = torch.zeros((T, cfg.d), dtype=torch.bfloat16, device="cuda:0").normal_()
+        y = torch.empty((T, cfg.d), dtype=torch.float32, device="cuda:0")
+        ws = P.alloc_workspace([dl], T, 1)
+        ev, seen = P.StageEvents(1), []
+        for _ in range(5):
+            P.lexi_moe_stack_forward([dl], [1], x, y, ws, stage_events=ev)
+            torch.cuda.synchronize()
+            seen.append(ev.stage_ms()[0][0])
+        ms.append(float(np.median(seen)))
+    assert ms[1] <= 12.0 * ms[0], ms
