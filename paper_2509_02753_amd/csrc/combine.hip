@@ -57,14 +57,14 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
     float ss = 0.0f;
     f32x4_t acc[NP];
     for (int c0 = 0; c0 < d; c0 += 1024 * NP) {
-        int j[NP];                                      // (pieces past the row re-read its start; never stored)
+        int j[NP];                                      // (pieces past the row all read its first 16 bytes; never stored)
         bool on[NP];
         f32x4_t sh[NP], hid[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             j[p] = c0 + 1024 * p + threadIdx.x * 4;
             on[p] = j[p] < d;
-            if (!on[p]) j[p] = threadIdx.x * 4 < d ? threadIdx.x * 4 : 0;
+            if (!on[p]) j[p] = 0;
             acc[p] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
             if (y_shared != nullptr) sh[p] = *(const f32x4_t*)(y_shared + (size_t)t * d + j[p]);
             if (residual != nullptr) hid[p] = *(const f32x4_t*)(residual + (size_t)t * d + j[p]);

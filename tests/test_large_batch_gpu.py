@@ -39,3 +39,23 @@ def test_permutation_does_not_grow_faster_than_the_batch():
             seen.append(ev.stage_ms()[0][0])
         ms.append(float(np.median(seen)))
     assert ms[1] <= 12.0 * ms[0], ms
+
+
+def test_combine_time_follows_the_bytes_of_a_ragged_width():
+    """d = 1280 is one whole and a quarter piece of 1024 features per token: the combine reads 1.25 times the bytes of d =
+    1024.  (Threads past the row once re-read its start: 1.6 times.)  The bound of 1.45 is halfway."""
+    import torch
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    T, k, us = 4096, 8, []
+    for d in (1024, 1280):
+        cfg = replace(S.mini(S.C2, L=1, d=d, F=64, F_shared=0), E=16)
+        dl, _ = device_and_host_layer(cfg, 0)
+        x, y = S.device_x(cfg, 0, T), torch.empty((T, d), dtype=torch.float32, device="cuda:0")
+        ws, ev, seen = P.alloc_workspace([dl], T, k), P.StageEvents(1), []
+        for _ in range(15):
+            P.lexi_moe_stack_forward([dl], [k], x, y, ws, stage_events=ev)
+            torch.cuda.synchronize()
+            seen.append(ev.stage_ms()[0][4])
+        us.append(1e3 * float(np.median(seen)))
+    assert us[1] <= 1.45 * us[0], us
