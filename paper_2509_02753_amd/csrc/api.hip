@@ -219,26 +219,33 @@ Workspace carve(const lexi_layer_t& ly, int T, int k, void* base) {
     // chained stack: the normalised MoE input.  First, so that its place does not depend on the layer or on k: a
     // block's combine writes the next block's input there.
     w.u = c.take<char>((size_t)T * ly.d * es);
-    const size_t partial = (size_t)(ly.d / 128) * T * 64;
-    w.partial = c.take<float>(partial);
-    w.topk_idx = c.take<int32_t>(A);
-    w.gates = c.take<float>(A);
+    const size_t partial_at = align_up(c.used, 256);
+    w.partial = c.take<float>((size_t)(ly.d / 128) * T * 64);
     w.local_rank = c.take<int32_t>(A);
     w.blk_hist = c.take<int32_t>(((size_t)T + 7) / 8 * 64);
-    // (blocks of 4 tokens: more histograms, but the partials then stay in LDS and leave their place)
-    const bool fine = T > kSmallRouterMaxT && T <= kFineRouterMaxT;
-    if (fine) w.blk_hist = (int32_t*)w.partial;
-    const size_t hist_in_partial = fine ? align_up(((size_t)T + 3) / 4 * 64, 64) : 0;
+    // What is written when the partials have been read shares their place: the expert table and, for many tokens, the sums of
+    // the histograms.  Where router and top-k are one launch the partials stay in LDS, and the histograms (blocks of 4 tokens:
+    // twice as many) take their place, with the table behind them.  Up to kFusedTailMaxT tokens there are neither ranks nor
+    // histograms, and the table may run into their place.
+    size_t sched_at = 0;
+    if (T > kSmallRouterMaxT && T <= kFineRouterMaxT) {
+        w.blk_hist = (int32_t*)w.partial;
+        sched_at = ((size_t)T + 3) / 4 * 64;
+    } else if (T <= kFusedTailMaxT) {
+        const size_t room = (align_up(c.used, 256) - partial_at) / sizeof(int32_t);
+        if (room < kSchedInts) c.take<int32_t>(kSchedInts - room);
+    }
+    w.topk_idx = c.take<int32_t>(A);
+    w.gates = c.take<float>(A);
     w.counts = c.take<int32_t>(64);
     w.offsets = c.take<int32_t>(68);
     w.perm = c.take<int32_t>(A);
     w.inv_perm = c.take<int32_t>(A);
     w.row_token = c.take<int32_t>(A);
-    // the sums of the histograms of many tokens and the expert table: the partials have been read when they are written
-    w.hist_sums = w.blk_hist;   // (unused up to kPermuteDirectBlocks blocks)
-    if (T > 16 * kPermuteDirectBlocks) w.hist_sums = (int32_t*)w.partial + kSchedInts;
-    if (base != nullptr && partial >= hist_in_partial + kSchedInts) w.sched = (int32_t*)w.partial + hist_in_partial;
-    if (partial < hist_in_partial + kSchedInts) w.sched = c.take<int32_t>(kSchedInts);
+    if (base != nullptr) {
+        w.sched = (int32_t*)w.partial + sched_at;
+        w.hist_sums = w.sched + kSchedInts;   // (more than kPermuteDirectBlocks router blocks only: the partials are far longer)
+    }
     w.act = c.take<char>(A * ly.F * es);
     // two planes wherever the down GEMM may split its reduction (independent of T and k, so that the size asked for
     // at (T_max, k_max) covers every smaller call)

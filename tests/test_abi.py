@@ -229,6 +229,26 @@ def test_tile_plans(T, k, E, d, F, gate_up, down):
             assert want[0] in (None, p["tile_rows"]) and p["waves"] == want[1], (which, p)
 
 
+def test_workspace_of_small_calls_has_not_grown():
+    """The workspace was once laid out as these arrays, each at a multiple of 256 bytes, with 32 bytes per token tile of 128
+    rows and a tile count; a caller that keeps a buffer of that size may go on using it."""
+    import itertools
+
+    import paper_2509_02753_amd as P
+    from paper_2509_02753_amd.binding import _lib
+    for T, k, E, d, F, dt in itertools.product(list(range(1, 21)) + [64, 65, 130, 1024, 1025, 9000], (1, 2, 7, 8, 9, 64), (1, 8, 64),
+                                               (128, 256, 384, 2048), (64, 128, 2048), (0, 1)):
+        if k > E:
+            continue
+        A, es = T * k, (4, 2)[dt]
+        planes = 2 if dt == 1 and F // 64 >= 32 and F // 64 % 2 == 0 else 1
+        arrays = [T * d * es, d // 128 * T * 256, *[4 * A] * 6, (T + 7) // 8 * 256, 256, 272, 32 * (A // 128 + min(A, E)), 16,
+                  A * F * es, A * d * 4 * planes]
+        earlier = sum((n + 255) // 256 * 256 for n in arrays)
+        size = _lib.lexi_moe_workspace_bytes(ctypes.byref(fake_layer(P, dtype=dt, d=d, E=E, F=F)), 1, T, k)
+        assert size <= earlier, (T, k, E, d, F, dt, size, earlier)
+
+
 def test_workspace_query_is_monotone_and_checked():
     import paper_2509_02753_amd as P
     from paper_2509_02753_amd.binding import _lib, lexi_layer_t
