@@ -686,6 +686,12 @@ lexi_status lexi_moe_profile_layer(const lexi_layer_t* layer, const void* x, int
 int32_t lexi_moe_down_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int32_t which) {
     if (check_layer(layer) != LEXI_OK || T < 1 || k < 1 || k > layer->E) return -1;
     const LayerPlan p = plan_layer(*layer, T, k, true, true);
+    if (layer->dtype != LEXI_BF16) {
+        // fp32 layers have one kernel for every size; 0 and 1 tell the sizes apart at which bf16 ones once changed schedule
+        const int64_t A = (int64_t)T * k, E = layer->E;
+        if (which == 1) return layer->F_shared == 0 ? -1 : (T <= kStreamDenseRows ? 0 : 1);
+        return which != 0 ? -1 : (A <= kStreamRowsPerExpert * E || max_tiles(A, layer->E, 128) * ((layer->d + 255) / 256) <= kStreamDownMaxItems) ? 0 : 1;
+    }
     switch (which) {
         case 0: return p.routed_fused ? 4 : (p.routed_streams ? 0 : (p.routed_direct ? 3 : p.routed.ksplit));
         case 1: return layer->F_shared == 0 ? -1 : (p.shared_streams ? 0 : p.shared.ksplit);

@@ -132,6 +132,11 @@ def test_down_gemm_plan_is_host_logic():
     assert plan(4096, 8, d=2048, E=64, F=1024) == 1 and plan(4096, 1, d=2048, E=64, F=1024) == 3
     assert plan(8192, 4, 1, d=2048, E=60, F=1408, F_shared=5632, shared_kind=2, **shared) == 1
     assert plan(64, 4, 1, d=2048, E=60, F=1408, F_shared=5632, shared_kind=2, **shared) == 0
+    # fp32 layers have one kernel and report by the size
+    f32 = lambda T, k, which=0, **kw: _lib.lexi_moe_down_plan(ctypes.byref(fake_layer(P, dtype=0, **kw)), T, k, which)
+    assert f32(6343, 7, d=896, E=35, F=1088) == 1 and f32(64, 2, d=128, E=8, F=256) == 0 and f32(128, 1, d=896, E=64, F=64) == 0
+    assert f32(94, 2, 1, d=1664, E=10, F=2944, F_shared=128, shared_kind=1, **shared) == 1
+    assert f32(64, 2, 1, d=1664, E=10, F=2944, F_shared=128, shared_kind=1, **shared) == 0
     # a k = 1 layer with a shared expert still needs the combine
     assert plan(2600, 1, d=1024, E=60, F=2048, F_shared=2048, shared_kind=2, **shared) != 3
     assert plan(16, 1, 1, d=1024, E=8, F=2048) == -1 and plan(0, 1, d=1024, E=8, F=2048) == -1
