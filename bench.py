@@ -464,6 +464,16 @@ def measure_regime(args, mods, cfg, layers, arr, T, cpu_seconds, extras):
     return rec
 
 
+def compact(rec):
+    """One regime's record for the benchmark line: rates, fractions and parity; the full record goes to --details."""
+    r = {k: rec[k] for k in ("workload", "regime", "hip_graph", "k_sum", "ms_per_step", "tokens_per_s",
+                             "speedup_vs_uniform_k", "stage_ms_per_step")}
+    r["rooflines"] = [{k: f[k] for k in ("stage", "bound", "achieved", "unit", "frac")} for f in rec["rooflines"]]
+    if rec["parity_on_sample"]:
+        r["parity_on_sample"] = {k: rec["parity_on_sample"][k] for k in ("tokens", "routing_mismatches", "max_err_over_rms")}
+    return r
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -489,6 +499,7 @@ def main():
                          "routing, the tiles and the bytes moved are the same but the matrix cores multiply by zero.  A probe of "
                          "how far the GEMM rates depend on the operand values (the chip lowers its clock when the multiplier "
                          "inputs toggle); NOT a valid benchmark result")
+    ap.add_argument("--details", default=None, metavar="FILE", help="also write the full record of every regime as JSON")
     ap.add_argument("--graph", default="auto", choices=["auto", "on", "off"],
                     help="replay the stack call from a captured HIP graph (auto: for decode-sized batches, whose steps are launch-bound)")
     args = ap.parse_args()
@@ -567,9 +578,12 @@ def main():
         "roofline": dict(h["rooflines"][0], per_k=h["per_k"]), "roofline_down": h["rooflines"][1],
         "whole_path": h["whole_path"], "chained_stack": h["chained_stack"], "stage1_profiling": h["stage1_profiling"],
         "measured_ceilings": ceilings, "cpu_baseline": h["cpu_baseline"], "parity_on_sample": h["parity_on_sample"],
-        "regimes": [{k: v for k, v in r.items() if k not in ("name",)} for r in regimes],
+        "regimes": [compact(r) for r in regimes],
     }
-    print(json.dumps(out), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(dict(out, regimes=regimes), f)
+    print(json.dumps(out), flush=True)     # one line that a log's last ten kilobytes hold whole
 
 
 if __name__ == "__main__":
