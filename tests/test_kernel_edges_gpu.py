@@ -59,32 +59,179 @@ def test_router_at_block_and_segment_edges(T, E, d, k, kind):
     run_and_check_layer(cfg, 0, T, k)
 
 
-@pytest.mark.parametrize("T,k,E,d,F,zipf", [
-    (161, 1, 1, 128, 64, 0.0), (160, 1, 1, 640, 192, 0.0),      # one tile of 160 rows; a second one of 16-row blocks
-    (320, 2, 2, 512, 128, 0.0), (321, 2, 2, 1152, 128, 0.0),    # every expert: whole tiles; one row more
-    (1100, 2, 8, 1152, 320, 0.0),     # column blocks of 512 whose last holds 128 features; gate/up blocks half empty
-    (1100, 3, 16, 256, 1024, 1.5),    # skewed: tall tiles for few experts, cuts of the item list by cost
-    (700, 4, 64, 384, 2048, 2.0),     # most experts with a handful of rows, a few with many; reduction cut in two
-    (130, 2, 3, 256, 4096, 0.0),      # 87 rows per expert, few items: cut in two where it streamed
-    (40, 2, 8, 256, 448, 0.0),        # 10 rows per expert, reduction too short to cut: whole, on tiles
-    (1030, 1, 8, 512, 128, 1.0),      # output rows stored directly from the wide form
+def route(dl, T, k, gemm):
+    """How a routed GEMM of a call is launched, as "<tile height> rows x<waves>" or "stream x<waves>"."""
+    import paper_2509_02753_amd as P
+    p = P.lexi_moe_gemm_plan(dl, T, k, gemm)
+    if p["fused"]:
+        return "fused"
+    if p["streams"]:
+        return f"stream x{p['waves']}"
+    return f"{p['tile_rows']} rows x{p['waves']}" + (" cut" if p["ksplit"] > 1 else "") + (" direct" if p["direct"] else "")
+
+
+@pytest.mark.parametrize("T,k,E,d,F,zipf,gate_up,down", [
+    # few items: low tiles, four waves, whatever the sizes
+    (161, 1, 1, 128, 64, 0.0, "64 rows x4", "64 rows x4 direct"), (160, 1, 1, 640, 192, 0.0, "64 rows x4", "64 rows x4 direct"),
+    (320, 2, 2, 512, 128, 0.0, "64 rows x4", "64 rows x4"), (321, 2, 2, 1152, 128, 0.0, "64 rows x4", "64 rows x4"),
+    (1100, 2, 8, 1152, 320, 0.0, "64 rows x4", "64 rows x4"),        # both column blocks of the last pair half empty
+    (1030, 1, 8, 512, 128, 1.0, "64 rows x4", "64 rows x4 direct"),
+    (1100, 3, 16, 256, 1024, 1.5, "128 rows x4", "64 rows x4"),       # skewed: tall experts, others with a handful of rows
+    (700, 4, 64, 384, 2048, 2.0, "64 rows x4", "64 rows x4 cut"),     # more skewed, reduction cut in two
+    (130, 2, 3, 256, 4096, 0.0, "64 rows x4", "64 rows x4 cut"),      # 87 rows per expert, few items
+    (40, 2, 8, 256, 448, 0.0, "64 rows x4", "stream x8"),             # 10 rows per expert, few units
+    (130, 3, 3, 512, 576, 0.0, "64 rows x4", "64 rows x4"), (65, 2, 2, 512, 576, 0.0, "96 rows x4", "96 rows x4"),
+    # every expert: 15 whole tiles of 160 rows, one row more, and tiles of 9 and 10 blocks; the last of the eight-wave form's
+    # column blocks of 512 holds 128 features
+    (2400, 8, 8, 1664, 192, 0.0, "160 rows x4", "160 rows x8"), (2401, 8, 8, 1664, 192, 0.0, "160 rows x4", "160 rows x8"),
+    (2380, 8, 8, 1664, 192, 0.0, "160 rows x4", "160 rows x8"), (2300, 8, 8, 1664, 192, 0.0, "160 rows x4", "128 rows x4"),
+    (1280, 8, 8, 1152, 64, 0.0, "64 rows x4", "128 rows x8"), (1281, 8, 8, 1152, 64, 0.0, "64 rows x4", "128 rows x8"),
+    # four waves at 160 rows, the last gate/up column block half empty
+    (800, 8, 16, 1152, 448, 0.0, "160 rows x4", "160 rows x4"), (1999, 8, 16, 512, 192, 1.1, "160 rows x4", "160 rows x4"),
+    # output rows stored directly: from eight waves (a ragged last column block), from four at 160 rows
+    (3000, 1, 2, 3200, 128, 0.0, "64 rows x4", "128 rows x8 direct"), (4001, 1, 16, 3200, 64, 1.0, "64 rows x4", "160 rows x8 direct"),
+    (4000, 1, 1, 2176, 64, 0.0, "64 rows x4", "160 rows x4 direct"),
 ])
-def test_grouped_gemm_tiles(T, k, E, d, F, zipf):
-    """Token tiles of up to 160 rows dealt out evenly, the eight-wave down GEMM, the cuts of the work list, and the sizes
-    around the streaming schedule's limits, against the oracle (routing bit for bit, TOL_BF16 of RMS)."""
+def test_grouped_gemm_tiles(T, k, E, d, F, zipf, gate_up, down):
+    """Every form of the tile schedule at the edges of its tiles and column blocks, against the oracle (routing bit for bit,
+    TOL_BF16 of RMS; above 1100 tokens the outputs of 64 of them)."""
+    import numpy as np
+    from helpers import device_and_host_layer
     cfg = replace(S.mini(S.C5 if zipf else S.C2, L=1, d=d, F=F, F_shared=0), E=E, F_shared=0, shared_kind=S.SHARED_NONE)
     if zipf:
         cfg = replace(cfg, zipf_s=zipf)
-    run_and_check_layer(cfg, 0, T, k)
+    dl, _ = device_and_host_layer(cfg, 0)
+    assert (route(dl, T, k, "gate_up"), route(dl, T, k, "down")) == (gate_up, down)
+    del dl
+    tokens = None
+    if T > 1100:
+        tokens = np.unique(np.concatenate([[0, 1, T - 2, T - 1], np.random.default_rng(T).integers(0, T, 60)])).astype(np.int32)
+    run_and_check_layer(cfg, 0, T, k, tokens=tokens)
 
 
-@pytest.mark.parametrize("T,k,E,d,F", [
-    (4, 4, 64, 2048, 1408), (6, 1, 64, 2048, 1408),     # 14 and 6 experts expected in use: 156 items of gate/up (tiles), 63 (streams)
-    (16, 4, 64, 256, 1408), (20, 4, 64, 2048, 128),     # gate/up on tiles with a streaming down GEMM, and the reverse
-    (2, 6, 64, 1024, 2816), (16, 1, 8, 2304, 8192),     # 240 items: streams; 443: tiles
-    (33, 2, 64, 2048, 1408),                            # both on tiles
+@pytest.mark.parametrize("T,k,E,d,F,gate_up,down", [
+    (4, 4, 64, 2048, 1408, "stream x4", "fused"), (6, 1, 64, 2048, 1408, "stream x4", "fused"),
+    (16, 4, 64, 256, 1408, "stream x4", "stream x4"), (20, 4, 64, 2048, 128, "stream x4", "stream x4"),
+    (2, 6, 64, 1024, 2816, "stream x4", "fused"), (33, 2, 64, 2048, 1408, "stream x4", "stream x4"),
+    (16, 1, 8, 2304, 8192, "stream x4", "stream x8"),        # a reduction of 8192: eight waves per unit
+    (17, 8, 64, 256, 1408, "64 rows x4", "stream x4"),       # just above two rows per expert
+    (33, 4, 64, 2048, 128, "64 rows x4", "64 rows x4"),
+    (21, 3, 3, 640, 2624, "64 rows x4", "stream x8"), (64, 2, 2, 512, 576, "64 rows x4", "stream x8"),   # few units, 2 and 4 blocks
+    (120, 2, 2, 384, 448, "64 rows x4", "stream x8"),        # 8 blocks, a short reduction
 ])
-def test_decode_schedules_around_their_limits(T, k, E, d, F):
-    """Decode-sized calls on either side of the line between weight streaming and tiles, against the oracle."""
+def test_decode_schedules_around_their_limits(T, k, E, d, F, gate_up, down):
+    """Decode-sized calls on either side of the lines between weight streaming and tiles, against the oracle."""
+    from helpers import device_and_host_layer
     cfg = replace(S.mini(S.C2, L=1, d=d, F=F, F_shared=0), E=E)
+    dl, _ = device_and_host_layer(cfg, 0)
+    assert (route(dl, T, k, "gate_up"), route(dl, T, k, "down")) == (gate_up, down)
+    del dl
     run_and_check_layer(cfg, 0, T, k)
+
+
+def _with_router(cfg, w_scale, x, dtype):
+    """The seeded layer of `cfg` with its router weights scaled, and x, on device and host."""
+    import numpy as np
+    import torch
+    import oracle as O
+    import paper_2509_02753_amd as P
+    host = S.host_layer(cfg, 0)
+    host["w_router"] = (host["w_router"] * np.float32(w_scale)).astype(np.float32)
+    dev = S.device_layer(cfg, 0)
+    dev["w_router"] = torch.from_numpy(host["w_router"]).cuda()
+    xd = torch.from_numpy(x).cuda().to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    xh = xd.view(torch.int16).cpu().numpy().view(np.uint16) if dtype == "bf16" else xd.cpu().numpy()
+    return P.Layer.from_tensors(dev, shared_kind=cfg.shared_kind), O.Layer.from_tensors(cfg, host), xd, xh
+
+
+def _route(dl, xd, k, E):
+    import torch
+    import paper_2509_02753_amd as P
+    T = xd.shape[0]
+    rout = P.RoutingOut(T, k, E)
+    P.lexi_moe_layer_forward(dl, xd, torch.empty((T, xd.shape[1]), dtype=torch.float32, device="cuda:0"), k,
+                             P.alloc_workspace([dl], T, k), routing=rout)
+    torch.cuda.synchronize()
+    return rout
+
+
+# one T in the range of every router kernel: whole segments per wave (64), router and top-k in one launch, partials through
+# memory -- the last in its wide and its narrow form (up to 16 experts)
+ROUTER_RANGES = [(64, 64), (65, 64), (1024, 17), (1025, 64), (1100, 17), (1100, 16), (1025, 5)]
+
+
+@pytest.mark.parametrize("T,E", ROUTER_RANGES)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_keeps_subnormal_products_and_sums(T, E, dtype):
+    """Products around 2^-142 and sums of 256 of them around 2^-138: every multiply-add rounds to a multiple of 2^-149, and
+    the order of the experts hangs on some thousand such steps.  Selection bit for bit as fmaf gives it; a kernel that
+    flushed them would select experts 0..k-1 everywhere."""
+    import numpy as np
+    import oracle as O
+    from helpers import check_routing
+    cfg = replace(S.mini(S.C1 if dtype == "f32" else S.C2, L=1, d=256, F=64, F_shared=0), E=E)
+    x = np.random.default_rng(T + E).standard_normal((T, cfg.d)).astype(np.float32) * np.float32(2.0 ** -56)
+    dl, hl, xd, xh = _with_router(cfg, 2.0 ** -80, x, dtype)
+    k = min(4, E)
+    ref = O.moe_layer(hl, xh, k, routing_only=True)
+    # (64 tokens that prefer one of 64 experts at random reach 40 of them)
+    assert 0.0 < np.abs(ref.logits).max() < 2.0 ** -126 and len(np.unique(ref.topk_idx[:, 0])) >= E // 3
+    check_routing(_route(dl, xd, k, E), ref)
+
+
+@pytest.mark.parametrize("T,E", ROUTER_RANGES)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_with_infinite_and_nan_activations(T, E, dtype):
+    """Two infinite activations leave a token's logits at +inf, -inf and NaN (both signs), one NaN all at NaN.  The logits are
+    those of the fmaf chain and a NaN ranks as -inf; every other token is routed as usual."""
+    import numpy as np
+    import oracle as O
+    from helpers import to_numpy
+    cfg = replace(S.mini(S.C1 if dtype == "f32" else S.C2, L=1, d=256, F=64, F_shared=0), E=E)
+    x = np.random.default_rng(T * E).standard_normal((T, cfg.d)).astype(np.float32)
+    x[3, 5], x[3, 200] = np.inf, np.inf
+    x[T - 1, 77] = np.nan
+    dl, hl, xd, xh = _with_router(cfg, 1.0, x, dtype)
+    k = min(6, E)
+    logits = O.moe_layer(hl, xh, k, routing_only=True).logits
+    assert np.isnan(logits[3]).any() and np.isinf(logits[3]).any() and np.isnan(logits[T - 1]).all()
+    want = np.argsort(-np.where(np.isnan(logits), -np.inf, logits), axis=1, kind="stable")[:, :k]
+    rout = _route(dl, xd, k, E)
+    assert np.array_equal(to_numpy(rout.topk_idx), want)
+    assert np.array_equal(np.sort(to_numpy(rout.perm)), np.arange(T * k))
+    g = to_numpy(rout.gates)
+    keep = ~np.isin(np.arange(T), (3, T - 1))
+    assert np.isnan(g[~keep]).all() and np.abs(g[keep].sum(axis=1) - 1.0).max() <= 1e-5
+
+
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** -70])
+def test_fp32_down_gemm_is_one_ascending_chain_of_fmaf(scale):
+    """One expert, gate exactly 1: the output rows are the down GEMM's.  Token t is the unit vector e_t and the gate weights
+    are all 64 (silu(64) is 64: 1 + exp(-64) rounds to 1), so its intermediate is 64 * W_up[:, t] exactly, and every output
+    equals the chain of fmaf from the C library bit for bit -- with subnormal products and sums at the small scale."""
+    import ctypes
+    import numpy as np
+    import torch
+    import paper_2509_02753_amd as P
+    T, d, F = 5, 128, 192
+    rng = np.random.default_rng(7)
+    w_up = (rng.standard_normal((F, d)) * scale).astype(np.float32)
+    w_down = (rng.standard_normal((d, F)) * scale).astype(np.float32)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+    dl = P.Layer.from_tensors(dict(w_router=dev(np.zeros((d, 1))), w_gate=dev(np.full((1, F, d), 64.0)), w_up=dev(w_up[None]),
+                                   w_down=dev(w_down[None])))
+    y = torch.empty((T, d), dtype=torch.float32, device="cuda:0")
+    P.lexi_moe_layer_forward(dl, dev(np.eye(T, d)), y, 1, P.alloc_workspace([dl], T, 1))
+    torch.cuda.synchronize()
+    fmaf = ctypes.CDLL("libm.so.6").fmaf
+    fmaf.restype, fmaf.argtypes = ctypes.c_float, [ctypes.c_float] * 3
+    want = np.zeros((T, d), dtype=np.float32)
+    for t in range(T):
+        act = [float(v) for v in np.float32(64.0) * w_up[:, t]]
+        for j in range(d):
+            acc = 0.0
+            for a, w in zip(act, w_down[j].tolist()):
+                acc = fmaf(a, w, acc)
+            want[t, j] = acc
+    assert scale == 1.0 or 0.0 < np.abs(want).max() < 2.0 ** -126
+    assert np.array_equal(y.cpu().numpy().view(np.int32), want.view(np.int32))
