@@ -311,9 +311,6 @@ lexi_status check_call(const lexi_layer_t* ly, const void* x, const void* y, int
     return LEXI_OK;
 }
 
-// Routing and the routed expert GEMMs of one layer at top-k = k: fills the routing arrays, act and y_slot of `w`.
-// `allow_split`: the down GEMM may write two planes of y_slot (w.slot_planes tells).  `direct_y` != null (k == 1, nothing
-// else to add): the down GEMM stores the output rows straight into the layer's output (w.direct tells whether it did).
 // Launch plan of the GEMMs of one call (what lexi_moe_gemm_plan and, its down part, lexi_moe_down_plan report).
 struct LayerPlan {
     bool gateup_streams;                   // weight-streaming schedule instead of the tile schedule
@@ -350,6 +347,9 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     return p;
 }
 
+// Routing and the routed expert GEMMs of one layer at top-k = k: fills the routing arrays, act and y_slot of `w`.
+// `allow_split`: the down GEMM may write two planes of y_slot (w.slot_planes tells).  `direct_y` != null (k == 1, nothing
+// else to add): the down GEMM stores the output rows straight into the layer's output (w.direct tells whether it did).
 lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t k, Workspace& w, hipStream_t s,
                        const lexi_stage_events_t* events, bool allow_split = true, void* direct_y = nullptr,
                        bool direct_bf16 = false, bool chained = false) {
@@ -461,7 +461,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
 
     // Nothing but y to produce (no residual, no normalised copy): the routed down launch may write y itself -- with
     // one active expert and no shared one on the tile schedule, or for a handful of tokens with the combine fused in
-    // (plan_down decides).
+    // (plan_layer decides).
     const bool direct = hidden == nullptr && u_out == nullptr;
     {
         const lexi_status st = run_routed(ly, x, T, k, w, s, events, true, direct ? y : nullptr, y_dtype == LEXI_BF16,

@@ -24,6 +24,9 @@ namespace lexi {
 //   NW = 8 (DOWN): one workgroup per CU, a token row is fetched for 512 weight rows instead of 256.  8 experts, d 4096,
 //   F 14336, 4096 tokens: 950 -> 780 us (k = 2), 506 -> 400 us (k = 1); 64 experts, F 1024, 2048 tokens, k = 8: 102 -> 88 us.
 //   Gate/up launches, whose items are shorter, gained nothing from it (between -6 and +15 %).
+//   At 256 registers the compiler spills 25 to 43 (72 to 96 bytes of scratch per lane), all outside the K loops: the price lies
+//   in prologue and epilogue and shows where the reduction is short (down, K 64 to 256, many thousand rows per expert: 1.05 to
+//   1.45 times the launch of the 128-row kernel without spills).
 //   GATEUP: a wave's blocks 0,1 are gate rows g0..g0+31 and blocks 2,3 the matching up rows, so the epilogue is
 //   silu(gate)*up -> bf16 act[row][f]; a workgroup of four waves covers 128 hidden features.
 //   DOWN:   a wave's blocks are 64 consecutive output features; the epilogue stores fp32 out[row][j].  Options: the
