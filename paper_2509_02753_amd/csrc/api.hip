@@ -39,13 +39,13 @@ struct TilePlan {
 };
 
 // Relative duration of a launch on the tile schedule: rounds of the chip times an item's duration (in 16-row blocks x
-// K-steps of a four-wave workgroup), the tallest item once.  An item pays about 5 blocks' worth per K-step whatever its height
+// K-steps of a four-wave workgroup), the tallest item once.  An item pays about 3 blocks' worth per K-step whatever its height
 // (the weight stream) and `store` K-steps' worth per block for storing its rows.  Launches of at most one four-wave item per
 // CU are priced apart, at 0.4 of a round: alone on its CU an item is faster than beside another (gate/up, 3315 tokens, k = 1, 8
 // experts of d 2560, F 896: 224 items of 128 rows 44 us, 392 of 64 rows 57).  A column block counts as a whole one where only
 // part of it holds features.  Fitted on 168 routed launches (60 to 3500 tokens, with and without a router bias, each timed at
 // every height in both forms): against 128 rows everywhere the choice takes gate/up launches from +1.3 % (constants without the
-// round of single items) to -0.7 %, down launches from -0.2 to -3.6 %, and the worst gate/up launch from 1.36 to 1.16 times.
+// round of single items) to -0.8 %, down launches from -0.2 to -3.4 %, and the worst gate/up launch from 1.36 to 1.16 times.
 double gemm_cost(int64_t rows, int groups, int K, int features, int store, const TilePlan& p, int col_width) {
     const double mean = (double)rows / groups, sd = groups > 1 ? sqrt(mean * (1.0 - 1.0 / groups)) : 0.0;
     const double in_use = groups > 1 && mean < 4.0 ? groups * (1.0 - exp(-mean)) : groups;
@@ -66,7 +66,7 @@ double gemm_cost(int64_t rows, int groups, int K, int features, int store, const
     else last = 0.25 + 0.75 * part;
     if (full > 0.0 && part <= 0.02) last = 0.0;
     const double steps = (double)(K / 64) / p.ksplit, scale = p.wide ? 0.86 : 1.0;
-    const double item = ((height + (p.wide ? 5.3 : 5.0)) * steps + store * height) * scale;
+    const double item = ((height + (p.wide ? 3.3 : 3.0)) * steps + store * height) * scale;
     return (full + last) * item + (tallest - height) * (steps + store) * scale;
 }
 

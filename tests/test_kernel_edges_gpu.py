@@ -87,9 +87,9 @@ def route(dl, T, k, gemm):
     (2380, 8, 8, 1664, 192, 0.0, "160 rows x4", "160 rows x8"), (2300, 8, 8, 1664, 192, 0.0, "160 rows x4", "128 rows x4"),
     (1280, 8, 8, 1152, 64, 0.0, "64 rows x4", "128 rows x8"), (1281, 8, 8, 1152, 64, 0.0, "64 rows x4", "128 rows x8"),
     # four waves at 160 rows, the last gate/up column block half empty
-    (800, 8, 16, 1152, 448, 0.0, "160 rows x4", "160 rows x4"), (1999, 8, 16, 512, 192, 1.1, "160 rows x4", "160 rows x4"),
+    (800, 8, 16, 1152, 448, 0.0, "160 rows x4", "160 rows x4"), (1999, 8, 16, 512, 192, 1.1, "160 rows x4", "64 rows x4"),
     # output rows stored directly: from eight waves (a ragged last column block), from four at 160 rows
-    (3000, 1, 2, 3200, 128, 0.0, "64 rows x4", "128 rows x8 direct"), (4001, 1, 16, 3200, 64, 1.0, "64 rows x4", "160 rows x8 direct"),
+    (4001, 1, 8, 3200, 64, 0.0, "64 rows x4", "128 rows x8 direct"), (4001, 1, 16, 3200, 128, 1.0, "64 rows x4", "160 rows x8 direct"),
     (4000, 1, 1, 2176, 64, 0.0, "64 rows x4", "160 rows x4 direct"),
 ])
 def test_grouped_gemm_tiles(T, k, E, d, F, zipf, gate_up, down):
