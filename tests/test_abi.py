@@ -277,6 +277,13 @@ def test_workspace_query_is_monotone_and_checked():
     assert _lib.lexi_moe_stack_forward(arr, 2, None, 0x50000, 0, 0x60000, 64 * 256, 0, 64, 0, 0x70000, 1 << 40, None, None) == -1
 
 
+def test_build_does_not_load_the_library_it_replaces():
+    import subprocess
+    import sys
+    code = "import sys, __graft_entry__ as g; g._lib_build(); assert 'paper_2509_02753_amd' not in sys.modules"
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, timeout=100)
+
+
 def test_product_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2509_02753_amd")
     for dirpath, _, files in os.walk(pkg):
