@@ -24,9 +24,11 @@ namespace lexi {
 //   NW = 8 (DOWN): one workgroup per CU, a token row is fetched for 512 weight rows instead of 256.  8 experts, d 4096,
 //   F 14336, 4096 tokens: 950 -> 780 us (k = 2), 506 -> 400 us (k = 1); 64 experts, F 1024, 2048 tokens, k = 8: 102 -> 88 us.
 //   Gate/up launches, whose items are shorter, gained nothing from it (between -6 and +15 %).
-//   At 256 registers the compiler spills 25 to 43 (72 to 96 bytes of scratch per lane), all outside the K loops: the price lies
-//   in prologue and epilogue and shows where the reduction is short (down, K 64 to 256, many thousand rows per expert: 1.05 to
-//   1.45 times the launch of the 128-row kernel without spills).
+//   Low tiles (a launch that reads weights for a few rows) have forms of their own.  Up to 96 rows the first weights are
+//   requested before the rows' numbers have arrived.  Up to 64 rows a DOWN wave takes 32 features instead of 64, in 128
+//   registers, four workgroups per CU: a CU streams at most 32 to 48 GB/s, so a launch takes as long as the CU with the most
+//   bytes, and its few column blocks (d / 256) deal out badly.  K 1408, d 2048: 24 experts 29.4 -> 29.0 us, 40: 51.6 -> 46.4, 48:
+//   57.6 -> 52.7, 60: 65.3 -> 66.4; K 896, d 1280, 64 experts: 40.9 -> 36.9.  (GATEUP has four times the items: -6 to +8 %.)
 //   GATEUP: a wave's blocks 0,1 are gate rows g0..g0+31 and blocks 2,3 the matching up rows, so the epilogue is
 //   silu(gate)*up -> bf16 act[row][f]; a workgroup of four waves covers 128 hidden features.
 //   DOWN:   a wave's blocks are 64 consecutive output features; the epilogue stores fp32 out[row][j].  Options: the
@@ -38,14 +40,16 @@ namespace lexi {
 // ---------------------------------------------------------------------------------------------------------
 template <int S> struct StageTag { static constexpr int value = S; };
 
-template <bool GATEUP, int NW>
-__global__ void __launch_bounds__(NW * 64, 2)
+template <bool GATEUP, int NW, int WB, int TT>
+__global__ void __launch_bounds__(NW * 64, WB == 2 ? 4 : 2)
 ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
                 const bf16_t* __restrict__ w1, int K, int features, int M, int tile_rows,
                 const int32_t* __restrict__ sched, void* __restrict__ out, int ksplit, size_t plane_stride,
                 const int32_t* __restrict__ scatter, int out_bf16) {
-    constexpr int TT = kTileRows, TB = TT / 16, WB = 4, KS = BK / 32;
-    constexpr int CB = NW * (GATEUP ? 32 : 64);      // output features of a workgroup
+    constexpr int TB = TT / 16, KS = BK / 32;
+    constexpr bool LOW = TT <= kLowTileRows;
+    constexpr int WF = GATEUP ? 8 * WB : 16 * WB;    // output features of a wave
+    constexpr int CB = NW * WF;                      // of the workgroup
     constexpr int ELD = CB + 8;                      // GATEUP: bf16 elements per row of the staged output tile
     constexpr int LDS_ELEMS = (GATEUP && TT * ELD > 2 * TT * LDS_LD) ? TT * ELD : 2 * TT * LDS_LD;
     __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS];
@@ -69,7 +73,7 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wave_f0 = cb * CB + wave * (GATEUP ? 32 : 64);  // first output feature
+    const int wave_f0 = cb * CB + wave * WF;  // first output feature
     const bool active = wave_f0 < features;
     const int l16 = lane & 15, kq = lane >> 4;
     const int koff = kq * 8;
@@ -84,8 +88,8 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
         int row;
         const bf16_t* base = w0;
         if (GATEUP) {
-            row = wave_f0 + 16 * (fb & 1);
-            if (fb >= 2) base = w1;
+            row = wave_f0 + 16 * (fb % (WB / 2));
+            if (fb >= WB / 2) base = w1;
         } else {
             row = wave_f0 + 16 * fb;
         }
@@ -102,15 +106,25 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
     constexpr int XP = TT / SR;
     constexpr bool HALF = TT % SR != 0;
     static_assert(!HALF || TT % SR == SR / 2, "the last pass stages a whole or a half set of rows");
-    auto x_row = [&](int r) {   // byte offset of tile row r from `in` (the launcher rejects inputs of 4 GiB or more)
+    auto x_row = [&](int r) {   // the row of `in` behind tile row r
         const int rr = min(r, ti.rows - 1);  // rows past the group end re-read its last row; never stored
-        const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
-        return (uint32_t)(((size_t)src_row * K + (size_t)kstep0 * BK) * 2);
+        return row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
     };
-    uint32_t xoff[XP], xoff_half = 0;
+    int xrow[XP], xrow_half = 0;
 #pragma unroll
-    for (int p = 0; p < XP; ++p) xoff[p] = x_row((tid >> 3) + SR * p) + (tid & 7) * 16;
-    if (HALF) xoff_half = x_row((tid >> 4) + SR * XP) + (tid & 15) * 8;
+    for (int p = 0; p < XP; ++p) xrow[p] = x_row((tid >> 3) + SR * p);
+    if (HALF) xrow_half = x_row((tid >> 4) + SR * XP);
+
+    // In the form for low tiles the first weights are requested here, while the rows' numbers and the code of the switch below
+    // are still on their way (T 64, 60 experts: 1.5 % of the launch).  The form for tall ones requests them behind the switch:
+    // alive across it they spill (72 to 96 bytes of scratch per lane; DOWN at K 1024 to 1408 2 to 5 % slower, GATEUP -1 to +1 %).
+    bf16x8_t afirst[WB][KS];
+    if constexpr (LOW) {
+#pragma unroll
+        for (int fb = 0; fb < WB; ++fb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) afirst[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)ks * 1024u));
+    }
 
     f32x4_t acc[WB][TB];
 #pragma unroll
@@ -119,12 +133,6 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
         for (int b = 0; b < TB; ++b)
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[a][b][v] = 0.0f;
-
-    bf16x8_t areg[WB][KS];
-#pragma unroll
-    for (int fb = 0; fb < WB; ++fb)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)ks * 1024u));
 
     // The K loop, specialised on the number of 16-token blocks the tile really holds: nothing is staged, read or multiplied
     // for blocks that would only hold padding.
@@ -142,6 +150,22 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
         constexpr int GB = TALL ? 2 : NTB;               // token blocks whose fragments are read together
         constexpr int NG = (NTB + GB - 1) / GB;
         static_assert(KS == 2, "a K-step has two halves");
+        // (a different statement for each number: the compiler would move what they have in common in front of the switch)
+        if constexpr (!LOW) asm volatile("; %0 token blocks" ::"n"(NTB));
+        bf16x8_t areg[WB][KS];
+#pragma unroll
+        for (int fb = 0; fb < WB; ++fb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                if constexpr (LOW) areg[fb][ks] = afirst[fb][ks];
+                else areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)ks * 1024u));
+            }
+        __builtin_amdgcn_sched_barrier(0);   // (the weights are on their way before the rows' numbers are waited for)
+        // byte offsets from `in` (the launcher rejects inputs of 4 GiB or more)
+        uint32_t xoff[NP], xoff_half = 0;
+#pragma unroll
+        for (int p = 0; p < NP; ++p) xoff[p] = (uint32_t)(((size_t)xrow[p] * K + (size_t)kstep0 * BK) * 2) + (tid & 7) * 16;
+        if (LAST_HALF) xoff_half = (uint32_t)(((size_t)xrow_half * K + (size_t)kstep0 * BK) * 2) + (tid & 15) * 8;
         u32x4_t xreg[PP];
         u32x2_t xreg_half;
         auto load_x = [&](int kt, int h) {
@@ -198,18 +222,15 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
             __syncthreads();
         }
     };
-    switch ((ti.rows + 15) >> 4) {
-        case 1: k_loop(StageTag<1>{}); break;
-        case 2: k_loop(StageTag<2>{}); break;
-        case 3: k_loop(StageTag<3>{}); break;
-        case 4: k_loop(StageTag<4>{}); break;
-        case 5: k_loop(StageTag<5>{}); break;
-        case 6: k_loop(StageTag<6>{}); break;
-        case 7: k_loop(StageTag<7>{}); break;
-        case 8: k_loop(StageTag<8>{}); break;
-        case 9: k_loop(StageTag<9>{}); break;
-        default: k_loop(StageTag<10>{}); break;
-    }
+    auto dispatch = [&](auto... n) {
+        const int blocks = (ti.rows + 15) >> 4;
+        (void)((blocks == decltype(n)::value ? (k_loop(n), true) : false) || ...);
+    };
+    if constexpr (TB == 4) dispatch(StageTag<1>{}, StageTag<2>{}, StageTag<3>{}, StageTag<4>{});
+    else if constexpr (TB == 6) dispatch(StageTag<1>{}, StageTag<2>{}, StageTag<3>{}, StageTag<4>{}, StageTag<5>{}, StageTag<6>{});
+    else dispatch(StageTag<1>{}, StageTag<2>{}, StageTag<3>{}, StageTag<4>{}, StageTag<5>{}, StageTag<6>{}, StageTag<7>{},
+                  StageTag<8>{}, StageTag<9>{}, StageTag<10>{});
+    static_assert(TB == 4 || TB == 6 || TB == 10, "a K loop for every number of token blocks");
     // ---- epilogue: in a 16 x 16 accumulator block a lane owns token (lane % 16) and features 4*(lane/16) + 0..3
     if (GATEUP) {
         // The workgroup's tokens x 128 features of silu(gate)*up are transposed through LDS (the token-tile
@@ -221,14 +242,14 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
         for (int tb = 0; tb < TB; ++tb) {
             if (tb * 16 >= ti.rows) break;
 #pragma unroll
-            for (int fb = 0; fb < 2; ++fb) {
+            for (int fb = 0; fb < WB / 2; ++fb) {
                 float v[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = silu(acc[fb][tb][i]) * acc[fb + 2][tb][i];
+                for (int i = 0; i < 4; ++i) v[i] = silu(acc[fb][tb][i]) * acc[fb + WB / 2][tb][i];
                 u32x2_t pk;
                 pk[0] = pack_bf16x2(v[0], v[1]);
                 pk[1] = pack_bf16x2(v[2], v[3]);
-                *(u32x2_t*)(&stage[(tb * 16 + l16) * ELD + wave * 32 + fb * 16 + kq * 4]) = pk;
+                *(u32x2_t*)(&stage[(tb * 16 + l16) * ELD + wave * WF + fb * 16 + kq * 4]) = pk;
             }
         }
         __syncthreads();
@@ -319,17 +340,23 @@ static hipError_t launch_ffn(const FfnArgs& a, hipStream_t s) {
     if (in_rows * (size_t)a.K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
     const int ksplit = GATEUP ? 1 : (a.ksplit > 1 ? a.ksplit : 1);
     if (ksplit > 1 && (a.K / BK < ksplit || a.scatter != nullptr)) return hipErrorInvalidValue;
-    auto launch = [&](auto nw) {
-        constexpr int NW = decltype(nw)::value, CB = NW * (GATEUP ? 32 : 64);
+    auto launch = [&](auto nw, auto wb, auto tt) {
+        constexpr int NW = decltype(nw)::value, WB = decltype(wb)::value, CB = NW * WB * (GATEUP ? 8 : 16);
         const long long pieces = (long long)((a.features + CB - 1) / CB) * a.max_tiles * ksplit;
         const dim3 grid((unsigned)((pieces + kXcds - 1) / kXcds * kXcds));
-        hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP, NW>), grid, dim3(NW * 64), 0, s, (const bf16_t*)a.in,
+        hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP, NW, WB, decltype(tt)::value>), grid, dim3(NW * 64), 0, s, (const bf16_t*)a.in,
                            a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
                            a.out, ksplit, a.plane_stride, GATEUP ? nullptr : a.scatter, a.out_bf16 ? 1 : 0);
     };
-    if constexpr (GATEUP) launch(StageTag<4>{});
-    else if (a.wide) launch(StageTag<8>{});
-    else launch(StageTag<4>{});
+    if constexpr (GATEUP) {
+        if (a.tile_rows <= kLowTileRows) launch(StageTag<4>{}, StageTag<4>{}, StageTag<kLowTileRows>{});
+        else launch(StageTag<4>{}, StageTag<4>{}, StageTag<kTileRows>{});
+    } else {
+        if (a.wide) launch(StageTag<8>{}, StageTag<4>{}, StageTag<kTileRows>{});
+        else if (a.tile_rows <= kHalfTileRows) launch(StageTag<4>{}, StageTag<2>{}, StageTag<kHalfTileRows>{});
+        else if (a.tile_rows <= kLowTileRows) launch(StageTag<4>{}, StageTag<4>{}, StageTag<kLowTileRows>{});
+        else launch(StageTag<4>{}, StageTag<4>{}, StageTag<kTileRows>{});
+    }
     return hipGetLastError();
 }
 
