@@ -276,7 +276,7 @@ def measure_regime(args, mods, cfg, layers, arr, T, cpu_seconds, extras):
 
     def timed(kv, chained=False):
         """K steps between two synchronisations (wall clock), one HIP event between consecutive steps (median)."""
-        if use_graph:   # the whole stack call (every launch of all L layers, a side-stream fork/join included) as one HIP graph
+        if use_graph:   # the whole stack call (every launch of all L layers) as one HIP graph
             run_steps(kv, 1, chained=chained)      # first-use set-up inside the library happens outside the capture
             torch.cuda.synchronize()
             g = torch.cuda.CUDAGraph()
@@ -334,10 +334,11 @@ def measure_regime(args, mods, cfg, layers, arr, T, cpu_seconds, extras):
     U = [int((c > 0).sum()) for c in counts]
 
     # ---- algorithmic work (only selected experts, only touched weights) ----
-    gu_flops = [4.0 * T * int(k) * cfg.d * cfg.F for k in kvec]
-    dn_flops = [2.0 * T * int(k) * cfg.d * cfg.F for k in kvec]
-    gu_bytes = [U[l] * 2.0 * cfg.d * cfg.F * es + T * cfg.d * es for l in range(L)]
-    dn_bytes = [U[l] * 1.0 * cfg.d * cfg.F * es + T * cfg.d * 4 for l in range(L)]     # weights + the layer's fp32 output
+    # (the stages hold the shared expert's GEMMs too: they run with the routed ones)
+    gu_flops = [4.0 * T * cfg.d * (int(k) * cfg.F + cfg.F_shared) for k in kvec]
+    dn_flops = [2.0 * T * cfg.d * (int(k) * cfg.F + cfg.F_shared) for k in kvec]
+    gu_bytes = [(U[l] * cfg.F + cfg.F_shared) * 2.0 * cfg.d * es + T * cfg.d * es for l in range(L)]
+    dn_bytes = [(U[l] * cfg.F + cfg.F_shared) * 1.0 * cfg.d * es + T * cfg.d * 4 for l in range(L)]     # weights + the layer's fp32 output
     tot_flops = sum(T * (2.0 * cfg.d * cfg.E + int(k) * 6.0 * cfg.d * cfg.F + 6.0 * cfg.d * cfg.F_shared) for k in kvec)
     tot_bytes = sum(U[l] * 3 * cfg.d * cfg.F * es + 3 * cfg.d * cfg.F_shared * es + cfg.d * cfg.E * 4 + T * cfg.d * es + T * cfg.d * 4
                     for l in range(L))

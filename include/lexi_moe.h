@@ -17,12 +17,8 @@
  *     lexi_layer_t / lexi_routing_out_t structs themselves, and k_vec, live in
  *     HOST memory.  The library never allocates, frees or keeps a pointer.
  *   - All work is enqueued on `hip_stream` (a hipStream_t passed as void*, NULL
- *     = the default stream) and the call returns without synchronising.  For
- *     batches of at most 1024 tokens the shared expert's kernels run on a
- *     library-owned side stream that forks from `hip_stream` at the start of
- *     the layer and joins it again before the combine (events, no host
- *     synchronisation): the caller sees plain stream semantics.  That stream
- *     and its two events are created once per device, on first use.
+ *     = the default stream) and the call returns without synchronising.  The
+ *     library creates no stream and no event.
  *   - On error a negative lexi_status is returned and nothing is launched.
  *   - Same inputs give the same output bits on every call; no call leaves
  *     state behind (k=2 then k=8 gives the k=8 result of a fresh call).
@@ -135,7 +131,7 @@ lexi_status lexi_moe_layer_forward(const lexi_layer_t* layer, const void* x, voi
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments minus the workspace, same
  * kernels, same result bits.  The scratch lives in a static device array inside the library (64 MiB; each GPU the
  * library runs on holds its copy until the process ends), whose address is looked up on the first call on a device.
- * The call allocates nothing, frees nothing, and creates no stream or event (a shared expert runs on `hip_stream`).
+ * The call allocates nothing and frees nothing.
  *   Limit: the call must need at most 64 MiB of workspace (lexi_moe_workspace_bytes(layer, 1, T, k) <= 67108864:
  *   decode-sized batches of every workload shape here), otherwise LEXI_ERR_WORKSPACE and nothing is launched.
  *   All calls on one GPU share the one array: calls that overlap in time on the same GPU (different streams or host
@@ -159,11 +155,11 @@ lexi_status lexi_moe_stack_forward(const lexi_layer_t* layers, int32_t L, const 
                                    void* hip_stream, const lexi_routing_out_t* dbg_per_layer);
 
 /* Stage boundaries of one layer, for timing from outside with HIP events: the library records ev[i] on the
- * stream at boundary i.  0 = layer start, 1 = routing done (router, top-k, gates, permutation), 2 = routed gate/up
- * GEMM + SwiGLU done, 3 = routed down GEMM done, 4 = shared expert done, 5 = combine done.  A NULL event is
- * skipped.  Events are hipEvent_t handles owned by the caller (host struct).  A call for a handful of tokens whose
- * down projection and combine are one launch (it consumes the shared expert's rows) records 4 BEFORE that launch and
- * 3 and 5 after it. */
+ * stream at boundary i.  0 = layer start, 1 = routing done (router, top-k, gates, permutation), 2 = gate/up GEMMs +
+ * SwiGLU done (routed and shared experts), 3 = down GEMMs done, 4 = shared expert done (with 3: its GEMMs run with the
+ * routed ones), 5 = combine done.  A NULL event is skipped.  Events are hipEvent_t handles owned by the caller (host
+ * struct).  A call for a handful of tokens whose down projection and combine are one launch (it consumes the shared
+ * expert's rows) records 4 BEFORE that launch and 3 and 5 after it. */
 #define LEXI_N_STAGE_EVENTS 6
 typedef struct {
     void* ev[LEXI_N_STAGE_EVENTS];

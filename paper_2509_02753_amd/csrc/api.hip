@@ -133,37 +133,12 @@ TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool all
     return best;
 }
 
-// The shared expert depends on x only, not on the routing, so for decode-sized batches (where its kernels are short
-// and latency-bound) it runs on a side stream that forks from the caller's stream at the start of the layer and joins
-// it again in front of the combine.  One side stream and one event pair per device, created on first use and kept
-// until the process ends; the caller sees plain stream semantics (and a capture of the caller's stream picks the
-// side stream up through the events).
-constexpr int kSideStreamMaxT = 1024;
-// Tile height of its GEMMs there: they share the chip with the routing and the routed GEMMs, so neither their own duration
-// nor the slots they take may grow (64 to 160 rows measured between -5 and +5 % of the call, 128 never the slower side).
-constexpr int kSideTileRows = 128;
-struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t fork = nullptr, join = nullptr;
-    bool tried = false, ok = false;
-};
+// Tokens up to which the shared expert's GEMMs take the routed GEMMs' kind of workgroup and tile height, so that each shares the
+// routed one's launch and form of the kernel (256 tokens: 1268 us at 128 rows, 1222 at the routed GEMMs' 64).  Beside streaming
+// or eight-wave routed GEMMs: 128 rows.  With more tokens a shared expert fills the chip by itself and keeps the tallest tiles.
+constexpr int kSharedJoinsMaxT = 1024;
+constexpr int kSharedTileRows = 128;
 constexpr int kMaxDevices = 16;
-SideStream g_side[kMaxDevices];
-std::mutex g_side_mutex, g_side_enqueue_mutex;
-
-SideStream* side_stream() {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
-    std::lock_guard<std::mutex> lock(g_side_mutex);
-    SideStream& ss = g_side[dev];
-    if (!ss.tried) {
-        ss.tried = true;
-        ss.ok = hipStreamCreateWithFlags(&ss.stream, hipStreamNonBlocking) == hipSuccess &&
-                hipEventCreateWithFlags(&ss.fork, hipEventDisableTiming) == hipSuccess &&
-                hipEventCreateWithFlags(&ss.join, hipEventDisableTiming) == hipSuccess;
-    }
-    return ss.ok ? &ss : nullptr;   // no side stream: the shared expert simply stays on the caller's stream
-}
 
 // Scratch of lexi_moe_layer_forward_static: the workspace of one decode-sized layer call, held in the library's own
 // device image so that the call needs no allocation and no workspace argument.  Every GPU the library runs on holds
@@ -330,7 +305,7 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     p.routed_streams = p.gateup_streams || (few_items <= kStreamDownMaxItems && down_streams(A, ly.E, ly.F, ly.d, direct));
     p.shared_streams = !bf || T <= kStreamDenseRows;
     p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
-    p.shared_gateup = TilePlan{false, T <= kSideStreamMaxT ? kSideTileRows : kTileRows, 1};
+    p.shared_gateup = TilePlan{false, T <= kSharedJoinsMaxT ? kSharedTileRows : kTileRows, 1};
     if (!p.gateup_streams) p.gateup = plan_gateup_tiles(A, ly.E, ly.d, ly.F);
     // (allow_direct: the caller wants nothing but y -- no slot rows, no residual, no normalised copy)
     p.routed_fused = bf && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&
@@ -342,17 +317,21 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     }
     if (ly.F_shared > 0 && !p.shared_streams) {
         p.shared = plan_down_tiles(T, 1, ly.F_shared, ly.d, true, false);
-        if (T <= kSideStreamMaxT) p.shared = TilePlan{false, kSideTileRows, p.shared.ksplit};
+        if (T <= kSharedJoinsMaxT) {
+            p.shared = TilePlan{p.routed.wide, p.routed_streams || p.routed.wide ? kSharedTileRows : p.routed.tile_rows, p.shared.ksplit};
+            if (!p.gateup_streams) p.shared_gateup.tile_rows = p.gateup.tile_rows;
+        }
     }
     return p;
 }
 
-// Routing and the routed expert GEMMs of one layer at top-k = k: fills the routing arrays, act and y_slot of `w`.
+// Routing and the expert GEMMs of one layer at top-k = k: fills the routing arrays, act and y_slot of `w`, and (`with_shared`)
+// act_shared and y_shared.
 // `allow_split`: the down GEMM may write two planes of y_slot (w.slot_planes tells).  `direct_y` != null (k == 1, nothing
 // else to add): the down GEMM stores the output rows straight into the layer's output (w.direct tells whether it did).
-lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t k, Workspace& w, hipStream_t s,
-                       const lexi_stage_events_t* events, bool allow_split = true, void* direct_y = nullptr,
-                       bool direct_bf16 = false, bool chained = false) {
+lexi_status run_experts(const lexi_layer_t& ly, const void* x, int32_t T, int32_t k, Workspace& w, hipStream_t s,
+                        const lexi_stage_events_t* events, bool with_shared, bool allow_split = true, void* direct_y = nullptr,
+                        bool direct_bf16 = false, bool chained = false) {
     auto mark = [&](int i) {
         if (events && events->ev[i]) (void)hipEventRecord((hipEvent_t)events->ev[i], s);
     };
@@ -371,16 +350,22 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
     if (launch_routing(r, s) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(1);
 
-    FfnArgs g{};
+    auto dense = [&](FfnArgs& f, int tile_rows) {   // the shared expert: one group of T rows
+        f.is_bf16 = bf; f.M = T; f.chained = chained; f.tile_rows = tile_rows; f.max_tiles = (T + tile_rows - 1) / tile_rows;
+    };
+    FfnArgs g{}, sg{};
     g.streaming = plan.gateup_streams;
     g.chained = chained;
     g.is_bf16 = bf; g.in = x; g.row_token = w.row_token; g.in_rows = T; g.w0 = ly.w_gate; g.w1 = ly.w_up; g.K = ly.d;
     g.features = ly.F; g.M = (int)A; g.tile_rows = r.plan.tile_rows[0];
     g.max_tiles = (int)max_tiles(A, ly.E, g.tile_rows); g.sched = w.sched; g.out = w.act;
-    if (launch_gateup(g, s) != hipSuccess) return LEXI_ERR_LAUNCH;
+    dense(sg, plan.shared_gateup.tile_rows);
+    sg.streaming = plan.shared_streams;
+    sg.in = x; sg.w0 = ly.ws_gate; sg.w1 = ly.ws_up; sg.K = ly.d; sg.features = ly.F_shared; sg.out = w.act_shared;
+    if (launch_gateup(g, with_shared ? &sg : nullptr, s) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(2);
 
-    FfnArgs dn{};
+    FfnArgs dn{}, sd{};
     dn.is_bf16 = bf; dn.in = w.act; dn.row_token = nullptr; dn.w0 = ly.w_down; dn.w1 = nullptr; dn.K = ly.F;
     dn.features = ly.d; dn.M = (int)A; dn.tile_rows = r.plan.tile_rows[1];
     dn.max_tiles = (int)max_tiles(A, ly.E, dn.tile_rows); dn.sched = w.sched; dn.out = w.y_slot;
@@ -389,13 +374,20 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
     dn.wide = plan.routed.wide;
     dn.ksplit = w.slot_planes = plan.routed.ksplit;
     dn.plane_stride = (size_t)A * ly.d;
+    dense(sd, plan.shared.tile_rows);
+    sd.streaming = plan.shared_streams;
+    sd.in = w.act_shared; sd.w0 = ly.ws_down; sd.K = ly.F_shared; sd.features = ly.d; sd.out = w.y_shared;
+    sd.wide = plan.shared.wide;
+    sd.ksplit = w.shared_planes = plan.shared.ksplit;
+    sd.plane_stride = (size_t)T * ly.d;
     w.direct = plan.routed_direct;
     w.fused = plan.routed_fused;
-    if (plan.routed_fused) return LEXI_OK;   // run_layer launches down + combine once the shared expert's rows are there
+    if (plan.routed_fused)   // run_layer launches down + combine; it consumes the shared expert's rows
+        return with_shared && launch_down(sd, nullptr, s) != hipSuccess ? LEXI_ERR_LAUNCH : LEXI_OK;
     if (plan.routed_direct) {
         dn.out = direct_y; dn.scatter = w.row_token; dn.out_bf16 = direct_bf16;
     }
-    if (launch_down(dn, s) != hipSuccess) return LEXI_ERR_LAUNCH;
+    if (launch_down(dn, with_shared ? &sd : nullptr, s) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(3);
     return LEXI_OK;
 }
@@ -407,7 +399,7 @@ lexi_status run_routed(const lexi_layer_t& ly, const void* x, int32_t T, int32_t
 lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_dtype, int32_t T, int32_t k,
                       void* workspace, hipStream_t s, const lexi_routing_out_t* dbg,
                       const lexi_stage_events_t* events = nullptr, const float* hidden = nullptr,
-                      const void* u_in = nullptr, void* u_out = nullptr, bool allow_side_stream = true) {
+                      const void* u_in = nullptr, void* u_out = nullptr) {
     auto mark = [&](int i) {
         if (events && events->ev[i]) (void)hipEventRecord((hipEvent_t)events->ev[i], s);
     };
@@ -430,56 +422,18 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         if (dbg->inv_perm) w.inv_perm = dbg->inv_perm;
     }
 
-    auto run_shared = [&](hipStream_t st) -> bool {
-        const LayerPlan plan = plan_layer(ly, T, k, true, false);
-        auto dense = [&](FfnArgs& a, int tile_rows) {   // one group of T rows
-            a.is_bf16 = bf; a.M = T; a.streaming = plan.shared_streams; a.chained = hidden != nullptr; a.tile_rows = tile_rows;
-            a.max_tiles = (T + tile_rows - 1) / tile_rows;
-        };
-        FfnArgs sg{};
-        sg.in = x; sg.w0 = ly.ws_gate; sg.w1 = ly.ws_up; sg.K = ly.d; sg.features = ly.F_shared; sg.out = w.act_shared;
-        dense(sg, plan.shared_gateup.tile_rows);
-        if (launch_gateup(sg, st) != hipSuccess) return false;
-        FfnArgs sd{};
-        sd.in = w.act_shared; sd.w0 = ly.ws_down; sd.K = ly.F_shared; sd.features = ly.d; sd.out = w.y_shared;
-        sd.wide = plan.shared.wide;
-        sd.ksplit = w.shared_planes = plan.shared.ksplit;
-        sd.plane_stride = (size_t)T * ly.d;
-        dense(sd, plan.shared.tile_rows);
-        return launch_down(sd, st) == hipSuccess;
-    };
-    SideStream* side = (allow_side_stream && ly.F_shared > 0 && T <= kSideStreamMaxT) ? side_stream() : nullptr;
-    // the fork/join events are shared by every call on the device: host threads enqueue their layers one at a time
-    std::unique_lock<std::mutex> side_lock(g_side_enqueue_mutex, std::defer_lock);
-    if (side) {
-        side_lock.lock();
-        if (hipEventRecord(side->fork, s) != hipSuccess || hipStreamWaitEvent(side->stream, side->fork, 0) != hipSuccess)
-            return LEXI_ERR_LAUNCH;
-        if (!run_shared(side->stream)) return LEXI_ERR_LAUNCH;
-        if (hipEventRecord(side->join, side->stream) != hipSuccess) return LEXI_ERR_LAUNCH;
-    }
-
     // Nothing but y to produce (no residual, no normalised copy): the routed down launch may write y itself -- with
     // one active expert and no shared one on the tile schedule, or for a handful of tokens with the combine fused in
     // (plan_layer decides).
     const bool direct = hidden == nullptr && u_out == nullptr;
     {
-        const lexi_status st = run_routed(ly, x, T, k, w, s, events, true, direct ? y : nullptr, y_dtype == LEXI_BF16,
-                                         hidden != nullptr);
+        const lexi_status st = run_experts(ly, x, T, k, w, s, events, ly.F_shared > 0, true, direct ? y : nullptr,
+                                          y_dtype == LEXI_BF16, hidden != nullptr);
         if (st != LEXI_OK) return st;
     }
-    const bool fused = w.fused;
-    if (fused) {
-        // the fused launch consumes the shared expert's rows, so the join (or the in-line shared expert) comes first;
-        // the stage events keep their meaning: 4 = shared expert done, 3 = routed down done (= 5, combine done)
-        if (ly.F_shared > 0) {
-            if (side) {
-                if (hipStreamWaitEvent(s, side->join, 0) != hipSuccess) return LEXI_ERR_LAUNCH;
-            } else if (!run_shared(s)) {
-                return LEXI_ERR_LAUNCH;
-            }
-            mark(4);
-        }
+    if (w.fused) {
+        // (the launch holds the routed down projection and the combine: 4 = shared expert done comes before 3 and 5)
+        if (ly.F_shared > 0) mark(4);
         DownCombineArgs f{};
         f.act = w.act; f.w_down = ly.w_down; f.F = ly.F; f.d = ly.d; f.T = T; f.k = k; f.sched = w.sched;
         f.inv_perm = w.inv_perm; f.gates = w.gates;
@@ -491,13 +445,6 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         return LEXI_OK;
     }
 
-    if (ly.F_shared > 0) {
-        if (side) {
-            if (hipStreamWaitEvent(s, side->join, 0) != hipSuccess) return LEXI_ERR_LAUNCH;
-        } else if (!run_shared(s)) {
-            return LEXI_ERR_LAUNCH;
-        }
-    }
     mark(4);
     if (w.direct) {   // y is complete
         mark(5);
@@ -566,10 +513,8 @@ lexi_status lexi_moe_layer_forward_static(const lexi_layer_t* layer, const void*
     if (st != LEXI_OK || T == 0) return st;
     void* ws = static_scratch();
     if (ws == nullptr) return LEXI_ERR_LAUNCH;
-    // every kernel writes the part of the scratch it reads later in the same call, so nothing needs clearing; the
-    // shared expert stays on the caller's stream (no library-owned stream or event is created or used)
-    return run_layer(*layer, x, y, y_dtype, T, k, ws, (hipStream_t)hip_stream, dbg, nullptr, nullptr, nullptr, nullptr,
-                     /*allow_side_stream=*/false);
+    // every kernel writes the part of the scratch it reads later in the same call, so nothing needs clearing
+    return run_layer(*layer, x, y, y_dtype, T, k, ws, (hipStream_t)hip_stream, dbg);
 }
 
 lexi_status lexi_moe_stack_forward_profiled(const lexi_layer_t* layers, int32_t L, const int32_t* k_vec,
@@ -673,7 +618,7 @@ lexi_status lexi_moe_profile_layer(const lexi_layer_t* layer, const void* x, int
     Workspace w = carve(*layer, T, k_base, workspace);
     if (workspace_bytes < w.bytes + align_up((size_t)n_k * T * sizeof(float), 256)) return LEXI_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
-    st = run_routed(*layer, x, T, k_base, w, s, nullptr, /*allow_split=*/false);
+    st = run_experts(*layer, x, T, k_base, w, s, nullptr, /*with_shared=*/false, /*allow_split=*/false);
     if (st != LEXI_OK) return st;
     ProfileArgs p{};
     p.y_slot = w.y_slot; p.inv_perm = w.inv_perm; p.gates = w.gates;
@@ -709,17 +654,30 @@ lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, 
     const LayerPlan p = plan_layer(*layer, T, k, true, !chained);
     const bool shared = which >= 2, down = which & 1;
     const TilePlan& t = shared ? (down ? p.shared : p.shared_gateup) : (down ? p.routed : p.gateup);
-    const int F = shared ? layer->F_shared : layer->F, K = down ? F : layer->d, features = down ? layer->d : F;
-    const int64_t tiles = shared ? (T + t.tile_rows - 1) / t.tile_rows : max_tiles((int64_t)T * k, layer->E, t.tile_rows);
     *out = lexi_gemm_plan_t{};
     out->streams = shared ? p.shared_streams : down ? p.routed_streams : p.gateup_streams;
     out->tile_rows = t.tile_rows;
     out->ksplit = t.ksplit;
     out->direct = down && !shared && p.routed_direct;
     out->fused = down && !shared && p.routed_fused;
-    if (out->fused) out->waves = 16;
-    else if (out->streams) out->waves = layer->dtype == LEXI_BF16 ? stream_waves(K, features, tiles, chained != 0) : 4;
-    else out->waves = t.wide ? 8 : 4;
+    if (out->fused) {
+        out->waves = 16;
+    } else if (!out->streams) {
+        out->waves = t.wide ? 8 : 4;
+    } else {
+        // streaming workgroups: four waves beside a tiled GEMM in the same launch, else by the units of the launch
+        const bool bf = layer->dtype == LEXI_BF16, with_shared = layer->F_shared > 0;
+        const bool alone = shared && down && p.routed_fused;      // (the routed one is another kernel)
+        const bool routed_streams = down ? p.routed_streams : p.gateup_streams;
+        const int Ks = down ? layer->F_shared : layer->d, fs = down ? layer->d : layer->F_shared, fr = down ? layer->d : layer->F;
+        const TilePlan &tr = down ? p.routed : p.gateup, &ts = down ? p.shared : p.shared_gateup;
+        int64_t units = 0;
+        if (!alone) units += (int64_t)(fr / 16) * max_tiles((int64_t)T * k, layer->E, tr.tile_rows);
+        if (with_shared) units += (int64_t)(fs / 16) * ((T + ts.tile_rows - 1) / ts.tile_rows);
+        const int Kr = down ? layer->F : layer->d, Kmax = alone ? Ks : with_shared && Ks > Kr ? Ks : Kr;
+        const bool joined_tiles = with_shared && !alone && !(routed_streams && p.shared_streams) && !(shared ? tr.wide : ts.wide);
+        out->waves = !bf || joined_tiles ? 4 : stream_waves(Kmax, units, chained != 0);
+    }
     return LEXI_OK;
 }
 

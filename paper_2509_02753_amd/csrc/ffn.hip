@@ -35,17 +35,16 @@ namespace lexi {
 //           reduction cut in two halves handled by two workgroups that write two planes of `out` (more, shorter work
 //           items when a launch would otherwise leave most CUs idle in its last round; the consumer adds the planes);
 //           rows stored at out[scatter[row]] in the caller's dtype (layers with one active expert: no combine pass).
+//   MIXED: one of the launch's two jobs takes the weight-streaming schedule instead (a shared expert of up to 64 tokens beside
+//   routed GEMMs on tiles): its units of 16 features are workgroups of the same launch.
 //   Token rows are gathered through row_token (no permuted copy of X is ever materialised).
 //   Waves whose feature range lies past `features` (ragged last workgroup column) only help staging the tokens.
 // ---------------------------------------------------------------------------------------------------------
 template <int S> struct StageTag { static constexpr int value = S; };
 
-template <bool GATEUP, int NW, int WB, int TT>
+template <bool GATEUP, int NW, int WB, int TT, bool MIXED>
 __global__ void __launch_bounds__(NW * 64, WB == 2 ? 4 : 2)
-ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
-                const bf16_t* __restrict__ w1, int K, int features, int M, int tile_rows,
-                const int32_t* __restrict__ sched, void* __restrict__ out, int ksplit, size_t plane_stride,
-                const int32_t* __restrict__ scatter, int out_bf16) {
+ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
     constexpr int TB = TT / 16, KS = BK / 32;
     constexpr bool LOW = TT <= kLowTileRows;
     constexpr int WF = GATEUP ? 8 * WB : 16 * WB;    // output features of a wave
@@ -55,9 +54,24 @@ ffn_mfma_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_t
     __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS];
     auto lds_x = [&](int buf) { return lds + buf * (TT * LDS_LD); };
 
+    int block = blockIdx.x;
+    const FfnJob j = pick_job(routed, shared, block);
     TileInfo ti;
+    if (MIXED && j.streams) {
+        static_assert(!MIXED || (NW == 4 && sizeof(lds) >= sizeof(f32x4_t) * NW * 2 * 64), "stream_unit's part sums");
+        const int units = j.features >> 4, tile = block / units;
+        if (!fetch_tile<GATEUP ? 0 : 1>(j.sched, tile, j.M, j.tile_rows, ti)) return;
+        stream_unit<GATEUP, NW>(j, ti, block - tile * units, (f32x4_t(*)[2][64])lds);
+        return;
+    }
+    const int K = j.K, features = j.features;
+    const bf16_t *in = (const bf16_t*)j.in, *w0 = (const bf16_t*)j.w0, *w1 = (const bf16_t*)j.w1;
+    const int32_t *row_token = j.row_token, *scatter = GATEUP ? nullptr : j.scatter;
+    void* out = j.out;
+    const int ksplit = GATEUP ? 1 : j.ksplit, out_bf16 = j.out_bf16;
+    const size_t plane_stride = j.plane_stride;
     int cb, part;
-    if (!fetch_item<GATEUP ? 0 : 1>(sched, (features + CB - 1) / CB, M, tile_rows, GATEUP ? 1 : ksplit, ti, cb, part)) return;
+    if (!fetch_item<GATEUP ? 0 : 1>(block, j.sched, (features + CB - 1) / CB, j.M, j.tile_rows, ksplit, ti, cb, part)) return;
     // (wave-uniform, but their divisions run on the vector unit: back to scalar registers, the loop has no vector ones to spare)
     ti.row0 = __builtin_amdgcn_readfirstlane(ti.row0);
     ti.rows = __builtin_amdgcn_readfirstlane(ti.rows);
@@ -330,37 +344,53 @@ hipError_t launch_pack(const void* src, void* dst, int64_t n_mat, int R, int K, 
 }
 
 template <bool GATEUP>
-static hipError_t launch_ffn(const FfnArgs& a, hipStream_t s) {
-    if (a.max_tiles <= 0) return hipSuccess;
-    if ((a.ksplit > 1 || a.scatter != nullptr) && !(a.is_bf16 && !a.streaming && !GATEUP))
-        return hipErrorInvalidValue;   // split reduction and scattered rows exist on the bf16 tile schedule's DOWN only
-    if (a.streaming) return GATEUP ? launch_gateup_stream(a, s) : launch_down_stream(a, s);
-    // the tile kernel addresses its input rows with 32-bit byte offsets
-    const size_t in_rows = a.row_token ? (size_t)a.in_rows : (size_t)a.M;
-    if (in_rows * (size_t)a.K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
-    const int ksplit = GATEUP ? 1 : (a.ksplit > 1 ? a.ksplit : 1);
-    if (ksplit > 1 && (a.K / BK < ksplit || a.scatter != nullptr)) return hipErrorInvalidValue;
-    auto launch = [&](auto nw, auto wb, auto tt) {
-        constexpr int NW = decltype(nw)::value, WB = decltype(wb)::value, CB = NW * WB * (GATEUP ? 8 : 16);
-        const long long pieces = (long long)((a.features + CB - 1) / CB) * a.max_tiles * ksplit;
-        const dim3 grid((unsigned)((pieces + kXcds - 1) / kXcds * kXcds));
-        hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP, NW, WB, decltype(tt)::value>), grid, dim3(NW * 64), 0, s, (const bf16_t*)a.in,
-                           a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
-                           a.out, ksplit, a.plane_stride, GATEUP ? nullptr : a.scatter, a.out_bf16 ? 1 : 0);
-    };
-    if constexpr (GATEUP) {
-        if (a.tile_rows <= kLowTileRows) launch(StageTag<4>{}, StageTag<4>{}, StageTag<kLowTileRows>{});
-        else launch(StageTag<4>{}, StageTag<4>{}, StageTag<kTileRows>{});
-    } else {
-        if (a.wide) launch(StageTag<8>{}, StageTag<4>{}, StageTag<kTileRows>{});
-        else if (a.tile_rows <= kHalfTileRows) launch(StageTag<4>{}, StageTag<2>{}, StageTag<kHalfTileRows>{});
-        else if (a.tile_rows <= kLowTileRows) launch(StageTag<4>{}, StageTag<4>{}, StageTag<kLowTileRows>{});
-        else launch(StageTag<4>{}, StageTag<4>{}, StageTag<kTileRows>{});
+static hipError_t launch_ffn(const FfnArgs& a, const FfnArgs* shared, hipStream_t s) {
+    if (shared != nullptr && !ffn_joins(a, *shared)) {
+        const hipError_t err = launch_ffn<GATEUP>(*shared, nullptr, s);
+        return err != hipSuccess ? err : launch_ffn<GATEUP>(a, nullptr, s);
     }
+    for (const FfnArgs* f : {&a, shared}) {
+        if (f == nullptr) continue;
+        const bool tiles = f->is_bf16 && !f->streaming;
+        // split reduction and scattered rows exist on the bf16 tile schedule's DOWN only
+        if ((f->ksplit > 1 || f->scatter != nullptr) && (!tiles || GATEUP)) return hipErrorInvalidValue;
+        if (f->ksplit > 1 && (f->K / BK < f->ksplit || f->scatter != nullptr)) return hipErrorInvalidValue;
+        // the tile kernel addresses its input rows with 32-bit byte offsets
+        const size_t in_rows = f->row_token ? (size_t)f->in_rows : (size_t)f->M;
+        if (tiles && in_rows * (size_t)f->K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+    }
+    if (!a.is_bf16 || (a.streaming && (shared == nullptr || shared->streaming)))
+        return GATEUP ? launch_gateup_stream(a, shared, s) : launch_down_stream(a, shared, s);
+    const bool mixed = a.streaming || (shared != nullptr && shared->streaming);
+    auto launch = [&](auto nw, auto wb, auto tt, auto mix) {
+        constexpr int NW = decltype(nw)::value, WB = decltype(wb)::value, CB = NW * WB * (GATEUP ? 8 : 16);
+        constexpr bool MIXED = decltype(mix)::value != 0;
+        auto job = [&](const FfnArgs* f) {
+            if (f == nullptr) return FfnJob{};
+            const long long columns = f->streaming ? f->features / 16 : (long long)((f->features + CB - 1) / CB) * (f->ksplit > 1 ? f->ksplit : 1);
+            return make_job(*f, round_to_xcds(columns * f->max_tiles));
+        };
+        const FfnJob jr = job(&a), js = job(shared);
+        if (jr.blocks + js.blocks <= 0) return;
+        hipLaunchKernelGGL((ffn_mfma_kernel<GATEUP, NW, WB, decltype(tt)::value, MIXED>), dim3((unsigned)(jr.blocks + js.blocks)), dim3(NW * 64), 0, s, jr, js);
+    };
+    int rows = a.streaming ? 0 : a.tile_rows;            // the tallest tile of the launch
+    if (shared != nullptr && !shared->streaming && shared->tile_rows > rows) rows = shared->tile_rows;
+    auto with = [&](auto nw, auto wb, auto tt) {
+        if (mixed) launch(nw, wb, tt, StageTag<1>{});
+        else launch(nw, wb, tt, StageTag<0>{});
+    };
+    if constexpr (!GATEUP) {
+        if (a.wide) launch(StageTag<8>{}, StageTag<4>{}, StageTag<kTileRows>{}, StageTag<0>{});
+        else if (rows <= kHalfTileRows) with(StageTag<4>{}, StageTag<2>{}, StageTag<kHalfTileRows>{});
+    }
+    if (!GATEUP && (a.wide || rows <= kHalfTileRows)) return hipGetLastError();
+    if (rows <= kLowTileRows) with(StageTag<4>{}, StageTag<4>{}, StageTag<kLowTileRows>{});
+    else with(StageTag<4>{}, StageTag<4>{}, StageTag<kTileRows>{});
     return hipGetLastError();
 }
 
-hipError_t launch_gateup(const FfnArgs& a, hipStream_t s) { return launch_ffn<true>(a, s); }
-hipError_t launch_down(const FfnArgs& a, hipStream_t s) { return launch_ffn<false>(a, s); }
+hipError_t launch_gateup(const FfnArgs& a, const FfnArgs* shared, hipStream_t s) { return launch_ffn<true>(a, shared, s); }
+hipError_t launch_down(const FfnArgs& a, const FfnArgs* shared, hipStream_t s) { return launch_ffn<false>(a, shared, s); }
 
 }  // namespace lexi

@@ -21,6 +21,51 @@ struct TileInfo {
     int expert, row0, rows;
 };
 
+// One grouped GEMM as the kernels see it (FfnArgs).  A launch takes two: the routed experts' and, in the blocks before it, the
+// shared expert's.
+struct FfnJob {
+    const void* in;
+    const int32_t* row_token;
+    const void *w0, *w1;
+    const int32_t *sched, *scatter;
+    void* out;
+    size_t plane_stride;
+    int K, features, M, tile_rows, ksplit, out_bf16;
+    int streams;              // taken by the weight-streaming schedule, blocks ordered (tile, unit of 16 features)
+    int blocks;               // workgroups of this job, a multiple of kXcds where a second job follows
+};
+inline FfnJob make_job(const FfnArgs& a, int blocks) {
+    return FfnJob{a.in, a.row_token, a.w0, a.w1, a.sched, a.scatter, a.out, a.plane_stride, a.K, a.features, a.M, a.tile_rows,
+                  a.ksplit > 1 ? a.ksplit : 1, a.out_bf16 ? 1 : 0, a.streaming ? 1 : 0, blocks};
+}
+// (by value: a conditional expression on two members would select between their addresses)
+template <typename T>
+__device__ __forceinline__ T choose(bool c, T a, T b) { return c ? a : b; }
+// The job block `block` belongs to (wave-uniform); `block` is then counted from the job's first.
+__device__ __forceinline__ FfnJob pick_job(const FfnJob& routed, const FfnJob& shared, int& block) {
+    const bool first = block < shared.blocks;
+    if (!first) block -= shared.blocks;
+    FfnJob j;
+    j.in = choose(first, shared.in, routed.in);
+    j.row_token = choose(first, shared.row_token, routed.row_token);
+    j.w0 = choose(first, shared.w0, routed.w0);
+    j.w1 = choose(first, shared.w1, routed.w1);
+    j.sched = choose(first, shared.sched, routed.sched);
+    j.scatter = choose(first, shared.scatter, routed.scatter);
+    j.out = choose(first, shared.out, routed.out);
+    j.plane_stride = choose(first, shared.plane_stride, routed.plane_stride);
+    j.K = choose(first, shared.K, routed.K);
+    j.features = choose(first, shared.features, routed.features);
+    j.M = choose(first, shared.M, routed.M);
+    j.tile_rows = choose(first, shared.tile_rows, routed.tile_rows);
+    j.ksplit = choose(first, shared.ksplit, routed.ksplit);
+    j.out_bf16 = choose(first, shared.out_bf16, routed.out_bf16);
+    j.streams = choose(first, shared.streams, routed.streams);
+    j.blocks = choose(first, shared.blocks, routed.blocks);
+    return j;
+}
+inline int round_to_xcds(long long blocks) { return (int)((blocks + kXcds - 1) / kXcds * kXcds); }
+
 // Tile t of the n = ceil(rows / tile height) tiles of a group: the group's 16-row blocks are dealt out evenly (heights
 // differ by one block at most), so no tile is a short remainder that streams a whole weight slab for a few rows.
 __device__ __forceinline__ void even_tile(int group_row0, int group_rows, int t, int n, TileInfo& ti) {
@@ -76,14 +121,14 @@ __device__ __forceinline__ bool fetch_tile(const int32_t* sched, int tile, int M
 // which favour sharing the much smaller token tile).  The item list is cut into 8 contiguous parts of equal length, XCD x
 // takes the x-th.  (Parts of equal estimated cost measured up to 60 % slower: a part only slightly longer than the average
 // needs a whole further round of its XCD's workgroup slots.)
-// The grid is 1-D: 8 * ceil(ncb * max_tiles / 8) workgroups, times ksplit.
+// The grid is 1-D: 8 * ceil(ncb * max_tiles / 8) workgroups, times ksplit; `block` is the workgroup's number in its job.
 constexpr int kCbGroup = 2;
 
 // With ksplit > 1 every item appears ksplit times in a row, once per part of the reduction dimension.
 template <int G>
-__device__ __forceinline__ bool fetch_item(const int32_t* sched, int ncb, int M, int tile_rows, int ksplit, TileInfo& ti, int& cb,
-                                           int& part) {
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+__device__ __forceinline__ bool fetch_item(int block, const int32_t* sched, int ncb, int M, int tile_rows, int ksplit, TileInfo& ti,
+                                           int& cb, int& part) {
+    const int xcd = block % kXcds, slot = block / kXcds;
     const int ntiles = sched != nullptr ? sched[kSchedTiles + 64 * G + 63] : (M + tile_rows - 1) / tile_rows;
     const int total = ntiles * ncb * ksplit;
     const int per = (total + kXcds - 1) / kXcds;
@@ -105,7 +150,101 @@ __device__ __forceinline__ bool fetch_item(const int32_t* sched, int ncb, int M,
     return true;
 }
 
-hipError_t launch_gateup_stream(const FfnArgs& a, hipStream_t s);
-hipError_t launch_down_stream(const FfnArgs& a, hipStream_t s);
+// Weight-streaming schedule: one unit of 16 output features of one token tile, by a workgroup of NW waves; red is LDS.
+template <int N> struct IntTag { static constexpr int value = N; };
+
+template <bool GATEUP, int NW>
+__device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64]) {
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int K = j.K, features = j.features, nkb = K >> 5;
+    const bf16_t* in = (const bf16_t*)j.in;
+    const int32_t* row_token = j.row_token;
+    void* out = j.out;
+    TileInfo ti = tile;
+    const int kb0 = wave * nkb / NW, kb1 = (wave + 1) * nkb / NW;
+    const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
+    const bf16_t* a0 = (const bf16_t*)j.w0 + wbase;
+    const bf16_t* a1 = GATEUP ? (const bf16_t*)j.w1 + wbase : nullptr;
+
+    auto body = [&](auto ntb_tag) {
+        constexpr int NTB = decltype(ntb_tag)::value;
+        const bf16_t* xp[NTB];
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
+            const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
+            xp[tb] = in + (size_t)src_row * K + kq * 8;
+        }
+        f32x4_t accg[NTB], accu[NTB];
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            accg[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            accu[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+        auto k_step = [&](int kb) {
+            const bf16x8_t ag = *(const bf16x8_t*)(a0 + (size_t)kb * 512);
+            bf16x8_t au;
+            if (GATEUP) au = *(const bf16x8_t*)(a1 + (size_t)kb * 512);
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) {
+                const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
+                accg[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, b, accg[tb], 0, 0, 0);
+                if (GATEUP) accu[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, b, accu[tb], 0, 0, 0);
+            }
+        };
+        constexpr int UNROLL = NTB <= 2 ? 8 : 4;  // K blocks whose loads are in flight together
+        int kb = kb0;
+        for (; kb + UNROLL <= kb1; kb += UNROLL) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) k_step(kb + u);
+        }
+        for (; kb < kb1; ++kb) k_step(kb);
+        // split-K reduction in wave order, one token block at a time; wave (tb % waves) finishes block tb
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            red[wave][0][lane] = accg[tb];
+            if (GATEUP) red[wave][1][lane] = accu[tb];
+            __syncthreads();
+            if (wave == tb % NW) {
+                f32x4_t g = red[0][0][lane], u = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int w = 1; w < NW; ++w) g += red[w][0][lane];
+                if (GATEUP) {
+                    u = red[0][1][lane];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) u += red[w][1][lane];
+                }
+                const int r = tb * 16 + l16;  // lane owns token (lane % 16), features 4*(lane/16) + 0..3 of the unit
+                if (r < ti.rows) {
+                    const size_t row = (size_t)(ti.row0 + r);
+                    if (GATEUP) {
+                        u32x2_t pk;
+                        pk[0] = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
+                        pk[1] = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
+                        *(u32x2_t*)((bf16_t*)out + row * features + unit * 16 + kq * 4) = pk;
+                    } else {
+                        *(f32x4_t*)((float*)out + row * features + unit * 16 + kq * 4) = g;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    };
+    // 128 rows at a time (a tile may be taller; the second pass over the weights is then served by the cache)
+    const int row_end = ti.row0 + ti.rows;
+    for (; ti.row0 < row_end; ti.row0 += 128) {
+        ti.rows = min(128, row_end - ti.row0);
+        const int ntb = (ti.rows + 15) >> 4;
+        if (ntb <= 1) body(IntTag<1>{});
+        else if (ntb <= 2) body(IntTag<2>{});
+        else if (ntb <= 4) body(IntTag<4>{});
+        else body(IntTag<8>{});
+    }
+}
+
+hipError_t launch_gateup_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
+hipError_t launch_down_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
 
 }  // namespace lexi

@@ -7,106 +7,22 @@
 // token blocks (16 tokens x 32 K, read straight from the token rows, which stay cache-resident) with
 // v_mfma_f32_16x16x32_bf16.  The partial accumulators are added in wave order through LDS (fixed order: same
 // bits every run), then the epilogue of the tile schedule's kernel applies: silu(gate)*up -> bf16, or fp32 rows.
+// (stream_unit in ffn_common.hpp: the tile kernel's launches take such units too.)
 #include "ffn_common.hpp"
 
 namespace lexi {
 
-template <int N> struct IntTag { static constexpr int value = N; };
-
 template <bool GATEUP, int NW>
 __global__ void __launch_bounds__(NW * 64)
-ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row_token, const bf16_t* __restrict__ w0,
-                  const bf16_t* __restrict__ w1, int K, int features, int M, int tile_rows,
-                  const int32_t* __restrict__ sched, void* __restrict__ out) {
+ffn_stream_kernel(FfnJob routed, FfnJob shared) {
     __shared__ __attribute__((aligned(16))) f32x4_t red[NW][2][64];
-
+    int block = blockIdx.x;
+    const FfnJob j = pick_job(routed, shared, block);
+    const int units = j.features >> 4;
+    const int tile = block / units;
     TileInfo ti;
-    if (!fetch_tile<GATEUP ? 0 : 1>(sched, blockIdx.y, M, tile_rows, ti)) return;
-
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int l16 = lane & 15, kq = lane >> 4;
-    const int unit = blockIdx.x;  // output features 16*unit .. 16*unit+15
-    const int nkb = K >> 5;
-    const int kb0 = wave * nkb / NW, kb1 = (wave + 1) * nkb / NW;
-    const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
-    const bf16_t* a0 = w0 + wbase;
-    const bf16_t* a1 = GATEUP ? w1 + wbase : nullptr;
-
-    auto body = [&](auto ntb_tag) {
-        constexpr int NTB = decltype(ntb_tag)::value;
-        const bf16_t* xp[NTB];
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-            const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
-            const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
-            xp[tb] = in + (size_t)src_row * K + kq * 8;
-        }
-        f32x4_t accg[NTB], accu[NTB];
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-            accg[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            accu[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        auto k_step = [&](int kb) {
-            const bf16x8_t ag = *(const bf16x8_t*)(a0 + (size_t)kb * 512);
-            bf16x8_t au;
-            if (GATEUP) au = *(const bf16x8_t*)(a1 + (size_t)kb * 512);
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) {
-                const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
-                accg[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, b, accg[tb], 0, 0, 0);
-                if (GATEUP) accu[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, b, accu[tb], 0, 0, 0);
-            }
-        };
-        constexpr int UNROLL = NTB <= 2 ? 8 : 4;  // K blocks whose loads are in flight together
-        int kb = kb0;
-        for (; kb + UNROLL <= kb1; kb += UNROLL) {
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) k_step(kb + u);
-        }
-        for (; kb < kb1; ++kb) k_step(kb);
-        // split-K reduction in wave order, one token block at a time; wave (tb % waves) finishes block tb
-#pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-            red[wave][0][lane] = accg[tb];
-            if (GATEUP) red[wave][1][lane] = accu[tb];
-            __syncthreads();
-            if (wave == tb % NW) {
-                f32x4_t g = red[0][0][lane], u = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                for (int w = 1; w < NW; ++w) g += red[w][0][lane];
-                if (GATEUP) {
-                    u = red[0][1][lane];
-#pragma unroll
-                    for (int w = 1; w < NW; ++w) u += red[w][1][lane];
-                }
-                const int r = tb * 16 + l16;  // lane owns token (lane % 16), features 4*(lane/16) + 0..3 of the unit
-                if (r < ti.rows) {
-                    const size_t row = (size_t)(ti.row0 + r);
-                    if (GATEUP) {
-                        u32x2_t pk;
-                        pk[0] = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
-                        pk[1] = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
-                        *(u32x2_t*)((bf16_t*)out + row * features + unit * 16 + kq * 4) = pk;
-                    } else {
-                        *(f32x4_t*)((float*)out + row * features + unit * 16 + kq * 4) = g;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    };
-    // 128 rows at a time (a tile may be taller; the second pass over the weights is then served by the cache)
-    const int row_end = ti.row0 + ti.rows;
-    for (; ti.row0 < row_end; ti.row0 += 128) {
-        ti.rows = min(128, row_end - ti.row0);
-        const int ntb = (ti.rows + 15) >> 4;
-        if (ntb <= 1) body(IntTag<1>{});
-        else if (ntb <= 2) body(IntTag<2>{});
-        else if (ntb <= 4) body(IntTag<4>{});
-        else body(IntTag<8>{});
-    }
+    if (!fetch_tile<GATEUP ? 0 : 1>(j.sched, tile, j.M, j.tile_rows, ti)) return;
+    stream_unit<GATEUP, NW>(j, ti, block - tile * units, red);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -120,16 +36,21 @@ ffn_stream_kernel(const bf16_t* __restrict__ in, const int32_t* __restrict__ row
 // ---------------------------------------------------------------------------------------------------------
 template <bool GATEUP>
 __global__ void __launch_bounds__(256)
-ffn_f32_kernel(const float* __restrict__ in, const int32_t* __restrict__ row_token, const float* __restrict__ w0,
-               const float* __restrict__ w1, int K, int features, int M, int tile_rows, const int32_t* __restrict__ sched,
-               float* __restrict__ out) {
+ffn_f32_kernel(FfnJob routed, FfnJob shared) {
+    int block = blockIdx.x;
+    const FfnJob j = pick_job(routed, shared, block);
+    const int K = j.K, features = j.features;
+    const int column = block % (features >> 6);          // 64 features each
     TileInfo ti;
-    if (!fetch_tile<GATEUP ? 0 : 1>(sched, blockIdx.y, M, tile_rows, ti)) return;
+    if (!fetch_tile<GATEUP ? 0 : 1>(j.sched, block / (features >> 6), j.M, j.tile_rows, ti)) return;
+    const float *in = (const float*)j.in, *w0 = (const float*)j.w0, *w1 = (const float*)j.w1;
+    const int32_t* row_token = j.row_token;
+    float* out = (float*)j.out;
     constexpr int NM = GATEUP ? 2 : 1;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // packed weights: a lane's feature is row lane % 16 of 16-row slab lane / 16; its 32 elements of a K block are four runs
     // of 8, 128 floats apart
-    const size_t slab = (size_t)ti.expert * (features >> 4) + blockIdx.x * 4 + (lane >> 4);
+    const size_t slab = (size_t)ti.expert * (features >> 4) + column * 4 + (lane >> 4);
     const float* wp[2] = {w0 + slab * ((size_t)K * 16) + (lane & 15) * 8, GATEUP ? w1 + slab * ((size_t)K * 16) + (lane & 15) * 8 : nullptr};
     struct Block { f32x4_t v[NM][4][2]; };
     auto fetch_w = [&](Block& b, int kb) {
@@ -171,27 +92,29 @@ ffn_f32_kernel(const float* __restrict__ in, const int32_t* __restrict__ row_tok
             if (r0 + i < ti.rows) {
                 float v = acc[0][i];
                 if (GATEUP) v = silu(v) * acc[NM - 1][i];
-                out[(size_t)(ti.row0 + r0 + i) * features + blockIdx.x * 64 + lane] = v;
+                out[(size_t)(ti.row0 + r0 + i) * features + column * 64 + lane] = v;
             }
         }
     }
 }
 
 template <bool GATEUP>
-static hipError_t launch_stream(const FfnArgs& a, hipStream_t s) {
-    if (a.max_tiles <= 0) return hipSuccess;
-    auto launch = [&](auto nw) {
-        constexpr int NW = decltype(nw)::value;
-        hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, NW>), dim3(a.features / 16, a.max_tiles), dim3(NW * 64), 0, s,
-                           (const bf16_t*)a.in, a.row_token, (const bf16_t*)a.w0, (const bf16_t*)a.w1, a.K, a.features, a.M,
-                           a.tile_rows, a.sched, a.out);
+static hipError_t launch_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s) {
+    const int width = a.is_bf16 ? 16 : 64;               // output features of a workgroup
+    auto job = [&](const FfnArgs* f) {
+        return f ? make_job(*f, round_to_xcds((long long)(f->features / width) * f->max_tiles)) : FfnJob{};
     };
-    if (a.is_bf16 && stream_waves(a.K, a.features, a.max_tiles, a.chained) == 8) launch(IntTag<8>{});
-    else if (a.is_bf16) launch(IntTag<4>{});
-    else
-        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, dim3(a.features / 64, a.max_tiles), dim3(256), 0, s, (const float*)a.in,
-                           a.row_token, (const float*)a.w0, (const float*)a.w1, a.K, a.features, a.M, a.tile_rows, a.sched,
-                           (float*)a.out);
+    const FfnJob jr = job(&a), js = job(shared);
+    if (jr.blocks + js.blocks <= 0) return hipSuccess;
+    const dim3 grid((unsigned)(jr.blocks + js.blocks));
+    if (!a.is_bf16) {
+        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, grid, dim3(256), 0, s, jr, js);
+    } else {
+        const int64_t units = (int64_t)(a.features / 16) * a.max_tiles + (shared ? (int64_t)(shared->features / 16) * shared->max_tiles : 0);
+        const int K = shared && shared->K > a.K ? shared->K : a.K;
+        if (stream_waves(K, units, a.chained) == 8) hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, 8>), grid, dim3(512), 0, s, jr, js);
+        else hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, 4>), grid, dim3(256), 0, s, jr, js);
+    }
     return hipGetLastError();
 }
 
@@ -328,7 +251,7 @@ hipError_t launch_down_combine(const DownCombineArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_gateup_stream(const FfnArgs& a, hipStream_t s) { return launch_stream<true>(a, s); }
-hipError_t launch_down_stream(const FfnArgs& a, hipStream_t s) { return launch_stream<false>(a, s); }
+hipError_t launch_gateup_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s) { return launch_stream<true>(a, shared, s); }
+hipError_t launch_down_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s) { return launch_stream<false>(a, shared, s); }
 
 }  // namespace lexi

@@ -83,12 +83,20 @@ struct FfnArgs {
 // 11.0 -> 10.1 us; 32 tokens, down (K 14336) 170 -> 164 us; but 16 tokens, 64 experts: 47 -> 52 us.
 // In the chained stack always four: which side of a bf16 rounding a block's input falls on may send a token to another
 // expert further down, so the order of a sum there must not depend on the batch the token is in.
-inline int stream_waves(int K, int features, int64_t max_tiles, bool chained) {
-    return !chained && ((features / 16) * max_tiles <= 256 || K >= 8192) ? 8 : 4;
-}
+inline int stream_waves(int K, int64_t units, bool chained) { return !chained && (units <= 256 || K >= 8192) ? 8 : 4; }
 
-hipError_t launch_gateup(const FfnArgs& a, hipStream_t s);
-hipError_t launch_down(const FfnArgs& a, hipStream_t s);
+// `shared`: null, or the same GEMM of the layer's shared expert (dense, no scatter).  It goes into the routed one's launch, in front of
+// it, where both take the same kind of workgroup (ffn_joins); otherwise it gets a launch of its own.  One launch instead of two: a
+// launch costs 4 to 5 us, a second stream 5 to 6 us at its fork and 6 to 10 at its join, and the two fill the last round together.
+// Whole calls, us: one token, 8 layers 375 -> 349; 16 tokens, 8 chained layers 726 -> 630; 64 tokens, 6 layers, shared width 5632
+// 1293 -> 1282; 256 tokens 1301 -> 1205; 777 tokens, d 1280 852 -> 852; 8192 tokens, 2 layers 1965 -> 1902 (two streams up to 1024
+// tokens, one after the other above, each time on the left).
+inline bool ffn_joins(const FfnArgs& a, const FfnArgs& shared) {
+    if (!a.is_bf16 || (a.streaming && shared.streaming)) return true;
+    return a.streaming ? !shared.wide : shared.streaming ? !a.wide : a.wide == shared.wide;
+}
+hipError_t launch_gateup(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
+hipError_t launch_down(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
 
 // row-major [n_mat][R][K] -> packed expert-weight layout (R % 16 == 0, K % 32 == 0)
 hipError_t launch_pack(const void* src, void* dst, int64_t n_mat, int R, int K, bool is_bf16, hipStream_t s);
