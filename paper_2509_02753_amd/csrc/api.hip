@@ -293,7 +293,7 @@ struct LayerPlan {
     TilePlan gateup, shared_gateup;        // gate/up GEMMs on the tile schedule
     TilePlan routed, shared;               // down GEMMs on the tile schedule
     bool routed_direct;                    // with k == 1 and nothing to add: rows stored straight into y
-    bool routed_fused;                     // a handful of tokens: down projection and combine in one launch
+    bool routed_fused;                     // a handful of tokens: down projections and combine in one launch
 };
 LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_split, bool allow_direct) {
     LayerPlan p{};
@@ -382,8 +382,7 @@ lexi_status run_experts(const lexi_layer_t& ly, const void* x, int32_t T, int32_
     sd.plane_stride = (size_t)T * ly.d;
     w.direct = plan.routed_direct;
     w.fused = plan.routed_fused;
-    if (plan.routed_fused)   // run_layer launches down + combine; it consumes the shared expert's rows
-        return with_shared && launch_down(sd, nullptr, s) != hipSuccess ? LEXI_ERR_LAUNCH : LEXI_OK;
+    if (plan.routed_fused) return LEXI_OK;   // run_layer launches down (routed and shared) + combine
     if (plan.routed_direct) {
         dn.out = direct_y; dn.scatter = w.row_token; dn.out_bf16 = direct_bf16;
     }
@@ -432,12 +431,13 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         if (st != LEXI_OK) return st;
     }
     if (w.fused) {
-        // (the launch holds the routed down projection and the combine: 4 = shared expert done comes before 3 and 5)
+        // (one launch for both down projections and the combine: 4 = shared expert done is recorded before it, 3 and 5 after it)
         if (ly.F_shared > 0) mark(4);
         DownCombineArgs f{};
         f.act = w.act; f.w_down = ly.w_down; f.F = ly.F; f.d = ly.d; f.T = T; f.k = k; f.sched = w.sched;
         f.inv_perm = w.inv_perm; f.gates = w.gates;
-        f.y_shared = ly.F_shared > 0 ? w.y_shared : nullptr; f.y = y; f.y_bf16 = y_dtype == LEXI_BF16;
+        if (ly.F_shared > 0) { f.act_shared = w.act_shared; f.ws_down = ly.ws_down; f.F_shared = ly.F_shared; }
+        f.y = y; f.y_bf16 = y_dtype == LEXI_BF16;
         if (launch_down_combine(f, s) != hipSuccess) return LEXI_ERR_LAUNCH;
         mark(3);
         if (ly.F_shared == 0) mark(4);
@@ -660,22 +660,20 @@ lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, 
     out->ksplit = t.ksplit;
     out->direct = down && !shared && p.routed_direct;
     out->fused = down && !shared && p.routed_fused;
-    if (out->fused) {
+    if (down && p.routed_fused) {
         out->waves = 16;
     } else if (!out->streams) {
         out->waves = t.wide ? 8 : 4;
     } else {
         // streaming workgroups: four waves beside a tiled GEMM in the same launch, else by the units of the launch
         const bool bf = layer->dtype == LEXI_BF16, with_shared = layer->F_shared > 0;
-        const bool alone = shared && down && p.routed_fused;      // (the routed one is another kernel)
         const bool routed_streams = down ? p.routed_streams : p.gateup_streams;
         const int Ks = down ? layer->F_shared : layer->d, fs = down ? layer->d : layer->F_shared, fr = down ? layer->d : layer->F;
         const TilePlan &tr = down ? p.routed : p.gateup, &ts = down ? p.shared : p.shared_gateup;
-        int64_t units = 0;
-        if (!alone) units += (int64_t)(fr / 16) * max_tiles((int64_t)T * k, layer->E, tr.tile_rows);
+        int64_t units = (int64_t)(fr / 16) * max_tiles((int64_t)T * k, layer->E, tr.tile_rows);
         if (with_shared) units += (int64_t)(fs / 16) * ((T + ts.tile_rows - 1) / ts.tile_rows);
-        const int Kr = down ? layer->F : layer->d, Kmax = alone ? Ks : with_shared && Ks > Kr ? Ks : Kr;
-        const bool joined_tiles = with_shared && !alone && !(routed_streams && p.shared_streams) && !(shared ? tr.wide : ts.wide);
+        const int Kr = down ? layer->F : layer->d, Kmax = with_shared && Ks > Kr ? Ks : Kr;
+        const bool joined_tiles = with_shared && !(routed_streams && p.shared_streams) && !(shared ? tr.wide : ts.wide);
         out->waves = !bf || joined_tiles ? 4 : stream_waves(Kmax, units, chained != 0);
     }
     return LEXI_OK;

@@ -121,113 +121,177 @@ static hipError_t launch_stream(const FfnArgs& a, const FfnArgs* shared, hipStre
 // ---------------------------------------------------------------------------------------------------------
 // down_combine_kernel: for a handful of tokens the down projection's output rows (T*k x d fp32) are so small that
 // writing them out and launching a second kernel to weight and add them costs more than the projection itself.  Here
-// a workgroup of 16 waves owns 16 output features of ALL rows: it walks the experts that have rows (one tile each:
-// an expert holds at most T <= 8 rows), several at a time -- the waves are dealt out as (experts per pass) x (parts
-// of the reduction), the fewer experts the finer the split -- adds the parts in order through LDS, keeps the rows'
-// 16 features in an LDS table, and finally forms y[t] = sum_s g[t][s] * row(t, s) in slot order, plus the shared
-// expert's row, exactly as the combine kernel does.  Fixed orders throughout: same bits on every run.
+// a workgroup owns 8 output features of ALL rows, the shared expert's included: the experts that have rows (one
+// tile each: an expert holds at most T <= 8 rows) and the shared expert lie one after the other in ONE list of reduction steps,
+// which is dealt out evenly over the waves, whatever the number of experts.  A wave adds up each expert's part of its share and
+// leaves it in LDS; the parts are added in list order, then y[t] = sum_s g[t][s] * row(t, s) in slot order, plus the
+// shared expert's row, exactly as the combine kernel does.  Fixed orders throughout: same bits on every run.
+// Eight features and eight rows fill a quarter of a 16 x 16 MFMA, so one instruction takes two K blocks at once: rows 0..7 of A
+// and columns 0..7 of B hold the even block, 8..15 the odd one (the two other quarters are not used).  That makes d / 8
+// workgroups: every CU of the chip streams at d = 2048, where 16 features each left half of them idle, and with 22 loads in
+// flight a wave's share is one or two round trips.  Wider layers fill the chip with 16 features each, whose blocks are read whole.
+// Whole calls of 8 layers against 16 features each, passes over the experts and the shared expert's down GEMM in a launch of its
+// own (us): one token, d 2048, F 1408, shared 2816, k 2 to 6 349 -> 306; k = 8, F 1024, no shared expert 303 -> 282; 8 tokens, k = 6,
+// shared 784 -> 643; 8 tokens, k = 8 1044 -> 916; one expert for one token 144 -> 146; d 4096, F 14336, k = 2 1135 -> 1143.
 // ---------------------------------------------------------------------------------------------------------
-template <bool Y_BF16>
-__global__ void __launch_bounds__(1024)
+// HALF: 8 features and steps of 64 elements, else 16 features and steps of 32.
+template <bool Y_BF16, bool HALF>
+__global__ void __launch_bounds__(HALF ? 512 : 1024)
 down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w_down, int K, int d,
                     const int32_t* __restrict__ sched, const int32_t* __restrict__ inv_perm,
-                    const float* __restrict__ gates, const float* __restrict__ y_shared, int T, int k, void* __restrict__ y) {
-    __shared__ __attribute__((aligned(16))) f32x4_t red[16][64];
-    __shared__ __attribute__((aligned(16))) f32x4_t ys[kFusedDownMaxRows][4];   // row -> the unit's 16 features
+                    const float* __restrict__ gates, const bf16_t* __restrict__ act_shared, const bf16_t* __restrict__ ws_down,
+                    int K_shared, int T, int k, void* __restrict__ y) {
+    constexpr int NW = HALF ? 8 : 16, UMAX = HALF ? 22 : 11;     // waves; steps in flight per wave
+    constexpr int SK = HALF ? 64 : 32, NQ = HALF ? 2 : 4;        // elements of a step; quads of features
+    // the parts of (wave, expert), at wave + the expert's place in the list; by (K block parity,) quad of features and row
+    __shared__ __attribute__((aligned(16))) f32x4_t red[NW + kFusedDownMaxRows][4][8];
+    __shared__ __attribute__((aligned(16))) f32x4_t ys[kFusedDownMaxRows + kFusedDownMaxT][NQ];   // row -> the features
+    __shared__ int32_t s_row0[kFusedDownMaxRows], s_rows[kFusedDownMaxRows], s_perm[kFusedDownMaxRows];
+    __shared__ float s_gate[kFusedDownMaxRows];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, kq = lane >> 4;
-    const int unit = blockIdx.x;   // output features 16*unit .. 16*unit+15
-    const int nkb = K >> 5;
+    const int kq = lane >> 4, l8 = lane & 7, par = (lane >> 3) & 1;
+    // (the two halves of a unit of 16 features go to the same XCD)
+    const int half = HALF ? (blockIdx.x / kXcds) & 1 : 0;
+    const int unit = HALF ? blockIdx.x / (2 * kXcds) * kXcds + blockIdx.x % kXcds : blockIdx.x;
+    const int f0 = unit * 16 + half * 8;
     // an expert with rows has one tile
     const int e_off = sched[kSchedOff + lane], e_cnt = sched[kSchedCount + lane];
     const int e_end = sched[kSchedTiles + 64 + lane];
     const int ntiles = __builtin_amdgcn_readlane(e_end, 63);
-    // combine: thread (t, q) owns features 16*unit + 4*q + 0..3 of token t; what it adds at the end that does not
-    // depend on the projection is fetched now, under the weight stream
-    const bool combiner = tid < T * 4;
-    const int ct = tid >> 2, cq = tid & 3;
-    const size_t cidx = (size_t)ct * d + unit * 16 + cq * 4;
-    f32x4_t shared_row = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (combiner && y_shared != nullptr) shared_row = *(const f32x4_t*)(y_shared + cidx);
-    constexpr int KPRE = 8;        // slots whose row index and gate are fetched ahead
-    int32_t pre_row[KPRE];
-    float pre_gate[KPRE];
-#pragma unroll
-    for (int s = 0; s < KPRE; ++s) {
-        const bool have = combiner && s < k;
-        pre_row[s] = have ? inv_perm[(size_t)ct * k + s] : 0;
-        pre_gate[s] = have ? gates[(size_t)ct * k + s] : 0.0f;
+    if (wave == 0 && e_cnt > 0) {
+        s_row0[e_end - 1] = e_off;
+        s_rows[e_end - 1] = e_cnt;
     }
-    // waves per expert: 16 for one expert, ..., 1 for nine or more (then 16 experts per pass)
-    const int wpt = ntiles >= 9 ? 1 : ntiles >= 5 ? 2 : ntiles >= 3 ? 4 : ntiles == 2 ? 8 : 16;
-    const int per_pass = 16 / wpt;
-    const int sub = wave / wpt, kpart = wave - sub * wpt;
-
-    for (int t0 = 0; t0 < ntiles; t0 += per_pass) {
-        const int tile = t0 + sub;
-        const bool live = tile < ntiles;   // wave-uniform
-        int row0 = 0, rows = 0;
-        f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (live) {
-            const int expert = __builtin_amdgcn_readfirstlane(__popcll(__ballot(e_end <= tile)));
-            row0 = __builtin_amdgcn_readlane(e_off, expert);
-            rows = min(__builtin_amdgcn_readlane(e_cnt, expert), 16);
-            const int kb0 = kpart * nkb / wpt, kb1 = (kpart + 1) * nkb / wpt;
-            const bf16_t* a0 = w_down + ((size_t)expert * (d >> 4) + unit) * ((size_t)K * 16) + lane * 8;
-            // rows past the expert's end re-read its last row; their results are never used
-            const bf16_t* xp = act + (size_t)(row0 + min(l16, rows - 1)) * K + kq * 8;
-            auto k_step = [&](int kb) {
-                const bf16x8_t ag = *(const bf16x8_t*)(a0 + (size_t)kb * 512);
-                const bf16x8_t b = *(const bf16x8_t*)(xp + kb * 32);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, b, acc, 0, 0, 0);
-            };
-            constexpr int UNROLL = 11;   // K blocks whose loads are in flight together
-            int kb = kb0;
-            for (; kb + UNROLL <= kb1; kb += UNROLL) {
-#pragma unroll
-                for (int u = 0; u < UNROLL; ++u) k_step(kb + u);
-            }
-            for (; kb + 4 <= kb1; kb += 4) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) k_step(kb + u);
-            }
-            for (; kb < kb1; ++kb) k_step(kb);
-        }
-        red[wave][lane] = acc;
-        __syncthreads();
-        if (live && kpart == 0) {
-            f32x4_t g = red[wave][lane];
-            for (int p = 1; p < wpt; ++p) g += red[wave + p][lane];
-            if (l16 < rows) ys[row0 + l16][kq] = g;   // lane owns row (lane % 16), features 4*(lane/16) + 0..3
-        }
-        __syncthreads();
+    if (wave == 1 && lane < T * k) {                             // (at most 64 assignments)
+        s_perm[lane] = inv_perm[lane];
+        s_gate[lane] = gates[lane];
     }
+    // the list: ntiles experts of `nd` steps, then the shared expert's `ns`
+    const int nd = K / SK, ns = act_shared != nullptr ? K_shared / SK : 0;
+    const int ntot = ntiles + (ns > 0 ? 1 : 0);
+    const int total = ntiles * nd + ns;
+    const int lo = wave * total / NW, hi = (wave + 1) * total / NW;   // this wave's share
+    // where a lane reads in a step: in the block (two blocks) of 16 rows x 32 K of the weights, in the elements of a row
+    const uint32_t a_lane = HALF ? par * 1024 + kq * 256 + (half * 8 + l8) * 16 : lane * 16;
+    const uint32_t b_lane = HALF ? par * 64 + kq * 16 : kq * 16;
 
-    if (!combiner) return;
+    int tile = min(lo / nd, ntiles), r = lo - tile * nd;         // (wave-uniform) where the wave is: expert and its step
+    struct Part {                                                // what is left of an expert in this wave's share
+        const char *a, *b;
+        uint32_t b_off;
+        int n, at;                                               // steps, place in the list
+    };
+    auto part = [&](int left) {
+        Part p;
+        const bool routed = tile < ntiles;
+        const int expert = __builtin_amdgcn_readfirstlane(__popcll(__ballot(e_end <= tile))) & 63;   // (64 past the last tile)
+        const int row0 = routed ? __builtin_amdgcn_readlane(e_off, expert) : 0;
+        const int rows = routed ? __builtin_amdgcn_readlane(e_cnt, expert) : T;
+        const int Kt = routed ? K : K_shared;
+        const char* w = routed ? (const char*)w_down + (size_t)expert * d * ((size_t)K * 2) : (const char*)ws_down;
+        p.a = w + (size_t)unit * ((size_t)Kt * 32) + (size_t)r * (SK * 32);
+        p.b = (routed ? (const char*)act : (const char*)act_shared) + (size_t)r * (SK * 2);
+        // (rows past the expert's end re-read its last row; their results are never used)
+        p.b_off = (uint32_t)(row0 + min(l8, rows - 1)) * (uint32_t)(Kt * 2) + b_lane;
+        p.n = min((routed ? nd : ns) - r, left);
+        p.at = tile;
+        return p;
+    };
+    auto advance = [&](int n) {                                  // past n steps of the present expert
+        r += n;
+        if (r == (tile < ntiles ? nd : ns)) {
+            r = 0;
+            ++tile;
+        }
+    };
+    f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    auto flush = [&](int at) {                                   // this wave's part of the expert at place `at` is complete
+        // (HALF: lanes with bit 3 set hold the odd block, in rows 8..15; else they hold no row)
+        if (par == (HALF ? kq >> 1 : 0)) red[wave + at][kq][l8] = acc;
+        acc = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    // The first n <= U steps of p and of q behind it, all their loads in flight together.
+    auto batch = [&](const Part& p, const Part& q, int n, auto u_tag) {
+        constexpr int U = decltype(u_tag)::value;
+        bf16x8_t a[U], b[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int v = min(u, n - 1);                         // (past the end the last step is fetched again, unused)
+            const bool second = v >= p.n;
+            const int i = second ? v - p.n : v;
+            a[u] = *(const bf16x8_t*)((second ? q.a : p.a) + (size_t)i * (SK * 32) + a_lane);
+            b[u] = *(const bf16x8_t*)((second ? q.b : p.b) + (size_t)i * (SK * 2) + (second ? q.b_off : p.b_off));
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (u < n) {
+                if (u == p.n) flush(p.at);
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u], acc, 0, 0, 0);
+            }
+        }
+    };
+    for (int s = lo; s < hi;) {
+        const Part p = part(hi - s);
+        Part q = p;
+        int n = p.n;
+        if (n < UMAX) {
+            advance(p.n);
+            if (s + p.n < hi) {
+                q = part(hi - s - p.n);
+                n = min(p.n + q.n, UMAX);
+                advance(n - p.n);
+            }
+        } else {
+            n = UMAX;
+            advance(n);
+        }
+        if (UMAX > 16 && n > 16) batch(p, q, n, IntTag<UMAX>{});
+        else if (UMAX > 11 && n > 11) batch(p, q, n, IntTag<(UMAX > 11 ? 16 : 1)>{});
+        else if (n > 6) batch(p, q, n, IntTag<11>{});
+        else if (n > 3) batch(p, q, n, IntTag<6>{});
+        else if (n > 1) batch(p, q, n, IntTag<3>{});
+        else batch(p, q, n, IntTag<1>{});
+        s += n;
+        const int at = n > p.n ? q.at : p.at;
+        if (s == hi || at != tile) flush(at);
+    }
+    __syncthreads();
+    // add the parts of every expert: thread (place in the list, row, quad)
+    for (int i = tid; i < ntot * 8 * NQ; i += NW * 64) {
+        const int at = i / (8 * NQ), row = i / NQ & 7, q = i % NQ;
+        const int first = at * nd, last = at < ntiles ? first + nd : total;
+        // the waves whose share holds its first and its last step
+        const int w0 = (NW * (first + 1) - 1) / total, w1 = (NW * last - 1) / total;
+        f32x4_t v = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int w = w0; w <= w1; ++w)
+            if (w * total / NW < (w + 1) * total / NW) {         // (fewer steps than waves leave some without any)
+                v = v + red[w + at][q][row];
+                if (HALF) v = v + red[w + at][2 + q % 2][row];
+            }
+        if (at == ntiles) ys[kFusedDownMaxRows + row][q] = v;
+        else if (row < s_rows[at]) ys[s_row0[at] + row][q] = v;
+    }
+    __syncthreads();
+
+    // combine: thread (t, q) owns features f0 + 4*q + 0..3 of token t
+    if (tid >= T * NQ) return;
+    const int ct = tid / NQ, cq = tid % NQ;
     f32x4_t o = {0.0f, 0.0f, 0.0f, 0.0f};
     for (int s = 0; s < k; ++s) {   // slot order = rank order
-        int32_t row;
-        float g;
-        if (s < KPRE) {
-            row = pre_row[0]; g = pre_gate[0];
-#pragma unroll
-            for (int i = 1; i < KPRE; ++i)
-                if (s == i) { row = pre_row[i]; g = pre_gate[i]; }
-        } else {
-            row = inv_perm[(size_t)ct * k + s];
-            g = gates[(size_t)ct * k + s];
-        }
-        const f32x4_t v = ys[row][cq];
+        const float g = s_gate[ct * k + s];
+        const f32x4_t v = ys[s_perm[ct * k + s]][cq];
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(g, v[i], o[i]);
     }
-    if (y_shared != nullptr) {
+    if (act_shared != nullptr) {
+        const f32x4_t v = ys[kFusedDownMaxRows + ct][cq];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(1.0f, shared_row[i], o[i]);
+        for (int i = 0; i < 4; ++i) o[i] = __builtin_fmaf(1.0f, v[i], o[i]);
     }
+    const size_t cidx = (size_t)ct * d + f0 + cq * 4;
     if (Y_BF16) {
         u32x2_t pk;
         pk[0] = pack_bf16x2(o[0], o[1]);
@@ -239,15 +303,18 @@ down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w
 }
 
 hipError_t launch_down_combine(const DownCombineArgs& a, hipStream_t s) {
-    if (a.T < 1 || a.T > kFusedDownMaxT || a.T * a.k > kFusedDownMaxRows || a.d % 16 != 0 || a.F % 32 != 0)
+    if (a.T < 1 || a.T > kFusedDownMaxT || a.T * a.k > kFusedDownMaxRows || a.d % 128 != 0 || a.F % 64 != 0 ||
+        (a.act_shared != nullptr && a.F_shared % 64 != 0))
         return hipErrorInvalidValue;
-    const dim3 grid(a.d / 16);
-    if (a.y_bf16)
-        hipLaunchKernelGGL(down_combine_kernel<true>, grid, dim3(1024), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
-                           a.F, a.d, a.sched, a.inv_perm, a.gates, a.y_shared, a.T, a.k, a.y);
-    else
-        hipLaunchKernelGGL(down_combine_kernel<false>, grid, dim3(1024), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
-                           a.F, a.d, a.sched, a.inv_perm, a.gates, a.y_shared, a.T, a.k, a.y);
+    // 8 features each where that is at most one workgroup per CU; wider layers fill the chip with 16
+    const bool half = a.d <= 2048;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(a.d / (half ? 8 : 16)), dim3(half ? 512 : 1024), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
+                           a.F, a.d, a.sched, a.inv_perm, a.gates, (const bf16_t*)a.act_shared, (const bf16_t*)a.ws_down, a.F_shared, a.T,
+                           a.k, a.y);
+    };
+    if (a.y_bf16) { if (half) launch(down_combine_kernel<true, true>); else launch(down_combine_kernel<true, false>); }
+    else          { if (half) launch(down_combine_kernel<false, true>); else launch(down_combine_kernel<false, false>); }
     return hipGetLastError();
 }
 

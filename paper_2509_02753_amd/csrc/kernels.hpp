@@ -124,7 +124,7 @@ hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 
 // Down projection and combine of a decode-sized batch in one launch (bf16 layers, T <= kFusedDownMaxT, T*k <=
 // kFusedDownMaxRows, shared expert absent or ungated): y[t] = sum_s gates[t][s] * (act[row(t, s)] . W_down[e]) in slot
-// order, then the shared expert's row.
+// order, then the shared expert's row, whose down projection is part of the launch.
 constexpr int kFusedDownMaxT = 8;      // beyond these the separate launches measured faster (more experts with rows than
 constexpr int kFusedDownMaxRows = 64;  // the d/16 workgroups of the fused launch can stream at full rate)
 struct DownCombineArgs {
@@ -134,7 +134,9 @@ struct DownCombineArgs {
     const int32_t* sched;      // work list (one tile per expert with rows)
     const int32_t* inv_perm;   // [T*k]
     const float* gates;        // [T*k]
-    const float* y_shared;     // [T][d] fp32 or null (added with coefficient 1)
+    const void* act_shared;    // [T][F_shared] bf16 or null: the shared expert, added with coefficient 1
+    const void* ws_down;       // packed [d][F_shared]
+    int F_shared;
     void* y;                   // [T][d]
     bool y_bf16;
 };

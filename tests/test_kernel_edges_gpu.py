@@ -129,6 +129,24 @@ def test_decode_schedules_around_their_limits(T, k, E, d, F, gate_up, down):
     run_and_check_layer(cfg, 0, T, k)
 
 
+@pytest.mark.parametrize("T,k,d,F,Fs", [
+    # the list of reduction steps dealt out over the waves: fewer steps than waves, parts of three experts in one share, a
+    # shared expert longer and shorter than the routed ones, none; 8 features per workgroup up to d = 2048, 16 above
+    (1, 1, 2048, 64, 0), (1, 1, 2176, 64, 64), (1, 2, 2048, 192, 64), (3, 6, 2048, 64, 2816), (8, 8, 2048, 64, 64),
+    (8, 8, 2176, 128, 1408), (2, 3, 4096, 1408, 0), (1, 8, 2176, 1024, 128), (8, 1, 128, 704, 320), (7, 6, 2176, 64, 0),
+])
+def test_down_and_combine_in_one_launch_at_its_edges(T, k, d, F, Fs):
+    """A handful of tokens: every way the reduction steps of the experts in use fall on the waves, against the oracle."""
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(S.C5, L=1, d=d, F=F), F_shared=Fs, shared_kind=S.SHARED_UNGATED if Fs else S.SHARED_NONE)
+    dl, _ = device_and_host_layer(cfg, 0)
+    assert route(dl, T, k, "down") == "fused"
+    assert not Fs or P.lexi_moe_gemm_plan(dl, T, k, "down", shared=True)["waves"] == 16
+    del dl
+    run_and_check_layer(cfg, 0, T, k)
+
+
 def _with_router(cfg, w_scale, x, dtype):
     """The seeded layer of `cfg` with its router weights scaled, and x, on device and host."""
     import numpy as np
