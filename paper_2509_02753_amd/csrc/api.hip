@@ -347,7 +347,9 @@ lexi_status run_experts(const lexi_layer_t& ly, const void* x, int32_t T, int32_
     const LayerPlan plan = plan_layer(ly, T, k, allow_split, direct_y != nullptr);
     r.plan.tile_rows[0] = plan.gateup.tile_rows;
     r.plan.tile_rows[1] = plan.routed.tile_rows;
-    if (launch_routing(r, s) != hipSuccess) return LEXI_ERR_LAUNCH;
+    // a handful of tokens on the streaming schedule: what follows the router's partials is part of the gate/up launch
+    const bool select = bf && plan.gateup_streams && T <= kSelectMaxT;
+    if ((select ? launch_router_partials(r, s) : launch_routing(r, s)) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(1);
 
     auto dense = [&](FfnArgs& f, int tile_rows) {   // the shared expert: one group of T rows
@@ -362,13 +364,18 @@ lexi_status run_experts(const lexi_layer_t& ly, const void* x, int32_t T, int32_
     dense(sg, plan.shared_gateup.tile_rows);
     sg.streaming = plan.shared_streams;
     sg.in = x; sg.w0 = ly.ws_gate; sg.w1 = ly.ws_up; sg.K = ly.d; sg.features = ly.F_shared; sg.out = w.act_shared;
-    if (launch_gateup(g, with_shared ? &sg : nullptr, s) != hipSuccess) return LEXI_ERR_LAUNCH;
+    if ((select ? launch_select_gateup(r, g, with_shared ? &sg : nullptr, s) : launch_gateup(g, with_shared ? &sg : nullptr, s)) != hipSuccess)
+        return LEXI_ERR_LAUNCH;
     mark(2);
 
     FfnArgs dn{}, sd{};
     dn.is_bf16 = bf; dn.in = w.act; dn.row_token = nullptr; dn.w0 = ly.w_down; dn.w1 = nullptr; dn.K = ly.F;
     dn.features = ly.d; dn.M = (int)A; dn.tile_rows = r.plan.tile_rows[1];
     dn.max_tiles = (int)max_tiles(A, ly.E, dn.tile_rows); dn.sched = w.sched; dn.out = w.y_slot;
+    if (select) {   // (the work list would lie where other workgroups of that launch still read the partials)
+        dn.sched = w.sched = nullptr;
+        dn.counts = w.counts; dn.E = ly.E;
+    }
     dn.streaming = plan.routed_streams;
     dn.chained = chained;
     dn.wide = plan.routed.wide;
@@ -435,6 +442,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         if (ly.F_shared > 0) mark(4);
         DownCombineArgs f{};
         f.act = w.act; f.w_down = ly.w_down; f.F = ly.F; f.d = ly.d; f.T = T; f.k = k; f.sched = w.sched;
+        f.counts = w.counts; f.E = ly.E;
         f.inv_perm = w.inv_perm; f.gates = w.gates;
         if (ly.F_shared > 0) { f.act_shared = w.act_shared; f.ws_down = ly.ws_down; f.F_shared = ly.F_shared; }
         f.y = y; f.y_bf16 = y_dtype == LEXI_BF16;

@@ -60,7 +60,7 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
     if (MIXED && j.streams) {
         static_assert(!MIXED || (NW == 4 && sizeof(lds) >= sizeof(f32x4_t) * NW * 2 * 64), "stream_unit's part sums");
         const int units = j.features >> 4, tile = block / units;
-        if (!fetch_tile<GATEUP ? 0 : 1>(j.sched, tile, j.M, j.tile_rows, ti)) return;
+        if (!fetch_tile<GATEUP ? 0 : 1>(j, tile, ti)) return;
         stream_unit<GATEUP, NW>(j, ti, block - tile * units, (f32x4_t(*)[2][64])lds);
         return;
     }

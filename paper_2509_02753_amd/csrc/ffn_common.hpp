@@ -27,16 +27,16 @@ struct FfnJob {
     const void* in;
     const int32_t* row_token;
     const void *w0, *w1;
-    const int32_t *sched, *scatter;
+    const int32_t *sched, *scatter, *counts;
     void* out;
     size_t plane_stride;
-    int K, features, M, tile_rows, ksplit, out_bf16;
+    int K, features, M, tile_rows, ksplit, out_bf16, E;
     int streams;              // taken by the weight-streaming schedule, blocks ordered (tile, unit of 16 features)
     int blocks;               // workgroups of this job, a multiple of kXcds where a second job follows
 };
 inline FfnJob make_job(const FfnArgs& a, int blocks) {
-    return FfnJob{a.in, a.row_token, a.w0, a.w1, a.sched, a.scatter, a.out, a.plane_stride, a.K, a.features, a.M, a.tile_rows,
-                  a.ksplit > 1 ? a.ksplit : 1, a.out_bf16 ? 1 : 0, a.streaming ? 1 : 0, blocks};
+    return FfnJob{a.in, a.row_token, a.w0, a.w1, a.sched, a.scatter, a.counts, a.out, a.plane_stride, a.K, a.features, a.M, a.tile_rows,
+                  a.ksplit > 1 ? a.ksplit : 1, a.out_bf16 ? 1 : 0, a.E, a.streaming ? 1 : 0, blocks};
 }
 // (by value: a conditional expression on two members would select between their addresses)
 template <typename T>
@@ -52,6 +52,8 @@ __device__ __forceinline__ FfnJob pick_job(const FfnJob& routed, const FfnJob& s
     j.w1 = choose(first, shared.w1, routed.w1);
     j.sched = choose(first, shared.sched, routed.sched);
     j.scatter = choose(first, shared.scatter, routed.scatter);
+    j.counts = choose(first, shared.counts, routed.counts);
+    j.E = choose(first, shared.E, routed.E);
     j.out = choose(first, shared.out, routed.out);
     j.plane_stride = choose(first, shared.plane_stride, routed.plane_stride);
     j.K = choose(first, shared.K, routed.K);
@@ -101,10 +103,27 @@ __device__ __forceinline__ bool fetch_group(const int32_t* sched, int tile, int 
     return true;
 }
 
+// The expert table of at most kSelectMaxT tokens from the experts' counts alone, lane = expert: rows, first row, and the number of
+// experts with rows up to and with this one (each has one tile).
+__device__ __forceinline__ void expert_table(const int32_t* counts, int E, int& count, int& offset, int& end) {
+    const int lane = threadIdx.x & 63;
+    count = lane < E ? counts[lane] : 0;
+    offset = wave_inclusive_sum(count) - count;
+    end = wave_inclusive_sum(count > 0 ? 1 : 0);
+}
+
 template <int G>
-__device__ __forceinline__ bool fetch_tile(const int32_t* sched, int tile, int M, int tile_rows, TileInfo& ti) {
+__device__ __forceinline__ bool fetch_tile(const FfnJob& j, int tile, TileInfo& ti) {
     TileGroup g;
-    if (!fetch_group<G>(sched, tile, M, tile_rows, g)) return false;
+    if (j.counts != nullptr) {
+        int count, offset, end;
+        expert_table(j.counts, j.E, count, offset, end);
+        if (tile >= __builtin_amdgcn_readlane(end, 63)) return false;
+        const int e = __builtin_amdgcn_readfirstlane(__popcll(__ballot(end <= tile)));
+        ti = TileInfo{e, __builtin_amdgcn_readlane(offset, e), __builtin_amdgcn_readlane(count, e)};
+        return true;
+    }
+    if (!fetch_group<G>(j.sched, tile, j.M, j.tile_rows, g)) return false;
     ti.expert = g.expert;
     ti.row0 = g.row0;
     ti.rows = g.rows;
@@ -151,16 +170,16 @@ __device__ __forceinline__ bool fetch_item(int block, const int32_t* sched, int 
 }
 
 // Weight-streaming schedule: one unit of 16 output features of one token tile, by a workgroup of NW waves; red is LDS.
+// `row_of(r)`: the row of `in` behind the tile's row r.  MAXB: 16-row blocks a tile holds at most.
 template <int N> struct IntTag { static constexpr int value = N; };
 
-template <bool GATEUP, int NW>
-__device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64]) {
+template <bool GATEUP, int NW, int MAXB, typename RowOf>
+__device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64], RowOf row_of) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int l16 = lane & 15, kq = lane >> 4;
     const int K = j.K, features = j.features, nkb = K >> 5;
     const bf16_t* in = (const bf16_t*)j.in;
-    const int32_t* row_token = j.row_token;
     void* out = j.out;
     TileInfo ti = tile;
     const int kb0 = wave * nkb / NW, kb1 = (wave + 1) * nkb / NW;
@@ -174,7 +193,7 @@ __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& til
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
             const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
-            const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
+            const int src_row = row_of(ti.row0 - tile.row0 + rr);
             xp[tb] = in + (size_t)src_row * K + kq * 8;
         }
         f32x4_t accg[NTB], accu[NTB];
@@ -237,11 +256,21 @@ __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& til
     for (; ti.row0 < row_end; ti.row0 += 128) {
         ti.rows = min(128, row_end - ti.row0);
         const int ntb = (ti.rows + 15) >> 4;
-        if (ntb <= 1) body(IntTag<1>{});
-        else if (ntb <= 2) body(IntTag<2>{});
-        else if (ntb <= 4) body(IntTag<4>{});
-        else body(IntTag<8>{});
+        if constexpr (MAXB == 1) {
+            body(IntTag<1>{});
+        } else {
+            if (ntb <= 1) body(IntTag<1>{});
+            else if (ntb <= 2) body(IntTag<2>{});
+            else if (ntb <= 4) body(IntTag<4>{});
+            else body(IntTag<8>{});
+        }
     }
+}
+template <bool GATEUP, int NW>
+__device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64]) {
+    const int32_t* row_token = j.row_token;
+    const int row0 = tile.row0;
+    stream_unit<GATEUP, NW, 8>(j, tile, unit, red, [&](int r) { return row_token ? row_token[row0 + r] : row0 + r; });
 }
 
 hipError_t launch_gateup_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);

@@ -39,6 +39,7 @@ struct RoutingArgs {
     int32_t* sched;           // [kSchedInts]
 };
 
+constexpr int kSelectMaxT = 8;          // T at or below which every workgroup of a streaming gate/up launch selects for itself
 constexpr int kFusedTailMaxT = 16;     // T at or below which one workgroup does everything after the segment partials
 constexpr int kSmallRouterMaxT = 64;   // T at or below which a wave takes one segment of one token
 constexpr int kFineRouterMaxT = 1024;  // T at or below which (down to the line above) router and top-k are one launch
@@ -47,6 +48,7 @@ constexpr int kFineRouterMaxT = 1024;  // T at or below which (down to the line 
 constexpr int kPermuteDirectBlocks = 512;
 constexpr int kHistSums = 512;
 hipError_t launch_routing(const RoutingArgs& a, hipStream_t s);
+hipError_t launch_router_partials(const RoutingArgs& a, hipStream_t s);   // only its first launch (T <= kSmallRouterMaxT)
 
 // One grouped (or dense) GEMM of the expert FFN.
 //   GATE/UP:  act[r][f] = silu(in[tok(r)] . Wg[e][f]) * (in[tok(r)] . Wu[e][f])      K = d, features = F
@@ -68,6 +70,8 @@ struct FfnArgs {
     int tile_rows;             // as in the work list (WorkPlan)
     int max_tiles;             // upper bound on the number of token tiles
     const int32_t* sched;      // null = dense
+    const int32_t* counts;     // null, or [E] (at most kSelectMaxT tokens, streaming): stands in for sched
+    int E;
     void* out;                 // GATE/UP: act [rows][F] (layer dtype);  DOWN: [rows][d] fp32
     // DOWN on the tile schedule only:
     bool wide;                 // workgroups of eight waves (512 output features) instead of four (256)
@@ -97,6 +101,9 @@ inline bool ffn_joins(const FfnArgs& a, const FfnArgs& shared) {
 }
 hipError_t launch_gateup(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
 hipError_t launch_down(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
+// Streaming gate/up of at most kSelectMaxT tokens with the rest of the routing in the same launch: r's router partials are
+// there, everything else of it is written.
+hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const FfnArgs* shared, hipStream_t s);
 
 // row-major [n_mat][R][K] -> packed expert-weight layout (R % 16 == 0, K % 32 == 0)
 hipError_t launch_pack(const void* src, void* dst, int64_t n_mat, int R, int K, bool is_bf16, hipStream_t s);
@@ -131,7 +138,9 @@ struct DownCombineArgs {
     const void* act;           // [T*k][F] bf16, permuted rows
     const void* w_down;        // [E] packed matrices of [d][F]
     int F, d, T, k;
-    const int32_t* sched;      // work list (one tile per expert with rows)
+    const int32_t* sched;      // work list (one tile per expert with rows), or null: then
+    const int32_t* counts;     // [E]
+    int E;
     const int32_t* inv_perm;   // [T*k]
     const float* gates;        // [T*k]
     const void* act_shared;    // [T][F_shared] bf16 or null: the shared expert, added with coefficient 1

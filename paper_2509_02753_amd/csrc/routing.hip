@@ -2,7 +2,7 @@
 // token-to-expert permutation (per-block histogram -> scan -> scatter).
 //
 // Paper Sec. 2: G(x) = Softmax(TopK[x * W_g]); k is a launch argument (Algorithm 1's UpdateTopk).
-#include "kernels.hpp"
+#include "routing_common.hpp"
 
 namespace lexi {
 
@@ -367,27 +367,6 @@ topk_kernel(const float* __restrict__ partial, int pstride, const float* __restr
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// write_work_list: the expert table and the tiles of the two grouped GEMMs, by one wave (lane = expert, `total` = its
-// rows); returns the expert's first permuted row.
-// ---------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ int32_t write_work_list(int32_t total, int E, const WorkPlan& plan, int32_t* __restrict__ counts,
-                                                   int32_t* __restrict__ offsets, int32_t* __restrict__ sched) {
-    const int lane = threadIdx.x & 63;
-    const int32_t off = wave_inclusive_sum(total) - total;
-    if (lane < E) {
-        counts[lane] = total;
-        offsets[lane] = off;
-    }
-    if (lane == 63) offsets[E] = off + total;       // lanes >= E hold no rows
-    sched[kSchedOff + lane] = off;
-    sched[kSchedCount + lane] = total;
-#pragma unroll
-    for (int g = 0; g < 2; ++g)
-        sched[kSchedTiles + 64 * g + lane] = wave_inclusive_sum((total + plan.tile_rows[g] - 1) / plan.tile_rows[g]);
-    return off;
-}
-
-// ---------------------------------------------------------------------------------------------------------
 // permute_kernel (T > kFusedTailMaxT): the stable counting sort from the block histograms of the selection.  A workgroup of
 // 16 waves scatters the assignments of its router blocks, kPermuteBlocks at a time: position of an assignment = offset of its
 // expert + assignments to it in earlier blocks + its rank in the block.  Every workgroup sums all histograms itself (256 bytes
@@ -590,6 +569,10 @@ static hipError_t launch_partials(const RoutingArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+hipError_t launch_router_partials(const RoutingArgs& a, hipStream_t s) {
+    return a.is_bf16 ? launch_partials<true>(a, s) : launch_partials<false>(a, s);
+}
+
 hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
     const int nseg = a.d / kRouterSegment;
     const int tb = router_tokens_per_block(a.T);
@@ -604,7 +587,7 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
                                a.k, a.topk_idx, a.gates, a.local_rank, a.blk_hist);
         err = hipGetLastError();
     } else {
-        err = a.is_bf16 ? launch_partials<true>(a, s) : launch_partials<false>(a, s);
+        err = launch_router_partials(a, s);
         if (err != hipSuccess) return err;
         if (a.T <= kFusedTailMaxT) {
             hipLaunchKernelGGL(topk_scan_kernel, dim3(1), dim3(1024), 0, s, a.partial, a.bias, a.T, nseg, a.E, a.k,

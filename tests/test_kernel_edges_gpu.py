@@ -253,3 +253,49 @@ def test_fp32_down_gemm_is_one_ascending_chain_of_fmaf(scale):
             want[t, j] = acc
     assert scale == 1.0 or 0.0 < np.abs(want).max() < 2.0 ** -126
     assert np.array_equal(y.cpu().numpy().view(np.int32), want.view(np.int32))
+
+
+@pytest.mark.parametrize("T,k,E,d", [
+    (1, 1, 1, 128), (1, 64, 64, 256), (2, 2, 16, 2048), (3, 5, 17, 2176), (4, 8, 60, 1920), (5, 1, 64, 4096), (7, 16, 64, 384),
+    (8, 8, 60, 2048), (8, 16, 64, 2304),
+])
+@pytest.mark.parametrize("zipf", [0.0, 1.1])
+def test_selection_inside_the_gate_up_launch(T, k, E, d, zipf):
+    """Up to eight tokens every workgroup of the gate/up launch selects for itself: one to eight tokens, one to 64 experts, one
+    segment of the router up to 32, around the 16 requested together; routing bit for bit, outputs, both as one layer and as a
+    block of the chained stack (where the down GEMM reads the expert table too), against the oracle."""
+    import torch
+    import oracle as O
+    import paper_2509_02753_amd as P
+    from helpers import check_routing, device_and_host_layer, rel_err, TOL_BF16
+    cfg = replace(S.mini(S.C5 if zipf else S.C2, L=1, d=d, F=128, F_shared=0), E=E, F_shared=0, shared_kind=S.SHARED_NONE)
+    run_and_check_layer(cfg, 0, T, k)
+    dl, hl = device_and_host_layer(cfg, 0)
+    assert P.lexi_moe_gemm_plan(dl, T, k, "gate_up", chained=True)["streams"] == 1
+    x = S.device_x(cfg, 0, T)
+    y = torch.empty((T, d), dtype=torch.float32, device="cuda:0")
+    rout = P.RoutingOut(T, k, E, moe_input=torch.empty_like(x))
+    P.lexi_moe_stack_forward([dl], [k], x, y, P.alloc_workspace([dl], T, k), routing=[rout], chained=True)
+    torch.cuda.synchronize()
+    u = rout.moe_input.view(torch.int16).cpu().numpy().view("uint16")
+    ref = O.moe_layer(hl, u, k, round_act=True)
+    check_routing(rout, ref)
+    assert rel_err(y.cpu().numpy() - x.float().cpu().numpy(), ref.out) <= TOL_BF16
+
+
+@pytest.mark.parametrize("T,E", [(8, 64), (5, 17), (8, 5)])
+def test_selection_inside_the_gate_up_launch_with_infinite_and_nan_logits(T, E):
+    import numpy as np
+    import oracle as O
+    from helpers import to_numpy
+    cfg = replace(S.mini(S.C2, L=1, d=256, F=64, F_shared=0), E=E)
+    x = np.random.default_rng(T * E).standard_normal((T, cfg.d)).astype(np.float32)
+    x[3, 5], x[3, 200] = np.inf, np.inf
+    x[T - 1, 77] = np.nan
+    dl, hl, xd, xh = _with_router(cfg, 1.0, x, "bf16")
+    k = 1 if E < 8 else 2
+    logits = O.moe_layer(hl, xh, k, routing_only=True).logits
+    want = np.argsort(-np.where(np.isnan(logits), -np.inf, logits), axis=1, kind="stable")[:, :k]
+    rout = _route(dl, xd, k, E)
+    assert np.array_equal(to_numpy(rout.topk_idx), want)
+    assert np.array_equal(np.sort(to_numpy(rout.perm)), np.arange(T * k))
