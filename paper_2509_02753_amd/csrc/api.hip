@@ -347,7 +347,7 @@ lexi_status run_experts(const lexi_layer_t& ly, const void* x, int32_t T, int32_
     const LayerPlan plan = plan_layer(ly, T, k, allow_split, direct_y != nullptr);
     r.plan.tile_rows[0] = plan.gateup.tile_rows;
     r.plan.tile_rows[1] = plan.routed.tile_rows;
-    // a handful of tokens on the streaming schedule: what follows the router's partials is part of the gate/up launch
+    // up to 16 tokens on the streaming schedule: what follows the router's partials is part of the gate/up launch
     const bool select = bf && plan.gateup_streams && T <= kSelectMaxT;
     if ((select ? launch_router_partials(r, s) : launch_routing(r, s)) != hipSuccess) return LEXI_ERR_LAUNCH;
     mark(1);

@@ -33,7 +33,8 @@ ffn_stream_kernel(FfnJob routed, FfnJob shared) {
 // a token are 64 bits, so counts, offsets, an expert's tokens and the tile's expert are a few bit operations.  One workgroup
 // writes the routing for the launches behind.  The workgroups take units of 16 features in steps of the grid, at most
 // kSelectBlocks of them (most tokens use far fewer experts than they might), the shared expert's come first.
-// One token, k 2 to 6, 8 layers: 302 -> 266 us; 8 tokens, k = 6: 643 -> 611; static call 43.3 -> 38.3.
+// Whole calls of 8 layers (us): one token, k 2 to 6 302 -> 265; 8 tokens, k = 6 643 -> 590; 16 tokens, k = 2 466 -> 424, k = 6 829 ->
+// 798, k = 8 without a shared expert 1231 -> 1203.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kSelectBlocks = 1024;
 
@@ -44,12 +45,12 @@ struct SelectArgs {
     float* gates;
 };
 
-template <int NW>
+template <int NW, int MAXT>
 __global__ void __launch_bounds__(NW * 64)
 select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
     __shared__ __attribute__((aligned(16))) f32x4_t red[NW][2][64];
-    __shared__ uint64_t s_mask[kSelectMaxT];
-    __shared__ uint8_t s_sel[kSelectMaxT][64];
+    __shared__ uint64_t s_mask[MAXT];
+    __shared__ uint8_t s_sel[MAXT][64];
     __shared__ int32_t s_off[64];
     const int lane = threadIdx.x & 63;
     if ((int)blockIdx.x < shared.blocks) {
@@ -59,7 +60,7 @@ select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
     }
     const int block = blockIdx.x - shared.blocks - 1;
     const bool writer = block < 0;
-    select_tokens<NW>(r.partial, r.bias, r.T, r.nseg, r.E, r.k, s_mask, [&](int t, int32_t sel, float val) {
+    select_tokens<NW, MAXT>(r.partial, r.bias, r.T, r.nseg, r.E, r.k, s_mask, [&](int t, int32_t sel, float val) {
         if (!writer) return;
         const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val), 0));   // slot 0 holds the largest
         const float ex = lane < r.k ? __expf(val - v0) : 0.0f;
@@ -108,7 +109,7 @@ select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
                                  item - tile * units, red, [&](int row) {
             int src = 0;
 #pragma unroll
-            for (int t = 0, c = 0; t < kSelectMaxT; ++t)
+            for (int t = 0, c = 0; t < MAXT; ++t)
                 if ((tok >> t) & 1) { src = c == row ? t : src; ++c; }
             return src;
         });
@@ -123,8 +124,14 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
     const SelectArgs sel{r.partial, r.bias, r.T, r.d / kRouterSegment, r.E, r.k, r.topk_idx, r.counts, r.offsets, r.perm, r.inv_perm,
                          r.row_token, r.gates};
     const dim3 grid((unsigned)(jr.blocks + js.blocks + 1));
-    if (stream_waves(a.K, units + shared_units, a.chained) == 8) hipLaunchKernelGGL(select_gateup_kernel<8>, grid, dim3(512), 0, s, jr, js, sel);
-    else hipLaunchKernelGGL(select_gateup_kernel<4>, grid, dim3(256), 0, s, jr, js, sel);
+    const bool few = r.T <= 8;
+    if (stream_waves(a.K, units + shared_units, a.chained) == 8) {
+        if (few) hipLaunchKernelGGL((select_gateup_kernel<8, 8>), grid, dim3(512), 0, s, jr, js, sel);
+        else hipLaunchKernelGGL((select_gateup_kernel<8, 16>), grid, dim3(512), 0, s, jr, js, sel);
+    } else {
+        if (few) hipLaunchKernelGGL((select_gateup_kernel<4, 8>), grid, dim3(256), 0, s, jr, js, sel);
+        else hipLaunchKernelGGL((select_gateup_kernel<4, 16>), grid, dim3(256), 0, s, jr, js, sel);
+    }
     return hipGetLastError();
 }
 

@@ -39,7 +39,7 @@ struct RoutingArgs {
     int32_t* sched;           // [kSchedInts]
 };
 
-constexpr int kSelectMaxT = 8;          // T at or below which every workgroup of a streaming gate/up launch selects for itself
+constexpr int kSelectMaxT = 16;         // T at or below which every workgroup of a streaming gate/up launch selects for itself
 constexpr int kFusedTailMaxT = 16;     // T at or below which one workgroup does everything after the segment partials
 constexpr int kSmallRouterMaxT = 64;   // T at or below which a wave takes one segment of one token
 constexpr int kFineRouterMaxT = 1024;  // T at or below which (down to the line above) router and top-k are one launch

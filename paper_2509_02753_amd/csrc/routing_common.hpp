@@ -26,17 +26,17 @@ __device__ __forceinline__ int32_t write_work_list(int32_t total, int E, const W
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Selection of a few tokens by every workgroup of a launch for itself (T <= kSelectMaxT): the experts token t selects as bits
+// Selection of a few tokens by every workgroup of a launch for itself (T <= MAXT <= kSelectMaxT): the experts token t selects as bits
 // of s_mask[t].  Logits are the ordered sums of the segment partials (plus bias), the selection the total order (logit
 // descending, index ascending), as everywhere.  A wave takes tokens wave, wave + NW, ...; `picked` is called for
 // each of them with the token, and per lane s < k the expert and the logit of slot s.
 // All segments' partials of a token (up to 16 at a time) are requested together: one round trip.
 // ---------------------------------------------------------------------------------------------------------
-template <int NW, typename Picked>
+template <int NW, int MAXT, typename Picked>
 __device__ __forceinline__ void select_tokens(const float* __restrict__ partial, const float* __restrict__ bias, int T, int nseg,
                                               int E, int k, uint64_t* s_mask, Picked picked) {
-    constexpr int TM = kSelectMaxT / NW;         // tokens per wave, interleaved
-    static_assert(TM * NW == kSelectMaxT, "");
+    constexpr int TM = MAXT / NW;                // tokens per wave, interleaved
+    static_assert(TM * NW == MAXT, "");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave >= T) return;

@@ -257,11 +257,11 @@ def test_fp32_down_gemm_is_one_ascending_chain_of_fmaf(scale):
 
 @pytest.mark.parametrize("T,k,E,d", [
     (1, 1, 1, 128), (1, 64, 64, 256), (2, 2, 16, 2048), (3, 5, 17, 2176), (4, 8, 60, 1920), (5, 1, 64, 4096), (7, 16, 64, 384),
-    (8, 8, 60, 2048), (8, 16, 64, 2304),
+    (8, 8, 60, 2048), (8, 16, 64, 2304), (9, 7, 64, 384), (12, 2, 17, 2176), (13, 1, 8, 128), (16, 8, 64, 2048),
 ])
 @pytest.mark.parametrize("zipf", [0.0, 1.1])
 def test_selection_inside_the_gate_up_launch(T, k, E, d, zipf):
-    """Up to eight tokens every workgroup of the gate/up launch selects for itself: one to eight tokens, one to 64 experts, one
+    """Up to 16 tokens every workgroup of the gate/up launch selects for itself: one to 16 tokens, one to 64 experts, one
     segment of the router up to 32, around the 16 requested together; routing bit for bit, outputs, both as one layer and as a
     block of the chained stack (where the down GEMM reads the expert table too), against the oracle."""
     import torch
@@ -283,7 +283,7 @@ def test_selection_inside_the_gate_up_launch(T, k, E, d, zipf):
     assert rel_err(y.cpu().numpy() - x.float().cpu().numpy(), ref.out) <= TOL_BF16
 
 
-@pytest.mark.parametrize("T,E", [(8, 64), (5, 17), (8, 5)])
+@pytest.mark.parametrize("T,E", [(8, 64), (5, 17), (8, 5), (16, 40)])
 def test_selection_inside_the_gate_up_launch_with_infinite_and_nan_logits(T, E):
     import numpy as np
     import oracle as O
