@@ -304,8 +304,8 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     const bool direct = allow_direct && k == 1 && ly.F_shared == 0;
     p.routed_streams = p.gateup_streams || (few_items <= kStreamDownMaxItems && down_streams(A, ly.E, ly.F, ly.d, direct));
     p.shared_streams = !bf || T <= kStreamDenseRows;
-    p.gateup = p.routed = p.shared = TilePlan{false, kTileRows, 1};
-    p.shared_gateup = TilePlan{false, T <= kSharedJoinsMaxT ? kSharedTileRows : kTileRows, 1};
+    p.gateup = p.routed = p.shared = TilePlan{false, bf ? kTileRows : kF32TileRows, 1};
+    p.shared_gateup = TilePlan{false, !bf ? kF32TileRows : T <= kSharedJoinsMaxT ? kSharedTileRows : kTileRows, 1};
     if (!p.gateup_streams) p.gateup = plan_gateup_tiles(A, ly.E, ly.d, ly.F);
     // (allow_direct: the caller wants nothing but y -- no slot rows, no residual, no normalised copy)
     p.routed_fused = bf && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&

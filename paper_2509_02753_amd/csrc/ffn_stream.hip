@@ -62,9 +62,7 @@ select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
     const bool writer = block < 0;
     select_tokens<NW, MAXT>(r.partial, r.bias, r.T, r.nseg, r.E, r.k, s_mask, [&](int t, int32_t sel, float val) {
         if (!writer) return;
-        const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val), 0));   // slot 0 holds the largest
-        const float ex = lane < r.k ? __expf(val - v0) : 0.0f;
-        const float g = ex / wave_sum(ex);
+        const float g = gate_of(val, r.k);
         if (lane < r.k) {
             r.topk_idx[t * r.k + lane] = sel;
             r.gates[t * r.k + lane] = g;
@@ -140,9 +138,11 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
 // that the rounding of a chained stack of fp32 layers (where a router may turn a last bit into another expert) does not
 // depend on how the work is dealt out.  v_mfma_f32_4x4x1_16b_f32 takes one element of the reduction per instruction, for
 // four token rows (broadcast) and 64 features (lane = feature): a wave owns 4 rows x 64 features, a workgroup 16 rows of a
-// tile at a time.  fp32 is used at test scale (d 128, F 256, 64 tokens, two experts each), where a launch is bound by the
-// latency of the chain (4.7 ns an instruction): 7.4 + 8.3 us for that layer's two GEMMs, where one output element per thread
-// walking K alone took 636 + 664 us (same bits).  Cutting K over the waves is faster still (4.8 + 4.6 us) but not the same sum.
+// tile, which is as high (more rows in a workgroup were walked one after the other).  fp32 is used at test scale (d 128, F 256,
+// 64 tokens, two experts each), where a launch is bound by round trips to memory: weights and x of 64 elements are requested a
+// step ahead, the first weights before the rows' numbers are known.  That layer's two GEMMs take 6.8 + 6.2 us (7.1 + 8.4 with
+// tiles of 160 rows and x requested when needed; 4 layers of d 384, F 384, 16 experts, 128 tokens, k = 4: call 486 -> 153 us; 1000
+// tokens, d 256, 2 layers 252 -> 125).  Cutting K over the waves is faster still (4.8 + 4.6 us) but not the same sum.
 // ---------------------------------------------------------------------------------------------------------
 template <bool GATEUP>
 __global__ void __launch_bounds__(256)
@@ -162,41 +162,57 @@ ffn_f32_kernel(FfnJob routed, FfnJob shared) {
     // of 8, 128 floats apart
     const size_t slab = (size_t)ti.expert * (features >> 4) + column * 4 + (lane >> 4);
     const float* wp[2] = {w0 + slab * ((size_t)K * 16) + (lane & 15) * 8, GATEUP ? w1 + slab * ((size_t)K * 16) + (lane & 15) * 8 : nullptr};
-    struct Block { f32x4_t v[NM][4][2]; };
-    auto fetch_w = [&](Block& b, int kb) {
+    struct Step {                                        // 64 elements of the reduction: weights of the lane's feature, an octet of x
+        f32x4_t w[2][NM][4][2], x[2];
+    };
+    auto fetch_w = [&](Step& s, int k0) {
 #pragma unroll
-        for (int m = 0; m < NM; ++m)
+        for (int b = 0; b < 2; ++b)
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+            for (int m = 0; m < NM; ++m)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) b.v[m][q][h] = *(const f32x4_t*)(wp[m] + (size_t)kb * 512 + q * 128 + 4 * h);
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) s.w[b][m][q][h] = *(const f32x4_t*)(wp[m] + (size_t)k0 * 16 + b * 512 + q * 128 + 4 * h);
     };
     for (int r0 = wave * 4; r0 < ti.rows; r0 += 16) {   // (no barrier in this kernel)
         const int rr = min(r0 + (lane & 3), ti.rows - 1);   // rows past the tile's end re-read its last row; never stored
         const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
+        Step s[2];                                       // one step in use, the next on its way
+        fetch_w(s[0], 0);
+        __builtin_amdgcn_sched_barrier(0);               // (in front of the wait for the row's number)
         const float* xp = in + (size_t)src_row * K + ((lane >> 2) & 7) * 8;   // octet (lane / 4) % 8 of 64 elements
+        auto fetch_x = [&](Step& s, int k0) {
+            s.x[0] = *(const f32x4_t*)(xp + k0);
+            s.x[1] = *(const f32x4_t*)(xp + k0 + 4);
+        };
+        fetch_x(s[0], 0);
         f32x4_t acc[NM];
 #pragma unroll
         for (int m = 0; m < NM; ++m) acc[m] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        Block w[2];
-        fetch_w(w[0], 0);
-        for (int k0 = 0; k0 < K; k0 += 64) {            // (K is a multiple of 64)
-            const f32x4_t x0 = *(const f32x4_t*)(xp + k0), x1 = *(const f32x4_t*)(xp + k0 + 4);
-            auto octet = [&](const Block& b, auto o) {  // elements k0 + 8 * O .. + 7, octet O % 4 of K block O / 4
-                constexpr int O = decltype(o)::value;
+        auto octet = [&](const Step& s, auto o) {       // elements 8 * O .. + 7 of the step
+            constexpr int O = decltype(o)::value;
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
+            for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int m = 0; m < NM; ++m)
-                        acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(e < 4 ? x0[e & 3] : x1[e & 3], b.v[m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
-            };
-            fetch_w(w[1], (k0 >> 5) + 1);
-            __builtin_amdgcn_sched_barrier(0);   // the next block's loads in front of this one's chain
-            octet(w[0], IntTag<0>{}); octet(w[0], IntTag<1>{}); octet(w[0], IntTag<2>{}); octet(w[0], IntTag<3>{});
-            fetch_w(w[0], min((k0 >> 5) + 2, (K >> 5) - 1));   // (the last one is not used)
+                for (int m = 0; m < NM; ++m)
+                    acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(s.x[e >> 2][e & 3], s.w[O >> 2][m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
+        };
+        auto step = [&](Step& now, Step& next, int k0) {
+            const int kn = min(k0 + 64, K - 64);         // (K is a multiple of 64; the last one is fetched again, unused)
+            fetch_w(next, kn);
+            fetch_x(next, kn);
+            __builtin_amdgcn_sched_barrier(0);           // the next step's loads in front of this one's chain
+            octet(now, IntTag<0>{}); octet(now, IntTag<1>{}); octet(now, IntTag<2>{}); octet(now, IntTag<3>{});
+            octet(now, IntTag<4>{}); octet(now, IntTag<5>{}); octet(now, IntTag<6>{}); octet(now, IntTag<7>{});
             __builtin_amdgcn_sched_barrier(0);
-            octet(w[1], IntTag<4>{}); octet(w[1], IntTag<5>{}); octet(w[1], IntTag<6>{}); octet(w[1], IntTag<7>{});
+        };
+        int k0 = 0;
+        for (; k0 + 128 <= K; k0 += 128) {
+            step(s[0], s[1], k0);
+            step(s[1], s[0], k0 + 64);
         }
+        if (k0 < K) step(s[0], s[1], k0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (r0 + i < ti.rows) {

@@ -7,6 +7,7 @@ namespace lexi {
 // Height of the token tiles of the grouped GEMMs (rows a tile holds at most), and the XCDs their work is dealt out to.
 constexpr int kTileRows = 160;
 constexpr int kLowTileRows = 96, kHalfTileRows = 64;   // up to these heights the tile kernel has forms for low tiles
+constexpr int kF32TileRows = 16;      // fp32 layers: what a workgroup takes at a time
 constexpr int kXcds = 8;
 
 // Tiles of the two grouped GEMMs of a layer (0: gate/up, 1: down), written by the routing kernels: an expert with n rows

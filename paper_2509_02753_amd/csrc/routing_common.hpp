@@ -25,6 +25,38 @@ __device__ __forceinline__ int32_t write_work_list(int32_t total, int E, const W
     return off;
 }
 
+// The top-k of TM tokens by one wave (lane = expert): total[m] are the logits before the bias; lane e learns whether token m took
+// expert e, lane s < k the expert and the logit of slot s.
+template <int TM>
+__device__ __forceinline__ void pick_experts(float (&total)[TM], const float* __restrict__ bias, int E, int k, bool (&taken)[TM],
+                                             int32_t (&sel)[TM], float (&val)[TM]) {
+    const int lane = threadIdx.x & 63;
+    const bool lane_valid = lane < E;
+    const float b = (bias != nullptr && lane_valid) ? bias[lane] : 0.0f;
+#pragma unroll
+    for (int m = 0; m < TM; ++m) {
+        if (bias != nullptr) total[m] = total[m] + b;
+        total[m] = total[m] == total[m] ? total[m] : -INFINITY;   // a NaN logit ranks last
+        taken[m] = false; sel[m] = 0; val[m] = -INFINITY;
+    }
+    for (int s = 0; s < k; ++s) {
+#pragma unroll
+        for (int m = 0; m < TM; ++m) {
+            const bool open = lane_valid && !taken[m];
+            const float mx = wave_max(open ? total[m] : -INFINITY);
+            const int e_star = __builtin_ctzll(__ballot(open && total[m] == mx));   // lowest index among equal logits
+            if (lane == e_star) taken[m] = true;
+            if (lane == s) { sel[m] = e_star; val[m] = mx; }
+        }
+    }
+}
+// Softmax over the selected: lane s < k gets the gate of slot s.
+__device__ __forceinline__ float gate_of(float val, int k) {
+    const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val), 0));   // slot 0 holds the largest
+    const float ex = (int)(threadIdx.x & 63) < k ? __expf(val - v0) : 0.0f;
+    return ex / wave_sum(ex);
+}
+
 // ---------------------------------------------------------------------------------------------------------
 // Selection of a few tokens by every workgroup of a launch for itself (T <= MAXT <= kSelectMaxT): the experts token t selects as bits
 // of s_mask[t].  Logits are the ordered sums of the segment partials (plus bias), the selection the total order (logit
@@ -40,8 +72,6 @@ __device__ __forceinline__ void select_tokens(const float* __restrict__ partial,
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave >= T) return;
-    const bool lane_valid = lane < E;
-    const float b = (bias != nullptr && lane_valid) ? bias[lane] : 0.0f;
     float total[TM];
 #pragma unroll
     for (int m = 0; m < TM; ++m) total[m] = 0.0f;
@@ -62,22 +92,7 @@ __device__ __forceinline__ void select_tokens(const float* __restrict__ partial,
     bool taken[TM];
     int32_t sel[TM];
     float val[TM];
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-        if (bias != nullptr) total[m] = total[m] + b;
-        total[m] = total[m] == total[m] ? total[m] : -INFINITY;   // a NaN logit ranks last
-        taken[m] = false; sel[m] = 0; val[m] = -INFINITY;
-    }
-    for (int s = 0; s < k; ++s) {
-#pragma unroll
-        for (int m = 0; m < TM; ++m) {
-            const bool open = lane_valid && !taken[m];
-            const float mx = wave_max(open ? total[m] : -INFINITY);
-            const int e_star = __builtin_ctzll(__ballot(open && total[m] == mx));   // lowest index among equal logits
-            if (lane == e_star) taken[m] = true;
-            if (lane == s) { sel[m] = e_star; val[m] = mx; }
-        }
-    }
+    pick_experts<TM>(total, bias, E, k, taken, sel, val);
 #pragma unroll
     for (int m = 0; m < TM; ++m) {
         const int t = wave + m * NW;
