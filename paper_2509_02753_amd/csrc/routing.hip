@@ -548,6 +548,107 @@ topk_scan_kernel(const float* partial, const float* __restrict__ bias, int T, in
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// route_small_kernel (T <= kSmallRouterMaxT, at most kSmallRouteSegs segments): the whole routing in ONE workgroup of 16 waves, four
+// tokens each.  A segment's W (at most 32 KB) goes through LDS once for all of them; v_mfma_f32_4x4x1_16b_f32 as in
+// router_topk_kernel leaves a token's partial with lane = expert, where it is added up and selected from.  The counting sort
+// needs no histograms: an expert's tokens are 64 bits.
+// Routing stage with events, one launch against three: 64 tokens, d 128, k = 2 11.1 us against 12.5.  One CU does all the work, at 1 us
+// per k and 2.7 us per further segment for 64 tokens: k = 6 15.1 / 13.2, d 256, k = 4 15.8 / 13.3; hence route_small's line at 192.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kSmallRouteSegs = 3;
+static bool route_small(int T, int k, int nseg) { return T <= kSmallRouterMaxT && nseg <= kSmallRouteSegs && T * (k + 3 * (nseg - 1)) <= 192; }
+
+template <bool IS_BF16>
+__global__ void __launch_bounds__(1024)
+route_small_kernel(const void* __restrict__ x, const float* __restrict__ w_router, const float* __restrict__ bias, int T, int d,
+                   int E, int k, WorkPlan plan, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
+                   int32_t* __restrict__ counts, int32_t* __restrict__ offsets, int32_t* __restrict__ sched,
+                   int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm, int32_t* __restrict__ row_token) {
+    __shared__ __attribute__((aligned(16))) float ws[kRouterSegment * 64];
+    __shared__ uint8_t s_bits[16][64];           // which of a wave's four tokens selected expert e
+    __shared__ uint64_t s_tokens[64];            // the tokens of expert e
+    __shared__ int32_t s_off[64];
+    __shared__ uint8_t s_sel[kSmallRouterMaxT * 64];   // the expert of assignment a
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tok0 = wave * 4;
+    const int nseg = d / kRouterSegment;
+    float wst[8];
+    Octet<IS_BF16> xo;                                                  // rows past T re-read the last row; never used
+    auto fetch = [&](int seg) {
+        const float* wp = w_router + (size_t)(seg * kRouterSegment + wave) * E + min(lane, E - 1);   // lanes >= E read a valid column
+#pragma unroll
+        for (int p = 0; p < 8; ++p) wst[p] = wp[(size_t)16 * p * E];
+        xo.load(x, (size_t)min(tok0 + (lane & 3), T - 1) * d + seg * kRouterSegment + 8 * (lane >> 2));
+    };
+    fetch(0);
+    float total[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int seg = 0; seg < nseg; ++seg) {
+#pragma unroll
+        for (int p = 0; p < 8; ++p) ws[tid + 1024 * p] = wst[p];
+        float xf[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) xf[e] = xo.get(e);
+        __syncthreads();
+        if (seg + 1 < nseg) fetch(seg + 1);
+        if (tok0 < T) {
+            f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+            auto octet = [&](auto b) {           // elements 8B .. 8B + 7 of the segment
+                constexpr int B = decltype(b)::value;
+                float w[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[e] = ws[(8 * B + e) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc = __builtin_amdgcn_mfma_f32_4x4x1f32(xf[e], w[e], acc, 4, B, 0);
+            };
+            octet(IntC<0>{}); octet(IntC<1>{}); octet(IntC<2>{}); octet(IntC<3>{});
+            octet(IntC<4>{}); octet(IntC<5>{}); octet(IntC<6>{}); octet(IntC<7>{});
+            octet(IntC<8>{}); octet(IntC<9>{}); octet(IntC<10>{}); octet(IntC<11>{});
+            octet(IntC<12>{}); octet(IntC<13>{}); octet(IntC<14>{}); octet(IntC<15>{});
+#pragma unroll
+            for (int m = 0; m < 4; ++m) total[m] = seg == 0 ? acc[m] : total[m] + acc[m];   // the first partial is taken as is
+        }
+        __syncthreads();                         // ws has been read
+    }
+    uint32_t bits = 0;
+    if (tok0 < T) {
+        bool taken[4];
+        int32_t sel[4];
+        float val[4];
+        pick_experts<4>(total, bias, E, k, taken, sel, val);
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int t = tok0 + m;
+            if (t >= T) break;
+            bits |= taken[m] ? 1u << m : 0u;
+            const float g = gate_of(val[m], k);
+            if (lane < k) {
+                topk_idx[t * k + lane] = sel[m];
+                gates[t * k + lane] = g;
+                s_sel[t * k + lane] = (uint8_t)sel[m];
+            }
+        }
+    }
+    s_bits[wave][lane] = (uint8_t)bits;
+    __syncthreads();
+    if (wave == 0) {
+        uint64_t tokens = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) tokens |= (uint64_t)s_bits[w][lane] << (4 * w);
+        s_tokens[lane] = tokens;
+        s_off[lane] = write_work_list(__popcll(tokens), E, plan, counts, offsets, sched);
+    }
+    __syncthreads();
+    for (int a = tid; a < T * k; a += 1024) {
+        const int t = a / k, e = s_sel[a];
+        const int at = s_off[e] + __popcll(s_tokens[e] & ((1ull << t) - 1));
+        perm[at] = a;
+        inv_perm[a] = at;
+        row_token[at] = t;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kNarrowRouterMaxE = 16;
@@ -578,6 +679,15 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
     const int tb = router_tokens_per_block(a.T);
     const int nblk = (a.T + tb - 1) / tb;
     hipError_t err;
+    if (route_small(a.T, a.k, nseg)) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E, a.k, a.plan, a.topk_idx, a.gates,
+                               a.counts, a.offsets, a.sched, a.perm, a.inv_perm, a.row_token);
+        };
+        if (a.is_bf16) launch(route_small_kernel<true>);
+        else launch(route_small_kernel<false>);
+        return hipGetLastError();
+    }
     if (a.T > kSmallRouterMaxT && a.T <= kFineRouterMaxT) {
         if (a.is_bf16)
             hipLaunchKernelGGL(router_topk_kernel<true>, dim3(nblk), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E,

@@ -299,3 +299,14 @@ def test_selection_inside_the_gate_up_launch_with_infinite_and_nan_logits(T, E):
     rout = _route(dl, xd, k, E)
     assert np.array_equal(to_numpy(rout.topk_idx), want)
     assert np.array_equal(np.sort(to_numpy(rout.perm)), np.arange(T * k))
+
+
+@pytest.mark.parametrize("T,k,E,d,kind", [
+    # all routing in one workgroup: one to 64 tokens (a wave's four partly there), one to three segments, one to 64 experts, on
+    # both sides of the line to the three launches
+    (1, 1, 1, 128, "c1"), (3, 60, 60, 128, "c1"), (64, 3, 8, 128, "c1"), (64, 3, 64, 128, "c2"), (63, 4, 64, 128, "c1"), (5, 2, 17, 384, "c1"),
+    (21, 3, 5, 384, "c2"), (24, 5, 40, 256, "c1"), (33, 1, 64, 256, "c2"), (21, 4, 5, 384, "c1"), (50, 1, 8, 256, "c1"),
+])
+def test_routing_in_one_workgroup(T, k, E, d, kind):
+    cfg = replace(S.mini(S.C1 if kind == "c1" else S.C2, L=1, d=d, F=64, F_shared=0), E=E)
+    run_and_check_layer(cfg, 0, T, k)
