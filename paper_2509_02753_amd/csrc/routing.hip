@@ -297,11 +297,13 @@ router_partial_mfma_kernel(const void* __restrict__ x, const float* __restrict__
     // W in groups of NG registers, the next group read from LDS while the current one is multiplied.  A register holds
     // element k of column `lane`, or (NARROW) elements 4j + 0..3 of the 16 columns.
     constexpr int NR = kRouterSegment * EW / 64, NG = 8;
+    // (column l16 of block q is expert 4 * l16 + q: the four blocks of an accumulator then hold four consecutive experts)
+    const int wcol = NARROW ? lane : 4 * l16 + q;
     f32x16 acc = {};
     float w[2][NG];
     auto read_w = [&](int g) {
 #pragma unroll
-        for (int i = 0; i < NG; ++i) w[g & 1][i] = ws[(g * NG + i) * 64 + lane];
+        for (int i = 0; i < NG; ++i) w[g & 1][i] = ws[(g * NG + i) * 64 + wcol];
     };
     read_w(0);
 #pragma unroll
@@ -336,12 +338,9 @@ router_partial_mfma_kernel(const void* __restrict__ x, const float* __restrict__
         if constexpr (NARROW) {                  // rows are experts, columns tokens
             const int t = t0 + 16 * b + l16;
             if (t < T) *(f32x4_t*)(out + (size_t)t * 16 + 4 * q) = f32x4_t{acc[4 * b], acc[4 * b + 1], acc[4 * b + 2], acc[4 * b + 3]};
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int t = t0 + 4 * q + i;
-                if (t < T) out[(size_t)t * 64 + 16 * b + l16] = acc[4 * b + i];
-            }
+        } else {                                 // rows are tokens: token 4q + b of the wave's, experts 4 * l16 + 0..3
+            const int t = t0 + 4 * q + b;
+            if (t < T) *(f32x4_t*)(out + (size_t)t * 64 + 4 * l16) = f32x4_t{acc[b], acc[4 + b], acc[8 + b], acc[12 + b]};
         }
     }
 }
