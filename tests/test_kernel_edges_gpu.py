@@ -310,3 +310,37 @@ def test_selection_inside_the_gate_up_launch_with_infinite_and_nan_logits(T, E):
 def test_routing_in_one_workgroup(T, k, E, d, kind):
     cfg = replace(S.mini(S.C1 if kind == "c1" else S.C2, L=1, d=d, F=64, F_shared=0), E=E)
     run_and_check_layer(cfg, 0, T, k)
+
+
+@pytest.mark.parametrize("T,k,E,d,F,Fs,routed,shared", [
+    # the two jobs of a GEMM launch, as (gate/up, down) of each: both stream; routed streams beside shared tiles; the other way round;
+    # tiles of both, low, of 96 rows and tall; eight waves; more than 1024 tokens, together and one after the other
+    (20, 2, 64, 256, 192, 320, ("stream x4", "stream x4"), ("stream x4", "stream x4")),
+    (100, 1, 64, 256, 192, 320, ("stream x4", "stream x4"), ("128 rows x4", "128 rows x4")),
+    (40, 4, 60, 384, 192, 704, ("64 rows x4", "stream x4"), ("stream x4", "stream x4")),
+    (40, 8, 8, 1024, 448, 320, ("64 rows x4", "64 rows x4"), ("stream x4", "stream x4")),
+    (200, 4, 60, 384, 192, 2048, ("64 rows x4", "64 rows x4"), ("64 rows x4", "64 rows x4 cut")),
+    (65, 2, 2, 512, 576, 64, ("96 rows x4", "96 rows x4"), ("96 rows x4", "96 rows x4")),
+    (800, 8, 16, 1152, 448, 320, ("160 rows x4", "160 rows x4"), ("160 rows x4", "160 rows x4")),
+    (1000, 4, 4, 4096, 192, 192, ("64 rows x4", "160 rows x8"), ("64 rows x4", "128 rows x8")),
+    (2401, 8, 8, 1664, 192, 192, ("160 rows x4", "160 rows x8"), ("160 rows x4", "96 rows x4")),
+    (1100, 2, 16, 256, 192, 320, ("64 rows x4", "64 rows x4"), ("160 rows x4", "64 rows x4")),
+])
+@pytest.mark.parametrize("kind", [S.SHARED_UNGATED, S.SHARED_SIGMOID])
+def test_shared_expert_as_second_job_of_the_routed_launches(T, k, E, d, F, Fs, routed, shared, kind):
+    """Every combination of schedules the routed and the shared expert's GEMMs meet in, against the oracle."""
+    import numpy as np
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(S.C2, L=1, d=d, F=F), E=E, F_shared=Fs, shared_kind=kind)
+    dl, _ = device_and_host_layer(cfg, 0)
+    for gemm, want, want_shared in zip(("gate_up", "down"), routed, shared):
+        for sh, w in ((False, want), (True, want_shared)):
+            p = P.lexi_moe_gemm_plan(dl, T, k, gemm, shared=sh)
+            got = f"stream x{p['waves']}" if p["streams"] else f"{p['tile_rows']} rows x{p['waves']}" + (" cut" if p["ksplit"] > 1 else "")
+            assert w is None or got == w, (gemm, sh, got)
+    del dl
+    tokens = None
+    if T > 1000:
+        tokens = np.unique(np.concatenate([[0, 1, T - 2, T - 1], np.random.default_rng(T).integers(0, T, 60)])).astype(np.int32)
+    run_and_check_layer(cfg, 0, T, k, tokens=tokens)
