@@ -13,17 +13,22 @@
 
 namespace lexi {
 
-template <bool GATEUP, int NW>
+// TWO: a second job; else a grid of units x tiles (most workgroups of a launch that uses few experts end at once, and neither choose
+// a job nor divide before they do).
+template <bool GATEUP, int NW, bool TWO>
 __global__ void __launch_bounds__(NW * 64)
 ffn_stream_kernel(FfnJob routed, FfnJob shared) {
     __shared__ __attribute__((aligned(16))) f32x4_t red[NW][2][64];
-    int block = blockIdx.x;
-    const FfnJob j = pick_job(routed, shared, block);
-    const int units = j.features >> 4;
-    const int tile = block / units;
+    int unit = blockIdx.x, tile = blockIdx.y;
+    const FfnJob j = TWO ? pick_job(routed, shared, unit) : routed;
+    if (TWO) {
+        const int units = j.features >> 4, block = unit;
+        tile = block / units;
+        unit = block - tile * units;
+    }
     TileInfo ti;
     if (!fetch_tile<GATEUP ? 0 : 1>(j, tile, ti)) return;
-    stream_unit<GATEUP, NW>(j, ti, block - tile * units, red);
+    stream_unit<GATEUP, NW>(j, ti, unit, red);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -238,8 +243,13 @@ static hipError_t launch_stream(const FfnArgs& a, const FfnArgs* shared, hipStre
     } else {
         const int64_t units = (int64_t)(a.features / 16) * a.max_tiles + (shared ? (int64_t)(shared->features / 16) * shared->max_tiles : 0);
         const int K = shared && shared->K > a.K ? shared->K : a.K;
-        if (stream_waves(K, units, a.chained) == 8) hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, 8>), grid, dim3(512), 0, s, jr, js);
-        else hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, 4>), grid, dim3(256), 0, s, jr, js);
+        auto launch = [&](auto nw) {
+            constexpr int NW = decltype(nw)::value;
+            if (shared) hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, NW, true>), grid, dim3(NW * 64), 0, s, jr, js);
+            else hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, NW, false>), dim3(a.features / 16, a.max_tiles), dim3(NW * 64), 0, s, jr, js);
+        };
+        if (stream_waves(K, units, a.chained) == 8) launch(IntTag<8>{});
+        else launch(IntTag<4>{});
     }
     return hipGetLastError();
 }
