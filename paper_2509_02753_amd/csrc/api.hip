@@ -676,13 +676,14 @@ lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, 
         // streaming workgroups: four waves beside a tiled GEMM in the same launch, else by the units of the launch
         const bool bf = layer->dtype == LEXI_BF16, with_shared = layer->F_shared > 0;
         const bool routed_streams = down ? p.routed_streams : p.gateup_streams;
-        const int Ks = down ? layer->F_shared : layer->d, fs = down ? layer->d : layer->F_shared, fr = down ? layer->d : layer->F;
         const TilePlan &tr = down ? p.routed : p.gateup, &ts = down ? p.shared : p.shared_gateup;
-        int64_t units = (int64_t)(fr / 16) * max_tiles((int64_t)T * k, layer->E, tr.tile_rows);
-        if (with_shared) units += (int64_t)(fs / 16) * ((T + ts.tile_rows - 1) / ts.tile_rows);
-        const int Kr = down ? layer->F : layer->d, Kmax = with_shared && Ks > Kr ? Ks : Kr;
+        FfnArgs r{}, sh{};
+        r.K = down ? layer->F : layer->d; r.features = down ? layer->d : layer->F; r.chained = chained != 0;
+        r.max_tiles = (int)max_tiles((int64_t)T * k, layer->E, tr.tile_rows);
+        sh.K = down ? layer->F_shared : layer->d; sh.features = down ? layer->d : layer->F_shared; sh.chained = chained != 0;
+        sh.max_tiles = (T + ts.tile_rows - 1) / ts.tile_rows;
         const bool joined_tiles = with_shared && !(routed_streams && p.shared_streams) && !(shared ? tr.wide : ts.wide);
-        out->waves = !bf || joined_tiles ? 4 : stream_waves(Kmax, units, chained != 0);
+        out->waves = !bf || joined_tiles ? 4 : stream_launch_waves(r, with_shared ? &sh : nullptr);
     }
     return LEXI_OK;
 }

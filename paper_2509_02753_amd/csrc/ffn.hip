@@ -50,7 +50,9 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
     constexpr int WF = GATEUP ? 8 * WB : 16 * WB;    // output features of a wave
     constexpr int CB = NW * WF;                      // of the workgroup
     constexpr int ELD = CB + 8;                      // GATEUP: bf16 elements per row of the staged output tile
-    constexpr int LDS_ELEMS = (GATEUP && TT * ELD > 2 * TT * LDS_LD) ? TT * ELD : 2 * TT * LDS_LD;
+    constexpr int TILE_LDS = (GATEUP && TT * ELD > 2 * TT * LDS_LD) ? TT * ELD : 2 * TT * LDS_LD;
+    constexpr int UNIT_LDS = MIXED ? stream_eight_lds<GATEUP>(4) * (int)(sizeof(f32x4_t) / sizeof(bf16_t)) : 0;
+    constexpr int LDS_ELEMS = UNIT_LDS > TILE_LDS ? UNIT_LDS : TILE_LDS;
     __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS];
     auto lds_x = [&](int buf) { return lds + buf * (TT * LDS_LD); };
 
@@ -58,10 +60,11 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
     const FfnJob j = pick_job(routed, shared, block);
     TileInfo ti;
     if (MIXED && j.streams) {
-        static_assert(!MIXED || (NW == 4 && sizeof(lds) >= sizeof(f32x4_t) * NW * 2 * 64), "stream_unit's part sums");
+        static_assert(!MIXED || NW == 4, "");
         const int units = j.features >> 4, tile = block / units;
         if (!fetch_tile<GATEUP ? 0 : 1>(j, tile, ti)) return;
-        stream_unit<GATEUP, NW>(j, ti, block - tile * units, (f32x4_t(*)[2][64])lds);
+        stream_unit_of<GATEUP, NW, 8>(j, ti, block - tile * units, (f32x4_t*)lds,
+                                      [&](int r) { return j.row_token ? j.row_token[ti.row0 + r] : ti.row0 + r; });
         return;
     }
     const int K = j.K, features = j.features;

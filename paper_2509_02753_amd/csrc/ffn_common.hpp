@@ -32,11 +32,12 @@ struct FfnJob {
     size_t plane_stride;
     int K, features, M, tile_rows, ksplit, out_bf16, E;
     int streams;              // taken by the weight-streaming schedule, blocks ordered (tile, unit of 16 features)
+    int parts;                // there: parts a sum is taken in (streamed_parts)
     int blocks;               // workgroups of this job, a multiple of kXcds where a second job follows
 };
 inline FfnJob make_job(const FfnArgs& a, int blocks) {
     return FfnJob{a.in, a.row_token, a.w0, a.w1, a.sched, a.scatter, a.counts, a.out, a.plane_stride, a.K, a.features, a.M, a.tile_rows,
-                  a.ksplit > 1 ? a.ksplit : 1, a.out_bf16 ? 1 : 0, a.E, a.streaming ? 1 : 0, blocks};
+                  a.ksplit > 1 ? a.ksplit : 1, a.out_bf16 ? 1 : 0, a.E, a.streaming ? 1 : 0, streamed_parts(a), blocks};
 }
 // (by value: a conditional expression on two members would select between their addresses)
 template <typename T>
@@ -63,6 +64,7 @@ __device__ __forceinline__ FfnJob pick_job(const FfnJob& routed, const FfnJob& s
     j.ksplit = choose(first, shared.ksplit, routed.ksplit);
     j.out_bf16 = choose(first, shared.out_bf16, routed.out_bf16);
     j.streams = choose(first, shared.streams, routed.streams);
+    j.parts = choose(first, shared.parts, routed.parts);
     j.blocks = choose(first, shared.blocks, routed.blocks);
     return j;
 }
@@ -173,6 +175,19 @@ __device__ __forceinline__ bool fetch_item(int block, const int32_t* sched, int 
 // `row_of(r)`: the row of `in` behind the tile's row r.  MAXB: 16-row blocks a tile holds at most.
 template <int N> struct IntTag { static constexpr int value = N; };
 
+// Four features of an output row: act = silu(g) * u in bf16, or g.
+template <bool GATEUP>
+__device__ __forceinline__ void store_unit(void* out, size_t at, const f32x4_t& g, const f32x4_t& u) {
+    if (GATEUP) {
+        u32x2_t pk;
+        pk[0] = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
+        pk[1] = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
+        *(u32x2_t*)((bf16_t*)out + at) = pk;
+    } else {
+        *(f32x4_t*)((float*)out + at) = g;
+    }
+}
+
 template <bool GATEUP, int NW, int MAXB, typename RowOf>
 __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64], RowOf row_of) {
     const int lane = threadIdx.x & 63;
@@ -235,18 +250,8 @@ __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& til
 #pragma unroll
                     for (int w = 1; w < NW; ++w) u += red[w][1][lane];
                 }
-                const int r = tb * 16 + l16;  // lane owns token (lane % 16), features 4*(lane/16) + 0..3 of the unit
-                if (r < ti.rows) {
-                    const size_t row = (size_t)(ti.row0 + r);
-                    if (GATEUP) {
-                        u32x2_t pk;
-                        pk[0] = pack_bf16x2(silu(g[0]) * u[0], silu(g[1]) * u[1]);
-                        pk[1] = pack_bf16x2(silu(g[2]) * u[2], silu(g[3]) * u[3]);
-                        *(u32x2_t*)((bf16_t*)out + row * features + unit * 16 + kq * 4) = pk;
-                    } else {
-                        *(f32x4_t*)((float*)out + row * features + unit * 16 + kq * 4) = g;
-                    }
-                }
+                // lane owns token (lane % 16), features 4*(lane/16) + 0..3 of the unit
+                if (tb * 16 + l16 < ti.rows) store_unit<GATEUP>(out, (size_t)(ti.row0 + tb * 16 + l16) * features + unit * 16 + kq * 4, g, u);
             }
             __syncthreads();
         }
@@ -266,11 +271,106 @@ __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& til
         }
     }
 }
-template <bool GATEUP, int NW>
-__device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64]) {
-    const int32_t* row_token = j.row_token;
-    const int row0 = tile.row0;
-    stream_unit<GATEUP, NW, 8>(j, tile, unit, red, [&](int r) { return row_token ? row_token[row0 + r] : row0 + r; });
+
+// The same with the sum in eight parts by a workgroup of four waves: a wave takes two parts one after the other.  All parts of up to
+// MAXB row blocks meet in LDS at once (stream_eight_lds), and a wave finishes one block.  The loop over the two parts is not
+// unrolled and nothing of the first stays in registers, so that as many loads are in flight as in four parts: 20 tokens, k = 1, shared
+// width 5632, 4 layers 327 us (four parts 331; the first part kept in registers 351; a block of each part in turn 388), 40
+// tokens, d 1280, shared 1792 446 (452; 468; 495).
+template <bool GATEUP> constexpr int stream_eight_lds(int maxb) { return 8 * maxb * (GATEUP ? 2 : 1) * 64; }   // f32x4_t's
+
+template <bool GATEUP, int MAXB, typename RowOf>
+__device__ __forceinline__ void stream_unit_eight(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t* red, RowOf row_of) {
+    static_assert(MAXB <= 4, "a wave finishes one row block");
+    constexpr int NM = GATEUP ? 2 : 1;
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int l16 = lane & 15, kq = lane >> 4;
+    const int K = j.K, features = j.features, nkb = K >> 5;
+    TileInfo ti = tile;
+    const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
+    const bf16_t* a[2] = {(const bf16_t*)j.w0 + wbase, GATEUP ? (const bf16_t*)j.w1 + wbase : nullptr};
+
+    auto body = [&](auto ntb_tag) {
+        constexpr int NTB = decltype(ntb_tag)::value;
+        auto at = [&](int part, int tb, int m) { return red + (((part * NTB + tb) * NM + m) * 64 + lane); };
+        const bf16_t* xp[NTB];
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) {
+            const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
+            xp[tb] = (const bf16_t*)j.in + (size_t)row_of(ti.row0 - tile.row0 + rr) * K + kq * 8;
+        }
+#pragma unroll 1
+        for (int part = 2 * wave; part < 2 * wave + 2; ++part) {
+            f32x4_t acc[NM][NTB];
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb) acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            const int kb1 = (part + 1) * nkb / 8;
+            int kb = part * nkb / 8;
+            auto steps = [&](auto n) {                       // K blocks whose loads are in flight together
+#pragma unroll
+                for (int v = 0; v < decltype(n)::value; ++v, ++kb) {
+                    bf16x8_t w[NM];
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) w[m] = *(const bf16x8_t*)(a[m] + (size_t)kb * 512);
+#pragma unroll
+                    for (int tb = 0; tb < NTB; ++tb) {
+                        const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
+#pragma unroll
+                        for (int m = 0; m < NM; ++m) acc[m][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m], b, acc[m][tb], 0, 0, 0);
+                    }
+                }
+            };
+            constexpr int UNROLL = NTB <= 2 ? 8 : 4;
+            while (kb + UNROLL <= kb1) steps(IntTag<UNROLL>{});
+            if (UNROLL > 4 && kb + 4 <= kb1) steps(IntTag<4>{});
+            if (kb + 2 <= kb1) steps(IntTag<2>{});
+            if (kb < kb1) steps(IntTag<1>{});
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+                for (int m = 0; m < NM; ++m) *at(part, tb, m) = acc[m][tb];
+        }
+        __syncthreads();
+        if (wave < NTB) {                                    // the wave's row block, its parts in order
+            f32x4_t g = *at(0, wave, 0), u = GATEUP ? *at(0, wave, 1) : f32x4_t{};
+#pragma unroll
+            for (int part = 1; part < 8; ++part) {
+                g += *at(part, wave, 0);
+                if (GATEUP) u += *at(part, wave, 1);
+            }
+            if (wave * 16 + l16 < ti.rows)
+                store_unit<GATEUP>(j.out, (size_t)(ti.row0 + wave * 16 + l16) * features + unit * 16 + kq * 4, g, u);
+        }
+        __syncthreads();
+    };
+    const int row_end = ti.row0 + ti.rows;
+    for (; ti.row0 < row_end; ti.row0 += 16 * MAXB) {
+        ti.rows = min(16 * MAXB, row_end - ti.row0);
+        if constexpr (MAXB == 1) {
+            body(IntTag<1>{});
+        } else {
+            const int ntb = (ti.rows + 15) >> 4;
+            if (ntb <= 1) body(IntTag<1>{});
+            else if (ntb <= 2) body(IntTag<2>{});
+            else body(IntTag<4>{});
+        }
+    }
+}
+
+// A unit of one job of a launch that may hold two, in the parts the job has in a launch of its own: the bits of its rows do not depend
+// on the other job.  (A launch has eight waves only where every job takes eight parts.)
+template <bool GATEUP, int NW, int MAXB, typename RowOf>
+__device__ __forceinline__ void stream_unit_of(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t* red, RowOf row_of) {
+    if constexpr (NW == 4) {
+        if (j.parts == 8) {
+            stream_unit_eight<GATEUP, (MAXB < 4 ? MAXB : 4)>(j, tile, unit, red, row_of);
+            return;
+        }
+    }
+    stream_unit<GATEUP, NW, MAXB>(j, tile, unit, (f32x4_t(*)[2][64])red, row_of);
 }
 
 hipError_t launch_gateup_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);

@@ -18,7 +18,9 @@ namespace lexi {
 template <bool GATEUP, int NW, bool TWO>
 __global__ void __launch_bounds__(NW * 64)
 ffn_stream_kernel(FfnJob routed, FfnJob shared) {
-    __shared__ __attribute__((aligned(16))) f32x4_t red[NW][2][64];
+    // (a streaming shared expert has at most 64 rows, and so has every expert beside it)
+    constexpr int MAXB = TWO ? 4 : 8;
+    __shared__ __attribute__((aligned(16))) f32x4_t red[TWO && NW == 4 ? stream_eight_lds<GATEUP>(MAXB) : NW * 2 * 64];
     int unit = blockIdx.x, tile = blockIdx.y;
     const FfnJob j = TWO ? pick_job(routed, shared, unit) : routed;
     if (TWO) {
@@ -28,7 +30,9 @@ ffn_stream_kernel(FfnJob routed, FfnJob shared) {
     }
     TileInfo ti;
     if (!fetch_tile<GATEUP ? 0 : 1>(j, tile, ti)) return;
-    stream_unit<GATEUP, NW>(j, ti, unit, red);
+    auto row_of = [&](int r) { return j.row_token ? j.row_token[ti.row0 + r] : ti.row0 + r; };
+    if (TWO) stream_unit_of<GATEUP, NW, MAXB>(j, ti, unit, red, row_of);
+    else stream_unit<GATEUP, NW, MAXB>(j, ti, unit, (f32x4_t(*)[2][64])red, row_of);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -53,14 +57,14 @@ struct SelectArgs {
 template <int NW, int MAXT>
 __global__ void __launch_bounds__(NW * 64)
 select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
-    __shared__ __attribute__((aligned(16))) f32x4_t red[NW][2][64];
+    __shared__ __attribute__((aligned(16))) f32x4_t red[8 * 2 * 64];   // (of stream_unit_eight, or of eight waves)
     __shared__ uint64_t s_mask[MAXT];
     __shared__ uint8_t s_sel[MAXT][64];
     __shared__ int32_t s_off[64];
     const int lane = threadIdx.x & 63;
     if ((int)blockIdx.x < shared.blocks) {
         const int units = shared.features >> 4;
-        if ((int)blockIdx.x < units) stream_unit<true, NW, 1>(shared, TileInfo{0, 0, r.T}, blockIdx.x, red, [](int row) { return row; });
+        if ((int)blockIdx.x < units) stream_unit_of<true, NW, 1>(shared, TileInfo{0, 0, r.T}, blockIdx.x, red, [](int row) { return row; });
         return;
     }
     const int block = blockIdx.x - shared.blocks - 1;
@@ -108,7 +112,7 @@ select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
         const int tile = item / units;
         const int e = __builtin_ctzll(__ballot(count > 0 && rank == tile));
         const uint32_t tok = (uint32_t)__builtin_amdgcn_readlane((int)tokens, e);
-        stream_unit<true, NW, 1>(routed, TileInfo{e, __builtin_amdgcn_readlane(offset, e), __builtin_amdgcn_readlane(count, e)},
+        stream_unit_of<true, NW, 1>(routed, TileInfo{e, __builtin_amdgcn_readlane(offset, e), __builtin_amdgcn_readlane(count, e)},
                                  item - tile * units, red, [&](int row) {
             int src = 0;
 #pragma unroll
@@ -128,7 +132,7 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
                          r.row_token, r.gates};
     const dim3 grid((unsigned)(jr.blocks + js.blocks + 1));
     const bool few = r.T <= 8;
-    if (stream_waves(a.K, units + shared_units, a.chained) == 8) {
+    if (stream_launch_waves(a, shared) == 8) {
         if (few) hipLaunchKernelGGL((select_gateup_kernel<8, 8>), grid, dim3(512), 0, s, jr, js, sel);
         else hipLaunchKernelGGL((select_gateup_kernel<8, 16>), grid, dim3(512), 0, s, jr, js, sel);
     } else {
@@ -241,14 +245,12 @@ static hipError_t launch_stream(const FfnArgs& a, const FfnArgs* shared, hipStre
     if (!a.is_bf16) {
         hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, grid, dim3(256), 0, s, jr, js);
     } else {
-        const int64_t units = (int64_t)(a.features / 16) * a.max_tiles + (shared ? (int64_t)(shared->features / 16) * shared->max_tiles : 0);
-        const int K = shared && shared->K > a.K ? shared->K : a.K;
         auto launch = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;
             if (shared) hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, NW, true>), grid, dim3(NW * 64), 0, s, jr, js);
             else hipLaunchKernelGGL((ffn_stream_kernel<GATEUP, NW, false>), dim3(a.features / 16, a.max_tiles), dim3(NW * 64), 0, s, jr, js);
         };
-        if (stream_waves(K, units, a.chained) == 8) launch(IntTag<8>{});
+        if (stream_launch_waves(a, shared) == 8) launch(IntTag<8>{});
         else launch(IntTag<4>{});
     }
     return hipGetLastError();

@@ -89,6 +89,12 @@ struct FfnArgs {
 // In the chained stack always four: which side of a bf16 rounding a block's input falls on may send a token to another
 // expert further down, so the order of a sum there must not depend on the batch the token is in.
 inline int stream_waves(int K, int64_t units, bool chained) { return !chained && (units <= 256 || K >= 8192) ? 8 : 4; }
+// Parts a streamed sum is taken in: the waves the GEMM has in a launch of its own.
+inline int streamed_parts(const FfnArgs& a) { return stream_waves(a.K, (int64_t)(a.features / 16) * a.max_tiles, a.chained); }
+// Waves of a launch of one or two streaming GEMMs: eight only where each takes eight parts (four waves can take eight parts, too).
+inline int stream_launch_waves(const FfnArgs& a, const FfnArgs* shared) {
+    return streamed_parts(a) == 8 && (shared == nullptr || streamed_parts(*shared) == 8) ? 8 : 4;
+}
 
 // `shared`: null, or the same GEMM of the layer's shared expert (dense, no scatter).  It goes into the routed one's launch, in front of
 // it, where both take the same kind of workgroup (ffn_joins); otherwise it gets a launch of its own.  One launch instead of two: a

@@ -344,3 +344,56 @@ def test_shared_expert_as_second_job_of_the_routed_launches(T, k, E, d, F, Fs, r
     if T > 1000:
         tokens = np.unique(np.concatenate([[0, 1, T - 2, T - 1], np.random.default_rng(T).integers(0, T, 60)])).astype(np.int32)
     run_and_check_layer(cfg, 0, T, k, tokens=tokens)
+
+
+def _random_layer(d, E, F, Fs, seed, zero=()):
+    """An ungated layer of seeded weights (the same ones for the same seed and sizes), those named in `zero` all 0."""
+    import torch
+    import paper_2509_02753_amd as P
+    t = {}
+    shapes = dict(w_router=(d, E), w_gate=(E, F, d), w_up=(E, F, d), w_down=(E, d, F))
+    if Fs:
+        shapes.update(ws_gate=(Fs, d), ws_up=(Fs, d), ws_down=(d, Fs))
+    for n, shape in shapes.items():
+        gen = torch.Generator(device="cuda:0").manual_seed(seed + sum(map(ord, n)))
+        w = torch.empty(shape, device="cuda:0").normal_(0.0, 0.05, generator=gen)
+        t[n] = w if n == "w_router" else (w * (n not in zero)).to(torch.bfloat16)
+    return P.Layer.from_tensors(t)
+
+
+def _forward(dl, x, k):
+    import torch
+    import paper_2509_02753_amd as P
+    y = torch.empty((x.shape[0], dl.d), dtype=torch.float32, device="cuda:0")
+    P.lexi_moe_layer_forward(dl, x, y, k, P.alloc_workspace([dl], x.shape[0], k))
+    torch.cuda.synchronize()
+    return y
+
+
+@pytest.mark.parametrize("T,d,Fs", [(9, 256, 320), (16, 2176, 2816), (20, 256, 64), (33, 384, 704), (64, 2048, 1408), (64, 128, 4160)])
+def test_streamed_shared_expert_does_not_depend_on_the_routed_ones(T, d, Fs):
+    """Rows of the shared expert, bit for bit, beside routed experts of any number and width: in launches of four and eight waves and
+    beside tiles.  (Routed down weights of 0 leave the output to the shared expert.)"""
+    import torch
+    x = torch.empty((T, d), device="cuda:0").normal_(generator=torch.Generator(device="cuda:0").manual_seed(T)).to(torch.bfloat16)
+    want = _forward(_random_layer(d, 64, 64, Fs, 3, zero=("w_down",)), x, 1)
+    assert float(want.abs().max()) > 0.0
+    # few units: eight waves; many: four; more than two rows per expert: tiles
+    for E, F, k in ((16, 64, 1), (64, 1408, 1), (4, 192, 3), (8, 1408, 8)):
+        assert torch.equal(_forward(_random_layer(d, E, F, Fs, 3, zero=("w_down",)), x, k), want), (E, F, k)
+
+
+@pytest.mark.parametrize("T,k,E,d,F", [
+    (9, 2, 16, 256, 64), (16, 2, 16, 1152, 128), (24, 2, 24, 128, 64), (40, 3, 3, 640, 2624), (64, 2, 2, 512, 576),
+    (70, 1, 40, 128, 64), (120, 2, 2, 384, 448),     # beside shared tiles; the last of up to 120 rows per expert
+])
+def test_streamed_routed_experts_do_not_depend_on_the_shared_one(T, k, E, d, F):
+    """The same for the routed experts beside shared ones of several widths, against the layer without one."""
+    import torch
+    import paper_2509_02753_amd as P
+    x = torch.empty((T, d), device="cuda:0").normal_(generator=torch.Generator(device="cuda:0").manual_seed(T)).to(torch.bfloat16)
+    alone = _random_layer(d, E, F, 0, 5)
+    assert P.lexi_moe_gemm_plan(alone, T, k, "down")["streams"] == 1
+    want = _forward(alone, x, k)
+    for Fs in (64, 704, 5632):
+        assert torch.equal(_forward(_random_layer(d, E, F, Fs, 5, zero=("ws_down",)), x, k), want), Fs
