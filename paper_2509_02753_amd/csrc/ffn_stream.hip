@@ -350,11 +350,23 @@ down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w
             ++tile;
         }
     };
-    f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    // Short chains, so that the fp32 rounding is that of a sum in eight parts or less: the steps of a batch go to NA accumulators in
+    // turn, the batches are added up.  Error against 64 bits with the intermediate known exactly, 8 tokens, k 6, F 1408, shared 2816:
+    // 0.93e-7 (two accumulators 1.12e-7, one chain through the whole share 2.20e-7, every GEMM in eight parts 1.30e-7); d 4096, F 14336,
+    // k 2: 1.1e-7 (1.2, 4.7, 5.4).  Four are no slower than one: 8 layers, 8 tokens, k 6, shared 2816 975 -> 960 us.
+    constexpr int NA = 4;
+    const f32x4_t zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4_t acc[NA] = {zero, zero, zero, zero}, sum = zero;
+    auto add_up = [&]() {
+        sum = sum + ((acc[0] + acc[1]) + (acc[2] + acc[3]));
+#pragma unroll
+        for (int i = 0; i < NA; ++i) acc[i] = zero;
+    };
     auto flush = [&](int at) {                                   // this wave's part of the expert at place `at` is complete
+        add_up();
         // (HALF: lanes with bit 3 set hold the odd block, in rows 8..15; else they hold no row)
-        if (par == (HALF ? kq >> 1 : 0)) red[wave + at][kq][l8] = acc;
-        acc = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (par == (HALF ? kq >> 1 : 0)) red[wave + at][kq][l8] = sum;
+        sum = zero;
     };
     // The first n <= U steps of p and of q behind it, all their loads in flight together.
     auto batch = [&](const Part& p, const Part& q, int n, auto u_tag) {
@@ -372,7 +384,7 @@ down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w
         for (int u = 0; u < U; ++u) {
             if (u < n) {
                 if (u == p.n) flush(p.at);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u], acc, 0, 0, 0);
+                acc[u % NA] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[u], acc[u % NA], 0, 0, 0);
             }
         }
     };
@@ -400,6 +412,7 @@ down_combine_kernel(const bf16_t* __restrict__ act, const bf16_t* __restrict__ w
         s += n;
         const int at = n > p.n ? q.at : p.at;
         if (s == hi || at != tile) flush(at);
+        else add_up();
     }
     __syncthreads();
     // add the parts of every expert: thread (place in the list, row, quad)

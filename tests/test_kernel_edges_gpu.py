@@ -397,3 +397,34 @@ def test_streamed_routed_experts_do_not_depend_on_the_shared_one(T, k, E, d, F):
     want = _forward(alone, x, k)
     for Fs in (64, 704, 5632):
         assert torch.equal(_forward(_random_layer(d, E, F, Fs, 5, zero=("ws_down",)), x, k), want), Fs
+
+
+@pytest.mark.parametrize("T,k,E,d,F,Fs", [(1, 6, 64, 2048, 1408, 2816), (8, 6, 64, 2048, 1408, 2816), (4, 4, 60, 2048, 1408, 5632),
+                                          (4, 4, 64, 1280, 896, 1792), (8, 2, 8, 4096, 14336, 0), (5, 2, 32, 2560, 4544, 1216)])
+def test_down_and_combine_in_one_launch_sums_in_short_chains(T, k, E, d, F, Fs):
+    """fp32 rounding of the fused launch alone: token t is the unit vector e_t and all gate weights are 64, so an intermediate is
+    64 * w_up[:, t] exactly (a bf16 number).  A sum of n MFMA steps in c chains rounds about n / c * n / 2 partial sums, each at
+    up to 2^-24 of its size, so its error grows with sqrt(n / c): in eight parts or more it is 0.9e-7 to 1.3e-7 at n = 88
+    (seen here: 0.9e-7 to 1.1e-7), in the one or two chains of a wave's whole share 1.6e-7 to 5e-7."""
+    import torch
+    import paper_2509_02753_amd as P
+    gen = torch.Generator(device="cuda:0").manual_seed(11)
+    normal = lambda *s: torch.empty(s, device="cuda:0").normal_(0.0, 0.02, generator=gen)
+    full = lambda *s: torch.full(s, 64.0, device="cuda:0").to(torch.bfloat16)
+    t = dict(w_router=normal(d, E), w_gate=full(E, F, d), w_up=normal(E, F, d).to(torch.bfloat16), w_down=normal(E, d, F).to(torch.bfloat16))
+    if Fs:
+        t.update(ws_gate=full(Fs, d), ws_up=normal(Fs, d).to(torch.bfloat16), ws_down=normal(d, Fs).to(torch.bfloat16))
+    dl = P.Layer.from_tensors(t)
+    assert P.lexi_moe_gemm_plan(dl, T, k, "down")["fused"] == 1
+    x = torch.eye(T, d, device="cuda:0").to(torch.bfloat16)
+    y, rout = torch.empty((T, d), dtype=torch.float32, device="cuda:0"), P.RoutingOut(T, k, E)
+    P.lexi_moe_layer_forward(dl, x, y, k, P.alloc_workspace([dl], T, k), routing=rout)
+    torch.cuda.synchronize()
+    want = torch.zeros((T, d), dtype=torch.float64, device="cuda:0")
+    for i in range(T):
+        for s in range(k):
+            e = int(rout.topk_idx[i, s])
+            want[i] += rout.gates[i, s].double() * (t["w_down"][e].double() @ (64.0 * t["w_up"][e, :, i].double()))
+        if Fs:
+            want[i] += t["ws_down"].double() @ (64.0 * t["ws_up"][:, i].double())
+    assert float((y.double() - want).norm() / want.norm()) <= 1.4e-7
