@@ -156,7 +156,7 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
 template <bool GATEUP>
 __global__ void __launch_bounds__(256)
 ffn_f32_kernel(FfnJob routed, FfnJob shared) {
-    int block = blockIdx.x;
+    int block = blockIdx.y * gridDim.x + blockIdx.x;     // (those past the last find no tile)
     const FfnJob j = pick_job(routed, shared, block);
     const int K = j.K, features = j.features;
     const int column = block % (features >> 6);          // 64 features each
@@ -243,7 +243,10 @@ static hipError_t launch_stream(const FfnArgs& a, const FfnArgs* shared, hipStre
     if (jr.blocks + js.blocks <= 0) return hipSuccess;
     const dim3 grid((unsigned)(jr.blocks + js.blocks));
     if (!a.is_bf16) {
-        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, grid, dim3(256), 0, s, jr, js);
+        // tiles of 16 rows: 262143 tokens, d 4096, k = 17 have 17.8 million workgroups, and a dimension of a grid holds fewer than 2^32 threads
+        constexpr unsigned row = 1u << 20;
+        const dim3 rows(grid.x < row ? grid.x : row, (grid.x + row - 1) / row);
+        hipLaunchKernelGGL(ffn_f32_kernel<GATEUP>, rows, dim3(256), 0, s, jr, js);
     } else {
         auto launch = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;

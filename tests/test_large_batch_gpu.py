@@ -59,3 +59,34 @@ def test_combine_time_follows_the_bytes_of_a_ragged_width():
             seen.append(ev.stage_ms()[0][4])
         us.append(1e3 * float(np.median(seen)))
     assert us[1] <= 1.45 * us[0], us
+
+
+def test_fp32_down_gemm_of_more_workgroups_than_one_grid_dimension_holds():
+    """The most tokens of d = 4096 that an fp32 call takes, every expert selected (k = E = 17): 64 column blocks x 278544 tiles of 16
+    rows are 2^32 threads and more (in one dimension the launch went through and most rows stayed unwritten).  Outputs of the
+    first, the last and some other tokens against float64.  Bound: a chain of 4096 fp32 fused multiply-adds rounds by about 2^-24 *
+    sqrt(4096) / 2 = 1.9e-6 of the result's RMS, the product of two by 2.7e-6, five times that at the largest of 3 * 10^5
+    outputs: 1.4e-5 (seen: 1.1e-5)."""
+    import torch
+    import paper_2509_02753_amd as P
+    T, d, E, F = 262143, 4096, 17, 64
+    assert (d // 64) * (T * E // 16) * 256 >= 1 << 32
+    gen = torch.Generator(device="cuda:0").manual_seed(2)
+    normal = lambda sigma, *s: torch.empty(s, device="cuda:0").normal_(0.0, sigma, generator=gen)
+    t = dict(w_router=normal(0.02, d, E), w_gate=normal(0.02, E, F, d), w_up=normal(0.02, E, F, d), w_down=normal(0.02, E, d, F))
+    x = normal(1.0, T, d)
+    dl = P.Layer.from_tensors(t)
+    y = torch.full((T, d), float("nan"), device="cuda:0")
+    P.lexi_moe_layer_forward(dl, x, y, E, P.alloc_workspace([dl], T, E))
+    torch.cuda.synchronize()
+    assert not torch.isnan(y[:, ::64]).any()
+    at = torch.cat([torch.tensor([0, 1, T - 2, T - 1]), torch.randint(0, T, (60,), generator=torch.Generator().manual_seed(3))]).cuda()
+    xs = x[at].double()
+    gates = torch.softmax(xs @ t["w_router"].double(), dim=1)
+    want = torch.zeros((len(at), d), dtype=torch.float64, device="cuda:0")
+    for e in range(E):
+        h = torch.nn.functional.silu(xs @ t["w_gate"][e].double().T) * (xs @ t["w_up"][e].double().T)
+        want += gates[:, e:e + 1] * (h @ t["w_down"][e].double().T)
+    assert float((y[at].double() - want).abs().max() / want.square().mean().sqrt()) <= 1.4e-5
+    del x, y, dl
+    torch.cuda.empty_cache()
