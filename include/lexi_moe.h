@@ -155,11 +155,12 @@ lexi_status lexi_moe_stack_forward(const lexi_layer_t* layers, int32_t L, const 
                                    void* hip_stream, const lexi_routing_out_t* dbg_per_layer);
 
 /* Stage boundaries of one layer, for timing from outside with HIP events: the library records ev[i] on the
- * stream at boundary i.  0 = layer start, 1 = routing done (router, top-k, gates, permutation), 2 = gate/up GEMMs +
- * SwiGLU done (routed and shared experts), 3 = down GEMMs done, 4 = shared expert done (with 3: its GEMMs run with the
- * routed ones), 5 = combine done.  A NULL event is skipped.  Events are hipEvent_t handles owned by the caller (host
- * struct).  A call for a handful of tokens whose down projection and combine are one launch (it consumes the shared
- * expert's rows) records 4 BEFORE that launch and 3 and 5 after it. */
+ * stream at boundary i, in this order.  0 = layer start, 1 = routing done (router, top-k, gates, permutation; for at most
+ * 16 tokens, where the gate/up GEMM streams, only the router's partial sums: the rest is part of the gate/up launch), 2 =
+ * gate/up GEMMs + SwiGLU done (routed and shared experts), 3 = down GEMMs done, 4 = shared expert done (with 3: its GEMMs
+ * run with the routed ones), 5 = combine done (with 3 and 4 where a call for a handful of tokens has its down projections
+ * and the combine in one launch).  A NULL event is skipped.  Events are hipEvent_t handles owned by the caller (host
+ * struct). */
 #define LEXI_N_STAGE_EVENTS 6
 typedef struct {
     void* ev[LEXI_N_STAGE_EVENTS];

@@ -372,13 +372,10 @@ class StageEvents:
 
     def stage_ms(self):
         """After a synchronize: per-layer list of the 5 stage durations in milliseconds (routing, gate/up, down, shared,
-        combine).  Where the library recorded "shared expert done" before "down done" (down projection and combine in
-        one launch), the wait for the shared expert is the shared stage and the launch is the down stage."""
+        combine).  What shares a launch with an earlier stage counts there: the shared expert's GEMMs with the routed ones, for a
+        handful of tokens the combine with the down projections, and up to 16 tokens the selection with gate/up."""
         out = []
         for row in self.events:
             t = [row[0].elapsed_time(e) for e in row]
-            if t[4] < t[3]:
-                out.append([t[1], t[2] - t[1], t[3] - t[4], t[4] - t[2], t[5] - t[3]])
-            else:
-                out.append([t[i + 1] - t[i] for i in range(N_STAGE_EVENTS - 1)])
+            out.append([t[i + 1] - t[i] for i in range(N_STAGE_EVENTS - 1)])
         return out

@@ -438,8 +438,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         if (st != LEXI_OK) return st;
     }
     if (w.fused) {
-        // (one launch for both down projections and the combine: 4 = shared expert done is recorded before it, 3 and 5 after it)
-        if (ly.F_shared > 0) mark(4);
+        // (one launch for both down projections and the combine: 3, 4 and 5 are recorded behind it)
         DownCombineArgs f{};
         f.act = w.act; f.w_down = ly.w_down; f.F = ly.F; f.d = ly.d; f.T = T; f.k = k; f.sched = w.sched;
         f.counts = w.counts; f.E = ly.E;
@@ -447,9 +446,7 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         if (ly.F_shared > 0) { f.act_shared = w.act_shared; f.ws_down = ly.ws_down; f.F_shared = ly.F_shared; }
         f.y = y; f.y_bf16 = y_dtype == LEXI_BF16;
         if (launch_down_combine(f, s) != hipSuccess) return LEXI_ERR_LAUNCH;
-        mark(3);
-        if (ly.F_shared == 0) mark(4);
-        mark(5);
+        for (int i : {3, 4, 5}) mark(i);
         return LEXI_OK;
     }
 

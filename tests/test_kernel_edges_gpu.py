@@ -428,3 +428,20 @@ def test_down_and_combine_in_one_launch_sums_in_short_chains(T, k, E, d, F, Fs):
         if Fs:
             want[i] += t["ws_down"].double() @ (64.0 * t["ws_up"][:, i].double())
     assert float((y.double() - want).norm() / want.norm()) <= 1.4e-7
+
+
+@pytest.mark.parametrize("T,Fs", [(3, 320), (8, 64), (3, 0), (12, 320), (40, 320), (200, 320)])
+def test_stage_events_are_recorded_in_their_order(T, Fs):
+    """"Shared expert done" lies behind the launch that holds its down projection, also where that launch holds the combine."""
+    import torch
+    import paper_2509_02753_amd as P
+    dl = _random_layer(256, 64, 384, Fs, 1)
+    x = torch.zeros((T, 256), dtype=torch.bfloat16, device="cuda:0").normal_()
+    y = torch.empty((T, 256), dtype=torch.float32, device="cuda:0")
+    ws, ev = P.alloc_workspace([dl], T, 2), P.StageEvents(1)
+    assert P.lexi_moe_gemm_plan(dl, T, 2, "down")["fused"] == (T <= 8)
+    for _ in range(3):
+        P.lexi_moe_stack_forward([dl], [2], x, y, ws, stage_events=ev)
+        torch.cuda.synchronize()
+        at = [ev.events[0][0].elapsed_time(e) for e in ev.events[0]]
+        assert at == sorted(at) and at[3] > at[2], at
