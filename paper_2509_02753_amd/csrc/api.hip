@@ -666,21 +666,23 @@ lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, 
     out->direct = down && !shared && p.routed_direct;
     out->fused = down && !shared && p.routed_fused;
     if (down && p.routed_fused) {
-        out->waves = 16;
+        out->waves = down_combine_features(layer->d);
     } else if (!out->streams) {
         out->waves = t.wide ? 8 : 4;
     } else {
-        // streaming workgroups: four waves beside a tiled GEMM in the same launch, else by the units of the launch
-        const bool bf = layer->dtype == LEXI_BF16, with_shared = layer->F_shared > 0;
-        const bool routed_streams = down ? p.routed_streams : p.gateup_streams;
-        const TilePlan &tr = down ? p.routed : p.gateup, &ts = down ? p.shared : p.shared_gateup;
+        // the two jobs as the launcher sees them; a streaming one has four waves beside a tiled one in the same launch
+        const bool bf = layer->dtype == LEXI_BF16;
         FfnArgs r{}, sh{};
-        r.K = down ? layer->F : layer->d; r.features = down ? layer->d : layer->F; r.chained = chained != 0;
-        r.max_tiles = (int)max_tiles((int64_t)T * k, layer->E, tr.tile_rows);
-        sh.K = down ? layer->F_shared : layer->d; sh.features = down ? layer->d : layer->F_shared; sh.chained = chained != 0;
-        sh.max_tiles = (T + ts.tile_rows - 1) / ts.tile_rows;
-        const bool joined_tiles = with_shared && !(routed_streams && p.shared_streams) && !(shared ? tr.wide : ts.wide);
-        out->waves = !bf || joined_tiles ? 4 : stream_launch_waves(r, with_shared ? &sh : nullptr);
+        auto fill = [&](FfnArgs& f, const TilePlan& tp, bool streaming, int F, int64_t tiles) {
+            f.is_bf16 = bf; f.streaming = streaming; f.wide = tp.wide; f.chained = chained != 0;
+            f.K = down ? F : layer->d; f.features = down ? layer->d : F; f.max_tiles = (int)tiles;
+        };
+        const TilePlan &tr = down ? p.routed : p.gateup, &ts = down ? p.shared : p.shared_gateup;
+        fill(r, tr, down ? p.routed_streams : p.gateup_streams, layer->F, max_tiles((int64_t)T * k, layer->E, tr.tile_rows));
+        fill(sh, ts, p.shared_streams, layer->F_shared, (T + ts.tile_rows - 1) / ts.tile_rows);
+        const bool joined = layer->F_shared > 0 && ffn_joins(r, sh);
+        if (!bf || (joined && !(r.streaming && sh.streaming))) out->waves = 4;
+        else out->waves = joined ? stream_launch_waves(r, &sh) : streamed_parts(shared ? sh : r);
     }
     return LEXI_OK;
 }

@@ -465,10 +465,10 @@ hipError_t launch_down_combine(const DownCombineArgs& a, hipStream_t s) {
     if (a.T < 1 || a.T > kFusedDownMaxT || a.T * a.k > kFusedDownMaxRows || a.d % 128 != 0 || a.F % 64 != 0 ||
         (a.act_shared != nullptr && a.F_shared % 64 != 0))
         return hipErrorInvalidValue;
-    // 8 features each where that is at most one workgroup per CU; wider layers fill the chip with 16
-    const bool half = a.d <= 2048;
+    const int features = down_combine_features(a.d);
+    const bool half = features == 8;
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(a.d / (half ? 8 : 16)), dim3(half ? 512 : 1024), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
+        hipLaunchKernelGGL(kernel, dim3(a.d / features), dim3(features * 64), 0, s, (const bf16_t*)a.act, (const bf16_t*)a.w_down,
                            a.F, a.d, a.sched, a.counts, a.E, a.inv_perm, a.gates, (const bf16_t*)a.act_shared, (const bf16_t*)a.ws_down, a.F_shared, a.T,
                            a.k, a.y);
     };

@@ -141,6 +141,8 @@ hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 // order, then the shared expert's row, whose down projection is part of the launch.
 constexpr int kFusedDownMaxT = 8;      // beyond these the separate launches measured faster (more experts with rows than
 constexpr int kFusedDownMaxRows = 64;  // the d/16 workgroups of the fused launch can stream at full rate)
+// Output features of a workgroup: 8 where that is at most one workgroup per CU, else 16, with as many waves as features.
+inline int down_combine_features(int d) { return d <= 2048 ? 8 : 16; }
 struct DownCombineArgs {
     const void* act;           // [T*k][F] bf16, permuted rows
     const void* w_down;        // [E] packed matrices of [d][F]

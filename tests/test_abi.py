@@ -234,6 +234,21 @@ def test_tile_plans(T, k, E, d, F, gate_up, down):
             assert want[0] in (None, p["tile_rows"]) and p["waves"] == want[1], (which, p)
 
 
+@pytest.mark.parametrize("T,k,E,d,F,Fs,which,waves", [
+    # down projections and combine in one launch: as many waves as output features of a workgroup, 8 up to d = 2048
+    (1, 1, 8, 128, 704, 320, 1, 8), (8, 6, 64, 2048, 1408, 2816, 1, 8), (8, 6, 64, 2048, 1408, 2816, 3, 8), (4, 2, 64, 2048, 1408, 0, 1, 8),
+    (4, 2, 64, 2176, 1408, 0, 1, 16), (4, 2, 64, 4096, 1408, 320, 1, 16), (4, 2, 64, 4096, 1408, 320, 3, 16),
+    # two streaming jobs: eight where both sums have eight parts, four where one has; beside tiles four
+    (12, 1, 16, 256, 64, 320, 0, 8), (12, 1, 16, 256, 64, 320, 2, 8), (12, 2, 64, 256, 1408, 320, 0, 4), (12, 2, 64, 256, 1408, 320, 2, 4),
+    (40, 8, 8, 1024, 448, 320, 3, 4),
+])
+def test_waves_of_streaming_launches(T, k, E, d, F, Fs, which, waves):
+    import paper_2509_02753_amd as P
+    shared = dict(F_shared=Fs, shared_kind=1, ws_gate=0x80000, ws_up=0x90000, ws_down=0xA0000) if Fs else {}
+    p = gemm_plan(P, fake_layer(P, dtype=1, d=d, E=E, F=F, **shared), T, k, which)
+    assert p["streams"] == 1 and p["waves"] == waves
+
+
 def test_workspace_of_small_calls_has_not_grown():
     """The workspace was once laid out as these arrays, each at a multiple of 256 bytes, with 32 bytes per token tile of 128
     rows and a tile count; a caller that keeps a buffer of that size may go on using it."""
