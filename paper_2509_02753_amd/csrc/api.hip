@@ -134,8 +134,11 @@ TilePlan plan_down_tiles(int64_t rows, int groups, int K, int features, bool all
 }
 
 // Tokens up to which the shared expert's GEMMs take the routed GEMMs' kind of workgroup and tile height, so that each shares the
-// routed one's launch and form of the kernel (256 tokens: 1268 us at 128 rows, 1222 at the routed GEMMs' 64).  Beside streaming
-// or eight-wave routed GEMMs: 128 rows.  With more tokens a shared expert fills the chip by itself and keeps the tallest tiles.
+// routed one's launch and form of the kernel (256 tokens: 1268 us at 128 rows, 1222 at the routed GEMMs' 64).  Beside an eight-wave
+// routed GEMM 128 rows; beside a streaming one 64 for the down GEMM, whose form has four workgroups per CU instead of two: most of the
+// launch are units that stream (100 tokens, k = 1, 64 experts of F 1024, shared 1408, 4 layers: d 4096 1197 us at 128 rows, 1076 at
+// 64, two launches in turn 1376; d 2048 637, 592, 763.  Gate/up has two per CU at any height: 128 or 64 rows within 2 %).  With more tokens a
+// shared expert fills the chip by itself and keeps the tallest tiles.
 constexpr int kSharedJoinsMaxT = 1024;
 constexpr int kSharedTileRows = 128;
 constexpr int kMaxDevices = 16;
@@ -318,7 +321,8 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     if (ly.F_shared > 0 && !p.shared_streams) {
         p.shared = plan_down_tiles(T, 1, ly.F_shared, ly.d, true, false);
         if (T <= kSharedJoinsMaxT) {
-            p.shared = TilePlan{p.routed.wide, p.routed_streams || p.routed.wide ? kSharedTileRows : p.routed.tile_rows, p.shared.ksplit};
+            const int rows = p.routed_streams ? kHalfTileRows : p.routed.wide ? kSharedTileRows : p.routed.tile_rows;
+            p.shared = TilePlan{p.routed.wide, rows, p.shared.ksplit};
             if (!p.gateup_streams) p.shared_gateup.tile_rows = p.gateup.tile_rows;
         }
     }

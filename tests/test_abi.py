@@ -249,6 +249,17 @@ def test_waves_of_streaming_launches(T, k, E, d, F, Fs, which, waves):
     assert p["streams"] == 1 and p["waves"] == waves
 
 
+@pytest.mark.parametrize("T,k,E,d,F,Fs", [(65, 1, 33, 128, 64, 64), (100, 1, 64, 4096, 1024, 1408), (128, 1, 64, 2048, 1408, 5632),
+                                          (120, 2, 2, 384, 448, 1408), (200, 2, 16, 512, 448, 2816)])
+def test_shared_tiles_beside_a_streaming_down_gemm_are_low(T, k, E, d, F, Fs):
+    """Up to 64 rows the tile kernel has four workgroups per CU for the routed units of the launch, above two."""
+    import paper_2509_02753_amd as P
+    ly = fake_layer(P, dtype=1, d=d, E=E, F=F, F_shared=Fs, shared_kind=1, ws_gate=0x80000, ws_up=0x90000, ws_down=0xA0000)
+    assert gemm_plan(P, ly, T, k, 1)["streams"] == 1
+    p = gemm_plan(P, ly, T, k, 3)
+    assert (p["streams"], p["waves"], p["tile_rows"]) == (0, 4, 64)
+
+
 def test_workspace_of_small_calls_has_not_grown():
     """The workspace was once laid out as these arrays, each at a multiple of 256 bytes, with 32 bytes per token tile of 128
     rows and a tile count; a caller that keeps a buffer of that size may go on using it."""

@@ -316,7 +316,7 @@ def test_routing_in_one_workgroup(T, k, E, d, kind):
     # the two jobs of a GEMM launch, as (gate/up, down) of each: both stream; routed streams beside shared tiles; the other way round;
     # tiles of both, low, of 96 rows and tall; eight waves; more than 1024 tokens, together and one after the other
     (20, 2, 64, 256, 192, 320, ("stream x4", "stream x4"), ("stream x4", "stream x4")),
-    (100, 1, 64, 256, 192, 320, ("stream x4", "stream x4"), ("128 rows x4", "128 rows x4")),
+    (100, 1, 64, 256, 192, 320, ("stream x4", "stream x4"), ("128 rows x4", "64 rows x4")),
     (40, 4, 60, 384, 192, 704, ("64 rows x4", "stream x4"), ("stream x4", "stream x4")),
     (40, 8, 8, 1024, 448, 320, ("64 rows x4", "64 rows x4"), ("stream x4", "stream x4")),
     (200, 4, 60, 384, 192, 2048, ("64 rows x4", "64 rows x4"), ("64 rows x4", "64 rows x4 cut")),
