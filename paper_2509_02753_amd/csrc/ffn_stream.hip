@@ -148,10 +148,11 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
 // depend on how the work is dealt out.  v_mfma_f32_4x4x1_16b_f32 takes one element of the reduction per instruction, for
 // four token rows (broadcast) and 64 features (lane = feature): a wave owns 4 rows x 64 features, a workgroup 16 rows of a
 // tile, which is as high (more rows in a workgroup were walked one after the other).  fp32 is used at test scale (d 128, F 256,
-// 64 tokens, two experts each), where a launch is bound by round trips to memory: weights and x of 64 elements are requested a
-// step ahead, the first weights before the rows' numbers are known.  That layer's two GEMMs take 6.8 + 6.2 us (7.1 + 8.4 with
-// tiles of 160 rows and x requested when needed; 4 layers of d 384, F 384, 16 experts, 128 tokens, k = 4: call 486 -> 153 us; 1000
-// tokens, d 256, 2 layers 252 -> 125).  Cutting K over the waves is faster still (4.8 + 4.6 us) but not the same sum.
+// 64 tokens, two experts each), where a launch is bound by round trips to memory: weights are requested a block of 32 elements ahead, x
+// a step of 64, the first weights before the rows' numbers are known (against tiles of 160 rows and x requested when needed: 4
+// layers of d 384, F 384, 16 experts, 128 tokens, k = 4 486 -> 153 us).  Weights 64 elements ahead take twice the registers (one wave
+// per SIMD) and more loads than the counter of loads in flight holds: 2 % more over 70 random layers, at worst 8 % (14 tokens, 3
+// experts of d 384, F 384: 27.2 -> 29.3 us; that test-scale layer 22.3 -> 23.2).  Cutting K over the waves is faster, but not the same sum.
 // ---------------------------------------------------------------------------------------------------------
 template <bool GATEUP>
 __global__ void __launch_bounds__(256)
@@ -171,57 +172,54 @@ ffn_f32_kernel(FfnJob routed, FfnJob shared) {
     // of 8, 128 floats apart
     const size_t slab = (size_t)ti.expert * (features >> 4) + column * 4 + (lane >> 4);
     const float* wp[2] = {w0 + slab * ((size_t)K * 16) + (lane & 15) * 8, GATEUP ? w1 + slab * ((size_t)K * 16) + (lane & 15) * 8 : nullptr};
-    struct Step {                                        // 64 elements of the reduction: weights of the lane's feature, an octet of x
-        f32x4_t w[2][NM][4][2], x[2];
-    };
-    auto fetch_w = [&](Step& s, int k0) {
+    struct Block { f32x4_t v[NM][4][2]; };               // 32 elements of the reduction: weights of the lane's feature
+    auto fetch_w = [&](Block& b, int kb) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int m = 0; m < NM; ++m)
 #pragma unroll
-            for (int m = 0; m < NM; ++m)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) s.w[b][m][q][h] = *(const f32x4_t*)(wp[m] + (size_t)k0 * 16 + b * 512 + q * 128 + 4 * h);
+                for (int h = 0; h < 2; ++h) b.v[m][q][h] = *(const f32x4_t*)(wp[m] + (size_t)kb * 512 + q * 128 + 4 * h);
     };
     for (int r0 = wave * 4; r0 < ti.rows; r0 += 16) {   // (no barrier in this kernel)
         const int rr = min(r0 + (lane & 3), ti.rows - 1);   // rows past the tile's end re-read its last row; never stored
         const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
-        Step s[2];                                       // one step in use, the next on its way
-        fetch_w(s[0], 0);
+        Block w[2];
+        fetch_w(w[0], 0);
         __builtin_amdgcn_sched_barrier(0);               // (in front of the wait for the row's number)
         const float* xp = in + (size_t)src_row * K + ((lane >> 2) & 7) * 8;   // octet (lane / 4) % 8 of 64 elements
-        auto fetch_x = [&](Step& s, int k0) {
-            s.x[0] = *(const f32x4_t*)(xp + k0);
-            s.x[1] = *(const f32x4_t*)(xp + k0 + 4);
+        f32x4_t x[2][2];                                 // of 64 elements, and of the next 64
+        auto fetch_x = [&](f32x4_t (&v)[2], int k0) {
+            v[0] = *(const f32x4_t*)(xp + k0);
+            v[1] = *(const f32x4_t*)(xp + k0 + 4);
         };
-        fetch_x(s[0], 0);
+        fetch_x(x[0], 0);
         f32x4_t acc[NM];
 #pragma unroll
         for (int m = 0; m < NM; ++m) acc[m] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        auto octet = [&](const Step& s, auto o) {       // elements 8 * O .. + 7 of the step
+        auto octet = [&](const Block& b, const f32x4_t (&xv)[2], auto o) {
             constexpr int O = decltype(o)::value;
 #pragma unroll
             for (int e = 0; e < 8; ++e)
 #pragma unroll
                 for (int m = 0; m < NM; ++m)
-                    acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(s.x[e >> 2][e & 3], s.w[O >> 2][m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
+                    acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[e >> 2][e & 3], b.v[m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
         };
-        auto step = [&](Step& now, Step& next, int k0) {
-            const int kn = min(k0 + 64, K - 64);         // (K is a multiple of 64; the last one is fetched again, unused)
-            fetch_w(next, kn);
-            fetch_x(next, kn);
-            __builtin_amdgcn_sched_barrier(0);           // the next step's loads in front of this one's chain
-            octet(now, IntTag<0>{}); octet(now, IntTag<1>{}); octet(now, IntTag<2>{}); octet(now, IntTag<3>{});
-            octet(now, IntTag<4>{}); octet(now, IntTag<5>{}); octet(now, IntTag<6>{}); octet(now, IntTag<7>{});
+        auto step = [&](const f32x4_t (&now)[2], f32x4_t (&next)[2], int k0) {
+            fetch_w(w[1], (k0 >> 5) + 1);
+            fetch_x(next, min(k0 + 64, K - 64));         // (the last ones are not used)
+            __builtin_amdgcn_sched_barrier(0);           // the next block's loads in front of this one's chain
+            octet(w[0], now, IntTag<0>{}); octet(w[0], now, IntTag<1>{}); octet(w[0], now, IntTag<2>{}); octet(w[0], now, IntTag<3>{});
+            fetch_w(w[0], min((k0 >> 5) + 2, (K >> 5) - 1));
             __builtin_amdgcn_sched_barrier(0);
+            octet(w[1], now, IntTag<4>{}); octet(w[1], now, IntTag<5>{}); octet(w[1], now, IntTag<6>{}); octet(w[1], now, IntTag<7>{});
         };
         int k0 = 0;
         for (; k0 + 128 <= K; k0 += 128) {
-            step(s[0], s[1], k0);
-            step(s[1], s[0], k0 + 64);
+            step(x[0], x[1], k0);
+            step(x[1], x[0], k0 + 64);
         }
-        if (k0 < K) step(s[0], s[1], k0);
+        if (k0 < K) step(x[0], x[1], k0);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (r0 + i < ti.rows) {
