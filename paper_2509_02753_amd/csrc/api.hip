@@ -185,7 +185,7 @@ struct Workspace {
     void *act, *act_shared, *u;
     int slot_planes = 1, shared_planes = 1;   // planes of y_slot / y_shared the last launches wrote
     bool direct = false;                      // the routed down GEMM wrote the layer's output itself
-    bool fused = false;                       // the caller launches down + combine as one kernel (run_routed stopped after gate/up)
+    bool fused = false;                       // the caller launches down + combine as one kernel (run_experts stopped after gate/up)
     size_t bytes;
 };
 

@@ -26,8 +26,8 @@ namespace lexi {
 //   Gate/up launches, whose items are shorter, gained nothing from it (between -6 and +15 %).
 //   Low tiles (a launch that reads weights for a few rows) have forms of their own.  Up to 96 rows the first weights are
 //   requested before the rows' numbers have arrived.  Up to 64 rows a DOWN wave takes 32 features instead of 64, in 128
-//   registers, four workgroups per CU: a CU streams at most 32 to 48 GB/s, so a launch takes as long as the CU with the most
-//   bytes, and its few column blocks (d / 256) deal out badly.  K 1408, d 2048: 24 experts 29.4 -> 29.0 us, 40: 51.6 -> 46.4, 48:
+//   registers, four workgroups per CU: a CU by itself reads at most 45 GB/s from HBM (22 where all 256 do), so a launch takes as
+//   long as the CU with the most bytes, and its few column blocks (d / 256) deal out badly.  K 1408, d 2048: 24 experts 29.4 -> 29.0 us, 40: 51.6 -> 46.4, 48:
 //   57.6 -> 52.7, 60: 65.3 -> 66.4; K 896, d 1280, 64 experts: 40.9 -> 36.9.  (GATEUP has four times the items: -6 to +8 %.)
 //   GATEUP: a wave's blocks 0,1 are gate rows g0..g0+31 and blocks 2,3 the matching up rows, so the epilogue is
 //   silu(gate)*up -> bf16 act[row][f]; a workgroup of four waves covers 128 hidden features.

@@ -42,8 +42,9 @@ ffn_stream_kernel(FfnJob routed, FfnJob shared) {
 // a token are 64 bits, so counts, offsets, an expert's tokens and the tile's expert are a few bit operations.  One workgroup
 // writes the routing for the launches behind.  The workgroups take units of 16 features in steps of the grid, at most
 // kSelectBlocks of them (most tokens use far fewer experts than they might), the shared expert's come first.
-// Whole calls of 8 layers (us): one token, k 2 to 6 302 -> 265; 8 tokens, k = 6 643 -> 590; 16 tokens, k = 2 466 -> 424, k = 6 829 ->
-// 798, k = 8 without a shared expert 1231 -> 1203.
+// Whole calls of 8 layers when it was made (us): one token, k 2 to 6 302 -> 265; 8 tokens, k = 6 643 -> 590; 16 tokens, k = 2 466 -> 424,
+// k = 6 829 -> 798, k = 8 without a shared expert 1231 -> 1203.  What every workgroup reads grows with T * d, but so does what it streams:
+// 10 to 16 tokens, k 4 to 8, d 3072 1 to 3 % less than with the launch, d 4096 to 8192 -1 to +2 %.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kSelectBlocks = 1024;
 
@@ -150,7 +151,7 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
 // tile, which is as high (more rows in a workgroup were walked one after the other).  fp32 is used at test scale (d 128, F 256,
 // 64 tokens, two experts each), where a launch is bound by round trips to memory: weights are requested a block of 32 elements ahead, x
 // a step of 64, the first weights before the rows' numbers are known (against tiles of 160 rows and x requested when needed: 4
-// layers of d 384, F 384, 16 experts, 128 tokens, k = 4 486 -> 153 us).  Weights 64 elements ahead take twice the registers (one wave
+// layers of d 384, F 384, 16 experts, 128 tokens, k = 4 203 -> 123 us; 2 of d 256, 1000 tokens 220 -> 139).  Weights 64 elements ahead take twice the registers (one wave
 // per SIMD) and more loads than the counter of loads in flight holds: 2 % more over 70 random layers, at worst 8 % (14 tokens, 3
 // experts of d 384, F 384: 27.2 -> 29.3 us; that test-scale layer 22.3 -> 23.2).  Cutting K over the waves is faster, but not the same sum.
 // ---------------------------------------------------------------------------------------------------------
@@ -267,11 +268,12 @@ static hipError_t launch_stream(const FfnArgs& a, const FfnArgs* shared, hipStre
 // shared expert's row, exactly as the combine kernel does.  Fixed orders throughout: same bits on every run.
 // Eight features and eight rows fill a quarter of a 16 x 16 MFMA, so one instruction takes two K blocks at once: rows 0..7 of A
 // and columns 0..7 of B hold the even block, 8..15 the odd one (the two other quarters are not used).  That makes d / 8
-// workgroups: every CU of the chip streams at d = 2048, where 16 features each left half of them idle, and with 22 loads in
-// flight a wave's share is one or two round trips.  Wider layers fill the chip with 16 features each, whose blocks are read whole.
-// Whole calls of 8 layers against 16 features each, passes over the experts and the shared expert's down GEMM in a launch of its
-// own (us): one token, d 2048, F 1408, shared 2816, k 2 to 6 349 -> 306; k = 8, F 1024, no shared expert 303 -> 282; 8 tokens, k = 6,
-// shared 784 -> 643; 8 tokens, k = 8 1044 -> 916; one expert for one token 144 -> 146; d 4096, F 14336, k = 2 1135 -> 1143.
+// workgroups: every CU of the chip streams at d = 2048, where 16 features each left half of them idle, and with 22 steps (a load of
+// weights and one of rows each) in flight a wave's share is one or two round trips.  Wider layers fill the chip with 16 features each, whose blocks are read whole.
+// Against 16 features each, passes over the experts and the shared expert's down GEMM in a launch of its own, when it was made
+// (whole calls of 8 layers, us): one token, d 2048, F 1408, shared 2816, k 2 to 6 349 -> 306; k = 8, F 1024, no shared expert 303 -> 282;
+// 8 tokens, k = 6, shared 784 -> 643; one expert for one token 144 -> 146; d 4096, F 14336, k = 2 1135 -> 1143.  With the short chains
+// below one token, k = 8, F 1024 257, 8 tokens, k = 8 810, d 4096, F 14336, one expert, 4 layers 306.
 // ---------------------------------------------------------------------------------------------------------
 // HALF: 8 features and steps of 64 elements, else 16 features and steps of 32.
 template <bool Y_BF16, bool HALF>

@@ -101,7 +101,10 @@ inline int stream_launch_waves(const FfnArgs& a, const FfnArgs* shared) {
 // launch costs 4 to 5 us, a second stream 5 to 6 us at its fork and 6 to 10 at its join, and the two fill the last round together.
 // Whole calls, us: one token, 8 layers 375 -> 349; 16 tokens, 8 chained layers 726 -> 630; 64 tokens, 6 layers, shared width 5632
 // 1293 -> 1282; 256 tokens 1301 -> 1205; 777 tokens, d 1280 852 -> 852; 8192 tokens, 2 layers 1965 -> 1902 (two streams up to 1024
-// tokens, one after the other above, each time on the left).
+// tokens, one after the other above, each time on the left).  Other sizes against two streams: 9 to 64 tokens 2 to 15 % less, 65
+// to 128 tokens, k = 1 (streaming routed experts, tiles of 64 rows) 5 to 15 %; 72 to 1000 tokens with five shapes 0 to 23 % less at 35
+// sizes of 40, but 256 tokens, d 4096, 8 experts of F 2048, shared 4096 6 % more, 400 tokens, d 3456, 29 experts 4 %, 600 tokens 2 %: the other
+// stream ran the shared gate/up under the routing, and here a few hundred items fall unevenly on the CUs.
 inline bool ffn_joins(const FfnArgs& a, const FfnArgs& shared) {
     if (!a.is_bf16 || (a.streaming && shared.streaming)) return true;
     return a.streaming ? !shared.wide : shared.streaming ? !a.wide : a.wide == shared.wide;
@@ -139,9 +142,13 @@ hipError_t launch_combine(const CombineArgs& a, hipStream_t s);
 // Down projection and combine of a decode-sized batch in one launch (bf16 layers, T <= kFusedDownMaxT, T*k <=
 // kFusedDownMaxRows, shared expert absent or ungated): y[t] = sum_s gates[t][s] * (act[row(t, s)] . W_down[e]) in slot
 // order, then the shared expert's row, whose down projection is part of the launch.
-constexpr int kFusedDownMaxT = 8;      // beyond these the separate launches measured faster (more experts with rows than
-constexpr int kFusedDownMaxRows = 64;  // the d/16 workgroups of the fused launch can stream at full rate)
-// Output features of a workgroup: 8 where that is at most one workgroup per CU, else 16, with as many waves as features.
+// Limits: an expert's rows are the 8 columns of half an MFMA operand, all rows' features lie in LDS.  Up to them, against separate
+// launches, 4 layers, one to 8 tokens, k 1 to 16, with and without a shared expert: d 2048 7 to 14 % less time, d 4096 5 to 10 %; d 640, whose 80
+// workgroups leave most CUs idle, 3 to 15 % less up to 8 assignments, up to 15 % more with 16 to 64 of them.
+constexpr int kFusedDownMaxT = 8;
+constexpr int kFusedDownMaxRows = 64;
+// Output features of a workgroup: 8 where that is at most one workgroup per CU, else 16, with as many waves as features (8 at d 2176
+// to 4096, 8 layers, one to 8 tokens: 0 to 10 % more time).
 inline int down_combine_features(int d) { return d <= 2048 ? 8 : 16; }
 struct DownCombineArgs {
     const void* act;           // [T*k][F] bf16, permuted rows

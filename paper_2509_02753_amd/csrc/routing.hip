@@ -552,7 +552,11 @@ topk_scan_kernel(const float* partial, const float* __restrict__ bias, int T, in
 // router_topk_kernel leaves a token's partial with lane = expert, where it is added up and selected from.  The counting sort
 // needs no histograms: an expert's tokens are 64 bits.
 // Routing stage with events, one launch against three: 64 tokens, d 128, k = 2 11.1 us against 12.5.  One CU does all the work, at 1 us
-// per k and 2.7 us per further segment for 64 tokens: k = 6 15.1 / 13.2, d 256, k = 4 15.8 / 13.3; hence route_small's line at 192.
+// per k and 2.7 us per further segment for 64 tokens: k = 6 15.1 / 13.2, d 256, k = 4 15.8 / 13.3; hence the line at 192.  A fourth
+// segment costs more than it saves (8 fp32 layers, d 512, 1 to 12 tokens 157 to 188 us against 143 to 173), the third pays above 16
+// tokens (d 384, 17 tokens, 8 experts 160 / 163, 64 experts 166 / 182).  Up to 16 tokens one launch replaces two only: called from the host
+// it is the faster one (d 256, 2 tokens, k 8 148 / 160; d 384, 2 tokens, k 1 144 / 155), in a replayed graph the selection's k rounds
+// and the third segment cost 3 to 5 % (148 / 140, 144 / 140); few tokens of such narrow layers come from the host.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kSmallRouteSegs = 3;
 static bool route_small(int T, int k, int nseg) { return T <= kSmallRouterMaxT && nseg <= kSmallRouteSegs && T * (k + 3 * (nseg - 1)) <= 192; }

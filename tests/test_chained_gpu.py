@@ -163,7 +163,7 @@ def test_chained_mode_rejects_what_it_cannot_run():
 
 
 def test_chained_stack_replayed_from_a_hip_graph_matches_eager():
-    """The whole chain (normalisation, routing, expert GEMMs, shared expert on its side stream, combine + residual of
+    """The whole chain (normalisation, routing, expert GEMMs, shared expert in their launches, combine + residual of
     every block) captured once and replayed: every replay equals the eager result, with eager work in between."""
     import torch
     import paper_2509_02753_amd as P

@@ -325,6 +325,11 @@ def test_routing_in_one_workgroup(T, k, E, d, kind):
     (1000, 4, 4, 4096, 192, 192, ("64 rows x4", "160 rows x8"), ("64 rows x4", "128 rows x8")),
     (2401, 8, 8, 1664, 192, 192, ("160 rows x4", "160 rows x8"), ("160 rows x4", "96 rows x4")),
     (1100, 2, 16, 256, 192, 320, ("64 rows x4", "64 rows x4"), ("160 rows x4", "64 rows x4")),
+    # the shared reduction cut in two in eight-wave workgroups; selection in the gate/up launch, of four and of eight waves
+    (1000, 4, 4, 4096, 192, 2048, ("64 rows x4", "160 rows x8"), ("64 rows x4", "128 rows x8 cut")),
+    (9, 3, 60, 384, 1408, 704, ("stream x4", "stream x4"), ("stream x4", "stream x4")),
+    (12, 2, 64, 256, 192, 320, ("stream x4", "stream x4"), ("stream x4", "stream x4")),
+    (16, 1, 16, 256, 64, 320, ("stream x8", "stream x8"), ("stream x8", "stream x8")),
 ])
 @pytest.mark.parametrize("kind", [S.SHARED_UNGATED, S.SHARED_SIGMOID])
 def test_shared_expert_as_second_job_of_the_routed_launches(T, k, E, d, F, Fs, routed, shared, kind):

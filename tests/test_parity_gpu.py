@@ -138,11 +138,11 @@ def test_pack_weights_matches_the_documented_index(dtype):
 
 
 @pytest.mark.parametrize("name,T", [
-    ("c3_qwen15", 40),     # sigmoid-gated shared expert: the side stream is in the capture, joined before the combine
-    ("c5_dsv2lite", 4),    # ungated shared expert, a handful of tokens: joined before the launch that holds down + combine
+    ("c3_qwen15", 40),     # sigmoid-gated shared expert: second job of both GEMM launches, combine on its own
+    ("c5_dsv2lite", 4),    # ungated shared expert, a handful of tokens: three launches a layer, the last of them down + combine
 ])
 def test_stack_replayed_from_a_hip_graph_matches_eager(name, T):
-    """A captured stack call (side-stream fork/join of the shared expert included) replays to the eager result,
+    """A captured stack call (the shared expert's jobs included) replays to the eager result,
     every time, with eager work and synchronisations between the replays."""
     import torch
     import paper_2509_02753_amd as P
@@ -237,12 +237,12 @@ def test_stack_of_layers_with_different_shapes():
 
 
 def test_two_host_threads_on_two_streams():
-    """Two host threads drive the same layers on their own streams, workspaces and outputs (the shared expert's side
-    stream and its events are shared by all callers of a device): every result equals the single-threaded one."""
+    """Two host threads drive the same layers on their own streams, workspaces and outputs (the library keeps no
+    stream, event or lock of its own): every result equals the single-threaded one."""
     import threading
     import torch
     import paper_2509_02753_amd as P
-    cfg = S.mini(S.C3, L=3, d=256, F=384)    # sigmoid-gated shared expert -> side stream in every layer
+    cfg = S.mini(S.C3, L=3, d=256, F=384)    # sigmoid-gated shared expert: two jobs in every GEMM launch
     T = 48
     kv = cfg.k_lexi()
     dls = [device_and_host_layer(cfg, l)[0] for l in range(cfg.L)]
@@ -328,19 +328,19 @@ def test_down_gemm_schedules(name, d, F, F_shared, T, k, want_routed, want_share
 
 
 @pytest.mark.parametrize("name,T,k,want", [
-    ("c4_mixtral", 1, 1, 4),     # one expert with rows: its reduction is dealt out over all sixteen waves
+    ("c4_mixtral", 1, 1, 4),     # one expert with rows: its reduction is dealt out over all waves
     ("c4_mixtral", 1, 2, 4),     # two experts
-    ("c2_olmoe", 1, 3, 4), ("c2_olmoe", 2, 4, 4), ("c2_olmoe", 3, 5, 4),   # 3, up to 8, nine or more experts per pass
-    ("c5_dsv2lite", 8, 6, 4),    # more experts than one pass holds, ungated shared expert added in the same launch
-    ("c2_olmoe", 8, 8, 4),       # the most tokens and rows the fused launch takes (slots beyond the prefetched eight: none)
-    ("c2_olmoe", 4, 16, 4),      # sixteen slots per token: the second half of the slots is fetched in the combine loop
+    ("c2_olmoe", 1, 3, 4), ("c2_olmoe", 2, 4, 4), ("c2_olmoe", 3, 5, 4),   # 3 to 15 experts in the list
+    ("c5_dsv2lite", 8, 6, 4),    # more experts than waves, the ungated shared expert last in the list
+    ("c2_olmoe", 8, 8, 4),       # the most tokens and rows the fused launch takes (and LDS holds)
+    ("c2_olmoe", 4, 16, 4),      # sixteen slots per token
     ("c2_olmoe", 8, 9, 0),       # one row too many: separate down and combine launches
     ("c5_dsv2lite", 9, 2, 0),    # one token too many
     ("c3_qwen15", 4, 4, 0),      # sigmoid-gated shared expert: its coefficient is evaluated by the combine kernel
 ])
 def test_down_projection_with_the_combine_fused_for_a_handful_of_tokens(name, T, k, want):
-    """Decode-sized calls: the routed down projection forms y itself (plan value 4) -- every way of dealing the waves
-    out over the experts, several passes, the shared expert's rows -- and the sizes just outside that path."""
+    """Decode-sized calls: the routed down projection forms y itself (plan value 4) -- fewer and more experts than waves, the
+    shared expert's rows -- and the sizes just outside that path."""
     import paper_2509_02753_amd as P
     cfg = S.mini(S.CONFIGS[name], L=1, d=256, F=448)     # 14 K-blocks of 32: not divisible by 4, 8 or 16 waves
     dl, _ = device_and_host_layer(cfg, 0)
@@ -352,8 +352,8 @@ def test_down_projection_with_the_combine_fused_for_a_handful_of_tokens(name, T,
 @pytest.mark.parametrize("name,T", [("c5_dsv2lite", 3), ("c5_dsv2lite", 150), ("c2_olmoe", 2), ("c3_qwen15", 5)])
 def test_profiled_stack_records_its_stage_events_and_changes_nothing(name, T):
     """lexi_moe_stack_forward_profiled: the same bits as the plain stack call, and five stage durations per layer
-    that are non-negative and add up to the layer's span -- also where the shared expert's join is recorded before
-    the launch that holds both the down projection and the combine (T = 2, 3: ungated / no shared expert)."""
+    that are non-negative and add up to the layer's span -- also where one
+    launch holds both down projections and the combine (T = 2, 3: ungated / no shared expert)."""
     import torch
     import paper_2509_02753_amd as P
     cfg = S.mini(S.CONFIGS[name], L=3, d=256, F=384)
