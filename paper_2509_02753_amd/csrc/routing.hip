@@ -72,46 +72,21 @@ __device__ __forceinline__ void sum_partials(const float* __restrict__ partial, 
 }
 
 // Selection for the TOK tokens of a workgroup of NW waves, one lane per expert (E <= 64); this wave's are m0 .. m0 + TM - 1
-// with the logits (before the bias) `logit`.
-//   top-k: k rounds of {wave maximum by DPP, ballot of the lanes that hold it, lowest set bit} -- the lowest index among
-//   equal logits wins; comparisons are on floats, so +0 == -0.
-//   gates: softmax over the k selected logits.
+// with the logits (before the bias) `logit`: top-k and gates as pick_experts and gate_of give them.
 //   Each selected (token, slot) also gets its rank among the workgroup's earlier assignments to the same expert (tokens
 //   ascending), which is what makes the later scatter a stable counting sort without atomics.
 template <int TOK, int TM, int NW>
-__device__ __forceinline__ void select_experts(const float (&logit)[TM], const float* __restrict__ bias, int m0, int tok0,
+__device__ __forceinline__ void select_experts(float (&logit)[TM], const float* __restrict__ bias, int m0, int tok0,
                                                int T, int E, int k, int32_t (*hit)[64], int32_t* __restrict__ topk_idx,
                                                float* __restrict__ gates, int32_t* __restrict__ local_rank,
                                                int32_t* __restrict__ blk_hist) {
     const int lane = threadIdx.x & 63;
     const bool owner = m0 < TOK;
-    const bool lane_valid = lane < E;
-    float total[TM];
     int32_t sel[TM];            // lane s (< k): expert in slot s
     float val[TM];              // lane s (< k): its logit
     bool taken[TM];             // lane e: the token selected expert e
-    const float b = (bias != nullptr && lane_valid) ? bias[lane] : 0.0f;
-#pragma unroll
-    for (int m = 0; m < TM; ++m) {
-        total[m] = bias != nullptr ? logit[m] + b : logit[m];
-        // Inputs are finite by contract.  A NaN logit (one NaN or Inf activation is enough) compares unequal to every
-        // maximum, which would leave the ballot below empty and the expert index undefined; it ranks as -inf instead, so
-        // every round selects a valid expert (all-NaN row: experts 0..k-1) and the token's gates and output come out NaN.
-        total[m] = (total[m] == total[m]) ? total[m] : -INFINITY;
-        sel[m] = 0; val[m] = -INFINITY; taken[m] = false;
-    }
     if (owner) {
-        for (int s = 0; s < k; ++s) {
-#pragma unroll
-            for (int m = 0; m < TM; ++m) {   // (rows past T hold the last row's logits; they are dropped below)
-                const bool open = lane_valid && !taken[m];
-                const float mx = wave_max(open ? total[m] : -INFINITY);
-                const uint64_t holders = __ballot(open && total[m] == mx);
-                const int e_star = __builtin_ctzll(holders);
-                if (lane == e_star) taken[m] = true;
-                if (lane == s) { sel[m] = e_star; val[m] = mx; }
-            }
-        }
+        pick_experts<TM>(logit, bias, E, k, taken, sel, val);   // (rows past T hold the last row's logits; they are dropped below)
 #pragma unroll
         for (int m = 0; m < TM; ++m) hit[m0 + m][lane] = (taken[m] && tok0 + m0 + m < T) ? 1 : 0;   // (hit is [TOK][64])
     }
@@ -127,9 +102,7 @@ __device__ __forceinline__ void select_experts(const float (&logit)[TM], const f
     for (int m = 0; m < TM; ++m) {
         const int t = tok0 + m0 + m;
         if (t >= T) break;
-        const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val[m]), 0));   // slot 0 holds the largest
-        const float ex = (lane < k) ? __expf(val[m] - v0) : 0.0f;
-        const float g = ex / wave_sum(ex);
+        const float g = gate_of(val[m], k);
         if (lane < k) {
             // rank among the block's earlier assignments to the same expert (tokens ascending), which is what makes the
             // later scatter a stable counting sort without atomics
@@ -484,46 +457,31 @@ topk_scan_kernel(const float* partial, const float* __restrict__ bias, int T, in
     __shared__ int16_t s_rank[kFusedTailMaxA];  // assignments to that expert by earlier tokens
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool lane_valid = lane < E;
     if (wave == 0) s_seen[lane] = 0;
-    const float b = (bias != nullptr && lane_valid) ? bias[lane] : 0.0f;
     __syncthreads();
     for (int t0 = 0; t0 < T; t0 += 16) {
         const int t = t0 + wave;
         const bool live = t < T;                // wave-uniform
-        int32_t sel = 0;
-        bool hit = false;
+        int32_t sel[1] = {0};
+        bool hit[1] = {false};
         if (live) {
-            float sum[1];
             const int tt[1] = {t};
+            float sum[1], val[1];
             sum_partials<1>(partial, 64, tt, T, nseg, lane, sum);
-            float total = sum[0];
-            if (bias != nullptr) total = total + b;
-            total = (total == total) ? total : -INFINITY;   // a NaN logit ranks last (see select_experts)
-            float val = -INFINITY;
-            for (int s = 0; s < k; ++s) {
-                const bool open = lane_valid && !hit;
-                const float mx = wave_max(open ? total : -INFINITY);
-                const uint64_t holders = __ballot(open && total == mx);
-                const int e_star = __builtin_ctzll(holders);   // lowest index among equal logits
-                if (lane == e_star) hit = true;
-                if (lane == s) { sel = e_star; val = mx; }
-            }
-            const float v0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(val), 0));
-            const float ex = (lane < k) ? __expf(val - v0) : 0.0f;
-            const float g = ex / wave_sum(ex);
+            pick_experts<1>(sum, bias, E, k, hit, sel, val);
+            const float g = gate_of(val[0], k);
             if (lane < k) {
                 const size_t a = (size_t)t * k + lane;
-                topk_idx[a] = sel;
+                topk_idx[a] = sel[0];
                 gates[a] = g;
-                s_e[a] = (uint8_t)sel;
+                s_e[a] = (uint8_t)sel[0];
             }
         }
-        wave_hit[wave][lane] = hit ? 1 : 0;
+        wave_hit[wave][lane] = hit[0] ? 1 : 0;
         __syncthreads();
         if (live && lane < k) {
-            int32_t before = s_seen[sel];
-            for (int w = 0; w < wave; ++w) before += wave_hit[w][sel];
+            int32_t before = s_seen[sel[0]];
+            for (int w = 0; w < wave; ++w) before += wave_hit[w][sel[0]];
             s_rank[t * k + lane] = (int16_t)before;
         }
         __syncthreads();

@@ -26,7 +26,11 @@ __device__ __forceinline__ int32_t write_work_list(int32_t total, int E, const W
 }
 
 // The top-k of TM tokens by one wave (lane = expert): total[m] are the logits before the bias; lane e learns whether token m took
-// expert e, lane s < k the expert and the logit of slot s.
+// expert e, lane s < k the expert and the logit of slot s.  k rounds of {wave maximum by DPP, ballot of the lanes that hold it, lowest
+// set bit}: the lowest index among equal logits wins; comparisons are on floats, so +0 == -0.
+// Inputs are finite by contract.  A NaN logit (one NaN or Inf activation is enough) compares unequal to every maximum, which would
+// leave the ballot empty and the expert index undefined; it ranks as -inf instead, so every round selects a valid expert (all-NaN
+// row: experts 0..k-1) and the token's gates and output come out NaN.
 template <int TM>
 __device__ __forceinline__ void pick_experts(float (&total)[TM], const float* __restrict__ bias, int E, int k, bool (&taken)[TM],
                                              int32_t (&sel)[TM], float (&val)[TM]) {
@@ -36,7 +40,7 @@ __device__ __forceinline__ void pick_experts(float (&total)[TM], const float* __
 #pragma unroll
     for (int m = 0; m < TM; ++m) {
         if (bias != nullptr) total[m] = total[m] + b;
-        total[m] = total[m] == total[m] ? total[m] : -INFINITY;   // a NaN logit ranks last
+        total[m] = total[m] == total[m] ? total[m] : -INFINITY;
         taken[m] = false; sel[m] = 0; val[m] = -INFINITY;
     }
     for (int s = 0; s < k; ++s) {
