@@ -22,28 +22,12 @@ __device__ __forceinline__ void store_normalised(void* u, size_t idx, const f32x
     }
 }
 
-// Eight consecutive elements (16 or 32 bytes, 16-byte aligned), widened exactly.
-template <bool IS_BF16>
-__device__ __forceinline__ void load8(const void* p, size_t i, float (&v)[8]) {
-    if (IS_BF16) {
-        const u32x4_t w = *(const u32x4_t*)((const bf16_t*)p + i);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = __uint_as_float((e & 1) ? (w[e >> 1] & 0xFFFF0000u) : (w[e >> 1] << 16));
-    } else {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const f32x4_t w = *(const f32x4_t*)((const float*)p + i + 4 * h);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[4 * h + e] = w[e];
-        }
-    }
-}
-
 // One workgroup per token; each thread owns 4 consecutive output features in each of NP pieces of 1024.  For a sigmoid-gated
 // shared expert the workgroup first evaluates its token's gate coefficient 1 / (1 + exp(-(x[t] . w_sg))) itself (wave sums
-// by DPP, the four wave results added in wave order), which saves a launch.  It stands in front of the slot rows, so x and w_sg are
-// read 16 bytes a thread, one load each at d = 2048 (two bytes and eight loads: 64 tokens 7.7 -> 6.0 us, 8192 tokens, two slots 52
-// -> 42, four slots 92 -> 87; 4096 tokens, d 4096, two slots 61 -> 52).
+// by DPP, the four wave results added in wave order), which saves a launch.  It stands in front of the slot rows: a thread
+// adds up elements j, j + 256, ..., chains of d / 256 however narrow the row is, and requests eight of x and of w_sg together (one of each
+// at a time: 64 tokens 7.7 us instead of 6.0, 8192 tokens, two slots 52 instead of 42).  16 bytes a thread as eight neighbouring
+// elements are no faster (+-1 % of the call) and round differently; through LDS to the same sums they cost 0.4 us.
 // Bound by reading the k slot rows (HBM) for many tokens, by latency for few: the rows of GS slots in NP pieces are
 // requested together, and the shared expert's row and the hidden state before them (16 tokens, chained: 6.8 -> 4.0 us; 256
 // tokens: 6.5 -> 5.0 us).
@@ -64,12 +48,17 @@ combine_kernel(const float* __restrict__ y_slot, const int32_t* __restrict__ inv
     float coef = (y_shared != nullptr) ? 1.0f : 0.0f;
     if (y_shared != nullptr && w_shared_gate != nullptr) {
         float acc = 0.0f;
-        for (int j = threadIdx.x * 8; j < d; j += 2048) {
+        for (int j = threadIdx.x; j < d; j += 2048) {
             float a[8], b[8];
-            load8<X_BF16>(x, (size_t)t * d + j, a);
-            load8<X_BF16>(w_shared_gate, (size_t)j, b);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc = __builtin_fmaf(a[i], b[i], acc);
+            for (int m = 0; m < 8; ++m) {               // (past the row: element j again, unused)
+                const int e = j + 256 * m < d ? j + 256 * m : j;
+                a[m] = load_as_f32<X_BF16>(x, (size_t)t * d + e);
+                b[m] = load_as_f32<X_BF16>(w_shared_gate, (size_t)e);
+            }
+#pragma unroll
+            for (int m = 0; m < 8; ++m)
+                if (j + 256 * m < d) acc = __builtin_fmaf(a[m], b[m], acc);
         }
         const float ws = wave_sum(acc);
         if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = ws;

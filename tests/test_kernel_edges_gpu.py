@@ -450,3 +450,52 @@ def test_stage_events_are_recorded_in_their_order(T, Fs):
         torch.cuda.synchronize()
         at = [ev.events[0][0].elapsed_time(e) for e in ev.events[0]]
         assert at == sorted(at) and at[3] > at[2], at
+
+
+def _gate_logits(x, w, strided):
+    """x . w per token in fp32 as 256 threads add it up: thread j takes elements j, j + 256, ... (strided) or 8 j .. 8 j + 7 of every
+    2048, the 64 threads of a wave are added as a binary tree, the four waves in order.  (Products of bf16 numbers and their
+    sums with an fp32 number are exact in float64 at these exponents: one rounding per step, as a fused multiply-add.)"""
+    import numpy as np
+    T, d = x.shape
+    acc = np.zeros((T, 256), dtype=np.float32)
+    for e in range(d):
+        j = e % 256 if strided else (e % 2048) // 8
+        acc[:, j] = (acc[:, j].astype(np.float64) + x[:, e].astype(np.float64) * np.float64(w[e])).astype(np.float32)
+    v = acc.reshape(T, 4, 64)
+    while v.shape[2] > 1:
+        v = v[:, :, 0::2] + v[:, :, 1::2]
+    v = v[:, :, 0]
+    return ((v[:, 0] + v[:, 1]) + v[:, 2]) + v[:, 3]
+
+
+@pytest.mark.parametrize("d", [128, 384, 2048, 2176, 4096, 4224])
+def test_order_of_the_shared_gate_dot_product(d):
+    """The gate coefficient 1 / (1 + exp(-z)) at z around -20 is exp(z), whose logarithm gives z back: the exponent z * log2(e) (below
+    2^5) is rounded by up to 2^-20, 6.6e-7 of z, exp2 and the divide by 3 ulp or 3.6e-7 more; together 1.02e-6, where one ulp of
+    z is 1.9e-6.  The routed experts contribute 0."""
+    import numpy as np
+    import torch
+    import paper_2509_02753_amd as P
+    T, E, F, Fs = 70, 8, 64, 64
+    rng = np.random.default_rng(d)
+    bf = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.float32)).cuda().to(torch.bfloat16)
+    x = bf(rng.standard_normal((T, d)))
+    w = bf(rng.standard_normal(d) * 2.0 / np.sqrt(d))
+    xf = x.float().cpu().numpy()
+    wf = w.float().cpu().numpy()
+    # shift every token's x along w so that z lands near -20
+    x = bf(xf - np.outer((xf @ wf + 20.0) / (wf @ wf), wf))
+    xf = x.float().cpu().numpy()
+    t = dict(w_router=torch.zeros((d, E), device="cuda:0"), w_gate=bf(rng.standard_normal((E, F, d)) * 0.02),
+             w_up=bf(rng.standard_normal((E, F, d)) * 0.02), w_down=bf(np.zeros((E, d, F))), ws_gate=bf(rng.standard_normal((Fs, d)) * 0.1),
+             ws_up=bf(rng.standard_normal((Fs, d)) * 0.1), ws_down=bf(rng.standard_normal((d, Fs))))
+    plain = _forward(P.Layer.from_tensors(t), x, 2).double()             # coefficient 1
+    gated = _forward(P.Layer.from_tensors(dict(t, w_shared_gate=w)), x, 2).double()
+    c = ((gated * plain).sum(1) / (plain * plain).sum(1)).cpu().numpy()  # (least squares: the roundings of d outputs average out)
+    z = np.log(c) - np.log1p(-c)
+    want, other = (_gate_logits(xf, wf, s).astype(np.float64) for s in (True, False))
+    assert np.abs(want + 20.0).max() < 4.0
+    assert np.abs(z - want).max() <= 1.02e-6, (np.abs(z - want).max(), np.abs(z - other).max())
+    if d != 128:
+        assert (np.abs(want - other) > 2.0 ** -20).sum() > T // 8        # (another order would not pass)
