@@ -335,7 +335,7 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
 template <typename VEC>
 __global__ void __launch_bounds__(256)
 pack_kernel(const VEC* __restrict__ src, VEC* __restrict__ dst, int R, int K, size_t runs_total) {
-    const size_t run = (size_t)blockIdx.x * 256 + threadIdx.x;  // index of the destination run
+    const size_t run = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;  // index of the destination run
     if (run >= runs_total) return;
     const size_t runs_per_mat = (size_t)R * (K >> 3);
     const size_t mat = run / runs_per_mat;
@@ -350,12 +350,14 @@ pack_kernel(const VEC* __restrict__ src, VEC* __restrict__ dst, int R, int K, si
 hipError_t launch_pack(const void* src, void* dst, int64_t n_mat, int R, int K, bool is_bf16, hipStream_t s) {
     const size_t runs = (size_t)n_mat * R * (K >> 3);
     if (runs == 0) return hipSuccess;
-    const unsigned blocks = (unsigned)((runs + 255) / 256);
+    // (a dimension of a grid holds fewer than 2^32 threads: 68 GB of bf16 weights)
+    const size_t row = (size_t)1 << 20, n = (runs + 255) / 256;
+    const dim3 blocks((unsigned)(n < row ? n : row), (unsigned)((n + row - 1) / row));
     if (is_bf16) {
-        hipLaunchKernelGGL(pack_kernel<u32x4_t>, dim3(blocks), dim3(256), 0, s, (const u32x4_t*)src, (u32x4_t*)dst, R, K, runs);
+        hipLaunchKernelGGL(pack_kernel<u32x4_t>, blocks, dim3(256), 0, s, (const u32x4_t*)src, (u32x4_t*)dst, R, K, runs);
     } else {
         typedef __attribute__((ext_vector_type(8))) uint32_t u32x8_t;
-        hipLaunchKernelGGL(pack_kernel<u32x8_t>, dim3(blocks), dim3(256), 0, s, (const u32x8_t*)src, (u32x8_t*)dst, R, K, runs);
+        hipLaunchKernelGGL(pack_kernel<u32x8_t>, blocks, dim3(256), 0, s, (const u32x8_t*)src, (u32x8_t*)dst, R, K, runs);
     }
     return hipGetLastError();
 }

@@ -90,3 +90,26 @@ def test_fp32_down_gemm_of_more_workgroups_than_one_grid_dimension_holds():
     assert float((y[at].double() - want).abs().max() / want.square().mean().sqrt()) <= 1.4e-5
     del x, y, dl
     torch.cuda.empty_cache()
+
+
+def test_packing_of_more_runs_than_one_grid_dimension_holds():
+    """2^32 + 2^19 runs of eight bf16 weights (64 GiB and 8 MiB more): the first, the last and the matrices around run 2^32."""
+    import torch
+    import paper_2509_02753_amd as P
+    R, K, n = 1024, 4096, 8193
+    runs = R * K // 8
+    assert n * runs > 1 << 32 and (n - 1) * runs == 1 << 32
+    torch.cuda.empty_cache()
+    w = torch.empty((n, R, K), dtype=torch.int16, device="cuda:0")
+    some = [0, 1, 4095, 8190, 8191, 8192]
+    w.zero_()
+    for m in some:
+        w[m].random_(-(1 << 15), 1 << 15, generator=torch.Generator(device="cuda:0").manual_seed(m))
+    packed = P.lexi_pack_weights(w.view(torch.bfloat16)).view(torch.int16)
+    torch.cuda.synchronize()
+    for m in some:
+        # [row block][row][K block][octet][8] -> [row block][K block][octet][row][8]
+        want = w[m].view(R // 16, 16, K // 32, 4, 8).permute(0, 2, 3, 1, 4).reshape(R, K)
+        assert torch.equal(packed[m], want), m
+    del w, packed
+    torch.cuda.empty_cache()
