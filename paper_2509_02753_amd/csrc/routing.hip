@@ -3,6 +3,7 @@
 //
 // Paper Sec. 2: G(x) = Softmax(TopK[x * W_g]); k is a launch argument (Algorithm 1's UpdateTopk).
 #include "routing_common.hpp"
+#include <utility>
 
 namespace lexi {
 
@@ -118,12 +119,16 @@ __device__ __forceinline__ void select_experts(float (&logit)[TM], const float* 
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// The segment chains of router_partial_mfma_kernel and router_topk_kernel run on the matrix cores: the fp32 MFMAs with a
+// The segment chains of router_partial_mfma_kernel, router_topk_kernel and router_topk_lds_kernel run on the matrix cores: the fp32 MFMAs with a
 // reduction length of ONE give every accumulator exactly one fused multiply-add per instruction (same bits as fmaf,
 // denormals, infinities and NaN included), so the order above is kept at twice the rate of v_fma_f32.  Their blocks are
 // used as a broadcast: one operand (CBSZ) is taken by all blocks from the lanes ABID names.
 // ---------------------------------------------------------------------------------------------------------
+constexpr int kNarrowRouterMaxE = 16;       // up to so many experts above kFineRouterMaxT tokens: partials of 16 columns, through memory
+constexpr int kHalfRouterMaxT = 2048, kLdsRouterMaxT = 12288;
 template <int N> struct IntC { static constexpr int value = N; };
+template <typename F, int... N>
+__device__ __forceinline__ void for_each_number(F& f, std::integer_sequence<int, N...>) { (f(IntC<N>{}), ...); }
 
 // Eight consecutive elements of a row of x as loaded, and widened exactly.
 template <bool IS_BF16> struct Octet;
@@ -227,15 +232,113 @@ router_topk_kernel(const void* __restrict__ x, const float* __restrict__ w_route
     select_experts<TOK, 1, NW>(total, bias, wave, tok0, T, E, k, hit, topk_idx, gates, local_rank, blk_hist);
 }
 
-// router_partial_mfma_kernel (T > kFineRouterMaxT): segment partials of 8 waves' tokens; a workgroup takes one segment,
-// whose W (512 * E bytes) it keeps in LDS for all its tokens.
+// router_topk_lds_kernel (kFineRouterMaxT < T <= kLdsRouterMaxT, more than kNarrowRouterMaxE experts): the same for TOK = 8 or 16 tokens
+// per workgroup, so that W is pulled through a CU for enough of them.  A wave's segment of W comes to LDS in pieces of four rows, 16 bytes
+// per lane straight from memory, kWRing of them on their way, and is read back one row per element of the reduction: lane = expert.
+// The partials then take the ring's place.  Bound by the multiply-adds (6.9 us at T = 4096, d = 2048, 16 tokens on each CU) and the round
+// trips before and after them; twice the pieces on their way change nothing, and two workgroups per CU (64 registers) spill: 24 instead of 20 us.
+// Router and selection against partials through memory and a top-k launch, us, 64 experts, d 2048: T 1500, k 2 14.9 -> 10.9; T 2048, k 8
+// 16.1 -> 12.1; T 4096, k 8 26.2 -> 19.9, k 1 22.7 -> 16.8; T 8192, k 2 34.5 -> 32.0; d 4096, T 4096 33.6 -> 28.1.  Up to
+// kHalfRouterMaxT tokens 8 per workgroup put all CUs to work, above, W would be pulled twice through each.  A workgroup has its CU to itself, so what
+// it gains is used up by the rounds: T 6000 31.1 / 31.2, T 12000 49.1 / 47.6, d 512 21.4 / 20.0, but T 20000, d 512 27.4 / 31.8, hence
+// the line at kLdsRouterMaxT.
+constexpr int kWRing = 4, kWPiece = 256;         // floats of a piece: four rows of at most 64
+// 16 bytes per lane from `base` + lane_offset + offset to LDS, the lanes' one behind the other.  (A buffer load: the compiler takes a global
+// one for a flat access, and then waits for all loads in flight where it waits for one.)
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t lane_offset, uint32_t offset, float* to) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xFFFFFFFFu, 0x00020000),
+                                             (__attribute__((address_space(3))) void*)to, 16, lane_offset, offset, 0, 0);
+}
+// The four rows of ring place SLOT at LDS byte addresses at[]: N younger pieces may still be on their way.  (Written out: the compiler
+// would wait for all of them before a read that may touch the same array.)
+template <int SLOT, int N>
+__device__ __forceinline__ void read_piece(float (&w)[4], const uint32_t (&at)[4]) {
+    asm volatile("s_waitcnt vmcnt(%9)\n\t"
+                 "ds_read_b32 %0, %4 offset:%8\n\tds_read_b32 %1, %5 offset:%8\n\t"
+                 "ds_read_b32 %2, %6 offset:%8\n\tds_read_b32 %3, %7 offset:%8\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+                 : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "n"(SLOT * kWPiece * 4), "n"(N) : "memory");
+}
+
+template <bool IS_BF16, int TOK>
+__global__ void __launch_bounds__(1024)
+router_topk_lds_kernel(const void* __restrict__ x, const float* __restrict__ w_router, const float* __restrict__ bias, int T,
+                       int d, int E, int k, int32_t* __restrict__ topk_idx, float* __restrict__ gates,
+                       int32_t* __restrict__ local_rank, int32_t* __restrict__ blk_hist) {
+    constexpr int NW = 16, G = TOK / 4, NP = kRouterSegment / 4;
+    static_assert(TOK * 64 <= kWRing * kWPiece, "a wave's partials fit its part of the ring");
+    __shared__ __attribute__((aligned(16))) float ring[NW][kWRing * kWPiece];
+    __shared__ int32_t hit[TOK][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tok0 = blockIdx.x * TOK;
+    const int nseg = d / kRouterSegment;
+    float* own = ring[wave];
+    uint32_t at[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)                  // lanes >= E read a valid column; never used
+        at[r] = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) float*)own + (uint32_t)(r * E + min(lane, E - 1)) * 4u;
+    float total[1] = {0.0f};
+    for (int s0 = 0; s0 < nseg; s0 += NW) {
+        const int seg = s0 + wave, j0 = seg * kRouterSegment;
+        if (seg < nseg) {
+            Octet<IS_BF16> xo[G];                // rows past T re-read the last row; never used
+#pragma unroll
+            for (int g = 0; g < G; ++g) xo[g].load(x, (size_t)min(tok0 + 4 * g + (lane & 3), T - 1) * d + j0 + 8 * (lane >> 2));
+            const float* wseg = w_router + (size_t)j0 * E;
+            // (a piece is 16 * E bytes, one lane's 16 per expert; the lanes past them repeat the last)
+            auto fetch = [&](int i) { load_to_lds(wseg, (uint32_t)min(lane, E - 1) * 16u, (uint32_t)i * (uint32_t)E * 16u, own + (i % kWRing) * kWPiece); };
+#pragma unroll
+            for (int i = 0; i < kWRing; ++i) fetch(i);
+            float xf[G][8];
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) xf[g][e] = xo[g].get(e);
+            f32x4_t acc[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) acc[g] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+            auto piece = [&](auto i_tag) {       // elements 4i .. 4i + 3 of the segment
+                constexpr int I = decltype(i_tag)::value;
+                float w[4];
+                read_piece<I % kWRing, (NP - 1 - I < kWRing - 1 ? NP - 1 - I : kWRing - 1)>(w, at);
+                if constexpr (I + kWRing < NP) fetch(I + kWRing);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+#pragma unroll
+                    for (int g = 0; g < G; ++g)
+                        acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(xf[g][(4 * I + r) % 8], w[r], acc[g], 4, I / 2, 0);
+            };
+            for_each_number(piece, std::make_integer_sequence<int, NP>{});
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) own[(4 * g + i) * 64 + lane] = acc[g][i];
+        }
+        __syncthreads();
+        if (wave < TOK) {                        // the segments in order; the first partial is taken as is
+            const int n = min(NW, nseg - s0);
+            float p[NW];
+#pragma unroll
+            for (int s = 0; s < NW; ++s) p[s] = ring[s][wave * 64 + lane];   // (rows past the last segment are not used)
+            total[0] = s0 == 0 ? p[0] : total[0] + p[0];
+#pragma unroll
+            for (int s = 1; s < NW; ++s)
+                if (s < n) total[0] = total[0] + p[s];
+        }
+        __syncthreads();
+    }
+    select_experts<TOK, 1, NW>(total, bias, wave, tok0, T, E, k, hit, topk_idx, gates, local_rank, blk_hist);
+}
+
+// router_partial_mfma_kernel (T > kFineRouterMaxT; with more than kNarrowRouterMaxE experts T > kLdsRouterMaxT): segment partials of 8
+// waves' tokens; a workgroup takes one segment, whose W (512 * E bytes) it keeps in LDS for all its tokens.
 //   NARROW = false: v_mfma_f32_16x16x1_4b_f32 as four groups of 16 experts x 16 tokens; the tokens (rows) are broadcast: a
 //                   lane holds octets 4o + lane / 16 of token lane % 16.  16 tokens per wave; partial rows of 64 floats.
 //   NARROW = true (E <= 16): four groups of 16 tokens x 16 experts; the experts (rows) are broadcast: a lane holds
 //                   W[4j + lane / 16][lane % 16], and all of its own token's segment.  64 tokens per wave, rows of 16.
-// Bound by the multiply-adds (2*T*d*64 flop at 157 TFLOP/s: 6.9 us at T = 4096, d = 2048; with E <= 16 by reading x).  One
-// workgroup per token block with all segments, partials in LDS (no memory round trip, one launch less) is bound by pulling
-// all of W through every CU at 31 B/clk instead: 27 us with the selection.
+// Bound by the multiply-adds (2*T*d*64 flop at 157 TFLOP/s: 6.9 us at T = 4096, d = 2048; with E <= 16 by reading x).
 // Measured against register-tiled v_fma_f32 kernels: 19.0 us against 27.4 at T = 4096, d = 2048, 64 experts (32.7 against
 // 41.9 at T = 8192, 9.9 against 21.7 at T = 2048); NARROW 16.5 us against 20.4 at T = 4096, d = 4096, 8 experts.  W is
 // read from LDS eight registers ahead (one read per multiply-add, waited for at once, took 22.7 us).
@@ -612,9 +715,13 @@ route_small_kernel(const void* __restrict__ x, const float* __restrict__ w_route
 // ---------------------------------------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kNarrowRouterMaxE = 16;
 
-static int router_tokens_per_block(int T) { return T <= kSmallRouterMaxT ? 8 : T <= kFineRouterMaxT ? 4 : 16; }
+static bool lds_router(int T, int E) { return T > kFineRouterMaxT && T <= kLdsRouterMaxT && E > kNarrowRouterMaxE; }
+static int router_tokens_per_block(int T, int E) {
+    if (T <= kSmallRouterMaxT) return 8;
+    if (T <= kFineRouterMaxT) return 4;
+    return lds_router(T, E) && T <= kHalfRouterMaxT ? 8 : 16;
+}
 
 template <bool IS_BF16>
 static hipError_t launch_partials(const RoutingArgs& a, hipStream_t s) {
@@ -637,7 +744,7 @@ hipError_t launch_router_partials(const RoutingArgs& a, hipStream_t s) {
 
 hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
     const int nseg = a.d / kRouterSegment;
-    const int tb = router_tokens_per_block(a.T);
+    const int tb = router_tokens_per_block(a.T, a.E);
     const int nblk = (a.T + tb - 1) / tb;
     hipError_t err;
     if (route_small(a.T, a.k, nseg)) {
@@ -656,6 +763,19 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
         else
             hipLaunchKernelGGL(router_topk_kernel<false>, dim3(nblk), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E,
                                a.k, a.topk_idx, a.gates, a.local_rank, a.blk_hist);
+        err = hipGetLastError();
+    } else if (lds_router(a.T, a.E)) {
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(nblk), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E, a.k, a.topk_idx, a.gates,
+                               a.local_rank, a.blk_hist);
+        };
+        if (tb == 8) {
+            if (a.is_bf16) launch(router_topk_lds_kernel<true, 8>);
+            else launch(router_topk_lds_kernel<false, 8>);
+        } else {
+            if (a.is_bf16) launch(router_topk_lds_kernel<true, 16>);
+            else launch(router_topk_lds_kernel<false, 16>);
+        }
         err = hipGetLastError();
     } else {
         err = launch_router_partials(a, s);

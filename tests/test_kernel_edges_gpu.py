@@ -59,6 +59,16 @@ def test_router_at_block_and_segment_edges(T, E, d, k, kind):
     run_and_check_layer(cfg, 0, T, k)
 
 
+@pytest.mark.parametrize("T,E,d,k,kind", [
+    (1030, 17, 128, 1, "c1"), (2048, 64, 2176, 8, "c2"), (2049, 33, 4224, 3, "c2"), (2055, 64, 640, 64, "c1"), (4111, 17, 2048, 4, "c2"),
+    (12288, 40, 128, 2, "c2"), (12289, 40, 128, 2, "c2")])
+def test_router_of_a_thousand_tokens_and_more_at_its_edges(T, E, d, k, kind):
+    """Router and selection in one launch: 8 tokens per workgroup up to 2048, 16 above, partials through memory from 12289 on; a ragged last
+    workgroup, one segment to 33 (two passes of 16 waves and one more), rows of W of 17 to 64 floats.  The routing is compared bit for bit."""
+    cfg = replace(S.mini(S.C1 if kind == "c1" else S.C2, L=1, d=d, F=64, F_shared=0), E=E)
+    run_and_check_layer(cfg, 0, T, k, tokens=[0, T // 2, T - 1])
+
+
 def route(dl, T, k, gemm):
     """How a routed GEMM of a call is launched, as "<tile height> rows x<waves>" or "stream x<waves>"."""
     import paper_2509_02753_amd as P
@@ -195,6 +205,12 @@ def test_router_keeps_subnormal_products_and_sums(T, E, dtype):
     # (64 tokens that prefer one of 64 experts at random reach 40 of them)
     assert 0.0 < np.abs(ref.logits).max() < 2.0 ** -126 and len(np.unique(ref.topk_idx[:, 0])) >= E // 3
     check_routing(_route(dl, xd, k, E), ref)
+
+
+@pytest.mark.parametrize("T,E", [(2049, 64), (12289, 17)])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_router_of_many_tokens_keeps_subnormal_products_and_sums(T, E, dtype):
+    test_router_keeps_subnormal_products_and_sums(T, E, dtype)
 
 
 @pytest.mark.parametrize("T,E", ROUTER_RANGES)
