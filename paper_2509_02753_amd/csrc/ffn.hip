@@ -12,7 +12,7 @@ namespace lexi {
 
 // ---------------------------------------------------------------------------------------------------------
 // ffn_mfma_kernel<GATEUP, NW>
-//   Workgroup = NW waves; a token tile of up to 160 rows is shared by all waves through double-buffered LDS; each wave owns
+//   Workgroup = NW waves; a token tile of up to 160 rows is shared by all waves through LDS; each wave owns
 //   its own 64 weight rows (4 feature blocks of 16) against all rows of the tile (up to 10 token blocks): up to 40
 //   accumulator blocks of 16 x 16 (v_mfma_f32_16x16x32_bf16) in at most 256 registers per lane, two waves per SIMD.  Weight
 //   rows are not shared between waves and are stored in the packed layout, so their MFMA operand fragments go straight from
@@ -20,6 +20,11 @@ namespace lexi {
 //   The loop is bound by the bytes a CU pulls through its vector-memory path (it delivers 31 B/clk, against the 47 B/clk
 //   that 256 rows x 128 tokens would need at full matrix rate), so the tile is as tall as the registers allow: 160 tokens
 //   instead of 128 take 8 to 14 % off the gate/up launches (64 experts, d 2048, F 1024, 2048 tokens, k = 8: 154 -> 137 us).
+//   The tokens of a tall tile (more than 96 rows) go from memory to LDS directly, two K-steps ahead in a ring of three stages (tall_step): no
+//   registers, no LDS stores and no wait for them at a step's end.  Against the next step's tile through registers into the other of two
+//   buffers, same bits: 8 experts, d 4096, F 14336, 4096 tokens, k = 1 gate/up 817 -> 780 us, down 430 -> 407, k = 2 1510 -> 1485 and
+//   866 -> 827; 60 experts, F 1408, shared 5632, 8192 tokens, k = 4 620 -> 605 and 372 -> 364; 64 experts, d 2048, F 1024, 4096 tokens,
+//   k = 8 239 -> 237 and 172 -> 169.  (Low tiles gain nothing from it, 256 tokens behind a skewed router lose 3 %.)
 //   NW = 4: two workgroups share a CU and one's prologue/epilogue overlaps the other's MFMA loop.
 //   NW = 8 (DOWN): one workgroup per CU, a token row is fetched for 512 weight rows instead of 256.  8 experts, d 4096,
 //   F 14336, 4096 tokens: 950 -> 780 us (k = 2), 506 -> 400 us (k = 1); 64 experts, F 1024, 2048 tokens, k = 8: 102 -> 88 us.
@@ -42,6 +47,69 @@ namespace lexi {
 // ---------------------------------------------------------------------------------------------------------
 template <int S> struct StageTag { static constexpr int value = S; };
 
+typedef __attribute__((address_space(3))) bf16_t lds_bf16;
+
+// 16 bytes per lane from `base` + lane_offset + offset to LDS, the lanes' one behind the other.  (A buffer load: the compiler takes a global
+// one for a flat access, and then waits for all loads in flight where it waits for one.)
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t lane_offset, uint32_t offset, lds_bf16* to) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xFFFFFFFFu, 0x00020000),
+                                             (__attribute__((address_space(3))) void*)to, 16, lane_offset, offset, 0, 0);
+}
+
+// Until at most N of the wave's memory operations are on their way (they complete in order) and its LDS operations are done, then
+// until the other waves are there too.
+template <int N>
+__device__ __forceinline__ void wait_and_meet() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+// First of the 8 rows that wave `wave` of the workgroup stages in pass p of SR rows.  (Waves past the tile's TT rows repeat its last 8: all
+// waves then have the same number of loads on their way.)
+template <int SR, int TT>
+__device__ __forceinline__ int staged_row(int p, int wave) { return min(SR * p + wave * 8, TT - 8); }
+
+// One K-step on NTB token blocks of a tall tile: stage `rd` against the wave's weights `w`, which are replaced by the next step's as soon as
+// they are used; the tokens of two steps ahead are sent for stage `wr` first.  A stage is TT rows of 128 bytes, 16-byte piece c of row r at place
+// c ^ (r % 8), so that the fragment reads (frag0, frag1: the lane's first element in either half of a row) fall on all banks.
+// `rd` and `wr` are different stages of one array: restrict tells the compiler, which would else wait for all loads to LDS
+// before it reads a fragment.  More than 8 blocks leave too few of the 256 registers for all fragments of a half: two at a time, the next
+// pair read while the current one is multiplied.
+template <int NTB, int NX, int SR, int TT, int WB, int TB>
+__device__ __forceinline__ void tall_step(const lds_bf16* __restrict__ rd, lds_bf16* __restrict__ wr, f32x4_t (&acc)[WB][TB], bf16x8_t (&w)[WB][2],
+                                          const char* const (&wbase)[WB], uint32_t wnext, const void* in, const uint32_t (&xoff)[NX],
+                                          uint32_t xnext, int frag0, int frag1, int wave) {
+    constexpr int GB = NTB > 8 ? 2 : NTB;
+    constexpr int NG = (NTB + GB - 1) / GB;
+#pragma unroll
+    for (int p = 0; p < NX; ++p) load_to_lds(in, xoff[p], xnext, wr + staged_row<SR, TT>(p, wave) * BK);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        bf16x8_t b[2][GB];
+        auto read_group = [&](int g) {
+#pragma unroll
+            for (int u = 0; u < GB; ++u)
+                if (GB * g + u < NTB)
+                    b[g & 1][u] = *(const __attribute__((address_space(3))) bf16x8_t*)(rd + (GB * g + u) * 16 * BK + (ks ? frag1 : frag0));
+        };
+        read_group(0);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (g + 1 < NG) read_group(g + 1);
+            if (NG > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int fb = 0; fb < WB; ++fb)
+#pragma unroll
+                for (int u = 0; u < GB; ++u)
+                    if (GB * g + u < NTB)
+                        acc[fb][GB * g + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[fb][ks], b[g & 1][u], acc[fb][GB * g + u], 0, 0, 0);
+        }
+#pragma unroll
+        for (int fb = 0; fb < WB; ++fb) w[fb][ks] = *(const bf16x8_t*)(wbase[fb] + (wnext + (uint32_t)ks * 1024u));
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 template <bool GATEUP, int NW, int WB, int TT, bool MIXED>
 __global__ void __launch_bounds__(NW * 64, WB == 2 ? 4 : 2)
 ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
@@ -50,11 +118,11 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
     constexpr int WF = GATEUP ? 8 * WB : 16 * WB;    // output features of a wave
     constexpr int CB = NW * WF;                      // of the workgroup
     constexpr int ELD = CB + 8;                      // GATEUP: bf16 elements per row of the staged output tile
-    constexpr int TILE_LDS = (GATEUP && TT * ELD > 2 * TT * LDS_LD) ? TT * ELD : 2 * TT * LDS_LD;
+    constexpr int STAGES_LDS = LOW ? 2 * TT * LDS_LD : 3 * TT * BK;
+    constexpr int TILE_LDS = (GATEUP && TT * ELD > STAGES_LDS) ? TT * ELD : STAGES_LDS;
     constexpr int UNIT_LDS = MIXED ? stream_eight_lds<GATEUP>(4) * (int)(sizeof(f32x4_t) / sizeof(bf16_t)) : 0;
     constexpr int LDS_ELEMS = UNIT_LDS > TILE_LDS ? UNIT_LDS : TILE_LDS;
-    __shared__ __attribute__((aligned(16))) bf16_t lds[LDS_ELEMS];
-    auto lds_x = [&](int buf) { return lds + buf * (TT * LDS_LD); };
+    __shared__ __attribute__((aligned(128))) bf16_t lds[LDS_ELEMS];
 
     int block = blockIdx.x;
     const FfnJob j = pick_job(routed, shared, block);
@@ -116,21 +184,15 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
     }
     const uint32_t alane = lane * 16;
 
-    // ---- token tile staging: thread owns 16-byte chunk (tid % 8) of rows tid/8 + SR*p; where the last pass has rows for
-    //      half of the threads only, everyone takes 8-byte chunk (tid % 16) of row SR*XP + tid/16 instead (a branch there
-    //      would make the wait for the weights at its join a wait for all loads) ----
+    // ---- token tile staging: in pass p this thread takes 16 bytes of row staged_row(p) + lane / 8
     constexpr int SR = NW * 8;                       // token rows staged per pass of the workgroup
-    constexpr int XP = TT / SR;
-    constexpr bool HALF = TT % SR != 0;
-    static_assert(!HALF || TT % SR == SR / 2, "the last pass stages a whole or a half set of rows");
-    auto x_row = [&](int r) {   // the row of `in` behind tile row r
-        const int rr = min(r, ti.rows - 1);  // rows past the group end re-read its last row; never stored
-        return row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
-    };
-    int xrow[XP], xrow_half = 0;
+    constexpr int XP = (TT + SR - 1) / SR;
+    int xrow[XP];                                    // the rows of `in` behind them
 #pragma unroll
-    for (int p = 0; p < XP; ++p) xrow[p] = x_row((tid >> 3) + SR * p);
-    if (HALF) xrow_half = x_row((tid >> 4) + SR * XP);
+    for (int p = 0; p < XP; ++p) {
+        const int r = min(staged_row<SR, TT>(p, wave) + (lane >> 3), ti.rows - 1);   // rows past the group end re-read its last row; never stored
+        xrow[p] = row_token ? row_token[ti.row0 + r] : ti.row0 + r;
+    }
 
     // In the form for low tiles the first weights are requested here, while the rows' numbers and the code of the switch below
     // are still on their way (T 64, 60 experts: 1.5 % of the launch).  The form for tall ones requests them behind the switch:
@@ -153,95 +215,102 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
 
     // The K loop, specialised on the number of 16-token blocks the tile really holds: nothing is staged, read or multiplied
     // for blocks that would only hold padding.
-    // Up to 8 blocks: the tile of the next K-step is fetched at the top of a step and stored at its end, the token
-    // fragments of a half step are read together.  9 and 10 blocks leave too few of the 256 registers for that: fragments
-    // are read two blocks at a time, the next pair while the current one is multiplied, and (four waves) the tile is
-    // fetched and stored in two halves, one per half step.
-    auto k_loop = [&](auto ntb_tag) {
+    // Low tiles: the tile of the next K-step is fetched at the top of a step and stored at its end, the token fragments of a half
+    // step are read together.
+    auto low_loop = [&](auto ntb_tag) {
         constexpr int NTB = decltype(ntb_tag)::value;
-        constexpr bool TALL = NTB > 8;
-        constexpr int NP = (NTB * 16 + SR - 1) / SR < XP ? (NTB * 16 + SR - 1) / SR : XP;   // 16-byte passes of this tile
-        constexpr bool LAST_HALF = HALF && NTB * 16 > SR * XP;
-        constexpr int PARTS = TALL && !HALF ? 2 : 1;     // the passes are fetched in this many parts per K-step
-        constexpr int PP = (NP + PARTS - 1) / PARTS;
-        constexpr int GB = TALL ? 2 : NTB;               // token blocks whose fragments are read together
-        constexpr int NG = (NTB + GB - 1) / GB;
-        static_assert(KS == 2, "a K-step has two halves");
-        // (a different statement for each number: the compiler would move what they have in common in front of the switch)
-        if constexpr (!LOW) asm volatile("; %0 token blocks" ::"n"(NTB));
+        constexpr int NP = (NTB * 16 + SR - 1) / SR;     // passes of this tile
         bf16x8_t areg[WB][KS];
 #pragma unroll
         for (int fb = 0; fb < WB; ++fb)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                if constexpr (LOW) areg[fb][ks] = afirst[fb][ks];
-                else areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)ks * 1024u));
-            }
+            for (int ks = 0; ks < KS; ++ks) areg[fb][ks] = afirst[fb][ks];
         __builtin_amdgcn_sched_barrier(0);   // (the weights are on their way before the rows' numbers are waited for)
         // byte offsets from `in` (the launcher rejects inputs of 4 GiB or more)
-        uint32_t xoff[NP], xoff_half = 0;
+        uint32_t xoff[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) xoff[p] = (uint32_t)(((size_t)xrow[p] * K + (size_t)kstep0 * BK) * 2) + (tid & 7) * 16;
-        if (LAST_HALF) xoff_half = (uint32_t)(((size_t)xrow_half * K + (size_t)kstep0 * BK) * 2) + (tid & 15) * 8;
-        u32x4_t xreg[PP];
-        u32x2_t xreg_half;
-        auto load_x = [&](int kt, int h) {
+        auto lds_x = [&](int buf) { return lds + buf * (TT * LDS_LD); };
+        u32x4_t xreg[NP];
+        auto load_x = [&](int kt) {
 #pragma unroll
-            for (int p = 0; p < PP; ++p)
-                if (h * PP + p < NP) xreg[p] = *(const u32x4_t*)((const char*)in + (xoff[h * PP + p] + (uint32_t)kt * (BK * 2)));
-            if (LAST_HALF) xreg_half = *(const u32x2_t*)((const char*)in + (xoff_half + (uint32_t)kt * (BK * 2)));
+            for (int p = 0; p < NP; ++p) xreg[p] = *(const u32x4_t*)((const char*)in + (xoff[p] + (uint32_t)kt * (BK * 2)));
         };
-        auto store_x = [&](int buf, int h) {
+        auto store_x = [&](int buf) {
 #pragma unroll
-            for (int p = 0; p < PP; ++p)
-                if (h * PP + p < NP)
-                    *(u32x4_t*)(lds_x(buf) + ((tid >> 3) + SR * (h * PP + p)) * LDS_LD + (tid & 7) * 8) = xreg[p];
-            if (LAST_HALF) *(u32x2_t*)(lds_x(buf) + ((tid >> 4) + SR * XP) * LDS_LD + (tid & 15) * 4) = xreg_half;
+            for (int p = 0; p < NP; ++p) *(u32x4_t*)(lds_x(buf) + ((tid >> 3) + SR * p) * LDS_LD + (tid & 7) * 8) = xreg[p];
         };
-#pragma unroll
-        for (int h = 0; h < PARTS; ++h) {
-            load_x(0, h);
-            store_x(0, h);
-        }
+        load_x(0);
+        store_x(0);
         __syncthreads();
         for (int kt = 0; kt < nk; ++kt) {
             const int buf = kt & 1;
             const int kn = min(kt + 1, nk - 1);  // the last stage re-fetches itself: branch-free, in bounds, unused
+            load_x(kn);
+            __builtin_amdgcn_sched_barrier(0);   // keep the token-tile loads in front: they are consumed after the MFMAs
             // (waves of a ragged last column run the same loop on weight row 0 instead of branching around it)
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                if (ks < PARTS) load_x(kn, ks);
-                __builtin_amdgcn_sched_barrier(0);  // keep the token-tile loads in front: they are consumed after the MFMAs
-                bf16x8_t b[2][GB];
-                auto read_group = [&](int g) {
+                bf16x8_t b[NTB];
 #pragma unroll
-                    for (int u = 0; u < GB; ++u)
-                        if (GB * g + u < NTB)
-                            b[g & 1][u] = *(const bf16x8_t*)(lds_x(buf) + ((GB * g + u) * 16 + l16) * LDS_LD + ks * 32 + koff);
-                };
-                read_group(0);
+                for (int tb = 0; tb < NTB; ++tb) b[tb] = *(const bf16x8_t*)(lds_x(buf) + (tb * 16 + l16) * LDS_LD + ks * 32 + koff);
 #pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    if (g + 1 < NG) read_group(g + 1);
-                    if (TALL) __builtin_amdgcn_sched_barrier(0);
+                for (int fb = 0; fb < WB; ++fb)
 #pragma unroll
-                    for (int fb = 0; fb < WB; ++fb)
-#pragma unroll
-                        for (int u = 0; u < GB; ++u)
-                            if (GB * g + u < NTB)
-                                acc[fb][GB * g + u] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg[fb][ks], b[g & 1][u], acc[fb][GB * g + u], 0, 0, 0);
-                }
+                    for (int tb = 0; tb < NTB; ++tb)
+                        acc[fb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(areg[fb][ks], b[tb], acc[fb][tb], 0, 0, 0);
 #pragma unroll
                 for (int fb = 0; fb < WB; ++fb) areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)(kn * KS + ks) * 1024u));
                 __builtin_amdgcn_sched_barrier(0);  // refill each fragment right after its last use, one k-step at a time
-                if (PARTS == 2 || ks == KS - 1) store_x(buf ^ 1, PARTS == 2 ? ks : 0);
             }
+            store_x(buf ^ 1);
             __syncthreads();
         }
     };
+    // Tall tiles: see tall_step.  A wave's loads in program order: weights of step 0 | tokens 0 | tokens 1 | step 0: tokens 2, weights 1 | step 1:
+    // tokens 3, weights 2 | ...  At the end of step kt everything but its own NX + WB * KS loads has to be there, tokens kt + 1 among it.
+    auto tall_loop = [&](auto ntb_tag) {
+        constexpr int NTB = decltype(ntb_tag)::value;
+        constexpr int NX = (NTB * 16 + SR - 1) / SR;     // passes of this tile
+        constexpr int STAGE = TT * BK;
+        // (a different statement for each number: the compiler would move what they have in common in front of the switch)
+        asm volatile("; %0 token blocks" ::"n"(NTB));
+        bf16x8_t areg[WB][KS];
+#pragma unroll
+        for (int fb = 0; fb < WB; ++fb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) areg[fb][ks] = *(const bf16x8_t*)(abase[fb] + (alane + (uint32_t)ks * 1024u));
+        asm volatile("" ::: "memory");       // (the weights are on their way before the rows' numbers are waited for)
+        // byte offsets from `in` (the launcher rejects inputs of 4 GiB or more); row r of a stage takes piece lane % 8 ^ r % 8 of its row
+        uint32_t xoff[NX];
+#pragma unroll
+        for (int p = 0; p < NX; ++p)
+            xoff[p] = (uint32_t)(((size_t)xrow[p] * K + (size_t)kstep0 * BK) * 2) + ((lane & 7) ^ (lane >> 3)) * 16;
+        auto stage = [&](int at) { return (lds_bf16*)lds + at; };
+        auto load_x = [&](int at, int kt) {
+#pragma unroll
+            for (int p = 0; p < NX; ++p) load_to_lds(in, xoff[p], (uint32_t)kt * (BK * 2), stage(at) + staged_row<SR, TT>(p, wave) * BK);
+        };
+        load_x(0, 0);
+        asm volatile("" ::: "memory");
+        load_x(STAGE, min(1, nk - 1));
+        wait_and_meet<NX>();
+        const int frag0 = l16 * BK + ((kq ^ (l16 & 7)) << 3), frag1 = frag0 ^ 32;
+        int rd = 0, wr = 2 * STAGE;
+        for (int kt = 0; kt < nk; ++kt) {
+            // (the last steps fetch the last one's again: branch-free, in bounds, unused; waves of a ragged last column run on weight row 0)
+            tall_step<NTB, NX, SR, TT>(stage(rd), stage(wr), acc, areg, abase, alane + (uint32_t)min(kt + 1, nk - 1) * (KS * 1024u), in, xoff,
+                                       (uint32_t)min(kt + 2, nk - 1) * (BK * 2), frag0, frag1, wave);
+            rd = rd == 2 * STAGE ? 0 : rd + STAGE;
+            wr = wr == 2 * STAGE ? 0 : wr + STAGE;
+            wait_and_meet<NX + WB * KS>();
+        }
+        wait_and_meet<0>();                  // nothing may be on its way to LDS when it is used again
+    };
     auto dispatch = [&](auto... n) {
         const int blocks = (ti.rows + 15) >> 4;
-        (void)((blocks == decltype(n)::value ? (k_loop(n), true) : false) || ...);
+        if constexpr (LOW) (void)((blocks == decltype(n)::value ? (low_loop(n), true) : false) || ...);
+        else (void)((blocks == decltype(n)::value ? (tall_loop(n), true) : false) || ...);
     };
     if constexpr (TB == 4) dispatch(StageTag<1>{}, StageTag<2>{}, StageTag<3>{}, StageTag<4>{});
     else if constexpr (TB == 6) dispatch(StageTag<1>{}, StageTag<2>{}, StageTag<3>{}, StageTag<4>{}, StageTag<5>{}, StageTag<6>{});
