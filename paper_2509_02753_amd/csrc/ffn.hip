@@ -131,7 +131,7 @@ ffn_mfma_kernel(FfnJob routed, FfnJob shared) {
         static_assert(!MIXED || NW == 4, "");
         const int units = j.features >> 4, tile = block / units;
         if (!fetch_tile<GATEUP ? 0 : 1>(j, tile, ti)) return;
-        stream_unit_of<GATEUP, NW, 8>(j, ti, block - tile * units, (f32x4_t*)lds,
+        stream_unit_of<GATEUP, NW, 8, 60>(j, ti, block - tile * units, (f32x4_t*)lds,
                                       [&](int r) { return j.row_token ? j.row_token[ti.row0 + r] : ti.row0 + r; });
         return;
     }

@@ -188,67 +188,99 @@ __device__ __forceinline__ void store_unit(void* out, size_t at, const f32x4_t& 
     }
 }
 
-template <bool GATEUP, int NW, int MAXB, typename RowOf>
+// K blocks [kb0, kb1) of a unit by one wave: NM weight matrices (w: their blocks 0 of the unit) against NTB row blocks (a lane's row of `in`
+// at byte xoff), summed into acc in ascending order; `before(kb)` is called in front of a block's multiply-adds.
+// Bound by round trips to memory, so the loads of U blocks are in flight all the time: a block's registers are loaded again, U blocks
+// ahead, as soon as it has been multiplied.  (Places of the last round past the end load the last block again, unused: branch-free.)
+// The scheduling barriers keep the loads where they stand: left to itself the compiler saves registers and waits for nearly
+// every block by itself (8 blocks in 7 to 10 round trips).  Launches before and after, us: down, 16 tokens, d 2048, K 1408, k 2 / 6 17.2 -> 14.6, 35.7 ->
+// 30.2, 20 tokens, 64 experts 59.2 -> 48.7; gate/up, 1 token, k 6 21.2 -> 18.8, 20 tokens 97.8 -> 91.3, 30 tokens of d 1536 20.1 -> 16.0;
+// beside tiles: down, 64 tokens, shared K 5632 74.6 -> 67.3, 100 tokens, k = 1 58.6 -> 51.7.
+template <int NM, int NTB, int U, typename Before>
+__device__ __forceinline__ void stream_blocks(const char* const (&w)[NM], const char* in, const uint32_t (&xoff)[NTB], int kb0, int kb1,
+                                              f32x4_t (&acc)[NM][NTB], Before before) {
+    const uint32_t lane16 = (threadIdx.x & 63) * 16;
+    bf16x8_t wr[U][NM], xr[U][NTB];
+    auto load = [&](int u, int kb) {
+        const char* x = in + (size_t)(uint32_t)kb * 64;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) wr[u][m] = *(const bf16x8_t*)(w[m] + (size_t)(uint32_t)kb * 1024 + lane16);
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb) xr[u][tb] = *(const bf16x8_t*)(x + xoff[tb]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int u, int kb) {
+        before(kb);
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+            for (int m = 0; m < NM; ++m) acc[m][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[u][m], xr[u][tb], acc[m][tb], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int kb = kb0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u, min(kb + u, kb1 - 1));
+    for (; kb + U < kb1; kb += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            multiply(u, kb + u);
+            load(u, min(kb + U + u, kb1 - 1));
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (kb + u >= kb1) return;
+        multiply(u, kb + u);
+    }
+}
+// Depth of the stream: as many blocks as REGS registers hold, 8 at most (a part seldom has more).
+template <int NM, int NTB, int REGS> constexpr int stream_depth() {
+    const int n = REGS / (4 * (NM + NTB));
+    return n < 1 ? 1 : n > 8 ? 8 : n;
+}
+
+template <bool GATEUP, int NW, int MAXB, int REGS, typename RowOf>
 __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t (*red)[2][64], RowOf row_of) {
+    constexpr int NM = GATEUP ? 2 : 1;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kq = lane >> 4;
     const int K = j.K, features = j.features, nkb = K >> 5;
-    const bf16_t* in = (const bf16_t*)j.in;
     void* out = j.out;
     TileInfo ti = tile;
     const int kb0 = wave * nkb / NW, kb1 = (wave + 1) * nkb / NW;
-    const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
-    const bf16_t* a0 = (const bf16_t*)j.w0 + wbase;
-    const bf16_t* a1 = GATEUP ? (const bf16_t*)j.w1 + wbase : nullptr;
+    const size_t slab = ((size_t)(uint32_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 32);
+    const char* w[NM] = {(const char*)j.w0 + slab};
+    if constexpr (GATEUP) w[1] = (const char*)j.w1 + slab;
 
     auto body = [&](auto ntb_tag) {
         constexpr int NTB = decltype(ntb_tag)::value;
-        const bf16_t* xp[NTB];
+        uint32_t xoff[NTB];
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
             const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
-            const int src_row = row_of(ti.row0 - tile.row0 + rr);
-            xp[tb] = in + (size_t)src_row * K + kq * 8;
+            xoff[tb] = (uint32_t)row_of(ti.row0 - tile.row0 + rr) * (uint32_t)(K * 2) + kq * 16;
         }
-        f32x4_t accg[NTB], accu[NTB];
+        f32x4_t acc[NM][NTB];
 #pragma unroll
-        for (int tb = 0; tb < NTB; ++tb) {
-            accg[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            accu[tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        auto k_step = [&](int kb) {
-            const bf16x8_t ag = *(const bf16x8_t*)(a0 + (size_t)kb * 512);
-            bf16x8_t au;
-            if (GATEUP) au = *(const bf16x8_t*)(a1 + (size_t)kb * 512);
+        for (int m = 0; m < NM; ++m)
 #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) {
-                const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
-                accg[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ag, b, accg[tb], 0, 0, 0);
-                if (GATEUP) accu[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(au, b, accu[tb], 0, 0, 0);
-            }
-        };
-        constexpr int UNROLL = NTB <= 2 ? 8 : 4;  // K blocks whose loads are in flight together
-        int kb = kb0;
-        for (; kb + UNROLL <= kb1; kb += UNROLL) {
-#pragma unroll
-            for (int u = 0; u < UNROLL; ++u) k_step(kb + u);
-        }
-        for (; kb < kb1; ++kb) k_step(kb);
+            for (int tb = 0; tb < NTB; ++tb) acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (kb0 < kb1) stream_blocks<NM, NTB, stream_depth<NM, NTB, REGS>()>(w, (const char*)j.in, xoff, kb0, kb1, acc, [](int) {});
         // split-K reduction in wave order, one token block at a time; wave (tb % waves) finishes block tb
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
-            red[wave][0][lane] = accg[tb];
-            if (GATEUP) red[wave][1][lane] = accu[tb];
+#pragma unroll
+            for (int m = 0; m < NM; ++m) red[wave][m][lane] = acc[m][tb];
             __syncthreads();
             if (wave == tb % NW) {
                 f32x4_t g = red[0][0][lane], u = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-                for (int w = 1; w < NW; ++w) g += red[w][0][lane];
+                for (int v = 1; v < NW; ++v) g += red[v][0][lane];
                 if (GATEUP) {
                     u = red[0][1][lane];
 #pragma unroll
-                    for (int w = 1; w < NW; ++w) u += red[w][1][lane];
+                    for (int v = 1; v < NW; ++v) u += red[v][1][lane];
                 }
                 // lane owns token (lane % 16), features 4*(lane/16) + 0..3 of the unit
                 if (tb * 16 + l16 < ti.rows) store_unit<GATEUP>(out, (size_t)(ti.row0 + tb * 16 + l16) * features + unit * 16 + kq * 4, g, u);
@@ -272,67 +304,53 @@ __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& til
     }
 }
 
-// The same with the sum in eight parts by a workgroup of four waves: a wave takes two parts one after the other.  All parts of up to
-// MAXB row blocks meet in LDS at once (stream_eight_lds), and a wave finishes one block.  The loop over the two parts is not
-// unrolled and nothing of the first stays in registers, so that as many loads are in flight as in four parts: 20 tokens, k = 1, shared
-// width 5632, 4 layers 327 us (four parts 331; the first part kept in registers 351; a block of each part in turn 388), 40
-// tokens, d 1280, shared 1792 446 (452; 468; 495).
+// The same with the sum in eight parts by a workgroup of four waves: a wave takes two parts, whose blocks follow each other, in one stream of
+// loads.  All parts of up to MAXB row blocks meet in LDS at once (stream_eight_lds), and a wave finishes one block.
 template <bool GATEUP> constexpr int stream_eight_lds(int maxb) { return 8 * maxb * (GATEUP ? 2 : 1) * 64; }   // f32x4_t's
 
-template <bool GATEUP, int MAXB, typename RowOf>
+template <bool GATEUP, int MAXB, int REGS, typename RowOf>
 __device__ __forceinline__ void stream_unit_eight(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t* red, RowOf row_of) {
     static_assert(MAXB <= 4, "a wave finishes one row block");
     constexpr int NM = GATEUP ? 2 : 1;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, kq = lane >> 4;
     const int K = j.K, features = j.features, nkb = K >> 5;
     TileInfo ti = tile;
-    const size_t wbase = ((size_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 16) + lane * 8;
-    const bf16_t* a[2] = {(const bf16_t*)j.w0 + wbase, GATEUP ? (const bf16_t*)j.w1 + wbase : nullptr};
+    const size_t slab = ((size_t)(uint32_t)ti.expert * (features >> 4) + unit) * ((size_t)K * 32);
+    const char* w[NM] = {(const char*)j.w0 + slab};
+    if constexpr (GATEUP) w[1] = (const char*)j.w1 + slab;
+    const int kb0 = 2 * wave * nkb / 8, second = (2 * wave + 1) * nkb / 8, kb1 = (2 * wave + 2) * nkb / 8;
 
     auto body = [&](auto ntb_tag) {
         constexpr int NTB = decltype(ntb_tag)::value;
         auto at = [&](int part, int tb, int m) { return red + (((part * NTB + tb) * NM + m) * 64 + lane); };
-        const bf16_t* xp[NTB];
+        uint32_t xoff[NTB];
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
             const int rr = min(tb * 16 + l16, ti.rows - 1);  // rows past the group end re-read its last row; never stored
-            xp[tb] = (const bf16_t*)j.in + (size_t)row_of(ti.row0 - tile.row0 + rr) * K + kq * 8;
+            xoff[tb] = (uint32_t)row_of(ti.row0 - tile.row0 + rr) * (uint32_t)(K * 2) + kq * 16;
         }
-#pragma unroll 1
-        for (int part = 2 * wave; part < 2 * wave + 2; ++part) {
-            f32x4_t acc[NM][NTB];
-#pragma unroll
-            for (int m = 0; m < NM; ++m)
-#pragma unroll
-                for (int tb = 0; tb < NTB; ++tb) acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-            const int kb1 = (part + 1) * nkb / 8;
-            int kb = part * nkb / 8;
-            auto steps = [&](auto n) {                       // K blocks whose loads are in flight together
-#pragma unroll
-                for (int v = 0; v < decltype(n)::value; ++v, ++kb) {
-                    bf16x8_t w[NM];
-#pragma unroll
-                    for (int m = 0; m < NM; ++m) w[m] = *(const bf16x8_t*)(a[m] + (size_t)kb * 512);
-#pragma unroll
-                    for (int tb = 0; tb < NTB; ++tb) {
-                        const bf16x8_t b = *(const bf16x8_t*)(xp[tb] + kb * 32);
-#pragma unroll
-                        for (int m = 0; m < NM; ++m) acc[m][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[m], b, acc[m][tb], 0, 0, 0);
-                    }
-                }
-            };
-            constexpr int UNROLL = NTB <= 2 ? 8 : 4;
-            while (kb + UNROLL <= kb1) steps(IntTag<UNROLL>{});
-            if (UNROLL > 4 && kb + 4 <= kb1) steps(IntTag<4>{});
-            if (kb + 2 <= kb1) steps(IntTag<2>{});
-            if (kb < kb1) steps(IntTag<1>{});
+        f32x4_t acc[NM][NTB];
+        auto store_part = [&](int part) {                    // and start the next
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-                for (int m = 0; m < NM; ++m) *at(part, tb, m) = acc[m][tb];
-        }
+                for (int m = 0; m < NM; ++m) {
+                    *at(part, tb, m) = acc[m][tb];
+                    acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+        };
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        if (second == kb0) store_part(2 * wave);             // (an empty first part)
+        if (kb0 < kb1)
+            stream_blocks<NM, NTB, stream_depth<NM, NTB, REGS>()>(w, (const char*)j.in, xoff, kb0, kb1, acc, [&](int kb) {
+                if (kb == second && second > kb0) store_part(2 * wave);
+            });
+        store_part(2 * wave + 1);
         __syncthreads();
         if (wave < NTB) {                                    // the wave's row block, its parts in order
             f32x4_t g = *at(0, wave, 0), u = GATEUP ? *at(0, wave, 1) : f32x4_t{};
@@ -362,15 +380,15 @@ __device__ __forceinline__ void stream_unit_eight(const FfnJob& j, const TileInf
 
 // A unit of one job of a launch that may hold two, in the parts the job has in a launch of its own: the bits of its rows do not depend
 // on the other job.  (A launch has eight waves only where every job takes eight parts.)
-template <bool GATEUP, int NW, int MAXB, typename RowOf>
+template <bool GATEUP, int NW, int MAXB, int REGS, typename RowOf>
 __device__ __forceinline__ void stream_unit_of(const FfnJob& j, const TileInfo& tile, int unit, f32x4_t* red, RowOf row_of) {
     if constexpr (NW == 4) {
         if (j.parts == 8) {
-            stream_unit_eight<GATEUP, (MAXB < 4 ? MAXB : 4)>(j, tile, unit, red, row_of);
+            stream_unit_eight<GATEUP, (MAXB < 4 ? MAXB : 4), REGS>(j, tile, unit, red, row_of);
             return;
         }
     }
-    stream_unit<GATEUP, NW, MAXB>(j, tile, unit, (f32x4_t(*)[2][64])red, row_of);
+    stream_unit<GATEUP, NW, MAXB, REGS>(j, tile, unit, (f32x4_t(*)[2][64])red, row_of);
 }
 
 hipError_t launch_gateup_stream(const FfnArgs& a, const FfnArgs* shared, hipStream_t s);

@@ -13,10 +13,16 @@
 
 namespace lexi {
 
+// Registers of the loads on their way (stream_blocks).  The more the fewer waves fit: with four per SIMD (128 registers) 64 for the down
+// GEMM, 48 beside the selection.  Down, us, 96 and three waves / 64 and four: 16 tokens, k 6 31.2 / 30.2, 64 experts without bias 53.0 / 51.3, 32 tokens,
+// K 14336 163 / 157; select_gateup_kernel, 96 and three waves / 60 / 48: 16 tokens, k 2 28.7 / 29.6 / 28.3, k 6 57.8 / 58.3 / 56.9, 10
+// tokens of d 1024 19.6 / 17.1 / 17.0.
+constexpr int kStreamRegs = 64, kSelectStreamRegs = 48;
+
 // TWO: a second job; else a grid of units x tiles (most workgroups of a launch that uses few experts end at once, and neither choose
 // a job nor divide before they do).
 template <bool GATEUP, int NW, bool TWO>
-__global__ void __launch_bounds__(NW * 64)
+__global__ void __launch_bounds__(NW * 64, GATEUP ? 2 : 4)
 ffn_stream_kernel(FfnJob routed, FfnJob shared) {
     // (a streaming shared expert has at most 64 rows, and so has every expert beside it)
     constexpr int MAXB = TWO ? 4 : 8;
@@ -31,8 +37,8 @@ ffn_stream_kernel(FfnJob routed, FfnJob shared) {
     TileInfo ti;
     if (!fetch_tile<GATEUP ? 0 : 1>(j, tile, ti)) return;
     auto row_of = [&](int r) { return j.row_token ? j.row_token[ti.row0 + r] : ti.row0 + r; };
-    if (TWO) stream_unit_of<GATEUP, NW, MAXB>(j, ti, unit, red, row_of);
-    else stream_unit<GATEUP, NW, MAXB>(j, ti, unit, (f32x4_t(*)[2][64])red, row_of);
+    if (TWO) stream_unit_of<GATEUP, NW, MAXB, kStreamRegs>(j, ti, unit, red, row_of);
+    else stream_unit<GATEUP, NW, MAXB, kStreamRegs>(j, ti, unit, (f32x4_t(*)[2][64])red, row_of);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -56,7 +62,7 @@ struct SelectArgs {
 };
 
 template <int NW, int MAXT>
-__global__ void __launch_bounds__(NW * 64)
+__global__ void __launch_bounds__(NW * 64, 4)
 select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
     __shared__ __attribute__((aligned(16))) f32x4_t red[8 * 2 * 64];   // (of stream_unit_eight, or of eight waves)
     __shared__ uint64_t s_mask[MAXT];
@@ -65,7 +71,7 @@ select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
     const int lane = threadIdx.x & 63;
     if ((int)blockIdx.x < shared.blocks) {
         const int units = shared.features >> 4;
-        if ((int)blockIdx.x < units) stream_unit_of<true, NW, 1>(shared, TileInfo{0, 0, r.T}, blockIdx.x, red, [](int row) { return row; });
+        if ((int)blockIdx.x < units) stream_unit_of<true, NW, 1, kSelectStreamRegs>(shared, TileInfo{0, 0, r.T}, blockIdx.x, red, [](int row) { return row; });
         return;
     }
     const int block = blockIdx.x - shared.blocks - 1;
@@ -113,7 +119,7 @@ select_gateup_kernel(FfnJob routed, FfnJob shared, SelectArgs r) {
         const int tile = item / units;
         const int e = __builtin_ctzll(__ballot(count > 0 && rank == tile));
         const uint32_t tok = (uint32_t)__builtin_amdgcn_readlane((int)tokens, e);
-        stream_unit_of<true, NW, 1>(routed, TileInfo{e, __builtin_amdgcn_readlane(offset, e), __builtin_amdgcn_readlane(count, e)},
+        stream_unit_of<true, NW, 1, kSelectStreamRegs>(routed, TileInfo{e, __builtin_amdgcn_readlane(offset, e), __builtin_amdgcn_readlane(count, e)},
                                  item - tile * units, red, [&](int row) {
             int src = 0;
 #pragma unroll
