@@ -297,6 +297,7 @@ struct LayerPlan {
     TilePlan routed, shared;               // down GEMMs on the tile schedule
     bool routed_direct;                    // with k == 1 and nothing to add: rows stored straight into y
     bool routed_fused;                     // a handful of tokens: down projections and combine in one launch
+    bool f32_fused;                        // a small fp32 call: the same
 };
 LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_split, bool allow_direct) {
     LayerPlan p{};
@@ -314,6 +315,7 @@ LayerPlan plan_layer(const lexi_layer_t& ly, int32_t T, int32_t k, bool allow_sp
     p.routed_fused = bf && allow_direct && T <= kFusedDownMaxT && A <= kFusedDownMaxRows &&
                      (p.gateup_streams || few_items <= kStreamDownMaxItems) && ly.shared_kind != LEXI_SHARED_SIGMOID;
     if (p.routed_fused) p.routed_streams = true;
+    p.f32_fused = !bf && allow_direct && ly.shared_kind != LEXI_SHARED_SIGMOID && f32_down_combine_fits(T, k, ly.d, ly.F, ly.F_shared);
     if (!p.routed_streams) {
         p.routed = plan_down_tiles(A, ly.E, ly.F, ly.d, allow_split, direct);
         p.routed_direct = direct && p.routed.ksplit == 1;
@@ -392,8 +394,8 @@ lexi_status run_experts(const lexi_layer_t& ly, const void* x, int32_t T, int32_
     sd.ksplit = w.shared_planes = plan.shared.ksplit;
     sd.plane_stride = (size_t)T * ly.d;
     w.direct = plan.routed_direct;
-    w.fused = plan.routed_fused;
-    if (plan.routed_fused) return LEXI_OK;   // run_layer launches down (routed and shared) + combine
+    w.fused = plan.routed_fused || plan.f32_fused;
+    if (w.fused) return LEXI_OK;   // run_layer launches down (routed and shared) + combine
     if (plan.routed_direct) {
         dn.out = direct_y; dn.scatter = w.row_token; dn.out_bf16 = direct_bf16;
     }
@@ -449,7 +451,8 @@ lexi_status run_layer(const lexi_layer_t& ly, const void* x, void* y, int32_t y_
         f.inv_perm = w.inv_perm; f.gates = w.gates;
         if (ly.F_shared > 0) { f.act_shared = w.act_shared; f.ws_down = ly.ws_down; f.F_shared = ly.F_shared; }
         f.y = y; f.y_bf16 = y_dtype == LEXI_BF16;
-        if (launch_down_combine(f, s) != hipSuccess) return LEXI_ERR_LAUNCH;
+        f.topk_idx = w.topk_idx;
+        if ((bf ? launch_down_combine(f, s) : launch_down_combine_f32(f, s)) != hipSuccess) return LEXI_ERR_LAUNCH;
         for (int i : {3, 4, 5}) mark(i);
         return LEXI_OK;
     }
@@ -668,9 +671,12 @@ lexi_status lexi_moe_gemm_plan(const lexi_layer_t* layer, int32_t T, int32_t k, 
     out->tile_rows = t.tile_rows;
     out->ksplit = t.ksplit;
     out->direct = down && !shared && p.routed_direct;
-    out->fused = down && !shared && p.routed_fused;
+    out->fused = down && !shared && (p.routed_fused || p.f32_fused);
     if (down && p.routed_fused) {
         out->waves = down_combine_features(layer->d);
+    } else if (down && p.f32_fused) {
+        const int slots = k + (layer->F_shared > 0 ? 1 : 0);
+        out->waves = slots < 16 ? slots : 16;
     } else if (!out->streams) {
         out->waves = t.wide ? 8 : 4;
     } else {

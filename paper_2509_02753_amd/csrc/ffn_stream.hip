@@ -161,24 +161,11 @@ hipError_t launch_select_gateup(const RoutingArgs& r, const FfnArgs& a, const Ff
 // per SIMD) and more loads than the counter of loads in flight holds: 2 % more over 70 random layers, at worst 8 % (14 tokens, 3
 // experts of d 384, F 384: 27.2 -> 29.3 us; that test-scale layer 22.3 -> 23.2).  Cutting K over the waves is faster, but not the same sum.
 // ---------------------------------------------------------------------------------------------------------
-template <bool GATEUP>
-__global__ void __launch_bounds__(256)
-ffn_f32_kernel(FfnJob routed, FfnJob shared) {
-    int block = blockIdx.y * gridDim.x + blockIdx.x;     // (those past the last find no tile)
-    const FfnJob j = pick_job(routed, shared, block);
-    const int K = j.K, features = j.features;
-    const int column = block % (features >> 6);          // 64 features each
-    TileInfo ti;
-    if (!fetch_tile<GATEUP ? 0 : 1>(j, block / (features >> 6), ti)) return;
-    const float *in = (const float*)j.in, *w0 = (const float*)j.w0, *w1 = (const float*)j.w1;
-    const int32_t* row_token = j.row_token;
-    float* out = (float*)j.out;
-    constexpr int NM = GATEUP ? 2 : 1;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // packed weights: a lane's feature is row lane % 16 of 16-row slab lane / 16; its 32 elements of a K block are four runs
-    // of 8, 128 floats apart
-    const size_t slab = (size_t)ti.expert * (features >> 4) + column * 4 + (lane >> 4);
-    const float* wp[2] = {w0 + slab * ((size_t)K * 16) + (lane & 15) * 8, GATEUP ? w1 + slab * ((size_t)K * 16) + (lane & 15) * 8 : nullptr};
+// The chains of four rows (lane % 4) and 64 features (lane) over K: wp are the lane's weights of the NM matrices, a lane's feature being row
+// lane % 16 of 16-row slab lane / 16 (its 32 elements of a K block are four runs of 8, 128 floats apart); `x_row()` gives the lane's row.
+template <int NM, typename XRow>
+__device__ __forceinline__ void f32_chains(const float* const (&wp)[NM], int K, f32x4_t (&acc)[NM], XRow x_row) {
+    const int lane = threadIdx.x & 63;
     struct Block { f32x4_t v[NM][4][2]; };               // 32 elements of the reduction: weights of the lane's feature
     auto fetch_w = [&](Block& b, int kb) {
 #pragma unroll
@@ -188,45 +175,68 @@ ffn_f32_kernel(FfnJob routed, FfnJob shared) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) b.v[m][q][h] = *(const f32x4_t*)(wp[m] + (size_t)kb * 512 + q * 128 + 4 * h);
     };
+    Block w[2];
+    fetch_w(w[0], 0);
+    __builtin_amdgcn_sched_barrier(0);                   // (in front of the wait for the row's number)
+    const float* xp = x_row() + ((lane >> 2) & 7) * 8;   // octet (lane / 4) % 8 of 64 elements
+    f32x4_t x[2][2];                                     // of 64 elements, and of the next 64
+    auto fetch_x = [&](f32x4_t (&v)[2], int k0) {
+        v[0] = *(const f32x4_t*)(xp + k0);
+        v[1] = *(const f32x4_t*)(xp + k0 + 4);
+    };
+    fetch_x(x[0], 0);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) acc[m] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    auto octet = [&](const Block& b, const f32x4_t (&xv)[2], auto o) {
+        constexpr int O = decltype(o)::value;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int m = 0; m < NM; ++m)
+                acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[e >> 2][e & 3], b.v[m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
+    };
+    auto step = [&](const f32x4_t (&now)[2], f32x4_t (&next)[2], int k0) {
+        fetch_w(w[1], (k0 >> 5) + 1);
+        fetch_x(next, min(k0 + 64, K - 64));             // (the last ones are not used)
+        __builtin_amdgcn_sched_barrier(0);               // the next block's loads in front of this one's chain
+        octet(w[0], now, IntTag<0>{}); octet(w[0], now, IntTag<1>{}); octet(w[0], now, IntTag<2>{}); octet(w[0], now, IntTag<3>{});
+        fetch_w(w[0], min((k0 >> 5) + 2, (K >> 5) - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        octet(w[1], now, IntTag<4>{}); octet(w[1], now, IntTag<5>{}); octet(w[1], now, IntTag<6>{}); octet(w[1], now, IntTag<7>{});
+    };
+    int k0 = 0;
+    for (; k0 + 128 <= K; k0 += 128) {
+        step(x[0], x[1], k0);
+        step(x[1], x[0], k0 + 64);
+    }
+    if (k0 < K) step(x[0], x[1], k0);
+}
+// A lane's weights of `column` of 64 features in packed matrix `e` of [features][K].
+__device__ __forceinline__ const float* f32_lane_weights(const float* w, int e, int features, int column, int K) {
+    const int lane = threadIdx.x & 63;
+    return w + ((size_t)e * (features >> 4) + column * 4 + (lane >> 4)) * ((size_t)K * 16) + (lane & 15) * 8;
+}
+
+template <bool GATEUP>
+__global__ void __launch_bounds__(256)
+ffn_f32_kernel(FfnJob routed, FfnJob shared) {
+    int block = blockIdx.y * gridDim.x + blockIdx.x;     // (those past the last find no tile)
+    const FfnJob j = pick_job(routed, shared, block);
+    const int K = j.K, features = j.features;
+    const int column = block % (features >> 6);          // 64 features each
+    TileInfo ti;
+    if (!fetch_tile<GATEUP ? 0 : 1>(j, block / (features >> 6), ti)) return;
+    const int32_t* row_token = j.row_token;
+    float* out = (float*)j.out;
+    constexpr int NM = GATEUP ? 2 : 1;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const float* wp[NM] = {f32_lane_weights((const float*)j.w0, ti.expert, features, column, K)};
+    if constexpr (GATEUP) wp[1] = f32_lane_weights((const float*)j.w1, ti.expert, features, column, K);
     for (int r0 = wave * 4; r0 < ti.rows; r0 += 16) {   // (no barrier in this kernel)
         const int rr = min(r0 + (lane & 3), ti.rows - 1);   // rows past the tile's end re-read its last row; never stored
         const int src_row = row_token ? row_token[ti.row0 + rr] : ti.row0 + rr;
-        Block w[2];
-        fetch_w(w[0], 0);
-        __builtin_amdgcn_sched_barrier(0);               // (in front of the wait for the row's number)
-        const float* xp = in + (size_t)src_row * K + ((lane >> 2) & 7) * 8;   // octet (lane / 4) % 8 of 64 elements
-        f32x4_t x[2][2];                                 // of 64 elements, and of the next 64
-        auto fetch_x = [&](f32x4_t (&v)[2], int k0) {
-            v[0] = *(const f32x4_t*)(xp + k0);
-            v[1] = *(const f32x4_t*)(xp + k0 + 4);
-        };
-        fetch_x(x[0], 0);
         f32x4_t acc[NM];
-#pragma unroll
-        for (int m = 0; m < NM; ++m) acc[m] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        auto octet = [&](const Block& b, const f32x4_t (&xv)[2], auto o) {
-            constexpr int O = decltype(o)::value;
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int m = 0; m < NM; ++m)
-                    acc[m] = __builtin_amdgcn_mfma_f32_4x4x1f32(xv[e >> 2][e & 3], b.v[m][O & 3][e >> 2][e & 3], acc[m], 4, O, 0);
-        };
-        auto step = [&](const f32x4_t (&now)[2], f32x4_t (&next)[2], int k0) {
-            fetch_w(w[1], (k0 >> 5) + 1);
-            fetch_x(next, min(k0 + 64, K - 64));         // (the last ones are not used)
-            __builtin_amdgcn_sched_barrier(0);           // the next block's loads in front of this one's chain
-            octet(w[0], now, IntTag<0>{}); octet(w[0], now, IntTag<1>{}); octet(w[0], now, IntTag<2>{}); octet(w[0], now, IntTag<3>{});
-            fetch_w(w[0], min((k0 >> 5) + 2, (K >> 5) - 1));
-            __builtin_amdgcn_sched_barrier(0);
-            octet(w[1], now, IntTag<4>{}); octet(w[1], now, IntTag<5>{}); octet(w[1], now, IntTag<6>{}); octet(w[1], now, IntTag<7>{});
-        };
-        int k0 = 0;
-        for (; k0 + 128 <= K; k0 += 128) {
-            step(x[0], x[1], k0);
-            step(x[1], x[0], k0 + 64);
-        }
-        if (k0 < K) step(x[0], x[1], k0);
+        f32_chains<NM>(wp, K, acc, [&]() { return (const float*)j.in + (size_t)src_row * K; });
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (r0 + i < ti.rows) {
@@ -236,6 +246,46 @@ ffn_f32_kernel(FfnJob routed, FfnJob shared) {
             }
         }
     }
+}
+
+// Down projection and combine of a small fp32 call in one launch (f32_down_combine_fits): a workgroup has 64 features of one token, a wave one of
+// its slots at a time (the shared expert is the last), so nothing of the permutation is needed but the slot's row.  A slot's row is the
+// same chain as in ffn_f32_kernel (its four rows are one here), the sum over slots combine_kernel's: same bits.  Bound by one chain of
+// multiply-adds and two round trips in front of it (64 tokens, k 2, d 128, F 256: 4.8 us against 6.2 and 3.0 in two launches).
+template <bool Y_BF16>
+__global__ void __launch_bounds__(1024)
+down_combine_f32_kernel(DownCombineArgs a) {
+    __shared__ float s_row[kF32FusedMaxSlots][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), waves = blockDim.x >> 6;
+    const int columns = a.d >> 6;
+    const int t = blockIdx.x / columns, column = blockIdx.x - t * columns;
+    const int slots = a.k + (a.act_shared != nullptr ? 1 : 0);
+    for (int s = wave; s < slots; s += waves) {
+        const bool routed = s < a.k;
+        const int K = routed ? a.F : a.F_shared;
+        const int e = routed ? a.topk_idx[t * a.k + s] : 0, row = routed ? a.inv_perm[t * a.k + s] : t;
+        const float* wp[1] = {f32_lane_weights((const float*)(routed ? a.w_down : a.ws_down), e, a.d, column, K)};
+        f32x4_t acc[1];
+        f32_chains<1>(wp, K, acc, [&]() { return (const float*)(routed ? a.act : a.act_shared) + (size_t)row * K; });
+        s_row[s][lane] = acc[0][0];
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    float o = 0.0f;
+    for (int s = 0; s < a.k; ++s) o = __builtin_fmaf(a.gates[t * a.k + s], s_row[s][lane], o);
+    if (a.act_shared != nullptr) o = __builtin_fmaf(1.0f, s_row[a.k][lane], o);
+    const size_t at = (size_t)t * a.d + column * 64 + lane;
+    if (Y_BF16) ((bf16_t*)a.y)[at] = f32_to_bf16(o);
+    else ((float*)a.y)[at] = o;
+}
+
+hipError_t launch_down_combine_f32(const DownCombineArgs& a, hipStream_t s) {
+    const int slots = a.k + (a.act_shared != nullptr ? 1 : 0);
+    if (a.T < 1 || slots > kF32FusedMaxSlots || a.d % 64 != 0 || a.F % 64 != 0 || (a.act_shared != nullptr && a.F_shared % 64 != 0)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)a.T * (unsigned)(a.d / 64)), block((slots < 16 ? slots : 16) * 64);
+    if (a.y_bf16) hipLaunchKernelGGL(down_combine_f32_kernel<true>, grid, block, 0, s, a);
+    else hipLaunchKernelGGL(down_combine_f32_kernel<false>, grid, block, 0, s, a);
+    return hipGetLastError();
 }
 
 template <bool GATEUP>

@@ -157,6 +157,7 @@ struct DownCombineArgs {
     const int32_t* sched;      // work list (one tile per expert with rows), or null: then
     const int32_t* counts;     // [E]
     int E;
+    const int32_t* topk_idx;   // [T*k] (fp32 layers only)
     const int32_t* inv_perm;   // [T*k]
     const float* gates;        // [T*k]
     const void* act_shared;    // [T][F_shared] bf16 or null: the shared expert, added with coefficient 1
@@ -166,6 +167,19 @@ struct DownCombineArgs {
     bool y_bf16;
 };
 hipError_t launch_down_combine(const DownCombineArgs& a, hipStream_t s);
+// The same for fp32 layers (act, weights and act_shared fp32, topk_idx in place of sched and counts): a workgroup per token and 64 features, and
+// every slot pulls its own 256 bytes of weights per element of the reduction, where the tiles of separate launches share them.  Bound by what a
+// CU pulls, so the line lies there.  Down + combine, separate launches against one, us (KB per CU): 64 tokens, k 2, d 128, F 256 9.2 / 4.8
+// (131); 1024 tokens, d 128, F 64 8.1 / 5.8 (262); 128 tokens, d 256, F 256 8.9 / 6.1 (262); d 384, F 128, shared 128 7.1 / 6.5 (295); then d 384,
+// F 384: 8 tokens, k 4 8.1 / 7.1 (393; the call 23.2 / 23.1), 64 tokens, k 2 9.0 / 8.8 (393; 31.4 / 31.7), 128 tokens 10.0 / 10.9 (590), 16 tokens,
+// k 8 8.9 / 12.2 (786).
+constexpr int kF32FusedMaxSlots = 65;
+constexpr int64_t kF32FusedBytesPerCu = 300 << 10;
+inline bool f32_down_combine_fits(int T, int k, int d, int F, int F_shared) {
+    const int64_t groups = (int64_t)T * (d / 64);
+    return (groups + 255) / 256 * ((int64_t)k * F + F_shared) * 256 <= kF32FusedBytesPerCu;
+}
+hipError_t launch_down_combine_f32(const DownCombineArgs& a, hipStream_t s);
 
 // chained stack: normalised MoE input u (layer dtype) from the fp32 hidden state h; h = widened x
 constexpr float kRmsEps = 1e-6f;

@@ -515,3 +515,27 @@ def test_order_of_the_shared_gate_dot_product(d):
     assert np.abs(z - want).max() <= 1.02e-6, (np.abs(z - want).max(), np.abs(z - other).max())
     if d != 128:
         assert (np.abs(want - other) > 2.0 ** -20).sum() > T // 8        # (another order would not pass)
+
+
+@pytest.mark.parametrize("T,k,E,d,F,Fs", [(1, 1, 2, 128, 64, 0), (3, 16, 16, 128, 64, 64), (64, 2, 8, 128, 256, 0), (17, 5, 8, 384, 64, 192),
+                                          (9, 18, 40, 128, 64, 0)])
+def test_fp32_down_and_combine_in_one_launch(T, k, E, d, F, Fs):
+    """Against the oracle, and bit for bit against the separate launches of a larger batch that starts with the same tokens; one wave to more
+    slots than waves, the shared expert as the last slot."""
+    import torch
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(S.C1, L=1, d=d, F=F, F_shared=0), E=E, F_shared=Fs, shared_kind=S.SHARED_UNGATED if Fs else S.SHARED_NONE)
+    run_and_check_layer(cfg, 0, T, k)
+    dl, _ = device_and_host_layer(cfg, 0)
+    many = T
+    while P.lexi_moe_gemm_plan(dl, many, k, "down")["fused"]:
+        many *= 2
+    assert P.lexi_moe_gemm_plan(dl, T, k, "down")["waves"] == min(k + (Fs > 0), 16) and many > T
+    x = S.device_x(cfg, 0, many)
+    y = torch.empty((many, d), dtype=torch.float32, device="cuda:0")
+    for n in (many, T):
+        out = y if n == many else torch.empty((n, d), dtype=torch.float32, device="cuda:0")
+        P.lexi_moe_layer_forward(dl, x[:n].contiguous(), out, k, P.alloc_workspace([dl], n, k))
+    torch.cuda.synchronize()
+    assert torch.equal(out, y[:T])
