@@ -569,8 +569,7 @@ lexi_status lexi_moe_stack_forward_profiled(const lexi_layer_t* layers, int32_t 
             return (dbg_per_layer && dbg_per_layer[l].moe_input) ? dbg_per_layer[l].moe_input : workspace;
         };
         float* h = (float*)y;
-        if (launch_widen(x, bf, (size_t)T * layers[0].d, h, s) != hipSuccess) return LEXI_ERR_LAUNCH;
-        if (launch_rmsnorm(h, T, layers[0].d, kRmsEps, u_of(0), bf, s) != hipSuccess) return LEXI_ERR_LAUNCH;
+        if (launch_start_chain(x, bf, T, layers[0].d, kRmsEps, h, u_of(0), s) != hipSuccess) return LEXI_ERR_LAUNCH;
         for (int l = 0; l < L; ++l) {
             float* h_out = (float*)y + (size_t)l * y_layer_stride;
             lexi_status st = run_layer(layers[l], nullptr, h_out, LEXI_F32, T, k_vec[l], workspace, s,

@@ -33,7 +33,7 @@ __device__ __forceinline__ void store_normalised(void* u, size_t idx, const f32x
 // tokens: 6.5 -> 5.0 us).
 // Chained stack: `residual` (the hidden state) is added to the block's output, and with `u_next` the same workgroup
 // also writes the NEXT block's normalised input from the row it has just produced -- the sum of squares in exactly
-// the order rmsnorm_kernel uses, so either route gives the same bits.  (x and u_next may be the same buffer: a
+// the order start_chain_kernel uses, so either route gives the same bits.  (x and u_next may be the same buffer: a
 // workgroup reads its row of x before it writes its row of u_next.)
 template <bool Y_BF16, bool X_BF16, int NP, int GS>
 __global__ void __launch_bounds__(256)
@@ -181,50 +181,64 @@ static void launch_combine_t(const CombineArgs& a, hipStream_t s) {
     else launch(Count<4>{}, Count<4>{});
 }
 
-// Chained stack: u[t] = h[t] / sqrt(mean_j h[t][j]^2 + eps), rounded to the layer dtype.  One workgroup per token;
-// the sum of squares in a fixed order (per-thread strided fused multiply-adds, DPP tree, the four waves in order).
-template <bool U_BF16>
+// The start of a chained stack: h = x widened exactly to fp32 (the hidden state starts as the input), and u[t] = h[t] / sqrt(mean_j h[t][j]^2
+// + eps) rounded to the layer dtype.  One workgroup per token; the sum of squares in combine_kernel's order (per-thread strided fused
+// multiply-adds, DPP tree, the four waves in order).  A thread reads its four pieces of x together and keeps them (a wider row is read again
+// from h, the thread's own stores).  A thread reads and writes only its own pieces of a row: u may be x, and so may h where x is fp32.
+// Widening in a launch of its own cost a launch for few tokens and a pass over h for many: 1 token of d 2048 4.3 -> 2.0 us, 777 of d 1280
+// 7.5 -> 4.3, 4096 of d 4096 48.4 -> 20.4 (134 MB at 6.6 TB/s), of d 8192 119 -> 66.
+template <bool X_BF16>
 __global__ void __launch_bounds__(256)
-rmsnorm_kernel(const float* __restrict__ h, int d, float eps, void* __restrict__ u) {
+start_chain_kernel(const void* x, int d, float eps, float* h, void* u) {
+    constexpr int NP = 4;
     __shared__ float wave_part[4];
-    const int t = blockIdx.x;
-    const float* ht = h + (size_t)t * d;
-    // d % 128 == 0 (checked at the boundary): 16-byte pieces, thread-strided
+    const size_t row = (size_t)blockIdx.x * d;
+    f32x4_t v[NP];
     float ss = 0.0f;
-    for (int j = threadIdx.x * 4; j < d; j += 1024) {
-        const f32x4_t v = *(const f32x4_t*)(ht + j);
+    for (int c0 = 0; c0 < d; c0 += 1024 * NP) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(v[i], v[i], ss);
+        for (int p = 0; p < NP; ++p) {                  // (pieces past the row all read its first four elements; never stored)
+            const int j = c0 + 1024 * p + threadIdx.x * 4;
+            const size_t at = row + (j < d ? j : 0);
+            if (X_BF16) {
+                const u32x2_t pk = *(const u32x2_t*)((const bf16_t*)x + at);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    v[p][2 * i] = __uint_as_float(pk[i] << 16);
+                    v[p][2 * i + 1] = __uint_as_float(pk[i] & 0xFFFF0000u);
+                }
+            } else {
+                v[p] = *(const f32x4_t*)((const float*)x + at);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int j = c0 + 1024 * p + threadIdx.x * 4;
+            if (j >= d) continue;
+            *(f32x4_t*)(h + row + j) = v[p];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ss = __builtin_fmaf(v[p][i], v[p][i], ss);
+        }
     }
     const float ws = wave_sum(ss);
     if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = ws;
     __syncthreads();
     const float total = ((wave_part[0] + wave_part[1]) + wave_part[2]) + wave_part[3];
     const float inv = 1.0f / sqrtf(total / (float)d + eps);
-    for (int j = threadIdx.x * 4; j < d; j += 1024) {
-        const f32x4_t v = *(const f32x4_t*)(ht + j);   // second read of the row: served by the cache
-        store_normalised<U_BF16>(u, (size_t)t * d + j, v, inv);
+    if (d <= 1024 * NP) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int j = 1024 * p + threadIdx.x * 4;
+            if (j < d) store_normalised<X_BF16>(u, row + j, v[p], inv);
+        }
+        return;
     }
+    for (int j = threadIdx.x * 4; j < d; j += 1024) store_normalised<X_BF16>(u, row + j, *(const f32x4_t*)(h + row + j), inv);
 }
 
-// h = x widened exactly to fp32 (the chained stack's hidden state starts as the input).
-template <bool X_BF16>
-__global__ void __launch_bounds__(256)
-widen_kernel(const void* __restrict__ x, size_t n, float* __restrict__ h) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) h[i] = load_as_f32<X_BF16>(x, i);
-}
-
-hipError_t launch_rmsnorm(const float* h, int T, int d, float eps, void* u, bool u_bf16, hipStream_t s) {
-    if (u_bf16) hipLaunchKernelGGL(rmsnorm_kernel<true>, dim3(T), dim3(256), 0, s, h, d, eps, u);
-    else hipLaunchKernelGGL(rmsnorm_kernel<false>, dim3(T), dim3(256), 0, s, h, d, eps, u);
-    return hipGetLastError();
-}
-
-hipError_t launch_widen(const void* x, bool x_bf16, size_t n, float* h, hipStream_t s) {
-    const unsigned blocks = (unsigned)((n + 255) / 256);
-    if (x_bf16) hipLaunchKernelGGL(widen_kernel<true>, dim3(blocks), dim3(256), 0, s, x, n, h);
-    else hipLaunchKernelGGL(widen_kernel<false>, dim3(blocks), dim3(256), 0, s, x, n, h);
+hipError_t launch_start_chain(const void* x, bool is_bf16, int T, int d, float eps, float* h, void* u, hipStream_t s) {
+    if (is_bf16) hipLaunchKernelGGL(start_chain_kernel<true>, dim3(T), dim3(256), 0, s, x, d, eps, h, u);
+    else hipLaunchKernelGGL(start_chain_kernel<false>, dim3(T), dim3(256), 0, s, x, d, eps, h, u);
     return hipGetLastError();
 }
 

@@ -181,10 +181,9 @@ inline bool f32_down_combine_fits(int T, int k, int d, int F, int F_shared) {
 }
 hipError_t launch_down_combine_f32(const DownCombineArgs& a, hipStream_t s);
 
-// chained stack: normalised MoE input u (layer dtype) from the fp32 hidden state h; h = widened x
+// chained stack: the fp32 hidden state h = widened x, and the first block's normalised MoE input u (layer dtype)
 constexpr float kRmsEps = 1e-6f;
-hipError_t launch_rmsnorm(const float* h, int T, int d, float eps, void* u, bool u_bf16, hipStream_t s);
-hipError_t launch_widen(const void* x, bool x_bf16, size_t n, float* h, hipStream_t s);
+hipError_t launch_start_chain(const void* x, bool is_bf16, int T, int d, float eps, float* h, void* u, hipStream_t s);
 
 // Stage-1 profiling: squared-difference reduction over the slot rows of one baseline pass.
 constexpr int kProfileMaxK = 64;

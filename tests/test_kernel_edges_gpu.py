@@ -539,3 +539,13 @@ def test_fp32_down_and_combine_in_one_launch(T, k, E, d, F, Fs):
         P.lexi_moe_layer_forward(dl, x[:n].contiguous(), out, k, P.alloc_workspace([dl], n, k))
     torch.cuda.synchronize()
     assert torch.equal(out, y[:T])
+
+
+@pytest.mark.parametrize("base", ["C1", "C2"])
+@pytest.mark.parametrize("T,d", [(1, 128), (3, 1024), (2, 1152), (5, 4096), (2, 4224), (1, 8320)])
+def test_start_of_a_chained_stack_at_its_edges(base, T, d):
+    """Rows of a part of a piece to more than a thread keeps: the normalised input against its definition, and the block on it."""
+    import numpy as np
+    from test_chained_gpu import _check_blocks
+    cfg = replace(S.mini(getattr(S, base), L=2, d=d, F=64, F_shared=0), E=4, k_base=2)
+    _check_blocks(cfg, T, np.array([1, 2]))
