@@ -25,8 +25,9 @@ struct RoutingArgs {
     const float* bias;        // [E] or null
     int T, d, E, k;
     WorkPlan plan;
-    float* partial;           // [d/128][T][64] segment partials of the logits, where they go through memory (T <= kSmallRouterMaxT or
-                              // T > kFineRouterMaxT; between them it may share memory with blk_hist)
+    float* partial;           // [d/128][T][64] segment partials of the logits, where they go through memory (T <= kSmallRouterMaxT, few
+                              // experts above kFineRouterMaxT, or many tokens; between kSmallRouterMaxT and kFineRouterMaxT it may share
+                              // memory with blk_hist)
     int32_t* topk_idx;        // [T*k]
     float* gates;             // [T*k]
     int32_t* local_rank;      // [T*k]  rank of the assignment inside its router block, per expert

@@ -549,3 +549,14 @@ def test_start_of_a_chained_stack_at_its_edges(base, T, d):
     from test_chained_gpu import _check_blocks
     cfg = replace(S.mini(getattr(S, base), L=2, d=d, F=64, F_shared=0), E=4, k_base=2)
     _check_blocks(cfg, T, np.array([1, 2]))
+
+
+@pytest.mark.parametrize("T,k,E,d,F", [(20, 2, 64, 128, 64), (40, 2, 64, 384, 192), (100, 1, 64, 1152, 576), (128, 1, 64, 2176, 1088), (33, 3, 60, 1280, 320)])
+@pytest.mark.parametrize("zipf", [0.0, 1.1])
+def test_streamed_parts_shorter_and_longer_than_the_loads_in_flight(T, k, E, d, F, zipf):
+    """Parts of no, one, three, eight, nine, ten and seventeen K blocks, where up to eight are in flight; one row to many per expert."""
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(S.C5 if zipf else S.C2, L=1, d=d, F=F, F_shared=0), E=E, F_shared=0, shared_kind=S.SHARED_NONE)
+    assert P.lexi_moe_gemm_plan(device_and_host_layer(cfg, 0)[0], T, k, "gate_up")["streams"] == 1
+    run_and_check_layer(cfg, 0, T, k)
