@@ -46,6 +46,21 @@ __device__ __forceinline__ float dpp_f32(float old, float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
 }
 
+// Maximum and sum over the 16 lanes of a row, in all of them (the first four steps of wave_max and wave_sum: with zeros in the other
+// rows the same sum).
+__device__ __forceinline__ float row_max(float v) {
+    v = fmaxf(v, dpp_f32<0xB1>(v, v));
+    v = fmaxf(v, dpp_f32<0x4E>(v, v));
+    v = fmaxf(v, dpp_f32<0x141>(v, v));
+    return fmaxf(v, dpp_f32<0x140>(v, v));
+}
+__device__ __forceinline__ float row_sum(float v) {
+    v += dpp_f32<0xB1>(0.0f, v);
+    v += dpp_f32<0x4E>(0.0f, v);
+    v += dpp_f32<0x141>(0.0f, v);
+    return v + dpp_f32<0x140>(0.0f, v);
+}
+
 // Maximum over the 64 lanes, returned to every lane (as a wave-uniform value).
 __device__ __forceinline__ float wave_max(float v) {
     v = fmaxf(v, dpp_f32<0xB1>(v, v));   // quad_perm [1,0,3,2]

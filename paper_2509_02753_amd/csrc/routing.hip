@@ -618,9 +618,15 @@ topk_scan_kernel(const float* partial, const float* __restrict__ bias, int T, in
 // tokens (d 384, 17 tokens, 8 experts 160 / 163, 64 experts 166 / 182).  Up to 16 tokens one launch replaces two only: called from the host
 // it is the faster one (d 256, 2 tokens, k 8 148 / 160; d 384, 2 tokens, k 1 144 / 155), in a replayed graph the selection's k rounds
 // and the third segment cost 3 to 5 % (148 / 140, 144 / 140); few tokens of such narrow layers come from the host.
+// Up to 16 experts a row of 16 lanes is enough for a token, so a wave selects from its four at once, a quarter of the work per k: 64 tokens, d 128,
+// k 2 9.0 -> 6.7 us, 32 tokens, k 4 7.0 -> 4.9.  The line moves with it, one launch against three: d 128, 64 tokens, k 4 7.0 / 9.9, 16 experts,
+// k 8 8.5 / 10.6; d 256, 64 tokens, k 4 10.0 / 11.0, k 8 10.4 / 10.8; d 384, 32 tokens, k 4 8.1 / 9.5, k 8 9.8 / 10.4, but 64 tokens, k 2 12.5 / 10.2.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kSmallRouteSegs = 3;
-static bool route_small(int T, int k, int nseg) { return T <= kSmallRouterMaxT && nseg <= kSmallRouteSegs && T * (k + 3 * (nseg - 1)) <= 192; }
+static bool route_small(int T, int k, int nseg, int E) {
+    if (T > kSmallRouterMaxT || nseg > kSmallRouteSegs) return false;
+    return E <= kNarrowRouterMaxE ? T * (k + 12 * (nseg - 1)) <= 1024 : T * (k + 3 * (nseg - 1)) <= 192;
+}
 
 template <bool IS_BF16>
 __global__ void __launch_bounds__(1024)
@@ -675,7 +681,36 @@ route_small_kernel(const void* __restrict__ x, const float* __restrict__ w_route
         __syncthreads();                         // ws has been read
     }
     uint32_t bits = 0;
-    if (tok0 < T) {
+    if (tok0 < T && E <= kNarrowRouterMaxE) {    // a row of 16 lanes has a token's experts: the four tokens at once, the same values and order
+        const int l16 = lane & 15, t = tok0 + (lane >> 4);
+        float v = __shfl(total[0], l16);
+#pragma unroll
+        for (int m = 1; m < 4; ++m) {
+            const float o = __shfl(total[m], l16);
+            v = lane >> 4 == m ? o : v;
+        }
+        if (bias != nullptr) v = v + bias[min(l16, E - 1)];
+        v = v == v ? v : -INFINITY;              // (as in pick_experts)
+        bool open = l16 < E;
+        int32_t sel = 0;
+        float val = -INFINITY;
+        for (int s = 0; s < k; ++s) {
+            const float mx = row_max(open ? v : -INFINITY);
+            const uint32_t holds = (uint32_t)(__ballot(open && v == mx) >> (lane & 48)) & 0xFFFFu;
+            const int e_star = __builtin_ctz(holds);
+            if (l16 == e_star) open = false;
+            if (l16 == s) { sel = e_star; val = mx; }
+        }
+        const float ex = l16 < k ? __expf(val - __shfl(val, lane & 48)) : 0.0f;
+        const float g = ex / row_sum(ex);
+        if (t < T && l16 < k) {
+            topk_idx[t * k + l16] = sel;
+            gates[t * k + l16] = g;
+            s_sel[t * k + l16] = (uint8_t)sel;
+        }
+        const uint64_t taken = __ballot(t < T && l16 < E && !open) >> l16;
+        if (lane < 16) bits = (uint32_t)(taken & 1) | (uint32_t)(taken >> 15 & 2) | (uint32_t)(taken >> 30 & 4) | (uint32_t)(taken >> 45 & 8);
+    } else if (tok0 < T) {
         bool taken[4];
         int32_t sel[4];
         float val[4];
@@ -747,7 +782,7 @@ hipError_t launch_routing(const RoutingArgs& a, hipStream_t s) {
     const int tb = router_tokens_per_block(a.T, a.E);
     const int nblk = (a.T + tb - 1) / tb;
     hipError_t err;
-    if (route_small(a.T, a.k, nseg)) {
+    if (route_small(a.T, a.k, nseg, a.E)) {
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, s, a.x, a.w_router, a.bias, a.T, a.d, a.E, a.k, a.plan, a.topk_idx, a.gates,
                                a.counts, a.offsets, a.sched, a.perm, a.inv_perm, a.row_token);

@@ -560,3 +560,21 @@ def test_streamed_parts_shorter_and_longer_than_the_loads_in_flight(T, k, E, d, 
     cfg = replace(S.mini(S.C5 if zipf else S.C2, L=1, d=d, F=F, F_shared=0), E=E, F_shared=0, shared_kind=S.SHARED_NONE)
     assert P.lexi_moe_gemm_plan(device_and_host_layer(cfg, 0)[0], T, k, "gate_up")["streams"] == 1
     run_and_check_layer(cfg, 0, T, k)
+
+
+@pytest.mark.parametrize("kind", ["c1", "c2"])
+@pytest.mark.parametrize("T,k,E,d", [
+    # rows of 16 lanes: one to 16 experts, a wave's four tokens partly there, on both sides of the line to three launches and to whole waves
+    (1, 1, 2, 128), (2, 16, 16, 128), (63, 15, 16, 128), (64, 8, 15, 128), (64, 4, 8, 256), (64, 5, 8, 256), (32, 8, 16, 384), (33, 8, 16, 384),
+    (42, 1, 3, 384), (9, 9, 17, 128),
+])
+def test_routing_in_one_workgroup_of_few_experts(T, k, E, d, kind):
+    cfg = replace(S.mini(S.C1 if kind == "c1" else S.C2, L=1, d=d, F=64, F_shared=0), E=E)
+    run_and_check_layer(cfg, 0, T, k)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,E", [(64, 16), (37, 5)])
+def test_routing_in_one_workgroup_of_few_experts_keeps_subnormals_infinities_and_nan(T, E, dtype):
+    test_router_keeps_subnormal_products_and_sums(T, E, dtype)
+    test_router_with_infinite_and_nan_activations(T, E, dtype)
