@@ -192,6 +192,8 @@ __device__ __forceinline__ void store_unit(void* out, size_t at, const f32x4_t& 
 // at byte xoff), summed into acc in ascending order; `before(kb)` is called in front of a block's multiply-adds.
 // Bound by round trips to memory, so the loads of U blocks are in flight all the time: a block's registers are loaded again, U blocks
 // ahead, as soon as it has been multiplied.  (Places of the last round past the end load the last block again, unused: branch-free.)
+// A part of fewer blocks loads only those it has: empty places took a tenth to a quarter of the launches of small layers (18 tokens, 12 experts, d
+// 256, F 128: gate/up 5.2 -> 4.0 us; 21 tokens, 24 experts, d 512: gate/up 5.2 -> 4.4, down 4.4 -> 3.6; calls 2 to 8 %).
 // The scheduling barriers keep the loads where they stand: left to itself the compiler saves registers and waits for nearly
 // every block by itself (8 blocks in 7 to 10 round trips).  Launches before and after, us: down, 16 tokens, d 2048, K 1408, k 2 / 6 17.2 -> 14.6, 35.7 ->
 // 30.2, 20 tokens, 64 experts 59.2 -> 48.7; gate/up, 1 token, k 6 21.2 -> 18.8, 20 tokens 97.8 -> 91.3, 30 tokens of d 1536 20.1 -> 16.0;
@@ -199,6 +201,8 @@ __device__ __forceinline__ void store_unit(void* out, size_t at, const f32x4_t& 
 template <int NM, int NTB, int U, typename Before>
 __device__ __forceinline__ void stream_blocks(const char* const (&w)[NM], const char* in, const uint32_t (&xoff)[NTB], int kb0, int kb1,
                                               f32x4_t (&acc)[NM][NTB], Before before) {
+    // (known from here on only: the compiler would compute every place's addresses in front of the caller's loop over rows, in 20 registers)
+    asm volatile("" : "+s"(kb0), "+s"(kb1));
     const uint32_t lane16 = (threadIdx.x & 63) * 16;
     bf16x8_t wr[U][NM], xr[U][NTB];
     auto load = [&](int u, int kb) {
@@ -217,9 +221,22 @@ __device__ __forceinline__ void stream_blocks(const char* const (&w)[NM], const 
             for (int m = 0; m < NM; ++m) acc[m][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wr[u][m], xr[u][tb], acc[m][tb], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
+    if (kb1 - kb0 < U) {                 // (never with U = 1: the part has blocks)
+#pragma unroll
+        for (int u = 0; u < U - 1; ++u) {
+            if (kb0 + u >= kb1) break;
+            load(u, kb0 + u);
+        }
+#pragma unroll
+        for (int u = 0; u < U - 1; ++u) {
+            if (kb0 + u >= kb1) return;
+            multiply(u, kb0 + u);
+        }
+        return;
+    }
     int kb = kb0;
 #pragma unroll
-    for (int u = 0; u < U; ++u) load(u, min(kb + u, kb1 - 1));
+    for (int u = 0; u < U; ++u) load(u, kb + u);
     for (; kb + U < kb1; kb += U) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -233,10 +250,20 @@ __device__ __forceinline__ void stream_blocks(const char* const (&w)[NM], const 
         multiply(u, kb + u);
     }
 }
-// Depth of the stream: as many blocks as REGS registers hold, 8 at most (a part seldom has more).
-template <int NM, int NTB, int REGS> constexpr int stream_depth() {
-    const int n = REGS / (4 * (NM + NTB));
-    return n < 1 ? 1 : n > 8 ? 8 : n;
+// The same, as many blocks deep as REGS registers hold, 8 at most.  Where that is 3 (down, four row blocks) or 5 (down, two; gate/up, one) a part of
+// 4n or 4n - 1 blocks takes 4: a place of row blocks that is loaded for nothing costs more than the depth gives (down: 60 tokens, one
+// expert, K 1408, parts of 5 and 6 blocks, the call 4 deep 211 us, 3 deep 200; 56 tokens, K 1920, parts of 7 and 8, the launch 10.7 and 11.4).
+template <int NM, int NTB, int REGS, typename Before>
+__device__ __forceinline__ void stream_part(const char* const (&w)[NM], const char* in, const uint32_t (&xoff)[NTB], int kb0, int kb1,
+                                            f32x4_t (&acc)[NM][NTB], Before before) {
+    constexpr int N = REGS / (4 * (NM + NTB)), U = N < 1 ? 1 : N > 8 ? 8 : N;
+    if constexpr (U == 3 || U == 5) {
+        if (((kb1 - kb0) & 3) == 0 || ((kb1 - kb0) & 3) == 3) {
+            stream_blocks<NM, NTB, 4>(w, in, xoff, kb0, kb1, acc, before);
+            return;
+        }
+    }
+    stream_blocks<NM, NTB, U>(w, in, xoff, kb0, kb1, acc, before);
 }
 
 template <bool GATEUP, int NW, int MAXB, int REGS, typename RowOf>
@@ -266,7 +293,7 @@ __device__ __forceinline__ void stream_unit(const FfnJob& j, const TileInfo& til
         for (int m = 0; m < NM; ++m)
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb) acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-        if (kb0 < kb1) stream_blocks<NM, NTB, stream_depth<NM, NTB, REGS>()>(w, (const char*)j.in, xoff, kb0, kb1, acc, [](int) {});
+        if (kb0 < kb1) stream_part<NM, NTB, REGS>(w, (const char*)j.in, xoff, kb0, kb1, acc, [](int) {});
         // split-K reduction in wave order, one token block at a time; wave (tb % waves) finishes block tb
 #pragma unroll
         for (int tb = 0; tb < NTB; ++tb) {
@@ -347,7 +374,7 @@ __device__ __forceinline__ void stream_unit_eight(const FfnJob& j, const TileInf
             for (int tb = 0; tb < NTB; ++tb) acc[m][tb] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
         if (second == kb0) store_part(2 * wave);             // (an empty first part)
         if (kb0 < kb1)
-            stream_blocks<NM, NTB, stream_depth<NM, NTB, REGS>()>(w, (const char*)j.in, xoff, kb0, kb1, acc, [&](int kb) {
+            stream_part<NM, NTB, REGS>(w, (const char*)j.in, xoff, kb0, kb1, acc, [&](int kb) {
                 if (kb == second && second > kb0) store_part(2 * wave);
             });
         store_part(2 * wave + 1);

@@ -562,6 +562,25 @@ def test_streamed_parts_shorter_and_longer_than_the_loads_in_flight(T, k, E, d, 
     run_and_check_layer(cfg, 0, T, k)
 
 
+@pytest.mark.parametrize("T", [9, 30, 60])
+@pytest.mark.parametrize("d,F,Fs,E", [
+    # down in eight parts of 1, 2, 3, 4, 4 to 5, 5 to 6, 7 to 8 and 8 to 9 blocks; up to 16, 32 and 64 rows of one expert or the shared one, both
+    # jobs streaming (E 64) and the routed one on tiles in gate/up (E 2), whose reductions are as long
+    (128, 256, 256, 2), (384, 512, 0, 2), (640, 768, 576, 2), (896, 1088, 1088, 64), (1152, 1408, 704, 64), (1920, 1920, 0, 2), (2176, 2176, 64, 64),
+])
+def test_streamed_parts_of_every_length_around_the_depth_of_the_ring(T, d, F, Fs, E):
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(S.C2, L=1, d=d, F=F, F_shared=0), E=E, F_shared=Fs, shared_kind=S.SHARED_UNGATED if Fs else S.SHARED_NONE)
+    k = 1 if E == 64 else 2
+    dl, _ = device_and_host_layer(cfg, 0)
+    if Fs:
+        assert all(P.lexi_moe_gemm_plan(dl, T, k, g, shared=True)["streams"] for g in ("gate_up", "down"))
+    else:
+        assert P.lexi_moe_gemm_plan(dl, T, k, "down")["streams"]
+    run_and_check_layer(cfg, 0, T, k)
+
+
 @pytest.mark.parametrize("kind", ["c1", "c2"])
 @pytest.mark.parametrize("T,k,E,d", [
     # rows of 16 lanes: one to 16 experts, a wave's four tokens partly there, on both sides of the line to three launches and to whole waves
