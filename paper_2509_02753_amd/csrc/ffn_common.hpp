@@ -377,6 +377,7 @@ __device__ __forceinline__ void stream_unit_eight(const FfnJob& j, const TileInf
             stream_part<NM, NTB, REGS>(w, (const char*)j.in, xoff, kb0, kb1, acc, [&](int kb) {
                 if (kb == second && second > kb0) store_part(2 * wave);
             });
+        if (second == kb1 && second > kb0) store_part(2 * wave);   // (an empty second part: 3 or 5 blocks in all)
         store_part(2 * wave + 1);
         __syncthreads();
         if (wave < NTB) {                                    // the wave's row block, its parts in order
