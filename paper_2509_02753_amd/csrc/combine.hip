@@ -192,23 +192,25 @@ __global__ void __launch_bounds__(256)
 start_chain_kernel(const void* x, int d, float eps, float* h, void* u) {
     constexpr int NP = 4;
     __shared__ float wave_part[4];
+    constexpr int ES = X_BF16 ? 2 : 4;
     const size_t row = (size_t)blockIdx.x * d;
+    // (a buffer of this row alone: lanes past its end read nothing)
+    const auto x_row = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)x + row * ES), 0, (unsigned)d * ES, 0x00020000);
     f32x4_t v[NP];
     float ss = 0.0f;
     for (int c0 = 0; c0 < d; c0 += 1024 * NP) {
 #pragma unroll
-        for (int p = 0; p < NP; ++p) {                  // (pieces past the row all read its first four elements; never stored)
+        for (int p = 0; p < NP; ++p) {
             const int j = c0 + 1024 * p + threadIdx.x * 4;
-            const size_t at = row + (j < d ? j : 0);
-            if (X_BF16) {
-                const u32x2_t pk = *(const u32x2_t*)((const bf16_t*)x + at);
+            if constexpr (X_BF16) {
+                const u32x2_t pk = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(x_row, (unsigned)j * ES, 0, 0));
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     v[p][2 * i] = __uint_as_float(pk[i] << 16);
                     v[p][2 * i + 1] = __uint_as_float(pk[i] & 0xFFFF0000u);
                 }
             } else {
-                v[p] = *(const f32x4_t*)((const float*)x + at);
+                v[p] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(x_row, (unsigned)j * ES, 0, 0));
             }
         }
 #pragma unroll

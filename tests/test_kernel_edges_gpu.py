@@ -551,6 +551,29 @@ def test_start_of_a_chained_stack_at_its_edges(base, T, d):
     _check_blocks(cfg, T, np.array([1, 2]))
 
 
+@pytest.mark.parametrize("base,T,d", [("C1", 3, 128), ("C1", 2, 1152), ("C1", 1, 4224), ("C2", 3, 384), ("C2", 2, 2176), ("C2", 1, 4224)])
+def test_chained_stack_in_the_place_of_its_input(base, T, d):
+    """The normalised input in the place of x, and for fp32 layers the hidden state there, give the bits of separate buffers."""
+    import torch
+    import paper_2509_02753_amd as P
+    from helpers import device_and_host_layer
+    cfg = replace(S.mini(getattr(S, base), L=2, d=d, F=64, F_shared=0), E=4, k_base=2)
+    layers = [device_and_host_layer(cfg, l)[0] for l in range(2)]
+    x, ws = S.device_x(cfg, 0, T), P.alloc_workspace(layers, T, 2)
+
+    def run(x, y, moe_input=None):
+        routing = [P.RoutingOut(T, k, cfg.E, moe_input=moe_input) for k in (1, 2)] if moe_input is not None else None
+        P.lexi_moe_stack_forward(layers, [1, 2], x, y, ws, routing=routing, chained=True)
+        return y
+
+    want = run(x, torch.empty((T, d), dtype=torch.float32, device="cuda:0"))
+    in_x = x.clone()
+    assert torch.equal(run(in_x, torch.empty_like(want), moe_input=in_x), want)
+    if cfg.dtype == "f32":
+        own = x.clone()
+        assert torch.equal(run(own, own), want)
+
+
 @pytest.mark.parametrize("T,k,E,d,F", [(20, 2, 64, 128, 64), (40, 2, 64, 384, 192), (100, 1, 64, 1152, 576), (128, 1, 64, 2176, 1088), (33, 3, 60, 1280, 320)])
 @pytest.mark.parametrize("zipf", [0.0, 1.1])
 def test_streamed_parts_shorter_and_longer_than_the_loads_in_flight(T, k, E, d, F, zipf):
