@@ -46,6 +46,14 @@ __device__ __forceinline__ float dpp_f32(float old, float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
 }
 
+// 16 bytes per lane from `base` + lane_offset + offset to LDS, the lanes' one behind the other.  (A buffer load: the compiler takes a global
+// one for a flat access, and then waits for all loads in flight where it waits for one.)
+template <typename P>
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t lane_offset, uint32_t offset, P to) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xFFFFFFFFu, 0x00020000),
+                                             (__attribute__((address_space(3))) void*)to, 16, lane_offset, offset, 0, 0);
+}
+
 // Maximum and sum over the 16 lanes of a row, in all of them (the first four steps of wave_max and wave_sum: with zeros in the other
 // rows the same sum).
 __device__ __forceinline__ float row_max(float v) {

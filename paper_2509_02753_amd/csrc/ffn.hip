@@ -49,13 +49,6 @@ template <int S> struct StageTag { static constexpr int value = S; };
 
 typedef __attribute__((address_space(3))) bf16_t lds_bf16;
 
-// 16 bytes per lane from `base` + lane_offset + offset to LDS, the lanes' one behind the other.  (A buffer load: the compiler takes a global
-// one for a flat access, and then waits for all loads in flight where it waits for one.)
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t lane_offset, uint32_t offset, lds_bf16* to) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xFFFFFFFFu, 0x00020000),
-                                             (__attribute__((address_space(3))) void*)to, 16, lane_offset, offset, 0, 0);
-}
-
 // Until at most N of the wave's memory operations are on their way (they complete in order) and its LDS operations are done, then
 // until the other waves are there too.
 template <int N>

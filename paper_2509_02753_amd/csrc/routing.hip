@@ -243,12 +243,6 @@ router_topk_kernel(const void* __restrict__ x, const float* __restrict__ w_route
 // it gains is used up by the rounds: T 6000 31.1 / 31.2, T 12000 49.1 / 47.6, d 512 21.4 / 20.0, but T 20000, d 512 27.4 / 31.8, hence
 // the line at kLdsRouterMaxT.
 constexpr int kWRing = 4, kWPiece = 256;         // floats of a piece: four rows of at most 64
-// 16 bytes per lane from `base` + lane_offset + offset to LDS, the lanes' one behind the other.  (A buffer load: the compiler takes a global
-// one for a flat access, and then waits for all loads in flight where it waits for one.)
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t lane_offset, uint32_t offset, float* to) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, 0xFFFFFFFFu, 0x00020000),
-                                             (__attribute__((address_space(3))) void*)to, 16, lane_offset, offset, 0, 0);
-}
 // The four rows of ring place SLOT at LDS byte addresses at[]: N younger pieces may still be on their way.  (Written out: the compiler
 // would wait for all of them before a read that may touch the same array.)
 template <int SLOT, int N>
