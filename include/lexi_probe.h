@@ -22,8 +22,8 @@ lexi_status lexi_probe_hbm_read(const void* src, size_t bytes, void* sink, void*
  *   Returns 0 = weight-streaming schedule (decode-sized), 1 = tile schedule, 2 = tile schedule with the reduction cut
  *   in two (two partial planes, added by the combine), 3 = tile schedule storing the output rows directly (k = 1 and
  *   nothing else to add: no combine pass), 4 = a handful of tokens: weight streaming with the combine in the same
- *   launch; -1 = invalid arguments or no shared expert.  fp32 layers have one kernel for every size and report 0 for small
- *   batches and 1 for others. */
+ *   launch; -1 = invalid arguments or no shared expert.  For fp32 layers, which have one GEMM kernel for every size and one that
+ *   holds the combine too, 0 and 1 only tell small batches from others: lexi_moe_gemm_plan says how such a call is launched. */
 int32_t lexi_moe_down_plan(const lexi_layer_t* layer, int32_t T, int32_t k, int32_t which);
 
 /* How one GEMM of a call is launched (a diagnostic like the above; reads the layer's sizes only).

@@ -436,9 +436,9 @@ static hipError_t launch_ffn(const FfnArgs& a, const FfnArgs* shared, hipStream_
         // split reduction and scattered rows exist on the bf16 tile schedule's DOWN only
         if ((f->ksplit > 1 || f->scatter != nullptr) && (!tiles || GATEUP)) return hipErrorInvalidValue;
         if (f->ksplit > 1 && (f->K / BK < f->ksplit || f->scatter != nullptr)) return hipErrorInvalidValue;
-        // the tile kernel addresses its input rows with 32-bit byte offsets
+        // input rows are addressed with 32-bit byte offsets
         const size_t in_rows = f->row_token ? (size_t)f->in_rows : (size_t)f->M;
-        if (tiles && in_rows * (size_t)f->K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
+        if (f->is_bf16 && in_rows * (size_t)f->K * 2 >= ((size_t)1 << 32)) return hipErrorInvalidValue;
     }
     if (!a.is_bf16 || (a.streaming && (shared == nullptr || shared->streaming)))
         return GATEUP ? launch_gateup_stream(a, shared, s) : launch_down_stream(a, shared, s);

@@ -152,7 +152,7 @@ constexpr int kFusedDownMaxRows = 64;
 // to 4096, 8 layers, one to 8 tokens: 0 to 10 % more time).
 inline int down_combine_features(int d) { return d <= 2048 ? 8 : 16; }
 struct DownCombineArgs {
-    const void* act;           // [T*k][F] bf16, permuted rows
+    const void* act;           // [T*k][F] bf16 (fp32 layers: fp32, as the weights and act_shared), permuted rows
     const void* w_down;        // [E] packed matrices of [d][F]
     int F, d, T, k;
     const int32_t* sched;      // work list (one tile per expert with rows), or null: then
@@ -161,14 +161,14 @@ struct DownCombineArgs {
     const int32_t* topk_idx;   // [T*k] (fp32 layers only)
     const int32_t* inv_perm;   // [T*k]
     const float* gates;        // [T*k]
-    const void* act_shared;    // [T][F_shared] bf16 or null: the shared expert, added with coefficient 1
+    const void* act_shared;    // [T][F_shared] or null: the shared expert, added with coefficient 1
     const void* ws_down;       // packed [d][F_shared]
     int F_shared;
     void* y;                   // [T][d]
     bool y_bf16;
 };
 hipError_t launch_down_combine(const DownCombineArgs& a, hipStream_t s);
-// The same for fp32 layers (act, weights and act_shared fp32, topk_idx in place of sched and counts): a workgroup per token and 64 features, and
+// The same for fp32 layers (topk_idx in place of sched and counts): a workgroup per token and 64 features, and
 // every slot pulls its own 256 bytes of weights per element of the reduction, where the tiles of separate launches share them.  Bound by what a
 // CU pulls, so the line lies there.  Down + combine, separate launches against one, us (KB per CU): 64 tokens, k 2, d 128, F 256 9.2 / 4.8
 // (131); 1024 tokens, d 128, F 64 8.1 / 5.8 (262); 128 tokens, d 256, F 256 8.9 / 6.1 (262); d 384, F 128, shared 128 7.1 / 6.5 (295); then d 384,

@@ -615,6 +615,8 @@ topk_scan_kernel(const float* partial, const float* __restrict__ bias, int T, in
 // Up to 16 experts a row of 16 lanes is enough for a token, so a wave selects from its four at once, a quarter of the work per k: 64 tokens, d 128,
 // k 2 9.0 -> 6.7 us, 32 tokens, k 4 7.0 -> 4.9.  The line moves with it, one launch against three: d 128, 64 tokens, k 4 7.0 / 9.9, 16 experts,
 // k 8 8.5 / 10.6; d 256, 64 tokens, k 4 10.0 / 11.0, k 8 10.4 / 10.8; d 384, 32 tokens, k 4 8.1 / 9.5, k 8 9.8 / 10.4, but 64 tokens, k 2 12.5 / 10.2.
+// Up to 16 tokens it pays in a replayed graph too (4 bf16 layers of d 384, two launches against one, replayed, from the host): 16 tokens, 8
+// experts, k 8 81.1 / 77.5, 86.2 / 76.7; 16 experts, k 16 96.5 / 91.6, 95.2 / 90.6; 9 tokens, k 16 91.3 / 88.7, 90.0 / 86.8.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kSmallRouteSegs = 3;
 static bool route_small(int T, int k, int nseg, int E) {
