@@ -250,7 +250,9 @@ __device__ __forceinline__ void stream_blocks(const char* const (&w)[NM], const 
         multiply(u, kb + u);
     }
 }
-// The same, as many blocks deep as REGS registers hold, 8 at most.  Where that is 3 (down, four row blocks) or 5 (down, two; gate/up, one) a part of
+// The same, as many blocks deep as REGS registers hold, 8 at most.  Eight row blocks leave one (its nine or ten loads fly together, none ahead),
+// still less time than the plain loop (64 experts, k 1, 97 to 128 tokens, nearly all of one expert, d 1024 to 4096: whole calls 0.65 to 0.75
+// times).  Where the depth would be 3 (down, four row blocks) or 5 (down, two; gate/up, one) a part of
 // 4n or 4n - 1 blocks takes 4: a place of row blocks that is loaded for nothing costs more than the depth gives (down: 60 tokens, one
 // expert, K 1408, parts of 5 and 6 blocks, the call 4 deep 211 us, 3 deep 200; 56 tokens, K 1920, parts of 7 and 8, the launch 10.7 and 11.4).
 template <int NM, int NTB, int REGS, typename Before>
