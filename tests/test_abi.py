@@ -132,7 +132,7 @@ def test_down_gemm_plan_is_host_logic():
     assert plan(4096, 8, d=2048, E=64, F=1024) == 1 and plan(4096, 1, d=2048, E=64, F=1024) == 3
     assert plan(8192, 4, 1, d=2048, E=60, F=1408, F_shared=5632, shared_kind=2, **shared) == 1
     assert plan(64, 4, 1, d=2048, E=60, F=1408, F_shared=5632, shared_kind=2, **shared) == 0
-    # fp32 layers have one kernel and report by the size
+    # fp32 layers report by the size, however they are launched (lexi_moe_gemm_plan tells)
     f32 = lambda T, k, which=0, **kw: _lib.lexi_moe_down_plan(ctypes.byref(fake_layer(P, dtype=0, **kw)), T, k, which)
     assert f32(6343, 7, d=896, E=35, F=1088) == 1 and f32(64, 2, d=128, E=8, F=256) == 0 and f32(128, 1, d=896, E=64, F=64) == 0
     assert f32(94, 2, 1, d=1664, E=10, F=2944, F_shared=128, shared_kind=1, **shared) == 1
@@ -170,6 +170,9 @@ def test_gemm_plan_agrees_with_the_down_plan():
             assert _lib.lexi_moe_down_plan(ctypes.byref(ly), T, k, 1) == (0 if p["streams"] else p["ksplit"])
         else:
             assert gemm_plan(P, ly, T, k, 3) == -2
+    small, large = fake_layer(P, dtype=0, d=128, E=8, F=256), fake_layer(P, dtype=0, d=896, E=35, F=1088)
+    assert gemm_plan(P, small, 64, 2, 1)["fused"] == 1 and gemm_plan(P, small, 64, 2, 1, chained=1)["fused"] == 0
+    assert gemm_plan(P, large, 6343, 7, 1)["fused"] == 0
     assert gemm_plan(P, fake_layer(P), 0, 1, 0) == -2 and gemm_plan(P, fake_layer(P), 1, 1, 4) == -2
 
 
